@@ -132,9 +132,15 @@ __host__ __device__ constexpr int tr_tile_bytes(int H, bool bf16) {
   return bf16 ? H * 40 * 2 : 32 * (H + 4) * 4;
 }
 
-// BF16 training keeps the encodings of a sub-tile's two 32-sample passes in LDS (BF16, 32 features
-// per sample) for the backward's recomputation, which then starts at the first layer.
-__host__ __device__ constexpr int enc_cache_bytes(bool bf16) { return bf16 ? 2 * 32 * kEnc * 2 : 0; }
+// Per-wave staging of the width-32 tile kernel, which takes a sub-tile's two 32-sample passes
+// together. dL/dz of the 64 slots: BF16 as four output rows of kDzPitch (the output layer's
+// weight-gradient operand), then sample-major, four per slot (the output layer's delta operand);
+// FP32 sample-major. Then tiles [32 samples][36] of deltas (one pass at a time) and of activations
+// (FP32: one pass at a time; BF16: both passes, and both passes' encodings).
+constexpr int kDzPitch = 72;
+__host__ __device__ constexpr int pair_dz_bytes(bool bf16) { return bf16 ? kOut * kDzPitch * 2 + 64 * kOut * 2 : 64 * kOut * 4; }
+__host__ __device__ constexpr int pair_tiles(bool bf16) { return bf16 ? 5 : 2; }
+__host__ __device__ constexpr int pair_tile_bytes(bool bf16) { return 32 * 36 * (bf16 ? 2 : 4); }
 
 // Every offset except `total` is independent of the wave count, so kernels evaluate the layout at
 // compile time (immediate LDS offsets) and only the host needs `total`.
@@ -173,7 +179,7 @@ __host__ __device__ constexpr LdsLayout lds_layout(int H, bool bf16, int nwaves)
   off = round_up(off + 3 * kFeatures * 4, 16);
   L.loss_off = off;  // the tile's loss per gradient copy (up to 4), then its non-finite flag
   off = round_up(off + 32, 16);
-  L.scratch_wave = round_up(dz_tile_bytes(bf16) + 2 * tr_tile_bytes(H, bf16) + enc_cache_bytes(bf16), 16);
+  L.scratch_wave = round_up(pair_dz_bytes(bf16) + pair_tiles(bf16) * pair_tile_bytes(bf16), 16);
   L.scratch_off = off;
   int scratch = nwaves * L.scratch_wave;
   // the tile's gradient at the end: red_copies(nwaves) copies, each summing a fixed set of waves

@@ -66,6 +66,13 @@ __device__ __forceinline__ void wave_lds_sync() {
   asm volatile("" ::: "memory");
 }
 
+// Keeps the compiler from moving LDS accesses across it. A wave's LDS instructions execute in
+// order, so its reads see its own earlier writes (any lane's) without a wait.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_wave_barrier();
+  asm volatile("" ::: "memory");
+}
+
 // BF16 operand tiles of the weight-gradient products are staged sample-major: row s (a sample)
 // holds the tile's features, TR_STRIDE elements apart. A lane writes its accumulator-layout
 // values as 8-byte runs of four consecutive features, and ds_read_b64_tr_b16 regroups them: in
@@ -523,6 +530,156 @@ __device__ __forceinline__ void forward_pass(const float xt[4], const unsigned c
   }  // weights in LDS
 }
 
+// Values of a wave's lower half (lanes 0..31, in lo) and upper half (in hi), on the lanes of both
+// halves, by one v_permlane32_swap_b32.
+__device__ __forceinline__ void half_split(float x, float& lo, float& hi) {
+  const unsigned int u = __builtin_bit_cast(unsigned int, x);
+  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  lo = __builtin_bit_cast(float, (unsigned int)r[0]);
+  hi = __builtin_bit_cast(float, (unsigned int)r[1]);
+}
+// a's lower half and b's lower half as one wave (lo), and both upper halves (hi).
+__device__ __forceinline__ void half_join(float a, float b, float& lo, float& hi) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned int, a),
+                                                  __builtin_bit_cast(unsigned int, b), false, false);
+  lo = __builtin_bit_cast(float, (unsigned int)r[0]);
+  hi = __builtin_bit_cast(float, (unsigned int)r[1]);
+}
+// Sum of x over lanes l and l ^ 32, on both.
+__device__ __forceinline__ float half_sum(float x) {
+  float lo, hi;
+  half_split(x, lo, hi);
+  return lo + hi;
+}
+
+// Gaussian Fourier features of both passes' samples into layer 0 (register r of a lane of half hf
+// holds feature rowof(r, hf): sines of 4hf + 0..3 and 8 + 4hf + 0..3, then the cosines). IPE: each
+// is its expectation under N(x, v I), attenuated by exp(-v |b_f|^2 / 2), v = xt[p][3]. One branch
+// for the whole encoding, so that the features' chains interleave.
+template <bool BF, bool IPE>
+__device__ __forceinline__ void encode_pair(const float xt[2][4], const float* Bm, int hf, Acts<32, BF> (&A)[2]) {
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+#pragma unroll
+    for (int i = 0; i < 4; i += 2) {
+      float b[3][2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) b[c][u] = Bm[c * kFeatures + 8 * g + 4 * hf + i + u];
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        float s[2], c[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const float phi = xt[p][0] * b[0][u] + xt[p][1] * b[1][u] + xt[p][2] * b[2][u];
+          vmap_sincosf(phi, &s[u], &c[u]);
+          if constexpr (IPE) {
+            const float nb = b[0][u] * b[0][u] + b[1][u] * b[1][u] + b[2][u] * b[2][u];
+            const float att = expf(-0.5f * xt[p][3] * nb);
+            s[u] *= att;
+            c[u] *= att;
+          }
+        }
+        A[p].set2(0, 0, 4 * g + i, s[0], s[1]);
+        A[p].set2(0, 0, 8 + 4 * g + i, c[0], c[1]);
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Forward of both 32-sample passes of a sub-tile at width 32, layer by layer together: each weight
+// operand is read from LDS once for the two passes, and their MFMA chains run side by side (one
+// pass after the other took 7.2 thousand cycles per 64-sample sub-tile in BF16, of a 16.8 thousand
+// cycle sub-tile; the chain of dependent products and conversions bounds it, not the MFMA rate).
+// xt[p]: the point of sample n = lane & 31 of pass p. Each pass's arithmetic is forward_pass's, in
+// the same order. zs: the output pre-activations of the lane's own slot (slot = lane).
+template <bool BF>
+__device__ __forceinline__ void forward_pair(const float xt[2][4], const unsigned char* smem, const float* Bm,
+                                             int lane, Acts<32, BF> (&A)[2], float zs[kOut], bool ipe) {
+  constexpr LdsLayout L = lds_layout(32, BF, 1);
+  asm volatile("" ::: "memory");  // weights are re-read for every sub-tile, not held in registers
+  const int n = lane & 31, hf = lane >> 5;
+  if (ipe) encode_pair<BF, true>(xt, Bm, hf, A);
+  else encode_pair<BF, false>(xt, Bm, hf, A);
+  f32x16 zero;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) zero[r] = 0.f;
+  const float* bias = reinterpret_cast<const float*>(smem + L.b_off);
+#pragma unroll
+  for (int l = 0; l < kLayers; ++l) {
+    const int ws = L.w_stride[l];
+    f32x16 acc[2];
+    if constexpr (BF) {
+      // both accumulators start at the bias (one MFMA, exact)
+      const bf16x8 ba = *reinterpret_cast<const bf16x8*>(
+          reinterpret_cast<const __bf16*>(smem + L.bA_off) + (l * 32 + n) * 16 + 8 * hf);
+      const bf16x8 ones3 = {(__bf16)1.0f, (__bf16)1.0f, (__bf16)1.0f, (__bf16)0.0f,
+                            (__bf16)0.0f, (__bf16)0.0f, (__bf16)0.0f, (__bf16)0.0f};
+      const __bf16* wrow = reinterpret_cast<const __bf16*>(smem + L.w_off[l]) + n * ws + 16 * hf;
+      const bf16x8 w0 = *reinterpret_cast<const bf16x8*>(wrow), w1 = *reinterpret_cast<const bf16x8*>(wrow + 8);
+      const f32x16 b16 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ba, ones3, zero, 0, 0, 0);
+#pragma unroll
+      for (int p = 0; p < 2; ++p) acc[p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w0, A[p].v[l][0][0], b16, 0, 0, 0);
+#pragma unroll
+      for (int p = 0; p < 2; ++p) acc[p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1, A[p].v[l][0][1], acc[p], 0, 0, 0);
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj) A[p].v[l + 1][0][jj] = relu_round8(acc[p], 8 * jj);
+    } else {
+      const float* wrow = reinterpret_cast<const float*>(smem + L.w_off[l]) + n * ws + 16 * hf;
+      acc[0] = acc[1] = zero;
+#pragma unroll
+      for (int q = 0; q < 16; ++q)
+#pragma unroll
+        for (int p = 0; p < 2; ++p) acc[p] = __builtin_amdgcn_mfma_f32_32x32x2f32(wrow[q], A[p].v[l][0][q], acc[p], 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float b = bias[l * 32 + rowof(r, hf)];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) A[p].set(l + 1, 0, r, fmaxf(acc[p][r] + b, 0.0f));
+      }
+    }
+  }
+  const float* bh = reinterpret_cast<const float*>(smem + L.bh_off);
+  if constexpr (BF) {
+    // output layer on MFMA: A = W_out with its four rows padded to 32 (zero rows held in
+    // registers); sample n's outputs land in rows 0..3 of lane n (half 0) of each pass
+    const __bf16* wh = reinterpret_cast<const __bf16*>(smem + L.whb_off) + n * 40 + 16 * hf;
+    f32x16 acc[2] = {zero, zero};
+#pragma unroll
+    for (int jj = 0; jj < 2; ++jj) {
+      bf16x8 wa = {};
+      if (n < kOut) wa = *reinterpret_cast<const bf16x8*>(wh + 8 * jj);
+#pragma unroll
+      for (int p = 0; p < 2; ++p) acc[p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, A[p].v[kLayers][0][jj], acc[p], 0, 0, 0);
+    }
+#pragma unroll
+    for (int c = 0; c < kOut; ++c) {
+      float unused;
+      half_join(acc[0][c] + bh[c], acc[1][c] + bh[c], zs[c], unused);
+    }
+  } else {
+    // output layer on the VALU: each half sums its 16 features, then the halves are added
+    const float* Wh = reinterpret_cast<const float*>(smem + L.wh_off);
+#pragma unroll
+    for (int c = 0; c < kOut; ++c) {
+      float s[2] = {0.f, 0.f};
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float w = Wh[c * 36 + 16 * hf + r];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) s[p] += w * A[p].v[kLayers][0][r];
+      }
+      float lo, hi;
+      half_join(s[0], s[1], lo, hi);
+      zs[c] = (lo + hi) + bh[c];
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------------------------
 // The step's tile kernel.
 
@@ -955,11 +1112,10 @@ __global__ void __launch_bounds__((BF && H == 32) ? 512 : 256, 1) k_step_tiles(c
   constexpr int MT = H / 32;
   constexpr bool TABLE = (MODE == MODE_STEP);  // tile table built here, not by k_worklist
   constexpr bool TRAIN = (MODE == MODE_TRAIN) || TABLE;
-  constexpr bool KEEP = TRAIN && !BF;  // activations kept across the rendering (no recompute)
+  constexpr int kTile = pair_tile_bytes(BF);  // staging tiles (vmap_internal.h)
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr LdsLayout L = lds_layout(H, BF, 1);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
-  const int n = lane & 31, hf = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, lane_ = lane, wave = tid >> 6, nw = blockDim.x >> 6;
   const int S = a.S;
   const int rpw = kSlots / S;
 
@@ -1079,67 +1235,47 @@ __global__ void __launch_bounds__((BF && H == 32) ? 512 : 256, 1) k_step_tiles(c
     }
     float wave_loss = 0.f;
 
-    unsigned char* scr = smem + L.scratch_off + wave * L.scratch_wave;
-    unsigned char* encc = scr + dz_tile_bytes(BF) + 2 * tr_tile_bytes(H, BF);
+    unsigned char* const dzt = smem + L.scratch_off + wave * L.scratch_wave;
+    unsigned char* const dtile = dzt + pair_dz_bytes(BF);
+    unsigned char* const htile = dtile + kTile;                // BF16: one per pass
+    unsigned char* const etile = htile + 2 * kTile;            // BF16: the encodings, one per pass
 
     for (int sub = wave; sub < nsub; sub += nw) {
       asm volatile("" ::: "memory");
+      // the lane's index through an empty asm statement: lane-dependent LDS addresses are computed
+      // where they are used, not hoisted out of the loop and spilled
+      int ln = lane_;
+      asm volatile("" : "+v"(ln));
+      const int lane = ln, n = ln & 31, hf = ln >> 5;
       const int r0 = ray_lo + sub * rpw;
       const int nr = min(rpw, ray_hi - r0);
       const int nslots = nr * S;
-      const RenderIn rin = render_inputs<TRAIN>(a, r0, nslots);  // in flight during the forward
+      const RenderIn rin = render_inputs<TRAIN>(a, r0, nslots);
+      // the lane's own sample: normalised point and (integrated encoding) normalised variance,
+      // then handed to the two lanes that hold its pass's column
+      float x[4] = {0.f, 0.f, 0.f, 0.f}, xt[2][4];
+      if (lane < nslots) {
+        const int ray = r0 + lane / S;
+        const double tt = (double)rin.tt;
+        const float* o3 = a.rays_o + 3 * (size_t)ray;
+        const float* d3 = a.rays_d + 3 * (size_t)ray;
+        x[0] = (float)(((double)o3[0] + tt * (double)d3[0] - cx) * inv_s);
+        x[1] = (float)(((double)o3[1] + tt * (double)d3[1] - cy) * inv_s);
+        x[2] = (float)(((double)o3[2] + tt * (double)d3[2] - cz) * inv_s);
+        if (a.var) x[3] = (float)((double)a.var[(size_t)r0 * S + lane] * inv_s * inv_s);
+      }
+#pragma unroll
+      for (int c = 0; c < 4; ++c) half_split(x[c], xt[0][c], xt[1][c]);
 
-      // ---------------- forward of both passes for the head outputs only. Each pass's
-      // activations are recomputed right before its backward (activation recomputation), so no
-      // activation is held across the rendering.
-      // the lane's sample: normalised point and (integrated encoding) normalised variance
-      auto point = [&](int p, float xt[4]) {
-        const int slot = 32 * p + n;
-        xt[0] = xt[1] = xt[2] = xt[3] = 0.f;
-        if (slot < nslots) {
-          const int ray = r0 + slot / S;
-          const double tt = (double)a.t[(size_t)r0 * S + slot];
-          const float* o3 = a.rays_o + 3 * (size_t)ray;
-          const float* d3 = a.rays_d + 3 * (size_t)ray;
-          xt[0] = (float)(((double)o3[0] + tt * (double)d3[0] - cx) * inv_s);
-          xt[1] = (float)(((double)o3[1] + tt * (double)d3[1] - cy) * inv_s);
-          xt[2] = (float)(((double)o3[2] + tt * (double)d3[2] - cz) * inv_s);
-          if (a.var) xt[3] = (float)((double)a.var[(size_t)r0 * S + slot] * inv_s * inv_s);
-        }
-      };
-      float zs[kOut] = {0.f, 0.f, 0.f, 0.f};
-      // FP32 (one wave per SIMD either way) keeps both passes' activations for the backward;
-      // BF16 recomputes them there from the encodings kept in LDS (no sine/cosine twice), which
-      // keeps it at two waves per SIMD (measured faster than keeping the activations).
-      Acts<H, BF> keep0, keep1;
-      if constexpr (KEEP) {
+      Acts<H, BF> act[2];  // kept for the backward
+      float zs[kOut];
+      forward_pair<BF>(xt, smem, Bl, lane, act, zs, a.var != nullptr);
+      if constexpr (TRAIN && BF) {  // the first layer's weight gradient reads them from LDS
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
-          float xt[4], z[kOut];
-          point(p, xt);
-          forward_pass<H, BF, true>(xt, smem, Bl, p == 0 ? keep0 : keep1, z, a.var != nullptr);
+        for (int p = 0; p < 2; ++p)
 #pragma unroll
-          for (int c = 0; c < kOut; ++c) zs[c] = (hf == p) ? z[c] : zs[c];
-        }
-      } else {  // (unrolled: the two passes' chains interleave)
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-          Acts<H, BF> tmp;
-          float xt[4], z[kOut];
-          point(p, xt);
-          forward_pass<H, BF, true>(xt, smem, Bl, tmp, z, a.var != nullptr);
-#pragma unroll
-          for (int c = 0; c < kOut; ++c) zs[c] = (hf == p) ? z[c] : zs[c];
-          if constexpr (TRAIN && BF) {
-            if (p == 1) {  // the last pass's activations stay for its backward, which runs first
-              keep1 = tmp;
-            } else {  // the first pass's encoding, for its recomputation
-#pragma unroll
-              for (int jj = 0; jj < 2; ++jj)
-                *reinterpret_cast<bf16x8*>(encc + lane * 32 + 16 * jj) = tmp.v[0][0][jj];
-            }
-          }
-        }
+          for (int jj = 0; jj < 2; ++jj)
+            write_runs(reinterpret_cast<__bf16*>(etile + p * kTile) + n * kTrStride + 16 * jj + 4 * hf, act[p].v[0][0][jj]);
       }
 
       float dzs[kOut];
@@ -1148,265 +1284,204 @@ __global__ void __launch_bounds__((BF && H == 32) ? 512 : 256, 1) k_step_tiles(c
 #pragma unroll
       for (int c = 0; c < kOut; ++c) accDbH[c] += dzs[c];
 
-      // ---------------- MLP backward, one pass of 32 samples at a time
-      unsigned char* dzt = scr;
-      unsigned char* dtile = scr + dz_tile_bytes(BF);
-      unsigned char* htile = dtile + tr_tile_bytes(H, BF);
-      // one pass's backward (p: which 32 samples); BF16 runs the last pass first, on the
-      // activations its forward left in registers, and recomputes only the first pass
-      auto backward_pass = [&](const int p) {
-        Acts<H, BF> act;
-        if constexpr (KEEP) {
+      // ---------------- MLP backward of both passes, layer by layer together. The wave's LDS
+      // accesses execute in order, so its staged tiles need no wait between writes and reads.
+      float dz[2][kOut];  // FP32: each pass's dL/dz on both halves
+      if constexpr (BF) {
+        bf16x4 d4;
 #pragma unroll
-          for (int l = 0; l <= kLayers; ++l)
-#pragma unroll
-            for (int b = 0; b < H / 32; ++b)
-#pragma unroll
-              for (int q = 0; q < (int)(sizeof(act.v[0][0]) / sizeof(act.v[0][0][0])); ++q)
-                act.v[l][b][q] = (p == 0) ? keep0.v[l][b][q] : keep1.v[l][b][q];
-        } else if constexpr (BF) {
-          if (p == 1) {
-            act = keep1;
-          } else {  // recompute from the pass's encoding kept in LDS
-#pragma unroll
-            for (int jj = 0; jj < 2; ++jj)
-              act.v[0][0][jj] = *reinterpret_cast<const bf16x8*>(encc + lane * 32 + 16 * jj);
-            float z[kOut];
-            forward_pass<H, BF, false, false>(nullptr, smem, Bl, act, z);
-          }
-        } else {
-          float xt[4], z[kOut];
-          point(p, xt);
-          forward_pass<H, BF, false>(xt, smem, Bl, act, z, a.var != nullptr);
+        for (int c = 0; c < kOut; ++c) {
+          d4[c] = (__bf16)dzs[c];
+          reinterpret_cast<__bf16*>(dzt)[c * kDzPitch + lane] = d4[c];
         }
-        // the pass's dL/dz sits in lanes 32p..32p+31; FP32 moves it to both halves
-        float dz[kOut];
-        if constexpr (!BF) {
+        *reinterpret_cast<bf16x4*>(dzt + kOut * kDzPitch * 2 + 8 * lane) = d4;
 #pragma unroll
-          for (int c = 0; c < kOut; ++c) dz[c] = __shfl(dzs[c], 32 * p + n);
-        }
-        // stage dz and h_L, transposed for the output layer's weight gradient
-        wave_lds_sync();
-        if constexpr (BF) {  // written by the lanes that hold it (no cross-lane move)
-          if (hf == p) {
-            bf16x4 d4;
+        for (int p = 0; p < 2; ++p)
 #pragma unroll
-            for (int c = 0; c < kOut; ++c) {
-              d4[c] = (__bf16)dzs[c];
-              reinterpret_cast<__bf16*>(dzt)[c * 40 + n] = d4[c];
-            }
-            *reinterpret_cast<bf16x4*>(dzt + kDzRowsBytes + 8 * n) = d4;
-          }
-        } else if (hf == 0) {
+          for (int jj = 0; jj < 2; ++jj)
+            write_runs(reinterpret_cast<__bf16*>(htile + p * kTile) + n * kTrStride + 16 * jj + 4 * hf, act[p].v[kLayers][0][jj]);
+      } else {
 #pragma unroll
-          for (int c = 0; c < kOut; ++c) reinterpret_cast<float*>(dzt)[n * kOut + c] = dz[c];
-        }
-        if constexpr (BF) {  // sample-major runs (register block jj: features 16jj + 4hf + 0..3, + 8)
+        for (int c = 0; c < kOut; ++c) half_split(dzs[c], dz[0][c], dz[1][c]);
+        *reinterpret_cast<f32x4*>(dzt + 16 * lane) = f32x4{dzs[0], dzs[1], dzs[2], dzs[3]};
+      }
+      wave_lds_order();
+      Deltas<H, BF> dl[2];
+      if constexpr (BF) {
+        // output-layer weight gradient on MFMA 16x16x32: rows = the four outputs (padded to 16),
+        // columns = 16 features, K = a pass's 32 samples
+        const int m16 = lane & 15, kg = lane >> 4;
 #pragma unroll
-          for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int jj = 0; jj < 2; ++jj)
-              write_runs(reinterpret_cast<__bf16*>(htile) + n * kTrStride + mt * 32 + 16 * jj + 4 * hf,
-                         act.v[kLayers][mt][jj]);
-        } else {
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-              reinterpret_cast<float*>(htile)[n * (H + 4) + mt * 32 + rowof(r, hf)] = act.v[kLayers][mt][r];
-        }
-        wave_lds_sync();
-        Deltas<H, BF> dl;
-        if constexpr (BF) {
-          // output-layer weight gradient on MFMA 16x16x32: rows = the four outputs (padded to 16),
-          // columns = 16 features, K = the pass's 32 samples
-          const int m16 = lane & 15, kg = lane >> 4;
+        for (int p = 1; p >= 0; --p) {
           bf16x8 da = {};
-          if (m16 < kOut) da = *reinterpret_cast<const bf16x8*>(reinterpret_cast<const __bf16*>(dzt) + m16 * 40 + 8 * kg);
+          if (m16 < kOut)
+            da = *reinterpret_cast<const bf16x8*>(reinterpret_cast<const __bf16*>(dzt) + m16 * kDzPitch + 32 * p + 8 * kg);
           // B operand (feature 16b + m16, samples 8kg..8kg+7): lane x of group kg addresses row
           // 8kg + x/4 at feature 16b + 4(x mod 4)
-          const __bf16* hq = reinterpret_cast<const __bf16*>(htile) + (8 * kg + (m16 >> 2)) * kTrStride + 4 * (m16 & 3);
+          const __bf16* hq = reinterpret_cast<const __bf16*>(htile + p * kTile) + (8 * kg + (m16 >> 2)) * kTrStride + 4 * (m16 & 3);
 #pragma unroll
           for (int b = 0; b < H / 16; ++b) {
             const bf16x8 hb = tr_read8(hq + 16 * b);
             accWh[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(da, hb, accWh[b], 0, 0, 0);
           }
-          // delta of the last hidden layer: W_out^T dz on MFMA (K = 4 outputs padded to 16)
+        }
+        // delta of the last hidden layer: W_out^T dz on MFMA (K = 4 outputs padded to 16)
+        bf16x8 wa = {};
+        if (hf == 0) {
+          const bf16x4 w4 = *reinterpret_cast<const bf16x4*>(smem + L.whtb_off + n * kOut * 2);
+#pragma unroll
+          for (int c = 0; c < kOut; ++c) wa[c] = w4[c];
+        }
+        f32x16 zero;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) zero[r] = 0.f;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
           bf16x8 dzb = {};
           if (hf == 0) {
-            const bf16x4 d4 = *reinterpret_cast<const bf16x4*>(dzt + kDzRowsBytes + 8 * n);
+            const bf16x4 d4 = *reinterpret_cast<const bf16x4*>(dzt + kOut * kDzPitch * 2 + 8 * (32 * p + n));
 #pragma unroll
             for (int c = 0; c < kOut; ++c) dzb[c] = d4[c];
           }
+          const f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, dzb, zero, 0, 0, 0);
 #pragma unroll
-          for (int mt = 0; mt < MT; ++mt) {
-            bf16x8 wa = {};
-            if (hf == 0) {
-              const __bf16* wt = reinterpret_cast<const __bf16*>(smem + L.whtb_off) + (mt * 32 + n) * kOut;
-#pragma unroll
-              for (int c = 0; c < kOut; ++c) wa[c] = wt[c];
-            }
-            f32x16 acc;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, dzb, acc, 0, 0, 0);
-#pragma unroll
-            for (int jj = 0; jj < 2; ++jj) dl.v[mt][jj] = relu_mask(round8(acc, 8 * jj), act.v[kLayers][mt][jj]);
-          }
-        } else {
-          // output-layer weight gradient: lane owns feature mt*32 + n, half hf takes 16 samples
-          const float* dzl = reinterpret_cast<const float*>(dzt);
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt) {
-#pragma unroll
-            for (int s2 = 0; s2 < 16; ++s2) {
-              const int s = 16 * hf + s2;
-              const float hv = reinterpret_cast<const float*>(htile)[s * (H + 4) + mt * 32 + n];
-#pragma unroll
-              for (int c = 0; c < kOut; ++c) accH[c][mt] += dzl[s * kOut + c] * hv;
-            }
-          }
-          // delta of the last hidden layer: (W_out^T dz) masked by ReLU'
-          const float* Wh = reinterpret_cast<const float*>(smem + L.wh_off);
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              float s = 0.f;
-#pragma unroll
-              for (int c = 0; c < kOut; ++c) s += Wh[c * (H + 4) + mt * 32 + 16 * hf + r] * dz[c];
-              const float hv = reinterpret_cast<const float*>(htile)[n * (H + 4) + mt * 32 + rowof(r, hf)];
-              dl.set(mt, r, (hv > 0.f) ? s : 0.f);
-            }
+          for (int jj = 0; jj < 2; ++jj) dl[p].v[0][jj] = relu_mask(round8(acc, 8 * jj), act[p].v[kLayers][0][jj]);
         }
+      } else {
+        // output-layer weight gradient: lane owns feature n, half hf takes 16 samples of a pass
+        const float* Wh = reinterpret_cast<const float*>(smem + L.wh_off);
 #pragma unroll
-        for (int l = kLayers - 1; l >= 0; --l) {
-          const int KB = (l == 0) ? 1 : MT;
-          // delta_{l-1} = (W_l^T delta_l) masked by ReLU' of layer l-1: its products first, so that
-          // they run while this layer's operands are staged and its weight gradient accumulates
-          const int ws = L.w_stride[l > 0 ? l : 1];
-          f32x16 nacc[MT];
+        for (int p = 0; p < 2; ++p) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            reinterpret_cast<float*>(htile)[n * (H + 4) + rowof(r, hf)] = act[p].v[kLayers][0][r];
+          wave_lds_order();
+#pragma unroll
+          for (int s2 = 0; s2 < 16; ++s2) {
+            const int s = 16 * hf + s2;
+            const float hv = reinterpret_cast<const float*>(htile)[s * (H + 4) + n];
+            const f32x4 d4 = *reinterpret_cast<const f32x4*>(dzt + 16 * (32 * p + s));
+#pragma unroll
+            for (int c = 0; c < kOut; ++c) accH[c][0] += d4[c] * hv;
+          }
+          wave_lds_order();
+        }
+        // delta of the last hidden layer: (W_out^T dz) masked by ReLU'
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          float w[kOut];
+#pragma unroll
+          for (int c = 0; c < kOut; ++c) w[c] = Wh[c * (H + 4) + 16 * hf + r];
+#pragma unroll
+          for (int p = 0; p < 2; ++p) {
+            float s = 0.f;
+#pragma unroll
+            for (int c = 0; c < kOut; ++c) s += w[c] * dz[p][c];
+            dl[p].set(0, r, (act[p].v[kLayers][0][r] > 0.f) ? s : 0.f);
+          }
+        }
+      }
+#pragma unroll
+      for (int l = kLayers - 1; l >= 0; --l) {
+        // delta_{l-1} = (W_l^T delta_l) masked by ReLU' of layer l-1: its products first, so that
+        // they run while this layer's operands are staged and its weight gradient accumulates
+        f32x16 nacc[2];
+        if (l > 0) {
+#pragma unroll
+          for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) nacc[p][r] = 0.f;
+          if constexpr (BF) {
+            // A = W_l^T from its transposed copy: 8 consecutive BF16 per lane
+            const __bf16* Wt = reinterpret_cast<const __bf16*>(smem + L.wt_off[l]) + n * (H + 8) + 16 * hf;
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj) {
+              const bf16x8 wa = *reinterpret_cast<const bf16x8*>(Wt + 8 * jj);
+#pragma unroll
+              for (int p = 0; p < 2; ++p)
+                nacc[p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, dl[p].v[0][jj], nacc[p], 0, 0, 0);
+            }
+          } else {
+            const float* W = reinterpret_cast<const float*>(smem + L.w_off[l]) + colpos(n);
+#pragma unroll
+            for (int qq = 0; qq < 16; ++qq) {
+              const float w = W[rowof(qq, hf) * L.w_stride[l]];
+#pragma unroll
+              for (int p = 0; p < 2; ++p)
+                nacc[p] = __builtin_amdgcn_mfma_f32_32x32x2f32(w, dl[p].v[0][qq], nacc[p], 0, 0, 0);
+            }
+          }
+        }
+        // stage delta_l (out features) and h_{l-1} (in features), sample-major, and accumulate the
+        // weight gradient dW_l += delta_l h_{l-1}^T over each pass's 32 samples
+        if constexpr (BF) {
           if (l > 0) {
 #pragma unroll
-            for (int mi = 0; mi < MT; ++mi) {
-              f32x16& acc = nacc[mi];
+            for (int p = 0; p < 2; ++p)
 #pragma unroll
-              for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-              const int col = mi * 32 + colpos(n);
-#pragma unroll
-              for (int ko = 0; ko < MT; ++ko) {
-                if constexpr (BF) {
-                  // A = W_l^T from its transposed copy: 8 consecutive BF16 per lane
-                  const __bf16* Wt = reinterpret_cast<const __bf16*>(smem + L.wt_off[l]) +
-                                     (mi * 32 + n) * (H + 8) + ko * 32 + 16 * hf;
-#pragma unroll
-                  for (int jj = 0; jj < 2; ++jj) {
-                    const bf16x8 wa = *reinterpret_cast<const bf16x8*>(Wt + 8 * jj);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, dl.v[ko][jj], acc, 0, 0, 0);
-                  }
-                } else {
-                  const float* W = reinterpret_cast<const float*>(smem + L.w_off[l]);
-#pragma unroll
-                  for (int qq = 0; qq < 16; ++qq)
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(W[(ko * 32 + rowof(qq, hf)) * ws + col],
-                                                               dl.v[ko][qq], acc, 0, 0, 0);
-                }
-              }
-            }
+              for (int jj = 0; jj < 2; ++jj)
+                write_runs(reinterpret_cast<__bf16*>(htile + p * kTile) + n * kTrStride + 16 * jj + 4 * hf, act[p].v[l][0][jj]);
           }
-          // stage delta_l (out features) and h_{l-1} (in features): BF16 sample-major runs, FP32
-          // sample-major
-          wave_lds_sync();
+          const unsigned char* const ht = l > 0 ? htile : etile;
+#pragma unroll
+          for (int p = 1; p >= 0; --p) {
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj)
+              write_runs(reinterpret_cast<__bf16*>(dtile) + n * kTrStride + 16 * jj + 4 * hf, dl[p].v[0][jj]);
+            wave_lds_order();
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj) {
+              // A and B operands (feature row lane & 31, samples 16jj + 8hf + 0..7): lane x of
+              // group G = lane / 16 addresses row 16jj + 8(G / 2) + x/4 at feature
+              // 16(G mod 2) + 4(x mod 4)
+              const int lo = (16 * jj + 8 * hf + ((lane & 15) >> 2)) * kTrStride + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+              const bf16x8 da = tr_read8(reinterpret_cast<const __bf16*>(dtile) + lo);
+              const bf16x8 hb = tr_read8(reinterpret_cast<const __bf16*>(ht + p * kTile) + lo);
+              accW[l][0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(da, hb, accW[l][0][0], 0, 0, 0);
+              // bias gradient: the 8 deltas' sum, two at a time (v_dot2)
+              typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+              typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+              const u4 dw = __builtin_bit_cast(u4, da);
+              const b2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+              float s = 0.f;
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(b2, (unsigned int)dw[e]), ones, s, false);
+              accDb[l][0] += s;
+            }
+            wave_lds_order();
+          }
+        } else {
+#pragma unroll
+          for (int p = 0; p < 2; ++p) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              reinterpret_cast<float*>(dtile)[n * (H + 4) + rowof(r, hf)] = dl[p].v[0][r];
+              reinterpret_cast<float*>(htile)[n * (H + 4) + rowof(r, hf)] = act[p].v[l][0][r];
+            }
+            wave_lds_order();
+#pragma unroll
+            for (int qq = 0; qq < 16; ++qq) {
+              const int s = 2 * qq + hf;
+              const float da = reinterpret_cast<const float*>(dtile)[s * (H + 4) + n];
+              const float hb = reinterpret_cast<const float*>(htile)[s * (H + 4) + n];
+              accW[l][0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(da, hb, accW[l][0][0], 0, 0, 0);
+              accDb[l][0] += da;
+            }
+            wave_lds_order();
+          }
+        }
+        if (l == 0) break;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
           if constexpr (BF) {
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-              for (int jj = 0; jj < 2; ++jj)
-                write_runs(reinterpret_cast<__bf16*>(dtile) + n * kTrStride + mt * 32 + 16 * jj + 4 * hf,
-                           dl.v[mt][jj]);
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-              for (int jj = 0; jj < 2; ++jj)
-                write_runs(reinterpret_cast<__bf16*>(htile) + n * kTrStride + kb * 32 + 16 * jj + 4 * hf,
-                           act.v[l][kb][jj]);
+            for (int jj = 0; jj < 2; ++jj) dl[p].v[0][jj] = relu_mask(round8(nacc[p], 8 * jj), act[p].v[l][0][jj]);
           } else {
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-              for (int r = 0; r < 16; ++r)
-                reinterpret_cast<float*>(dtile)[n * (H + 4) + mt * 32 + rowof(r, hf)] = dl.v[mt][r];
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-              for (int r = 0; r < 16; ++r)
-                reinterpret_cast<float*>(htile)[n * (H + 4) + kb * 32 + rowof(r, hf)] = act.v[l][kb][r];
+            for (int r = 0; r < 16; ++r) dl[p].set(0, r, (act[p].v[l][0][r] > 0.f) ? nacc[p][r] : 0.f);
           }
-          wave_lds_sync();
-          // weight gradient dW_l += delta_l h_{l-1}^T over the pass's 32 samples
-#pragma unroll
-          for (int mo = 0; mo < MT; ++mo) {
-#pragma unroll
-            for (int ki = 0; ki < KB; ++ki) {
-              if constexpr (BF) {
-#pragma unroll
-                for (int jj = 0; jj < 2; ++jj) {
-                  // A and B operands (feature row lane & 31, samples 16jj + 8hf + 0..7): lane x of
-                  // group G = lane / 16 addresses row 16jj + 8(G / 2) + x/4 at feature
-                  // 16(G mod 2) + 4(x mod 4)
-                  const int lo = (16 * jj + 8 * hf + ((lane & 15) >> 2)) * kTrStride + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-                  const bf16x8 da = tr_read8(reinterpret_cast<const __bf16*>(dtile) + lo + mo * 32);
-                  const bf16x8 hb = tr_read8(reinterpret_cast<const __bf16*>(htile) + lo + ki * 32);
-                  accW[l][mo][ki] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(da, hb, accW[l][mo][ki], 0, 0, 0);
-                  if (ki == 0) {  // bias gradient: the 8 deltas' sum, two at a time (v_dot2)
-                    typedef unsigned int u4 __attribute__((ext_vector_type(4)));
-                    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-                    const u4 dw = __builtin_bit_cast(u4, da);
-                    const b2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-                    float s = 0.f;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                      s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(b2, (unsigned int)dw[e]), ones, s, false);
-                    accDb[l][mo] += s;
-                  }
-                }
-              } else {
-#pragma unroll
-                for (int qq = 0; qq < 16; ++qq) {
-                  const int s = 2 * qq + hf;
-                  const float da = reinterpret_cast<const float*>(dtile)[s * (H + 4) + mo * 32 + n];
-                  const float hb = reinterpret_cast<const float*>(htile)[s * (H + 4) + ki * 32 + n];
-                  accW[l][mo][ki] = __builtin_amdgcn_mfma_f32_32x32x2f32(da, hb, accW[l][mo][ki], 0, 0, 0);
-                  if (ki == 0) accDb[l][mo] += da;
-                }
-              }
-            }
-          }
-          if (l == 0) break;
-          Deltas<H, BF> nd;
-#pragma unroll
-          for (int mi = 0; mi < MT; ++mi) {
-            const f32x16& acc = nacc[mi];
-            if constexpr (BF) {
-#pragma unroll
-              for (int jj = 0; jj < 2; ++jj) nd.v[mi][jj] = relu_mask(round8(acc, 8 * jj), act.v[l][mi][jj]);
-            } else {
-#pragma unroll
-              for (int r = 0; r < 16; ++r) {
-                const float hv = reinterpret_cast<const float*>(htile)[n * (H + 4) + mi * 32 + rowof(r, hf)];
-                nd.set(mi, r, (hv > 0.f) ? acc[r] : 0.f);
-              }
-            }
-          }
-          dl = nd;
         }
-      };
-      if constexpr (BF) {
-        backward_pass(1);
-        backward_pass(0);
-      } else {
-#pragma unroll 1
-        for (int p = 0; p < 2; ++p) backward_pass(p);
       }
     }  // sub-tiles
 
