@@ -148,6 +148,8 @@ __host__ __device__ constexpr int pair_tile_bytes(bool bf16) { return 32 * 36 * 
 // into copy w mod copies, and the partial is the copies' sum in order.
 __host__ __device__ constexpr int red_copies(int nwaves) { return nwaves >= 8 ? 4 : (nwaves >= 2 ? 2 : 1); }
 
+constexpr int kRedCopyBytes = (n_params_of(32) + 3) / 4 * 16;
+
 __host__ __device__ constexpr LdsLayout lds_layout(int H, bool bf16, int nwaves) {
   LdsLayout L{};
   const int es = bf16 ? 2 : 4;
@@ -183,7 +185,8 @@ __host__ __device__ constexpr LdsLayout lds_layout(int H, bool bf16, int nwaves)
   L.scratch_off = off;
   int scratch = nwaves * L.scratch_wave;
   // the tile's gradient at the end: red_copies(nwaves) copies, each summing a fixed set of waves
-  const int red = red_copies(nwaves) * round_up(n_params_of(H), 4) * 4;
+  // (four waves: a copy each, the fourth over the weights)
+  const int red = (nwaves == 4 ? 3 : red_copies(nwaves)) * round_up(n_params_of(H), 4) * 4;
   if (red > scratch) scratch = red;
   off = round_up(off + scratch, 16);
   L.total = off;
@@ -427,6 +430,7 @@ struct StepArgs {
   int32_t* t_next;
   int32_t* tile_bad;
   int lds_table;
+  int lds_rays;          // the table keeps the batch's ray offsets and object ids in LDS too
 };
 
 // The layered path (generic_width objects of one width H per launch chain). Row = sample:

@@ -106,12 +106,11 @@ __device__ __forceinline__ void write_runs(__bf16* p, bf16x8 v) {
 // XCD b mod 8, each with its own L2); when the grid has a workgroup per tile, the first n_tiles
 // workgroups of one XCD take consecutive tiles, so that an object's tiles (its weights, rays and
 // samples) share one L2 instead of being fetched into all eight. Workgroups past n_tiles (the
-// last dispatched) stay without a tile. Otherwise tile = workgroup index. Only for launches whose
+// last dispatched) stay without a tile. Otherwise tile = workgroup index (b of `blocks`). Only for launches whose
 // tiles all do work: each XCD gets an equal share of tiles, not of work.
-__device__ __forceinline__ int first_tile_of_block(int n_tiles) {
+__device__ __forceinline__ int first_tile_of_block(int b, int blocks, int n_tiles) {
   constexpr int kXcds = 8;
-  const int b = blockIdx.x;
-  if ((int)gridDim.x < n_tiles || b >= n_tiles) return b;
+  if (blocks < n_tiles || b >= n_tiles) return b;
   const int x = b % kXcds;
   int start = 0;
   for (int y = 0; y < x; ++y) start += (n_tiles - y + kXcds - 1) / kXcds;  // workgroups of XCD y
@@ -530,6 +529,23 @@ __device__ __forceinline__ void forward_pass(const float xt[4], const unsigned c
   }  // weights in LDS
 }
 
+// Cross-lane moves of the ray scans, by DPP (a VALU operand modifier, no LDS round trip). DPP
+// controls: row_shr:n (lane l takes lane l - n of its row of 16), row_shl:n (lane l + n),
+// row_ror:n (rotation by n lanes within a row),
+// wave_shr:1 / wave_shl:1 (lane l - 1 / l + 1 across the wave), row_bcast:15 (lane 15 of each row
+// into the next row, rows 1 and 3 written), row_bcast:31 (lane 31 into rows 2 and 3). Lanes whose
+// source does not exist keep 0; the scans below never use those lanes' results. A move reads its
+// source lane's register only if that lane is active, so every move runs with the whole wave
+// active (computed before any select that uses it, never in a conditional arm).
+constexpr int kDppRowShr = 0x110, kDppRowShl = 0x100, kDppRowRor = 0x120, kDppWaveShl1 = 0x130, kDppWaveShr1 = 0x138,
+              kDppBcast15 = 0x142, kDppBcast31 = 0x143;
+
+template <int CTRL, int ROW_MASK = 0xf>
+__device__ __forceinline__ float dpp_mov(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL,
+                                                               ROW_MASK, 0xf, false));
+}
+
 // Values of a wave's lower half (lanes 0..31, in lo) and upper half (in hi), on the lanes of both
 // halves, by one v_permlane32_swap_b32.
 __device__ __forceinline__ void half_split(float x, float& lo, float& hi) {
@@ -550,6 +566,20 @@ __device__ __forceinline__ float half_sum(float x) {
   float lo, hi;
   half_split(x, lo, hi);
   return lo + hi;
+}
+// Sum over the wave's lanes, on every lane, by lane swaps and rotations within rows of 16: the
+// additions of a butterfly over lane distances 32, 16, 8, 4, 2, 1 (the rotations meet values that
+// are already equal at that distance), without its LDS round trips.
+__device__ __forceinline__ float wave_sum(float x) {
+  x = half_sum(x);
+  const unsigned int u = __builtin_bit_cast(unsigned int, x);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  x = __builtin_bit_cast(float, (unsigned int)r[0]) + __builtin_bit_cast(float, (unsigned int)r[1]);
+  x += dpp_mov<kDppRowRor + 8>(x);
+  x += dpp_mov<kDppRowRor + 4>(x);
+  x += dpp_mov<kDppRowRor + 2>(x);
+  x += dpp_mov<kDppRowRor + 1>(x);
+  return x;
 }
 
 // Gaussian Fourier features of both passes' samples into layer 0 (register r of a lane of half hf
@@ -738,20 +768,30 @@ __device__ __forceinline__ RenderIn render_inputs(const StepArgs& a, int r0, int
   return in;
 }
 
-// Cross-lane moves of the ray scans, by DPP (a VALU operand modifier, no LDS round trip). DPP
-// controls: row_shr:n (lane l takes lane l - n of its row of 16), row_shl:n (lane l + n),
-// wave_shr:1 / wave_shl:1 (lane l - 1 / l + 1 across the wave), row_bcast:15 (lane 15 of each row
-// into the next row, rows 1 and 3 written), row_bcast:31 (lane 31 into rows 2 and 3). Lanes whose
-// source does not exist keep 0; the scans below never use those lanes' results. A move reads its
-// source lane's register only if that lane is active, so every move runs with the whole wave
-// active (computed before any select that uses it, never in a conditional arm).
-constexpr int kDppRowShr = 0x110, kDppRowShl = 0x100, kDppWaveShl1 = 0x130, kDppWaveShr1 = 0x138,
-              kDppBcast15 = 0x142, kDppBcast31 = 0x143;
+// Everything a lane loads for its slot of sub-tile `sub` of a tile of the width-32 kernel (rays
+// [ray_lo, ray_hi), rpw rays a sub-tile; a sub-tile past the tile's last has no slots).
+struct SubTileIn {
+  RenderIn r;
+  float o[3], d[3], var;
+};
 
-template <int CTRL, int ROW_MASK = 0xf>
-__device__ __forceinline__ float dpp_mov(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL,
-                                                               ROW_MASK, 0xf, false));
+template <bool TRAIN>
+__device__ __forceinline__ SubTileIn subtile_inputs(const StepArgs& a, int ray_lo, int ray_hi, int sub, int rpw) {
+  const int lane = threadIdx.x & 63;
+  const int r0 = ray_lo + sub * rpw;
+  const int nslots = max(0, min(rpw, ray_hi - r0)) * a.S;
+  SubTileIn in{};
+  in.r = render_inputs<TRAIN>(a, r0, nslots);
+  if (lane < nslots) {
+    const int ray = r0 + lane / a.S;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      in.o[c] = a.rays_o[3 * (size_t)ray + c];
+      in.d[c] = a.rays_d[3 * (size_t)ray + c];
+    }
+    if (a.var) in.var = a.var[(size_t)r0 * a.S + lane];
+  }
+  return in;
 }
 
 // Inclusive scans within the rays of a sub-tile. A ray is a segment of S consecutive lanes from
@@ -1049,10 +1089,53 @@ __device__ __forceinline__ void adam_elem(const AdamCoef& c, float g, float& th,
 // own tile_bad entry instead of the object's flag (which workgroup 0 may clear concurrently), and
 // k_reduce_adam reads those entries.
 
+// Inclusive scan over the wave by DPP: shifts within rows of 16, then lane 15 of each row into the
+// next row and lane 31 into rows 2 and 3 (every move with the whole wave active).
+__device__ __forceinline__ int wave_scan(int x) {
+  const int lane = threadIdx.x & 63, lr = lane & 15;
+  int y = __builtin_amdgcn_update_dpp(0, x, kDppRowShr + 1, 0xf, 0xf, false);
+  x += (lr >= 1) ? y : 0;
+  y = __builtin_amdgcn_update_dpp(0, x, kDppRowShr + 2, 0xf, 0xf, false);
+  x += (lr >= 2) ? y : 0;
+  y = __builtin_amdgcn_update_dpp(0, x, kDppRowShr + 4, 0xf, 0xf, false);
+  x += (lr >= 4) ? y : 0;
+  y = __builtin_amdgcn_update_dpp(0, x, kDppRowShr + 8, 0xf, 0xf, false);
+  x += (lr >= 8) ? y : 0;
+  y = __builtin_amdgcn_update_dpp(0, x, kDppBcast15, 0xa, 0xf, false);
+  x += ((lane >> 4) & 1) ? y : 0;
+  y = __builtin_amdgcn_update_dpp(0, x, kDppBcast31, 0xc, 0xf, false);
+  x += (lane >= 32) ? y : 0;
+  return x;
+}
+
+// Batch object j of a wave's lane j (at most 64 objects): first tile, tiles, ray segment and id.
+struct LaneTable {
+  int first, count, o0, o1, k;
+};
+
+// The tile table of a batch of at most 64 objects in registers: every wave of the workgroup scans
+// it by itself, without LDS or barriers. Returns the tile count or -1 as step_table does.
+__device__ __forceinline__ int step_table_small(const StepArgs& a, LaneTable& t) {
+  const int j = threadIdx.x & 63;
+  t = LaneTable{0, 0, 0, 0, -1};
+  bool ok = true;
+  if (j < a.n_objects) {
+    t.o0 = a.ray_offsets[j];
+    t.o1 = a.ray_offsets[j + 1];
+    t.k = a.object_ids[j];
+    ok = batch_segment_ok(j, a.n_objects, t.o0, t.o1, a.n_rays);
+    t.count = ok ? tiles_of(t.o1 - t.o0, a.rays_per_tile) : 0;
+  }
+  const int x = wave_scan(t.count);
+  t.first = x - t.count;
+  return __ballot(!ok) ? -1 : __builtin_amdgcn_readlane(x, 63);
+}
+
 // tbl[j] = first tile of batch object j, tbl[n_objects] = tiles: the exclusive scan of
 // ceil(rays_j / rays_per_tile) over the batch (the launch's objects share one width, so one tile
 // size); tray[j] = the batch's ray offsets (n_objects + 1 of them) and tk[j] = object ids, so that
-// a tile finds its object and rays in LDS. Returns the tile count, or -1 when the offsets fail
+// a tile finds its object and rays in LDS (without a.lds_rays they are read from the batch, and only
+// tbl is kept: the launcher's choice for many objects). Returns the tile count, or -1 when the offsets fail
 // the check of segment_ok (ray_offsets[0] = 0, every segment inside [0, n_rays] and in order,
 // ray_offsets[n] = n_rays); then no tile runs. Called by every thread of the workgroup.
 __device__ int step_table(const StepArgs& a, int32_t* tbl, int32_t* tray, int32_t* tk) {
@@ -1065,29 +1148,16 @@ __device__ int step_table(const StepArgs& a, int32_t* tbl, int32_t* tray, int32_
     int cnt = 0;
     if (j < a.n_objects) {
       const int o0 = a.ray_offsets[j], o1 = a.ray_offsets[j + 1];
-      tray[j] = o0;
-      tk[j] = a.object_ids[j];
-      if (j == a.n_objects - 1) tray[j + 1] = o1;
+      if (a.lds_rays) {
+        tray[j] = o0;
+        tk[j] = a.object_ids[j];
+        if (j == a.n_objects - 1) tray[j + 1] = o1;
+      }
       const bool ok = batch_segment_ok(j, a.n_objects, o0, o1, a.n_rays);
       bad |= !ok;
       cnt = ok ? tiles_of(o1 - o0, rpt) : 0;
     }
-    // inclusive scan over the wave by DPP: shifts within rows of 16, then lane 15 of each row
-    // into the next row and lane 31 into rows 2 and 3 (every move with the whole wave active)
-    int x = cnt;
-    const int lr = lane & 15;
-    int y = __builtin_amdgcn_update_dpp(0, x, kDppRowShr + 1, 0xf, 0xf, false);
-    x += (lr >= 1) ? y : 0;
-    y = __builtin_amdgcn_update_dpp(0, x, kDppRowShr + 2, 0xf, 0xf, false);
-    x += (lr >= 2) ? y : 0;
-    y = __builtin_amdgcn_update_dpp(0, x, kDppRowShr + 4, 0xf, 0xf, false);
-    x += (lr >= 4) ? y : 0;
-    y = __builtin_amdgcn_update_dpp(0, x, kDppRowShr + 8, 0xf, 0xf, false);
-    x += (lr >= 8) ? y : 0;
-    y = __builtin_amdgcn_update_dpp(0, x, kDppBcast15, 0xa, 0xf, false);
-    x += ((lane >> 4) & 1) ? y : 0;
-    y = __builtin_amdgcn_update_dpp(0, x, kDppBcast31, 0xc, 0xf, false);
-    x += (lane >= 32) ? y : 0;
+    const int x = wave_scan(cnt);
     if (lane == kWave - 1) wtot[wave] = x;
     __syncthreads();
     int before = carry, total = 0;
@@ -1127,20 +1197,37 @@ __global__ void __launch_bounds__((BF && H == 32) ? 512 : 256, 1) k_step_tiles(c
   int32_t* tk = tray + tbl_words;
   auto first_tile = [&](int j) { return TABLE ? tbl[j] : a.tile_start[j]; };
   int n_tiles;
+  LaneTable lt{};
+  const bool small = TABLE && a.n_objects <= kWave;
   if constexpr (TABLE) {
-    n_tiles = step_table(a, tbl, tray, tk);
+    if (small) {
+      n_tiles = step_table_small(a, lt);
+      if (wave == 0 && lane < a.n_objects) {  // for a workgroup's later tiles
+        tbl[lane] = lt.first;
+        tray[lane] = lt.o0;
+        tk[lane] = lt.k;
+        if (lane == a.n_objects - 1) {
+          tbl[lane + 1] = lt.first + lt.count;
+          tray[lane + 1] = lt.o1;
+        }
+      }
+    } else {
+      n_tiles = step_table(a, tbl, tray, tk);
+    }
     if (blockIdx.x == 0) {  // what k_worklist leaves for the optimiser
       if (tid == 0) {
         a.scaler->batch_ok = n_tiles >= 0;
         if (n_tiles < 0) atomicOr(&a.scaler->device_error, DERR_OFFSETS);
       }
+      if (small) __syncthreads();
       for (int j = tid; j <= a.n_objects; j += blockDim.x) a.tile_start_out[j] = n_tiles >= 0 ? tbl[j] : 0;
       for (int j = tid; j < a.n_objects; j += blockDim.x) {
-        const int k = tk[j];
+        const int k = a.lds_rays ? tk[j] : a.object_ids[j];
         const bool valid = k >= 0 && k < a.max_objects;
         if (valid) a.flags[k] = 0;
         a.t_next[j] = (valid && a.desc[k].registered) ? a.desc[k].step + 1 : 0;
       }
+      return;  // the other workgroups run the tiles
     }
   } else {
     n_tiles = a.tile_start[a.n_objects];
@@ -1153,24 +1240,42 @@ __global__ void __launch_bounds__((BF && H == 32) ? 512 : 256, 1) k_step_tiles(c
 
   // XCD-aware order only when every tile belongs to this launch (tiles of other widths would
   // crowd the XCDs that hold them)
-  for (int tile = TABLE ? first_tile_of_block(n_tiles) : (int)blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-    // object of this tile: the j with first_tile(j) <= tile < first_tile(j + 1) (objects without
-    // rays have an empty range), 64 candidates per wave at a time
-    int j = 0;
-    for (int base = 0; base < a.n_objects; base += kWave) {
-      const int jj = base + lane;
-      const bool hit = jj < a.n_objects && first_tile(jj) <= tile && tile < first_tile(jj + 1);
-      const unsigned long long m = __ballot(hit);
-      if (m) {
-        j = base + __ffsll((long long)m) - 1;
-        break;
+  // (with the table, workgroup 0 has published it and returned: the tiles' workgroups follow)
+  const int wg = TABLE ? (int)blockIdx.x - 1 : (int)blockIdx.x, wgs = TABLE ? (int)gridDim.x - 1 : (int)gridDim.x;
+  int tile = TABLE ? first_tile_of_block(wg, wgs, n_tiles) : wg;
+  // object of a tile: the j with first_tile(j) <= tile < first_tile(j + 1) (objects without rays
+  // have an empty range), 64 candidates per wave at a time; a workgroup's first tile of a small
+  // batch from the lanes' own entries
+  int j = 0, k = -1, o0 = 0, o1 = 0, ft = 0;
+  bool known = false;
+  if (small && tile < n_tiles) {
+    j = __ffsll((long long)__ballot(lt.first <= tile && tile < lt.first + lt.count)) - 1;
+    k = __builtin_amdgcn_readlane(lt.k, j);
+    o0 = __builtin_amdgcn_readlane(lt.o0, j);
+    o1 = __builtin_amdgcn_readlane(lt.o1, j);
+    ft = __builtin_amdgcn_readlane(lt.first, j);
+    known = true;
+  }
+  for (; tile < n_tiles; tile += wgs, known = false) {
+    if (!known) {
+      j = 0;
+      for (int base = 0; base < a.n_objects; base += kWave) {
+        const int jj = base + lane;
+        const bool hit = jj < a.n_objects && first_tile(jj) <= tile && tile < first_tile(jj + 1);
+        const unsigned long long m = __ballot(hit);
+        if (m) {
+          j = base + __ffsll((long long)m) - 1;
+          break;
+        }
       }
+      const bool lds = TABLE && a.lds_rays;
+      k = lds ? tk[j] : a.object_ids[j];
+      o0 = lds ? tray[j] : a.ray_offsets[j];
+      o1 = lds ? tray[j + 1] : a.ray_offsets[j + 1];
+      ft = first_tile(j);
     }
-    const int k = TABLE ? tk[j] : a.object_ids[j];
     const int rpt = tile_rays(H, a.rays_per_tile, a.rays_per_tile_wide);
-    const RayRange rr = tile_ray_range(TABLE ? tray[j] : a.ray_offsets[j],
-                                       TABLE ? tray[j + 1] : a.ray_offsets[j + 1],
-                                       tile - first_tile(j), rpt, a.n_rays);
+    const RayRange rr = tile_ray_range(o0, o1, tile - ft, rpt, a.n_rays);
     const int ray_lo = rr.lo, ray_hi = rr.hi;
     const int nrays = ray_hi - ray_lo;
     const int nsub = (nrays + rpw - 1) / rpw;
@@ -1190,17 +1295,29 @@ __global__ void __launch_bounds__((BF && H == 32) ? 512 : 256, 1) k_step_tiles(c
     const int registered = od.registered, hidden = od.hidden;
     const double cx = od.centre[0], cy = od.centre[1], cz = od.centre[2];
     const double inv_s = od.inv_scale;
-    float wseed = 1.0f;
+    float wseed = 1.0f, inv = 1.0f;
     if constexpr (TRAIN) {
       if (a.dloss) wseed = a.dloss[j];
-      if (a.use_scale) wseed *= a.scaler->scale;
+      if (a.use_scale) {
+        const float scale = a.scaler->scale;
+        wseed *= scale;
+        inv = 1.0f / scale;
+      }
     }
+    // the wave's first sub-tile's inputs are touched while the image is on its way (kept in
+    // registers across the loop they would spill)
+    const SubTileIn warm = subtile_inputs<TRAIN>(a, ray_lo, ray_hi, wave, rpw);
     if (!k_ok || !registered) {
       if (tid == 0) atomicOr(&a.scaler->device_error, 1);
+      if (TABLE) __syncthreads();  // (the table in LDS is complete before a later tile reads it)
       continue;
     }
-    if (kernel_width(hidden) != H) continue;  // handled by the launch for that width
+    if (kernel_width(hidden) != H) {  // handled by the launch for that width
+      if (TABLE) __syncthreads();
+      continue;
+    }
     if (restage) {
+      asm volatile("" ::"v"(warm.r.tt), "v"(warm.r.D), "v"(warm.r.M), "v"(warm.r.rgb[0]), "v"(warm.o[0]), "v"(warm.d[0]));
       __builtin_amdgcn_s_waitcnt(0);  // this thread's part of the image is in LDS
       staged = k;
     }
@@ -1250,19 +1367,17 @@ __global__ void __launch_bounds__((BF && H == 32) ? 512 : 256, 1) k_step_tiles(c
       const int r0 = ray_lo + sub * rpw;
       const int nr = min(rpw, ray_hi - r0);
       const int nslots = nr * S;
-      const RenderIn rin = render_inputs<TRAIN>(a, r0, nslots);
+      SubTileIn in = subtile_inputs<TRAIN>(a, ray_lo, ray_hi, sub, rpw);
+      const RenderIn rin = in.r;
       // the lane's own sample: normalised point and (integrated encoding) normalised variance,
       // then handed to the two lanes that hold its pass's column
       float x[4] = {0.f, 0.f, 0.f, 0.f}, xt[2][4];
       if (lane < nslots) {
-        const int ray = r0 + lane / S;
         const double tt = (double)rin.tt;
-        const float* o3 = a.rays_o + 3 * (size_t)ray;
-        const float* d3 = a.rays_d + 3 * (size_t)ray;
-        x[0] = (float)(((double)o3[0] + tt * (double)d3[0] - cx) * inv_s);
-        x[1] = (float)(((double)o3[1] + tt * (double)d3[1] - cy) * inv_s);
-        x[2] = (float)(((double)o3[2] + tt * (double)d3[2] - cz) * inv_s);
-        if (a.var) x[3] = (float)((double)a.var[(size_t)r0 * S + lane] * inv_s * inv_s);
+        x[0] = (float)(((double)in.o[0] + tt * (double)in.d[0] - cx) * inv_s);
+        x[1] = (float)(((double)in.o[1] + tt * (double)in.d[1] - cy) * inv_s);
+        x[2] = (float)(((double)in.o[2] + tt * (double)in.d[2] - cz) * inv_s);
+        if (a.var) x[3] = (float)((double)in.var * inv_s * inv_s);
       }
 #pragma unroll
       for (int c = 0; c < 4; ++c) half_split(x[c], xt[0][c], xt[1][c]);
@@ -1280,7 +1395,9 @@ __global__ void __launch_bounds__((BF && H == 32) ? 512 : 256, 1) k_step_tiles(c
 
       float dzs[kOut];
       render_subtile<TRAIN>(a, r0, nslots, wseed, rin, zs, dzs, wave_loss);
-      if constexpr (!TRAIN) continue;
+      if constexpr (!TRAIN) {
+        continue;
+      }
 #pragma unroll
       for (int c = 0; c < kOut; ++c) accDbH[c] += dzs[c];
 
@@ -1487,29 +1604,33 @@ __global__ void __launch_bounds__((BF && H == 32) ? 512 : 256, 1) k_step_tiles(c
 
     // ---------------- combine the waves of the workgroup in a fixed order
     // per-wave reductions in registers first
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) wave_loss += __shfl_xor(wave_loss, off);
+    wave_loss = wave_sum(wave_loss);
     if constexpr (TRAIN) {
 #pragma unroll
       for (int c = 0; c < kOut; ++c) {
+        accDbH[c] = wave_sum(accDbH[c]);
 #pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) accDbH[c] += __shfl_xor(accDbH[c], off);
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) accH[c][mt] += __shfl_xor(accH[c][mt], 32);
+        for (int mt = 0; mt < MT; ++mt) accH[c][mt] = half_sum(accH[c][mt]);
       }
 #pragma unroll
       for (int l = 0; l < kLayers; ++l)
 #pragma unroll
-        for (int mo = 0; mo < MT; ++mo) accDb[l][mo] += __shfl_xor(accDb[l][mo], 32);
+        for (int mo = 0; mo < MT; ++mo) accDb[l][mo] = half_sum(accDb[l][mo]);
     }
-    __syncthreads();  // staging buffers are free: reuse them for the tile's gradient
-    // nc copies of the tile's gradient and loss (two for two to seven waves, four for eight): the
-    // first nc waves write them, the others then add theirs in turn (copy c = waves c, c + nc, ...,
-    // in that order); the partial is the sum of the copies in order.
-    constexpr int kRedWords = round_up(n_params_of(H), 4);
-    const int nc = red_copies(nw);
+    __syncthreads();  // staging buffers and weights are free: reuse them for the tile's gradient
+    // nc copies of the tile's gradient and loss. Four waves write a copy each (the fourth over the
+    // weights, which the next tile stages again) and the partial is (0 + 2) + (1 + 3): one barrier,
+    // no read-modify-write (two copies, to which waves 2 and 3 added theirs after a barrier, took
+    // 7.9 thousand cycles to the sum, a fifth of a tile of two sub-tiles per wave). Other wave
+    // counts keep red_copies(nw) copies (two for two to seven waves, four for eight): the first nc
+    // waves write them, the others then add theirs in turn (copy c = waves c, c + nc, ..., in that
+    // order), and the partial is the sum of the copies in order: the same sum for four waves.
+    constexpr int kRedWords = kRedCopyBytes / 4;
+    const bool four = (nw == 4);
+    const int nc = four ? 4 : red_copies(nw);
     float* red0 = reinterpret_cast<float*>(smem + L.scratch_off);
-    float* red = red0 + (wave % nc) * kRedWords;
+    float* red3 = four ? reinterpret_cast<float*>(smem) : red0 + 3 * kRedWords;  // the fourth copy
+    float* red = (wave % nc == 3) ? red3 : red0 + (wave % nc) * kRedWords;
     float* lsum = reinterpret_cast<float*>(smem + L.loss_off);
     int* any_bad = reinterpret_cast<int*>(smem + L.loss_off + 16);
     if (tid == 0) *any_bad = 0;  // read after the barriers below
@@ -1517,7 +1638,7 @@ __global__ void __launch_bounds__((BF && H == 32) ? 512 : 256, 1) k_step_tiles(c
     // here, not hoisted to the kernel's start and kept (spilled) across the sub-tiles
     int rl = lane;
     asm volatile("" : "+v"(rl));
-    const int rn = rl & 31, rh = rl >> 5;
+    const int rn = rl & 31, rh = rl >> 5, et = 64 * wave + rl;
     for (int ph = 0; ph < (nw + nc - 1) / nc; ++ph) {
       if (wave / nc == ph) {
         const bool first = (ph == 0);
@@ -1567,7 +1688,7 @@ __global__ void __launch_bounds__((BF && H == 32) ? 512 : 256, 1) k_step_tiles(c
               }
           }
           off += kOut * H;
-          if (lane == 0) {
+          if (rl == 0) {
 #pragma unroll
             for (int c = 0; c < kOut; ++c) red[off + c] = (first ? 0.f : red[off + c]) + accDbH[c];
           }
@@ -1578,17 +1699,25 @@ __global__ void __launch_bounds__((BF && H == 32) ? 512 : 256, 1) k_step_tiles(c
     if constexpr (TRAIN) {
       // unscale (exact: the scale is a power of two) and report a partial that is not finite or
       // too large to be summed safely (partial_bad)
-      const int P = n_params_of(H);
-      const float inv = a.use_scale ? 1.0f / a.scaler->scale : 1.0f;
-      float* dst = a.partial + (size_t)tile * a.p_stride;
+      static_assert(n_params_of(H) % 4 == 0, "the partial is written four elements at a time");
+      float* dst = a.partial + (size_t)tile * a.p_stride;  // (p_stride is a multiple of 64)
       int bad = 0;
-      for (int e = tid; e < P; e += blockDim.x) {
-        float g = red0[e];
-        for (int c = 1; c < nc; ++c) g += red0[c * kRedWords + e];
-        g *= inv;
-        bad |= partial_bad(g);
-        __builtin_nontemporal_store(g, &dst[e]);  // read once, by the next kernel
+      for (int e = 4 * et; e < n_params_of(H); e += 4 * blockDim.x) {
+        f32x4 g = *reinterpret_cast<const f32x4*>(red0 + e);
+        if (four) {
+          g = (g + *reinterpret_cast<const f32x4*>(red0 + 2 * kRedWords + e)) +
+              (*reinterpret_cast<const f32x4*>(red0 + kRedWords + e) + *reinterpret_cast<const f32x4*>(red3 + e));
+        } else {
+          for (int c = 1; c < nc; ++c) g += *reinterpret_cast<const f32x4*>((c == 3 ? red3 : red0 + c * kRedWords) + e);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          g[i] *= inv;
+          bad |= partial_bad(g[i]);
+        }
+        __builtin_nontemporal_store(g, reinterpret_cast<f32x4*>(dst + e));  // read once, by the next kernel
       }
+      if (four) staged = -1;  // the fourth copy lies over the weights
       if (bad) *any_bad = 1;  // every writer stores the same value
       __syncthreads();
       if (tid == 0) {
@@ -1598,7 +1727,8 @@ __global__ void __launch_bounds__((BF && H == 32) ? 512 : 256, 1) k_step_tiles(c
     }
     if (tid == 0) {
       float l = lsum[0];
-      for (int c = 1; c < nc; ++c) l += lsum[c];
+      if (four) l = (l + lsum[2]) + (lsum[1] + lsum[3]);
+      else for (int c = 1; c < nc; ++c) l += lsum[c];
       a.tile_loss[tile] = l;
     }
     __syncthreads();
@@ -2800,11 +2930,17 @@ static hipError_t launch_tiles_t(const StepArgs& a_in, int nwaves, int grid, hip
   int bytes;
   if constexpr (H == 32) {
     fn = reinterpret_cast<const void*>(k_step_tiles<H, BF, MODE>);
-    bytes = lds_layout(H, BF, nwaves).total;
+    // forward mode stages weights only, so that more workgroups fit on a CU (with the training
+    // staging it ran two waves per SIMD instead of the four its registers allow)
+    bytes = MODE == MODE_FWD ? lds_layout(H, BF, nwaves).scratch_off : lds_layout(H, BF, nwaves).total;
     if constexpr (MODE == MODE_STEP) {  // the tile table follows the layout
       if (a.n_objects > kTableMaxObjects || !a.tile_bad) return hipErrorInvalidValue;
       a.lds_table = bytes;  // first tiles, ray offsets and object ids
-      bytes += 3 * round_up(a.n_objects + 1, 4) * 4;
+      const int words = round_up(a.n_objects + 1, 4) * 4;
+      // past about 500 objects the three arrays would leave room for one workgroup on a CU, not
+      // two: a load per tile from the batch costs less than half the waves
+      a.lds_rays = 2 * (bytes + 3 * words) <= 160 * 1024;
+      bytes += (a.lds_rays ? 3 : 1) * words;
     }
   } else {
     static_assert(MODE != MODE_STEP, "the in-kernel tile table is built for width 32 only");
@@ -2814,8 +2950,9 @@ static hipError_t launch_tiles_t(const StepArgs& a_in, int nwaves, int grid, hip
   }
   hipError_t e = allow_lds(fn, bytes, &allowed);
   if (e != hipSuccess) return e;
+  // (with the table, a workgroup more: the first publishes it for the optimiser)
   if constexpr (H == 32)
-    hipLaunchKernelGGL((k_step_tiles<H, BF, MODE>), dim3(grid), dim3(nwaves * kWave), bytes, s, a);
+    hipLaunchKernelGGL((k_step_tiles<H, BF, MODE>), dim3(MODE == MODE_STEP ? grid + 1 : grid), dim3(nwaves * kWave), bytes, s, a);
   else
     hipLaunchKernelGGL((k_step_coop<H, BF, MODE>), dim3(grid), dim3(nwaves * kWave), bytes, s, a);
   return hipGetLastError();
