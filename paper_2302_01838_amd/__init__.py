@@ -208,11 +208,13 @@ class ObjectSet:
         # launch shape from the autotuner's cache when none is given
         self.tuned = None
         if rays_per_tile == 0 and autotune:
-            from .tune import lookup
+            from .tune import fit_rays_per_tile, lookup
             # hidden 16 runs in the width-32 kernels (zero-padded) and takes their tuned shape
             self.tuned = lookup(32 if hidden == 16 else hidden, max_samples_per_ray, precision)
             if self.tuned:
                 rays_per_tile = int(self.tuned["rays_per_tile"])
+                if (max_hidden or hidden) <= 32 and rays_per_tile > 0:
+                    rays_per_tile = fit_rays_per_tile(self.tuned, max_samples_per_ray, max_rays, max_objects)
         if rays_per_tile_wide == 0 and autotune and (max_hidden or hidden) > 32:
             from .tune import lookup
             wide = lookup(max_hidden or hidden, max_samples_per_ray, precision)
@@ -245,8 +247,8 @@ class ObjectSet:
         self.ctx = ctx
         self.n_params: Dict[int, int] = {}
         self.p_stride = 0
-        # launch shape (the library's default tile: two sub-tiles of floor(64 / S) rays for each
-        # of four waves)
+        # launch shape (without a tuned one the library picks the tile from the capacity; the figure
+        # kept here is its tile of two sub-tiles of floor(64 / S) rays for each of four waves)
         self.rays_per_tile = rays_per_tile or max(1, 64 // max_samples_per_ray) * 8
         self.waves, self.grid = 4, 0
         if self.tuned:

@@ -72,10 +72,32 @@ const char* check_config(const vmap_config* c) {
   return nullptr;
 }
 
+// Rays per tile of the width-32 kernel: whole rounds of a four-wave workgroup (a sub-tile per wave
+// each). A launch of width-32 objects lasts as long as the most rounds one workgroup slot gets, and
+// a round takes the time a wave needs for its chain of dependent products whether the chip is full
+// or not. So the tile is the shortest whose tiles, at the stack's capacity, all run at once (512
+// workgroups in BF16, 256 in FP32, which runs one wave per SIMD): BF16 50 objects of 120 rays at
+// S = 10, 22.9 us per step with one round a tile against 27.0 with two, and 18.9 against 23.4 with
+// one object. Past one round two are kept (200 such objects: 56 against 60 us), and in BF16 three
+// or four where they fit and two do not: 18,132 rays at S = 20, 530 tiles of three rounds take
+// 55 us, 404 of four 47. FP32 takes one round also where the estimate is up to an eighth over the
+// slots: it gains 17 us where the tiles fit after all (50 objects of 120 rays: 36 against 51 us)
+// and loses 11 where they do not. Capacity decides, not the batch: an object's sums do not depend
+// on the other objects of its batch. Stacks with wider objects keep two rounds (the tile bounds
+// the number of their far larger partials).
 int default_rays_per_tile(const vmap_config* c) {
   if (c->rays_per_tile > 0) return c->rays_per_tile;
   const int rpw = std::max(1, kSlots / c->max_samples_per_ray);
-  return rpw * 4 * 2;  // two sub-tiles per wave of a four-wave block
+  const int round = rpw * 4;
+  if (kernel_width(c->max_hidden) != 32) return round * 2;
+  const bool bf = c->precision == VMAP_BF16;
+  const int slots = bf ? 512 : 256;
+  for (int m = 1; m <= (bf ? 4 : 2); ++m) {
+    // an object's last tile is half empty on average
+    const long long tiles = ((long long)c->max_rays + round * m - 1) / (round * m) + c->max_objects / 2;
+    if (tiles <= slots + (!bf && m == 1 ? slots / 8 : 0)) return round * m;
+  }
+  return round * 2;
 }
 
 // Objects wider than 32 run in the cooperative kernel, whose tiles hold whole rounds (a sub-tile
