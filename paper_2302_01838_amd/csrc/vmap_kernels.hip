@@ -1735,6 +1735,498 @@ __global__ void __launch_bounds__((BF && H == 32) ? 512 : 256, 1) k_step_tiles(c
   }
 }
 
+// Batch object of element t (a row tile, row block or work tile) of a chain given by its exclusive
+// scan: the largest j below n_objects with scan[j] <= t (objects without elements have an empty
+// range and are passed over; scan[0] = 0 <= t). Searched by the whole wave, 64 ways at a time: the
+// lanes read 64 evenly spaced entries of the remaining range together and a ballot keeps the last
+// one at or below t, so a lookup waits on ceil(log64 n) loads rather than log2 n dependent ones.
+// Every lane of the wave must be active and pass the same t.
+__device__ __forceinline__ int gen_object(const int32_t* __restrict__ scan, int n_objects, int t) {
+  const int lane = (int)(threadIdx.x & 63);
+  int lo = 0, len = n_objects;  // the answer lies in [lo, lo + len), scan[lo] <= t
+  while (len > 1) {
+    const int step = (len + 63) >> 6;
+    const int i = lane * step;
+    const bool le = i < len && scan[lo + i] <= t;  // a prefix of the lanes (scan is nondecreasing)
+    const int c = __popcll(__ballot(le)) - 1;      // lane 0 always counts
+    lo += c * step;
+    len = min(step, len - c * step);
+  }
+  return lo;
+}
+
+// Sum of the eight BF16 of an MFMA operand, two at a time (v_dot2 against ones), added to s.
+__device__ __forceinline__ float operand_sum(bf16x8 v, float s) {
+  typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+  typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+  const u4 w = __builtin_bit_cast(u4, v);
+  const b2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+#pragma unroll
+  for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(b2, (unsigned int)w[e]), ones, s, false);
+  return s;
+}
+
+// ---------------------------------------------------------------------------------------------
+// Tile kernel for hidden 64 in BF16: the four waves of a workgroup take a sub-tile each and split
+// every weight gradient by rows, over the 128 samples of the four waves' current pass, as
+// k_step_coop does (below). Two workgroups fit on a CU (256 registers, 77 KB of LDS), so that one
+// runs while the other waits at a barrier or for its chain of products:
+//   - the forward takes a sub-tile's two passes together (each weight operand read once for both);
+//     each pass's activations are recomputed for its backward, from its encoding (kept through the
+//     rendering they spill);
+//   - the input-gradient products read W transposed (ds_read_b64_tr_b16) from the forward's copy;
+//   - deltas and activations are staged sample-major in 8-byte runs and read transposed, where
+//     k_step_coop stores single BF16 values.
+// The LDS reads bound it: per round of four sub-tiles about 1.3 MB a CU, 10 thousand cycles.
+// 256 objects, 558,935 rays of 32 samples: 7.05 ms for k_step_coop (one wave per SIMD, 412
+// registers), 2.81 ms here.
+
+struct Lds64 {
+  int w_off[kLayers];  // W_l, BF16, permuted columns, row stride 40 (l = 0) or 72
+  int bA_off;          // biases as (hi, mid, lo, 0 ...): 16 bytes per row
+  int whb_off;         // output weights [4][72], permuted columns
+  int whtb_off;        // output weights transposed [64][4]
+  int bh_off, B_off, loss_off;
+  int scratch_off, scratch_wave, total;
+};
+constexpr int kS64 = 68;                                          // BF16 elements per staged sample
+constexpr int kDz64 = kDzRowsBytes + 32 * kOut * 2;               // seeds of a pass (both layouts)
+constexpr int kTile64 = 32 * kS64 * 2;
+__host__ __device__ constexpr int w_stride64(int l) { return l == 0 ? kEnc + 8 : 72; }
+__host__ __device__ constexpr Lds64 lds64() {
+  Lds64 L{};
+  int off = 0;
+  for (int l = 0; l < kLayers; ++l) {
+    L.w_off[l] = off;
+    off += 64 * w_stride64(l) * 2;
+  }
+  L.bA_off = off; off += kLayers * 64 * 16;
+  L.whb_off = off; off += kOut * 72 * 2;
+  L.whtb_off = off; off += 64 * kOut * 2;
+  L.bh_off = off; off += 16;
+  L.B_off = off; off += 3 * kFeatures * 4;
+  L.loss_off = off; off += 32;
+  L.scratch_off = round_up(off, 16);
+  L.scratch_wave = kDz64 + 2 * kTile64;
+  L.total = L.scratch_off + 4 * L.scratch_wave;
+  return L;
+}
+static_assert(2 * lds64().total <= 160 * 1024, "two workgroups of the hidden-64 kernel on a CU");
+
+// Eight BF16 of a transposing read: rows r..r+3 at p, rows further down at p + second.
+__device__ __forceinline__ bf16x8 tr_read_pair(const __bf16* p, int second) {
+  typedef __attribute__((address_space(3))) v4i16 lds_v4;
+  const v4i16 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4*)(p));
+  const v4i16 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4*)(p + second));
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// Object's parameters into LDS by 256 threads, 16-byte loads all in flight together.
+__device__ __forceinline__ void stage64(const float* __restrict__ th, unsigned char* smem, int tid) {
+  asm volatile("" : "+v"(tid));  // (addresses are computed here, not kept from the kernel's start)
+  constexpr Lds64 L = lds64();
+  constexpr int H = 64;
+  f32x4 x[14];
+  int q = 0;
+#pragma unroll
+  for (int l = 0; l < kLayers; ++l) {
+    const float* W = th + layer_param_off(H, l);
+#pragma unroll
+    for (int i = 0; i < (l == 0 ? 2 : 4); ++i) x[q++] = *reinterpret_cast<const f32x4*>(W + 4 * (tid + 256 * i));
+  }
+  const int bl = tid >> 6, br = tid & 63;
+  const float b = th[layer_param_off(H, bl) + H * (bl == 0 ? kEnc : H) + br];
+  const float wh = th[layer_param_off(H, kLayers) + tid];
+  const float bh = tid < kOut ? th[layer_param_off(H, kLayers) + kOut * H + tid] : 0.f;
+  typedef unsigned int u2w __attribute__((ext_vector_type(2)));
+  q = 0;
+#pragma unroll
+  for (int l = 0; l < kLayers; ++l) {
+    const int K = (l == 0) ? kEnc : H;
+#pragma unroll
+    for (int i = 0; i < (l == 0 ? 2 : 4); ++i, ++q) {
+      const int e = 4 * (tid + 256 * i), row = e / K, col = e % K;
+      *reinterpret_cast<u2w*>(smem + L.w_off[l] + (row * w_stride64(l) + (col & ~31) + colpos(col & 31)) * 2) =
+          u2w{pack2(x[q][0], x[q][1]), pack2(x[q][2], x[q][3])};
+    }
+  }
+  const __bf16 hi = (__bf16)b;
+  const __bf16 mid = (__bf16)(b - (float)hi);
+  const __bf16 lo = (__bf16)((b - (float)hi) - (float)mid);
+  bf16x8 pieces = {};
+  pieces[0] = hi;
+  pieces[1] = mid;
+  pieces[2] = lo;
+  *reinterpret_cast<bf16x8*>(smem + L.bA_off + 16 * tid) = pieces;
+  reinterpret_cast<__bf16*>(smem + L.whb_off)[bl * 72 + (br & ~31) + colpos(br & 31)] = (__bf16)wh;
+  reinterpret_cast<__bf16*>(smem + L.whtb_off)[br * kOut + bl] = (__bf16)wh;
+  if (tid < kOut) reinterpret_cast<float*>(smem + L.bh_off)[tid] = bh;
+}
+
+// One layer of NP passes: out = ReLU(W_l in + b), rounded to BF16 in the accumulator layout.
+template <int NP>
+__device__ __forceinline__ void layer64(const unsigned char* smem, int l, int lane, const bf16x8 (&in)[NP][2][2],
+                                        bf16x8 (&out)[NP][2][2]) {
+  constexpr Lds64 L = lds64();
+  const int n = lane & 31, hf = lane >> 5, ws = w_stride64(l), KB = (l == 0) ? 1 : 2;
+  asm volatile("" ::: "memory");  // weight reads stay in their layer
+  f32x16 zero;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) zero[r] = 0.f;
+#pragma unroll
+  for (int mo = 0; mo < 2; ++mo) {
+    bf16x8 ba = {};
+    if (hf == 0) ba = *reinterpret_cast<const bf16x8*>(smem + L.bA_off + 16 * (l * 64 + mo * 32 + n));
+    const bf16x8 ones3 = {(__bf16)1.0f, (__bf16)1.0f, (__bf16)1.0f, (__bf16)0.0f,
+                          (__bf16)0.0f, (__bf16)0.0f, (__bf16)0.0f, (__bf16)0.0f};
+    const f32x16 b16 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ba, ones3, zero, 0, 0, 0);
+    f32x16 acc[NP];
+    const __bf16* wrow = reinterpret_cast<const __bf16*>(smem + L.w_off[l]) + (mo * 32 + n) * ws + 16 * hf;
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+      for (int jj = 0; jj < 2; ++jj) {
+        const bf16x8 wa = *reinterpret_cast<const bf16x8*>(wrow + kb * 32 + 8 * jj);
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+          acc[p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, in[p][kb][jj], (kb == 0 && jj == 0) ? b16 : acc[p], 0, 0, 0);
+      }
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+      for (int jj = 0; jj < 2; ++jj) out[p][mo][jj] = relu_round8(acc[p], 8 * jj);
+  }
+}
+
+template <int MODE>
+__global__ void __launch_bounds__(256, 2) k_step_64(const StepArgs a_in) {
+  constexpr int H = 64;
+  constexpr bool TRAIN = (MODE == MODE_TRAIN);
+  constexpr Lds64 L = lds64();
+  constexpr int RW = H / 4;         // weight-gradient rows of one wave
+  StepArgs a = a_in;
+  read_batch(a);
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int tid = threadIdx.x, lane_ = tid & 63, wave = tid >> 6;
+  const int S = a.S;
+  const int rpw = kSlots / S;
+  const int n_tiles = clamp_tiles(a.tile_start[a.n_objects], a.max_tiles);
+  float* Bl = reinterpret_cast<float*>(smem + L.B_off);
+  if (tid < 3 * kFeatures) Bl[tid] = a.B[tid];
+  int staged = -1;
+
+  for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+    const int j = gen_object(a.tile_start, a.n_objects, tile);
+    const int k = __builtin_amdgcn_readfirstlane(a.object_ids[j]);
+    if (k < 0 || k >= a.max_objects || !a.desc[k].registered) {
+      if (tid == 0) atomicOr(&a.scaler->device_error, 1);
+      continue;
+    }
+    if (kernel_width(a.desc[k].hidden) != H) continue;
+    const int rpt = tile_rays(H, a.rays_per_tile, a.rays_per_tile_wide);
+    const RayRange rr = tile_ray_range(a.ray_offsets[j], a.ray_offsets[j + 1], tile - a.tile_start[j],
+                                       rpt, a.n_rays);
+    const int ray_lo = rr.lo, ray_hi = rr.hi;
+    if (k != staged) {
+      __syncthreads();
+      stage64(a.theta + (size_t)k * a.p_stride, smem, tid);
+      staged = k;
+    }
+    __syncthreads();
+    const double cx = a.desc[k].centre[0], cy = a.desc[k].centre[1], cz = a.desc[k].centre[2];
+    const double inv_s = a.desc[k].inv_scale;
+    float wseed = 1.0f, inv = 1.0f;
+    if constexpr (TRAIN) {
+      if (a.dloss) wseed = a.dloss[j];
+      if (a.use_scale) {
+        const float scale = a.scaler->scale;
+        wseed *= scale;
+        inv = 1.0f / scale;
+      }
+    }
+
+    f32x4 accW[kLayers][4];  // this wave's 16 rows of dW_l, 16-column blocks (layer 0: two)
+    float accDb[kLayers];    // lane sums of this wave's rows of db_l
+    f32x4 accWh;             // this wave's 16 columns of the output layer's dW
+    float accDbH[kOut];
+    if constexpr (TRAIN) {
+#pragma unroll
+      for (int l = 0; l < kLayers; ++l) {
+        accDb[l] = 0.f;
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) accW[l][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+      accWh = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < kOut; ++c) accDbH[c] = 0.f;
+    }
+    float wave_loss = 0.f;
+    unsigned char* const scr0 = smem + L.scratch_off;
+    unsigned char* const dzt = scr0 + wave * L.scratch_wave;
+    unsigned char* const dtile = dzt + kDz64;
+    unsigned char* const htile = dtile + kTile64;
+    const int nsub = (ray_hi - ray_lo + rpw - 1) / rpw;
+    const int rounds = (nsub + 3) / 4;
+
+    // Every wave runs every round (a wave without a sub-tile carries zero seeds), since the
+    // weight-gradient products of a round read all four waves' staging tiles.
+    for (int rd = 0; rd < rounds; ++rd) {
+      // (lane-dependent LDS addresses are computed where they are used, not hoisted and spilled)
+      int ln = lane_;
+      asm volatile("" : "+v"(ln)::"memory");
+      const int lane = ln, n = ln & 31, hf = ln >> 5;
+      const int sub = rd * 4 + wave;
+      const int r0 = ray_lo + sub * rpw;
+      const int nslots = max(0, min(rpw, ray_hi - r0)) * S;
+      const SubTileIn in = subtile_inputs<TRAIN>(a, ray_lo, ray_hi, sub, rpw);
+      float x[4] = {0.f, 0.f, 0.f, 0.f}, xt[2][4];
+      if (lane < nslots) {
+        const double tt = (double)in.r.tt;
+        x[0] = (float)(((double)in.o[0] + tt * (double)in.d[0] - cx) * inv_s);
+        x[1] = (float)(((double)in.o[1] + tt * (double)in.d[1] - cy) * inv_s);
+        x[2] = (float)(((double)in.o[2] + tt * (double)in.d[2] - cz) * inv_s);
+        if (a.var) x[3] = (float)((double)in.var * inv_s * inv_s);
+      }
+#pragma unroll
+      for (int c = 0; c < 4; ++c) half_split(x[c], xt[0][c], xt[1][c]);
+      Acts<32, true> E[2];  // layer 0 only: the encodings
+      if (a.var) encode_pair<true, true>(xt, Bl, hf, E);
+      else encode_pair<true, false>(xt, Bl, hf, E);
+
+      // forward of both passes, for the outputs alone
+      bf16x8 h[2][2][2];
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj) h[p][0][jj] = E[p].v[0][0][jj];
+#pragma unroll
+      for (int l = 0; l < kLayers; ++l) {
+        bf16x8 o[2][2][2];
+        layer64<2>(smem, l, lane, h, o);
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+          for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj) h[p][mt][jj] = o[p][mt][jj];
+      }
+      f32x16 zero;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) zero[r] = 0.f;
+      float zs[kOut];
+      {
+        const __bf16* wh = reinterpret_cast<const __bf16*>(smem + L.whb_off) + n * 72 + 16 * hf;
+        f32x16 acc[2] = {zero, zero};
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+          for (int jj = 0; jj < 2; ++jj) {
+            bf16x8 wa = {};
+            if (n < kOut) wa = *reinterpret_cast<const bf16x8*>(wh + mt * 32 + 8 * jj);
+#pragma unroll
+            for (int p = 0; p < 2; ++p) acc[p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, h[p][mt][jj], acc[p], 0, 0, 0);
+          }
+        const float* bh = reinterpret_cast<const float*>(smem + L.bh_off);
+#pragma unroll
+        for (int c = 0; c < kOut; ++c) {
+          float unused;
+          half_join(acc[0][c] + bh[c], acc[1][c] + bh[c], zs[c], unused);
+        }
+      }
+      float dzs[kOut];
+      render_subtile<TRAIN>(a, r0, nslots, wseed, in.r, zs, dzs, wave_loss);
+      if constexpr (!TRAIN) continue;
+#pragma unroll
+      for (int c = 0; c < kOut; ++c) accDbH[c] += dzs[c];
+
+      const int m16 = lane & 15, kg = lane >> 4;
+      // this lane's place in a transposing read of a staged tile: K = samples 8 kg + 0..7 (rows),
+      // the operand's row or column = feature base + m16
+      const int tr0 = (8 * kg + (m16 >> 2)) * kS64 + 4 * (m16 & 3);
+      // ... and of W_l^T: in-feature n of block mi, the outputs of K slot (hf, e) of block ko
+      const int wc = 4 * (m16 & 3) + 16 * (kg & 1);
+      const int wt0 = (4 * hf + (m16 >> 2)) * 72 + colpos(wc);
+#pragma unroll 1
+      for (int p = 0; p < 2; ++p) {
+        // the pass's activations again, from its encoding
+        bf16x8 act[kLayers + 1][2][2];
+        {
+          bf16x8 c[1][2][2];
+#pragma unroll
+          for (int jj = 0; jj < 2; ++jj) act[0][0][jj] = c[0][0][jj] = (p == 0) ? E[0].v[0][0][jj] : E[1].v[0][0][jj];
+#pragma unroll
+          for (int l = 0; l < kLayers; ++l) {
+            bf16x8 o[1][2][2];
+            layer64<1>(smem, l, lane, c, o);
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+              for (int jj = 0; jj < 2; ++jj) act[l + 1][mt][jj] = c[0][mt][jj] = o[0][mt][jj];
+          }
+        }
+        __syncthreads();  // every wave is done reading the staging tiles
+        if (hf == p) {    // the pass's seeds, by the lanes that hold them
+          bf16x4 d4;
+#pragma unroll
+          for (int c = 0; c < kOut; ++c) {
+            d4[c] = (__bf16)dzs[c];
+            reinterpret_cast<__bf16*>(dzt)[c * 40 + n] = d4[c];
+          }
+          *reinterpret_cast<bf16x4*>(dzt + kDzRowsBytes + 8 * n) = d4;
+        }
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+          for (int jj = 0; jj < 2; ++jj)
+            write_runs(reinterpret_cast<__bf16*>(htile) + n * kS64 + mt * 32 + 16 * jj + 4 * hf, act[kLayers][mt][jj]);
+        __syncthreads();
+        // output layer: this wave's 16 columns of dW over the four waves' samples
+#pragma unroll
+        for (int w2 = 0; w2 < 4; ++w2) {
+          const unsigned char* dz2 = scr0 + w2 * L.scratch_wave;
+          bf16x8 da = {};
+          if (m16 < kOut)
+            da = *reinterpret_cast<const bf16x8*>(reinterpret_cast<const __bf16*>(dz2) + m16 * 40 + 8 * kg);
+          const bf16x8 hb = tr_read_pair(reinterpret_cast<const __bf16*>(dz2 + kDz64 + kTile64) + tr0 + 16 * wave, 4 * kS64);
+          accWh = __builtin_amdgcn_mfma_f32_16x16x32_bf16(da, hb, accWh, 0, 0, 0);
+        }
+        // delta of the last hidden layer, own samples: (W_out^T dz) masked by ReLU'
+        bf16x8 dl[2][2];
+        {
+          bf16x8 dzb = {};
+          if (hf == 0) {
+            const bf16x4 d4 = *reinterpret_cast<const bf16x4*>(dzt + kDzRowsBytes + 8 * n);
+#pragma unroll
+            for (int c = 0; c < kOut; ++c) dzb[c] = d4[c];
+          }
+#pragma unroll
+          for (int mt = 0; mt < 2; ++mt) {
+            bf16x8 wa = {};
+            if (hf == 0) {
+              const bf16x4 w4 = *reinterpret_cast<const bf16x4*>(smem + L.whtb_off + (mt * 32 + n) * kOut * 2);
+#pragma unroll
+              for (int c = 0; c < kOut; ++c) wa[c] = w4[c];
+            }
+            const f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, dzb, zero, 0, 0, 0);
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj) dl[mt][jj] = relu_mask(round8(acc, 8 * jj), act[kLayers][mt][jj]);
+          }
+        }
+#pragma unroll
+        for (int l = kLayers - 1; l >= 0; --l) {
+          const int KB = (l == 0) ? 1 : 2;
+          // delta_{l-1} = W_l^T delta_l, own samples, before this layer's operands are staged
+          f32x16 nacc[2];
+          if (l > 0) {
+            const __bf16* W = reinterpret_cast<const __bf16*>(smem + L.w_off[l]) + wt0;
+#pragma unroll
+            for (int mi = 0; mi < 2; ++mi) {
+              nacc[mi] = zero;
+#pragma unroll
+              for (int ko = 0; ko < 2; ++ko)
+#pragma unroll
+                for (int jj = 0; jj < 2; ++jj) {
+                  const bf16x8 wa = tr_read_pair(W + (ko * 32 + 16 * jj) * 72 + mi * 32, 8 * 72);
+                  nacc[mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, dl[ko][jj], nacc[mi], 0, 0, 0);
+                }
+            }
+          }
+          __syncthreads();  // every wave is done reading the staging tiles
+#pragma unroll
+          for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj)
+              write_runs(reinterpret_cast<__bf16*>(dtile) + n * kS64 + mt * 32 + 16 * jj + 4 * hf, dl[mt][jj]);
+#pragma unroll
+          for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj)
+              write_runs(reinterpret_cast<__bf16*>(htile) + n * kS64 + kb * 32 + 16 * jj + 4 * hf, act[l][kb][jj]);
+          __syncthreads();  // every wave's tiles are staged
+          // this wave's rows of dW_l: D lane holds row 4 kg + i, column 16 cb + m16
+#pragma unroll
+          for (int w2 = 0; w2 < 4; ++w2) {
+            const __bf16* d2 = reinterpret_cast<const __bf16*>(scr0 + w2 * L.scratch_wave + kDz64) + tr0;
+            const __bf16* h2 = d2 + kTile64 / 2;
+            const bf16x8 da = tr_read_pair(d2 + wave * RW, 4 * kS64);
+            accDb[l] += operand_sum(da, 0.f);
+#pragma unroll
+            for (int cb = 0; cb < 2 * KB; ++cb) {
+              const bf16x8 hb = tr_read_pair(h2 + 16 * cb, 4 * kS64);
+              accW[l][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(da, hb, accW[l][cb], 0, 0, 0);
+            }
+          }
+          if (l == 0) break;
+#pragma unroll
+          for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj) dl[mi][jj] = relu_mask(round8(nacc[mi], 8 * jj), act[l][mi][jj]);
+        }
+      }
+    }  // rounds
+
+    // ---------------- tile result: loss and output-layer bias combined in wave order, every
+    // wave writes its own gradient slices
+    int le = lane_;
+    asm volatile("" : "+v"(le));
+    const int lane = le, m16 = lane & 15, kg = lane >> 4;
+    int bad = 0;
+    float* dst = a.partial + (size_t)tile * a.p_stride;
+    wave_loss = wave_sum(wave_loss);
+    if constexpr (TRAIN) {
+#pragma unroll
+      for (int c = 0; c < kOut; ++c) accDbH[c] = wave_sum(accDbH[c]);
+#pragma unroll
+      for (int l = 0; l < kLayers; ++l) {
+        accDb[l] += __shfl_xor(accDb[l], 16);
+        accDb[l] += __shfl_xor(accDb[l], 32);
+      }
+    }
+    float* lsum = reinterpret_cast<float*>(smem + L.loss_off);
+    int* any_bad = reinterpret_cast<int*>(smem + L.loss_off + 20);
+    __syncthreads();
+    for (int w = 0; w < 4; ++w) {
+      if (wave == w && lane == 0) {
+        lsum[0] = (w == 0 ? 0.f : lsum[0]) + wave_loss;
+        if constexpr (TRAIN) {
+#pragma unroll
+          for (int c = 0; c < kOut; ++c) lsum[1 + c] = (w == 0 ? 0.f : lsum[1 + c]) + accDbH[c];
+          if (w == 0) *any_bad = 0;
+        }
+      }
+      __syncthreads();
+    }
+    if constexpr (TRAIN) {
+      auto put = [&](int idx, float g) {
+        g *= inv;
+        bad |= partial_bad(g);
+        dst[idx] = g;
+      };
+#pragma unroll
+      for (int l = 0; l < kLayers; ++l) {
+        const int K = (l == 0) ? kEnc : H;
+        const int off = layer_param_off(H, l);
+#pragma unroll
+        for (int cb = 0; cb < K / 16; ++cb)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) put(off + (wave * RW + 4 * kg + i) * K + cb * 16 + m16, accW[l][cb][i]);
+        if (kg == 0) put(off + H * K + wave * RW + m16, accDb[l]);
+      }
+      const int offh = layer_param_off(H, kLayers);
+      if (lane < 16) {
+#pragma unroll
+        for (int c = 0; c < kOut; ++c) put(offh + c * H + wave * 16 + lane, accWh[c]);
+      }
+      if (wave == 0 && lane < kOut) put(offh + kOut * H + lane, lsum[1 + lane]);
+      if (bad) *any_bad = 1;  // every writer stores the same value
+      __syncthreads();
+      if (tid == 0 && *any_bad) atomicOr(&a.flags[k], 1);
+    }
+    if (tid == 0) a.tile_loss[tile] = lsum[0];
+    __syncthreads();
+  }
+}
+
 // ---------------------------------------------------------------------------------------------
 // Tile kernel for wide models (H = 64, 128): the four waves of a workgroup split every weight
 // gradient by rows. Each wave runs the forward, rendering, adjoint and delta chain of its own
@@ -2942,6 +3434,10 @@ static hipError_t launch_tiles_t(const StepArgs& a_in, int nwaves, int grid, hip
       a.lds_rays = 2 * (bytes + 3 * words) <= 160 * 1024;
       bytes += (a.lds_rays ? 3 : 1) * words;
     }
+  } else if constexpr (H == 64 && BF) {
+    fn = reinterpret_cast<const void*>(k_step_64<MODE>);
+    bytes = MODE == MODE_FWD ? lds64().scratch_off : lds64().total;
+    nwaves = 4;
   } else {
     static_assert(MODE != MODE_STEP, "the in-kernel tile table is built for width 32 only");
     fn = reinterpret_cast<const void*>(k_step_coop<H, BF, MODE>);
@@ -2953,6 +3449,8 @@ static hipError_t launch_tiles_t(const StepArgs& a_in, int nwaves, int grid, hip
   // (with the table, a workgroup more: the first publishes it for the optimiser)
   if constexpr (H == 32)
     hipLaunchKernelGGL((k_step_tiles<H, BF, MODE>), dim3(MODE == MODE_STEP ? grid + 1 : grid), dim3(nwaves * kWave), bytes, s, a);
+  else if constexpr (H == 64 && BF)
+    hipLaunchKernelGGL((k_step_64<MODE>), dim3(grid), dim3(nwaves * kWave), bytes, s, a);
   else
     hipLaunchKernelGGL((k_step_coop<H, BF, MODE>), dim3(grid), dim3(nwaves * kWave), bytes, s, a);
   return hipGetLastError();
@@ -2966,6 +3464,7 @@ int tile_waves(int H, int requested) { return H == 32 ? requested : 4; }
 
 int tile_lds_bytes(int H, bool bf16, int nwaves) {
   if (generic_width(H)) return kGenLdsBytes;
+  if (H == 64 && bf16) return lds64().total;
   return H == 32 ? lds_layout(H, bf16, nwaves).total : coop_layout(H, bf16).total;
 }
 
@@ -3127,26 +3626,6 @@ hipError_t launch_init_scaler(ScalerState* sc, float scale, hipStream_t s) {
 // Weight gradients (k_gen_dw, k_gen_dw_small): rows = outputs, n = inputs, k = samples;
 // A = delta^T, B = h_l^T, both staged as the sample rows lie and read transposed.
 
-// Batch object of element t (a row tile, row block or work tile) of a chain given by its exclusive
-// scan: the largest j below n_objects with scan[j] <= t (objects without elements have an empty
-// range and are passed over; scan[0] = 0 <= t). Searched by the whole wave, 64 ways at a time: the
-// lanes read 64 evenly spaced entries of the remaining range together and a ballot keeps the last
-// one at or below t, so a lookup waits on ceil(log64 n) loads rather than log2 n dependent ones.
-// Every lane of the wave must be active and pass the same t.
-__device__ __forceinline__ int gen_object(const int32_t* __restrict__ scan, int n_objects, int t) {
-  const int lane = (int)(threadIdx.x & 63);
-  int lo = 0, len = n_objects;  // the answer lies in [lo, lo + len), scan[lo] <= t
-  while (len > 1) {
-    const int step = (len + 63) >> 6;
-    const int i = lane * step;
-    const bool le = i < len && scan[lo + i] <= t;  // a prefix of the lanes (scan is nondecreasing)
-    const int c = __popcll(__ballot(le)) - 1;      // lane 0 always counts
-    lo += c * step;
-    len = min(step, len - c * step);
-  }
-  return lo;
-}
-
 // Buffer of the deltas at layer m's outputs (m = 0..3): the two buffers alternately (layer m in
 // buffer (3 - m) mod 2). A select: indexing the kernel argument's array by a run-time value would
 // put the whole argument block in per-lane scratch memory.
@@ -3297,17 +3776,6 @@ __device__ __forceinline__ bf16x8 tr_operand(const uint16_t* T, int kb, int cb, 
   const v4i16 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4*)(p));
   const v4i16 y = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4*)(p + 4 * P));
   return __builtin_bit_cast(bf16x8, __builtin_shufflevector(x, y, 0, 1, 2, 3, 4, 5, 6, 7));
-}
-
-// Sum of the eight BF16 of an MFMA operand, two at a time (v_dot2 against ones), added to s.
-__device__ __forceinline__ float operand_sum(bf16x8 v, float s) {
-  typedef unsigned int u4 __attribute__((ext_vector_type(4)));
-  typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-  const u4 w = __builtin_bit_cast(u4, v);
-  const b2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-#pragma unroll
-  for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(b2, (unsigned int)w[e]), ones, s, false);
-  return s;
 }
 
 // Rows of product block b of the layered chain: T = 64, row tile b (at most 64 rows, whole rays);
