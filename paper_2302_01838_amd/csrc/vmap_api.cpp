@@ -31,7 +31,7 @@ struct StateLayout {
 };
 
 struct WorkLayout {
-  size_t tile_start, flags, t_next, mark, batch, tile_bad, tile_loss, partial, wimage, img32, gimg, total;
+  size_t tile_start, width_start, flags, t_next, mark, batch, tile_bad, tile_loss, partial, wimage, img32, gimg, total;
   size_t wimage_stride;
   int max_tiles;
   // layered path (generic widths): row tiles, their losses, activations, deltas, z and dz
@@ -148,6 +148,8 @@ WorkLayout work_layout(const vmap_config* c) {
   w.max_tiles = (c->max_rays + rpt - 1) / rpt + c->max_objects;
   size_t off = 0;
   w.tile_start = off; off = align256(off + ((size_t)c->max_objects + 1) * 4);
+  // the same over the objects of width 32, 64 and 128 alone
+  w.width_start = off; off = align256(off + 3 * ((size_t)c->max_objects + 1) * 4);
   w.flags = off; off = align256(off + (size_t)c->max_objects * 4);
   w.t_next = off; off = align256(off + (size_t)c->max_objects * 4);
   w.mark = off; off = align256(off + (size_t)c->max_objects * 4);  // debug validation of ids
@@ -247,6 +249,10 @@ struct vmap_ctx {
   float* v() { return reinterpret_cast<float*>(state + sl.v); }
   float* grad() { return reinterpret_cast<float*>(state + sl.grad); }
   int32_t* tile_start() { return reinterpret_cast<int32_t*>(work + wl.tile_start); }
+  // first tile of each batch object among those of kernel width H (32, 64 or 128)
+  int32_t* width_start(int H) {
+    return reinterpret_cast<int32_t*>(work + wl.width_start) + (size_t)(H == 32 ? 0 : H == 64 ? 1 : 2) * (cfg.max_objects + 1);
+  }
   int32_t* flags() { return reinterpret_cast<int32_t*>(work + wl.flags); }
   int32_t* t_next() { return reinterpret_cast<int32_t*>(work + wl.t_next); }
   int32_t* mark() { return reinterpret_cast<int32_t*>(work + wl.mark); }
@@ -373,7 +379,7 @@ hipError_t enqueue_worklist(vmap_ctx* c, const vmap_batch* b, hipStream_t s,
                             const BatchDev* bd = nullptr) {
   return launch_worklist(b->n_objects, b->n_rays_total, b->object_ids, b->ray_offsets,
                          c->rays_per_tile, c->rays_per_tile_wide, gen_work_rays(c, b->samples_per_ray),
-                         c->cfg.max_objects, c->desc(), c->scaler(), c->tile_start(), c->flags(),
+                         c->cfg.max_objects, c->desc(), c->scaler(), c->tile_start(), c->width_start(32), c->flags(),
                          c->t_next(), bd, s);
 }
 
@@ -437,10 +443,14 @@ int enqueue_tiles(vmap_ctx* c, const vmap_batch* b, int mode, const float* dloss
     hipError_t e = hipEventRecord(tl.a, s);
     if (e != hipSuccess) return c->hip_fail(e, "hipEventRecord");
   }
-  // Width groups run as separate kernels; with more than one, every group after the first goes
-  // to a side stream (forked from and joined back into `s` by events, which graph capture
-  // follows), so that the groups overlap on the GPU.
-  const std::vector<int> widths = widths_present(c);
+  // Width groups run as separate kernels, widest first; with more than one, every group after the
+  // first goes to a side stream (forked from and joined back into `s` by events, which graph
+  // capture follows), so that the groups overlap on the GPU. Widest first because a workgroup of
+  // the hidden-128 kernel takes a whole CU's LDS: launched after the hidden-32 group it waits for
+  // CUs that group has filled to empty again (room workload, 100 of its workgroups beside 312
+  // hidden-32 tiles: 76 us against 46 alone; the step 122 us in that order, 101 in this).
+  std::vector<int> widths = widths_present(c);
+  std::reverse(widths.begin(), widths.end());
   const bool fork = widths.size() > 1;
   if (fork) {
     if (!c->side_stream) {
@@ -490,8 +500,12 @@ int enqueue_tiles(vmap_ctx* c, const vmap_batch* b, int mode, const float* dloss
     // The weight images are current (staged when parameters are set, then kept by the optimiser).
     // This width's tiles are at most ceil(rays / its rays per tile) + objects: wider tiles need
     // fewer workgroups than the stack's smallest tile size gives (the kernels stride over tiles).
+    // At hidden 128 a workgroup takes a CU by itself: no more than 256, which stride over the tiles
+    // (the bound counts every width's rays, and a workgroup without a tile waits for a CU too).
     const int rpt_h = tile_rays(H, c->rays_per_tile, c->rays_per_tile_wide);
-    const int grid_h = std::min(grid, (b->n_rays_total + rpt_h - 1) / rpt_h + b->n_objects);
+    int grid_h = std::min(grid, (b->n_rays_total + rpt_h - 1) / rpt_h + b->n_objects);
+    if (H == 128 && mode == MODE_TRAIN) grid_h = std::min(grid_h, 256);
+    a.width_start = c->width_start(H);
     hipError_t e = launch_tiles(H, bf, mode, a, c->waves, grid_h, si);
     if (e != hipSuccess) return c->hip_fail(e, "tile kernel launch");
   }

@@ -97,17 +97,20 @@ __host__ __device__ constexpr int tiles_of(int nr, int rpt) { return nr > 0 ? (n
 constexpr float kPartialLimit = 18446744073709551616.0f;  // 2^64
 __host__ __device__ inline bool partial_bad(float g) { return !(g > -kPartialLimit && g < kPartialLimit); }
 
+// Widths whose weights are kept in a per-object image in device memory (hidden 128, below).
+__host__ __device__ constexpr bool weights_global(int H) { return H >= 128; }
+
 // Byte offsets of the LDS regions of the tile kernel (computed identically on host and device).
 struct LdsLayout {
   int w_off[kLayers];   // W_l, rows = H, padded row stride, permuted columns
   int w_stride[kLayers];
-  int wt_off[kLayers];  // BF16 only: W_l^T for l >= 1 (rows = inputs), stride H + 8
+  int wt_off[kLayers];  // BF16, H = 32: W_l^T for l >= 1 (rows = inputs), stride H + 8
   int b_off;            // kLayers x H biases (FP32)
   int wh_off;           // head weights [4][H + 4] FP32, permuted columns (FP32 mode)
   int whb_off;          // BF16: head weights [4][H + 8] BF16, permuted columns
   int whtb_off;         // BF16: head weights transposed [H][4] BF16
   int bh_off;           // head biases [4]
-  int bA_off;           // BF16: bias operand table [kLayers][H][16] (hi, mid, lo split)
+  int bA_off;           // BF16, H <= 64: bias operand table [kLayers][H][16] (hi, mid, lo split)
   int B_off;            // encoding matrix [3][16] FP32
   int scratch_off;      // per-wave staging, then the tile's gradient sum
   int scratch_wave;     // bytes per wave
@@ -163,7 +166,7 @@ __host__ __device__ constexpr LdsLayout lds_layout(int H, bool bf16, int nwaves)
   }
   for (int l = 0; l < kLayers; ++l) {
     L.wt_off[l] = off;
-    if (bf16 && l > 0) off = round_up(off + H * (H + 8) * 2, 16);
+    if (bf16 && H == 32 && l > 0) off = round_up(off + H * (H + 8) * 2, 16);
   }
   L.b_off = off;
   off = round_up(off + kLayers * H * 4, 16);
@@ -176,7 +179,7 @@ __host__ __device__ constexpr LdsLayout lds_layout(int H, bool bf16, int nwaves)
   L.bh_off = off;
   off = round_up(off + kOut * 4, 16);
   L.bA_off = off;
-  if (bf16) off = round_up(off + kLayers * H * 32, 16);
+  if (bf16 && !weights_global(H)) off = round_up(off + kLayers * H * 32, 16);
   L.B_off = off;
   off = round_up(off + 3 * kFeatures * 4, 16);
   L.loss_off = off;  // the tile's loss per gradient copy (up to 4), then its non-finite flag
@@ -196,7 +199,6 @@ __host__ __device__ constexpr LdsLayout lds_layout(int H, bool bf16, int nwaves)
 // Wide models (H >= 128) keep their weights in a per-object image in device memory with the byte
 // layout of the LDS staging above (offsets below B_off), since weights and BF16 transposes do not
 // fit in LDS next to the cooperative kernel's staging tiles.
-__host__ __device__ constexpr bool weights_global(int H) { return H >= 128; }
 __host__ __device__ constexpr int image_bytes(int H, bool bf16) {
   return round_up(lds_layout(H, bf16, 1).B_off, 256);
 }
@@ -408,6 +410,7 @@ struct StepArgs {
   const float* B;        // [3][16]
   // work buffers
   const int32_t* tile_start;  // [n_objects + 1]
+  const int32_t* width_start; // [n_objects + 1] the same over this launch's width alone (k_worklist)
   float* partial;             // [tiles][p_stride]
   float* tile_loss;           // [tiles]
   const float* dloss;         // [n_objects] upstream weights (backward) or NULL
@@ -528,7 +531,7 @@ hipError_t launch_worklist(int n_objects, int n_rays, const int32_t* object_ids,
                            const int32_t* ray_offsets, int rays_per_tile, int rays_per_tile_wide,
                            int rays_per_tile_gen,
                            int max_objects, const ObjDesc* desc, ScalerState* scaler,
-                           int32_t* tile_start, int32_t* flags, int32_t* t_next,
+                           int32_t* tile_start, int32_t* width_start, int32_t* flags, int32_t* t_next,
                            const BatchDev* bd, hipStream_t s);
 hipError_t launch_tiles(int H, bool bf16, int mode, const StepArgs& a, int nwaves, int grid,
                         hipStream_t s);

@@ -106,8 +106,7 @@ __device__ __forceinline__ void write_runs(__bf16* p, bf16x8 v) {
 // XCD b mod 8, each with its own L2); when the grid has a workgroup per tile, the first n_tiles
 // workgroups of one XCD take consecutive tiles, so that an object's tiles (its weights, rays and
 // samples) share one L2 instead of being fetched into all eight. Workgroups past n_tiles (the
-// last dispatched) stay without a tile. Otherwise tile = workgroup index (b of `blocks`). Only for launches whose
-// tiles all do work: each XCD gets an equal share of tiles, not of work.
+// last dispatched) stay without a tile. Otherwise tile = workgroup index (b of `blocks`).
 __device__ __forceinline__ int first_tile_of_block(int b, int blocks, int n_tiles) {
   constexpr int kXcds = 8;
   if (blocks < n_tiles || b >= n_tiles) return b;
@@ -227,7 +226,7 @@ __device__ __forceinline__ void place_param(unsigned char* img, int p, float w) 
     if (p < off + H * K) {
       const int e = p - off, row = e / K, col = e - row * K;
       reinterpret_cast<WT*>(img + L.w_off[l])[row * L.w_stride[l] + (col & ~31) + colpos(col & 31)] = (WT)w;
-      if constexpr (BF) {
+      if constexpr (BF && H == 32) {
         if (l > 0)
           reinterpret_cast<__bf16*>(img + L.wt_off[l])[col * (H + 8) + (row & ~31) + colpos(row & 31)] = (__bf16)w;
       }
@@ -237,7 +236,7 @@ __device__ __forceinline__ void place_param(unsigned char* img, int p, float w) 
     if (p < off + H) {
       const int row = p - off;
       reinterpret_cast<float*>(img + L.b_off)[l * H + row] = w;
-      if constexpr (BF) {
+      if constexpr (BF && !weights_global(H)) {
         const __bf16 hi = (__bf16)w;
         const __bf16 mid = (__bf16)(w - (float)hi);
         const __bf16 lo = (__bf16)((w - (float)hi) - (float)mid);
@@ -308,7 +307,7 @@ __device__ __forceinline__ void stage_weights(const float* __restrict__ th, unsi
       const int row = e / K, col = e - row * K;
       const WT w = (WT)param(off + e);
       W[row * ws + (col & ~31) + colpos(col & 31)] = w;
-      if constexpr (BF) {
+      if constexpr (BF && H == 32) {
         if (l > 0) {  // W^T[col][row], rows of the transpose permuted like the forward's K axis
           __bf16* Wt = reinterpret_cast<__bf16*>(smem + L.wt_off[l]);
           Wt[col * (H + 8) + (row & ~31) + colpos(row & 31)] = w;
@@ -332,7 +331,7 @@ __device__ __forceinline__ void stage_weights(const float* __restrict__ th, unsi
   off += kOut * H;
   float* bh = reinterpret_cast<float*>(smem + L.bh_off);
   for (int e = tid; e < kOut; e += nt) bh[e] = param(off + e);
-  if constexpr (BF) {
+  if constexpr (BF && !weights_global(H)) {
     // bias as an MFMA operand: b = hi + mid + lo exactly (three BF16 pieces of 8 bits each)
     __bf16* bA = reinterpret_cast<__bf16*>(smem + L.bA_off);
     int boff[kLayers];
@@ -1195,7 +1194,7 @@ __global__ void __launch_bounds__((BF && H == 32) ? 512 : 256, 1) k_step_tiles(c
   int32_t* tbl = reinterpret_cast<int32_t*>(smem + a.lds_table);
   int32_t* tray = tbl + tbl_words;
   int32_t* tk = tray + tbl_words;
-  auto first_tile = [&](int j) { return TABLE ? tbl[j] : a.tile_start[j]; };
+  auto first_tile = [&](int j) { return TABLE ? tbl[j] : a.width_start[j]; };  // among this width's tiles
   int n_tiles;
   LaneTable lt{};
   const bool small = TABLE && a.n_objects <= kWave;
@@ -1230,7 +1229,7 @@ __global__ void __launch_bounds__((BF && H == 32) ? 512 : 256, 1) k_step_tiles(c
       return;  // the other workgroups run the tiles
     }
   } else {
-    n_tiles = a.tile_start[a.n_objects];
+    n_tiles = a.width_start[a.n_objects];
   }
   n_tiles = clamp_tiles(n_tiles, a.max_tiles);
 
@@ -1238,11 +1237,9 @@ __global__ void __launch_bounds__((BF && H == 32) ? 512 : 256, 1) k_step_tiles(c
   if (tid < 3 * kFeatures) Bl[tid] = a.B[tid];
   int staged = -1;
 
-  // XCD-aware order only when every tile belongs to this launch (tiles of other widths would
-  // crowd the XCDs that hold them)
   // (with the table, workgroup 0 has published it and returned: the tiles' workgroups follow)
   const int wg = TABLE ? (int)blockIdx.x - 1 : (int)blockIdx.x, wgs = TABLE ? (int)gridDim.x - 1 : (int)gridDim.x;
-  int tile = TABLE ? first_tile_of_block(wg, wgs, n_tiles) : wg;
+  int tile = first_tile_of_block(wg, wgs, n_tiles);  // (every tile belongs to this launch)
   // object of a tile: the j with first_tile(j) <= tile < first_tile(j + 1) (objects without rays
   // have an empty range), 64 candidates per wave at a time; a workgroup's first tile of a small
   // batch from the lanes' own entries
@@ -1279,6 +1276,9 @@ __global__ void __launch_bounds__((BF && H == 32) ? 512 : 256, 1) k_step_tiles(c
     const int ray_lo = rr.lo, ray_hi = rr.hi;
     const int nrays = ray_hi - ray_lo;
     const int nsub = (nrays + rpw - 1) / rpw;
+    // the tile's index in the batch's work list (its partial, loss and report)
+    const int slot = TABLE ? tile : a.tile_start[j] + tile - ft;
+    if (slot < 0 || slot >= a.max_tiles) continue;  // (not for a consistent work list)
     // The object's weight image goes to LDS before its descriptor is checked, so that the two are
     // fetched together (an id out of range fetches object 0's image, which is then discarded).
     const bool k_ok = k >= 0 && k < a.max_objects;
@@ -1700,7 +1700,7 @@ __global__ void __launch_bounds__((BF && H == 32) ? 512 : 256, 1) k_step_tiles(c
       // unscale (exact: the scale is a power of two) and report a partial that is not finite or
       // too large to be summed safely (partial_bad)
       static_assert(n_params_of(H) % 4 == 0, "the partial is written four elements at a time");
-      float* dst = a.partial + (size_t)tile * a.p_stride;  // (p_stride is a multiple of 64)
+      float* dst = a.partial + (size_t)slot * a.p_stride;  // (p_stride is a multiple of 64)
       int bad = 0;
       for (int e = 4 * et; e < n_params_of(H); e += 4 * blockDim.x) {
         f32x4 g = *reinterpret_cast<const f32x4*>(red0 + e);
@@ -1721,7 +1721,7 @@ __global__ void __launch_bounds__((BF && H == 32) ? 512 : 256, 1) k_step_tiles(c
       if (bad) *any_bad = 1;  // every writer stores the same value
       __syncthreads();
       if (tid == 0) {
-        if constexpr (TABLE) a.tile_bad[tile] = *any_bad;
+        if constexpr (TABLE) a.tile_bad[slot] = *any_bad;
         else if (*any_bad) atomicOr(&a.flags[k], 1);
       }
     }
@@ -1729,7 +1729,7 @@ __global__ void __launch_bounds__((BF && H == 32) ? 512 : 256, 1) k_step_tiles(c
       float l = lsum[0];
       if (four) l = (l + lsum[2]) + (lsum[1] + lsum[3]);
       else for (int c = 1; c < nc; ++c) l += lsum[c];
-      a.tile_loss[tile] = l;
+      a.tile_loss[slot] = l;
     }
     __syncthreads();
   }
@@ -1910,13 +1910,15 @@ __global__ void __launch_bounds__(256, 2) k_step_64(const StepArgs a_in) {
   const int tid = threadIdx.x, lane_ = tid & 63, wave = tid >> 6;
   const int S = a.S;
   const int rpw = kSlots / S;
-  const int n_tiles = clamp_tiles(a.tile_start[a.n_objects], a.max_tiles);
+  const int n_tiles = clamp_tiles(a.width_start[a.n_objects], a.max_tiles);  // of this width
   float* Bl = reinterpret_cast<float*>(smem + L.B_off);
   if (tid < 3 * kFeatures) Bl[tid] = a.B[tid];
   int staged = -1;
 
-  for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-    const int j = gen_object(a.tile_start, a.n_objects, tile);
+  for (int t = first_tile_of_block(blockIdx.x, gridDim.x, n_tiles); t < n_tiles; t += gridDim.x) {
+    const int j = gen_object(a.width_start, a.n_objects, t);
+    const int ti = t - a.width_start[j], tile = a.tile_start[j] + ti;  // of the object; of the work list
+    if (tile < 0 || tile >= a.max_tiles) continue;  // (not for a consistent work list)
     const int k = __builtin_amdgcn_readfirstlane(a.object_ids[j]);
     if (k < 0 || k >= a.max_objects || !a.desc[k].registered) {
       if (tid == 0) atomicOr(&a.scaler->device_error, 1);
@@ -1924,8 +1926,7 @@ __global__ void __launch_bounds__(256, 2) k_step_64(const StepArgs a_in) {
     }
     if (kernel_width(a.desc[k].hidden) != H) continue;
     const int rpt = tile_rays(H, a.rays_per_tile, a.rays_per_tile_wide);
-    const RayRange rr = tile_ray_range(a.ray_offsets[j], a.ray_offsets[j + 1], tile - a.tile_start[j],
-                                       rpt, a.n_rays);
+    const RayRange rr = tile_ray_range(a.ray_offsets[j], a.ray_offsets[j + 1], ti, rpt, a.n_rays);
     const int ray_lo = rr.lo, ray_hi = rr.hi;
     if (k != staged) {
       __syncthreads();
@@ -2227,6 +2228,368 @@ __global__ void __launch_bounds__(256, 2) k_step_64(const StepArgs a_in) {
   }
 }
 
+// Lane `lane`'s MFMA operand from a row-major BF16 tile T (pitch P elements, a multiple of 4): the
+// operand's K index runs down the rows kb + 8 (lane / 32) + 0..7 and its row or column index is
+// column cb + (lane mod 32). Lanes x, x + 4, x + 8 and x + 12 of each 16-lane group address four
+// consecutive rows at the same four-column run, so each ds_read_b64_tr_b16 hands every lane four
+// consecutive rows of its own column (the lane mapping the fused kernels' weight gradients use);
+// the second read, four rows further down, gives the other four of its eight.
+template <int P>
+__device__ __forceinline__ bf16x8 tr_operand(const uint16_t* T, int kb, int cb, int lane) {
+  typedef __attribute__((address_space(3))) v4i16 lds_v4;
+  const uint16_t* p = T + (kb + 8 * (lane >> 5) + ((lane & 15) >> 2)) * P + cb + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+  const v4i16 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4*)(p));
+  const v4i16 y = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4*)(p + 4 * P));
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(x, y, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// ---------------------------------------------------------------------------------------------
+// Training tile kernel for hidden 128 (BF16): eight waves work on one sub-tile together. Wave w
+// computes the 32 x 32 block (features 32 (w mod 4).., samples of pass w / 4) of every layer, so
+// the chain of a sub-tile is four blocks' length, not four times four; activations and deltas pass
+// between layers through LDS, beside the object's weights (112 KB of the image; the input gradient
+// reads them transposed). Each weight gradient's sixteen 32 x 32 blocks are split two to a wave and
+// accumulate in registers over the tile's sub-tiles (112 of them), so the partial is written once.
+//
+// k_step_coop ran a sub-tile per wave, one wave per SIMD, spilling, with weights read from device
+// memory for every product and the gradient read and written there for every layer and pass: 179
+// us for a background of 1,200 rays of 20 samples (100 tiles, 24,000 samples); 46 us here. The
+// LDS bounds it: a sub-tile's products read 1.1 MB of operands (about 9 thousand cycles).
+//
+// Columns of staged tiles (activations, deltas) and of the weights are in the permuted order of
+// colpos: a wave's accumulator registers are sixteen consecutive columns, written as two 16-byte
+// stores and read back as the next layer's operands.
+
+struct Lds128 {
+  int B_off, loss_off, dz_off, enc_off, buf_off, total;
+};
+constexpr int kS128 = 136;  // BF16 elements per staged sample of 128 features
+constexpr int kE128 = 40;   // ... of 32 encodings
+__host__ __device__ constexpr Lds128 lds128() {
+  Lds128 L{};
+  int off = lds_layout(128, true, 1).B_off;  // the weight image's bytes
+  L.B_off = off; off += 3 * kFeatures * 4;
+  L.loss_off = off; off += 32;
+  L.dz_off = off; off += pair_dz_bytes(true);
+  L.enc_off = off; off += 64 * kE128 * 2;
+  L.buf_off = off; off += 2 * 64 * kS128 * 2;
+  L.total = off;
+  return L;
+}
+static_assert(lds128().total <= 160 * 1024, "the hidden-128 kernel's LDS");
+// Feature at permuted column `pos` (0..31) of a block: the inverse of colpos.
+__host__ __device__ constexpr int colfeat(int pos) { return (((pos >> 2) & 3) << 3) + ((pos >> 4) << 2) + (pos & 3); }
+
+__global__ void __launch_bounds__(512, 2) k_step_128(const StepArgs a_in) {
+  constexpr int H = 128;
+  constexpr LdsLayout W = lds_layout(H, true, 1);
+  constexpr Lds128 L = lds128();
+  StepArgs a = a_in;
+  read_batch(a);
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int tid = threadIdx.x, lane_ = tid & 63, wave = tid >> 6;
+  const int fb = wave & 3, pass = wave >> 2;    // this wave's feature block and pass
+  const int ob = wave >> 1, ib = (wave & 1) * 2;  // its weight-gradient blocks: outputs ob, inputs ib and ib + 1
+  const int S = a.S;
+  const int rpw = kSlots / S;
+  const int n_tiles = clamp_tiles(a.width_start[a.n_objects], a.max_tiles);  // of this width
+  float* Bl = reinterpret_cast<float*>(smem + L.B_off);
+  if (tid < 3 * kFeatures) Bl[tid] = a.B[tid];
+  int staged = -1;
+  uint16_t* const enc = reinterpret_cast<uint16_t*>(smem + L.enc_off);
+  uint16_t* const buf0 = reinterpret_cast<uint16_t*>(smem + L.buf_off);
+  uint16_t* const buf1 = buf0 + 64 * kS128;
+  unsigned char* const dzt = smem + L.dz_off;
+
+  for (int t = first_tile_of_block(blockIdx.x, gridDim.x, n_tiles); t < n_tiles; t += gridDim.x) {
+    const int j = gen_object(a.width_start, a.n_objects, t);
+    const int ti = t - a.width_start[j], tile = a.tile_start[j] + ti;  // of the object; of the work list
+    if (tile < 0 || tile >= a.max_tiles) continue;  // (not for a consistent work list)
+    const int k = __builtin_amdgcn_readfirstlane(a.object_ids[j]);
+    if (k < 0 || k >= a.max_objects || !a.desc[k].registered) {
+      if (tid == 0) atomicOr(&a.scaler->device_error, 1);
+      continue;
+    }
+    if (kernel_width(a.desc[k].hidden) != H) continue;
+    const int rpt = tile_rays(H, a.rays_per_tile, a.rays_per_tile_wide);
+    const RayRange rr = tile_ray_range(a.ray_offsets[j], a.ray_offsets[j + 1], ti, rpt, a.n_rays);
+    const int ray_lo = rr.lo, ray_hi = rr.hi;
+    if (k != staged) {
+      __syncthreads();
+      fetch_image_lds(a.wimage + (size_t)k * a.wimage_stride, smem, W.B_off, lane_, wave, 8);
+      staged = k;
+    }
+    const double cx = a.desc[k].centre[0], cy = a.desc[k].centre[1], cz = a.desc[k].centre[2];
+    const double inv_s = a.desc[k].inv_scale;
+    float wseed = 1.0f, inv = 1.0f;
+    if (a.dloss) wseed = a.dloss[j];
+    if (a.use_scale) {
+      const float scale = a.scaler->scale;
+      wseed *= scale;
+      inv = 1.0f / scale;
+    }
+    f32x16 zero;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) zero[r] = 0.f;
+    f32x16 accW[kLayers - 1][2], accW0;  // dW_1..3: blocks (ob, ib), (ob, ib + 1); dW_0: (ob, 0), even waves
+    float accDb[kLayers];                // lane sums of db_l's rows ob, even waves
+    f32x4 accWh = {0.f, 0.f, 0.f, 0.f};  // this wave's 16 columns of the output layer's dW
+    float accDbH[kOut];
+    accW0 = zero;
+#pragma unroll
+    for (int l = 0; l < kLayers - 1; ++l) accW[l][0] = accW[l][1] = zero;
+#pragma unroll
+    for (int l = 0; l < kLayers; ++l) accDb[l] = 0.f;
+#pragma unroll
+    for (int c = 0; c < kOut; ++c) accDbH[c] = 0.f;
+    float wave_loss = 0.f;
+    __builtin_amdgcn_s_waitcnt(0);  // this thread's part of the image is in LDS
+    __syncthreads();
+
+    const int nsub = (ray_hi - ray_lo + rpw - 1) / rpw;
+    for (int sub = 0; sub < nsub; ++sub) {
+      // (lane-dependent LDS addresses are computed where they are used, not hoisted and spilled)
+      int ln = lane_;
+      asm volatile("" : "+v"(ln)::"memory");
+      const int lane = ln, n = ln & 31, hf = ln >> 5;
+      const int r0 = ray_lo + sub * rpw;
+      const int nslots = max(0, min(rpw, ray_hi - r0)) * S;
+      const SubTileIn in = subtile_inputs<true>(a, ray_lo, ray_hi, sub, rpw);
+      // encoding: every lane its own slot's point, every wave two of the sixteen frequencies
+      {
+        float x[4] = {0.f, 0.f, 0.f, 0.f};
+        if (lane < nslots) {
+          const double tt = (double)in.r.tt;
+          x[0] = (float)(((double)in.o[0] + tt * (double)in.d[0] - cx) * inv_s);
+          x[1] = (float)(((double)in.o[1] + tt * (double)in.d[1] - cy) * inv_s);
+          x[2] = (float)(((double)in.o[2] + tt * (double)in.d[2] - cz) * inv_s);
+          if (a.var) x[3] = (float)((double)in.var * inv_s * inv_s);
+        }
+        float sv[2], cv[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const int f = 2 * wave + u;
+          const float b0 = Bl[f], b1 = Bl[kFeatures + f], b2 = Bl[2 * kFeatures + f];
+          const float phi = x[0] * b0 + x[1] * b1 + x[2] * b2;
+          vmap_sincosf(phi, &sv[u], &cv[u]);
+          if (a.var) {  // expectation under N(x, v I): attenuation exp(-v |b_f|^2 / 2)
+            const float nb = b0 * b0 + b1 * b1 + b2 * b2;
+            const float att = expf(-0.5f * x[3] * nb);
+            sv[u] *= att;
+            cv[u] *= att;
+          }
+        }
+        *reinterpret_cast<unsigned int*>(enc + lane * kE128 + colpos(2 * wave)) = pack2(sv[0], sv[1]);
+        *reinterpret_cast<unsigned int*>(enc + lane * kE128 + colpos(kFeatures + 2 * wave)) = pack2(cv[0], cv[1]);
+      }
+      __syncthreads();
+
+      // forward: this wave's block of each layer, kept for the ReLU masks and the restaging
+      const int row = 32 * pass + n;                       // this lane's sample
+      const int col = fb * 32 + 16 * hf;                   // its sixteen columns in a staged row
+      bf16x8 act[kLayers + 1][2];                          // [1..4]
+#pragma unroll
+      for (int l = 0; l < kLayers; ++l) {
+        const int ws = W.w_stride[l], KB = (l == 0) ? 1 : 4;
+        const uint16_t* src = (l == 0) ? enc + row * kE128 + 16 * hf : ((l & 1) ? buf0 : buf1) + row * kS128 + 16 * hf;
+        const uint16_t* wrow = reinterpret_cast<const uint16_t*>(smem + W.w_off[l]) + (fb * 32 + n) * ws + 16 * hf;
+        f32x16 acc = zero;
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+          for (int jj = 0; jj < 2; ++jj)
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(wrow + kb * 32 + 8 * jj),
+                                                         *reinterpret_cast<const bf16x8*>(src + kb * 32 + 8 * jj), acc, 0, 0, 0);
+        const float* bias = reinterpret_cast<const float*>(smem + W.b_off) + l * H + fb * 32 + 4 * hf;
+        typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+        typedef short s2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj) {
+          u4 w;
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {  // rows 16 jj + 8 q + 4 hf + i
+            const f32x4 b4 = *reinterpret_cast<const f32x4*>(bias + 16 * jj + 8 * q);
+            float y[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) y[i] = fmaxf(acc[8 * jj + 4 * q + i] + b4[i], 0.0f);
+#pragma unroll
+            for (int i = 0; i < 2; ++i)  // (a -0 becomes +0: the masks test the bits)
+              w[2 * q + i] = __builtin_bit_cast(unsigned int, __builtin_elementwise_max(
+                                 __builtin_bit_cast(s2, pack2(y[2 * i], y[2 * i + 1])), (s2){0, 0}));
+          }
+          act[l + 1][jj] = __builtin_bit_cast(bf16x8, w);
+        }
+        uint16_t* dst = ((l & 1) ? buf1 : buf0) + row * kS128 + col;
+        *reinterpret_cast<bf16x8*>(dst) = act[l + 1][0];
+        *reinterpret_cast<bf16x8*>(dst + 8) = act[l + 1][1];
+        __syncthreads();
+      }
+      // output layer, rendering and its adjoint: wave 0, both passes (h_4 in buf1)
+      if (wave == 0) {
+        const uint16_t* wh = reinterpret_cast<const uint16_t*>(smem + W.whb_off) + n * (H + 8) + 16 * hf;
+        const uint16_t* h4 = buf1 + n * kS128 + 16 * hf;
+        f32x16 acc[2] = {zero, zero};
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+          for (int jj = 0; jj < 2; ++jj) {
+            bf16x8 wa = {};
+            if (n < kOut) wa = *reinterpret_cast<const bf16x8*>(wh + mt * 32 + 8 * jj);
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+              acc[p] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                  wa, *reinterpret_cast<const bf16x8*>(h4 + p * 32 * kS128 + mt * 32 + 8 * jj), acc[p], 0, 0, 0);
+          }
+        const float* bh = reinterpret_cast<const float*>(smem + W.bh_off);
+        float zs[kOut], dzs[kOut];
+#pragma unroll
+        for (int c = 0; c < kOut; ++c) {
+          float unused;
+          half_join(acc[0][c] + bh[c], acc[1][c] + bh[c], zs[c], unused);
+        }
+        render_subtile<true>(a, r0, nslots, wseed, in.r, zs, dzs, wave_loss);
+        bf16x4 d4;
+#pragma unroll
+        for (int c = 0; c < kOut; ++c) {
+          accDbH[c] += dzs[c];
+          d4[c] = (__bf16)dzs[c];
+          reinterpret_cast<__bf16*>(dzt)[c * kDzPitch + lane] = d4[c];
+        }
+        *reinterpret_cast<bf16x4*>(dzt + kOut * kDzPitch * 2 + 8 * lane) = d4;
+      }
+      __syncthreads();
+      // output layer's dW: this wave's 16 columns, K = a pass's 32 samples
+      const int m16 = lane & 15, kg = lane >> 4;
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        bf16x8 da = {};
+        if (m16 < kOut)
+          da = *reinterpret_cast<const bf16x8*>(reinterpret_cast<const __bf16*>(dzt) + m16 * kDzPitch + 32 * p + 8 * kg);
+        const bf16x8 hb = tr_read_pair(reinterpret_cast<const __bf16*>(buf1) + (32 * p + 8 * kg + (m16 >> 2)) * kS128 +
+                                           16 * wave + 4 * (m16 & 3), 4 * kS128);
+        accWh = __builtin_amdgcn_mfma_f32_16x16x32_bf16(da, hb, accWh, 0, 0, 0);
+      }
+      // delta of the last hidden layer: this wave's block of W_out^T dz, masked by ReLU'
+      bf16x8 dl[2];
+      {
+        bf16x8 dzb = {}, wa = {};
+        if (hf == 0) {
+          const bf16x4 d4 = *reinterpret_cast<const bf16x4*>(dzt + kOut * kDzPitch * 2 + 8 * row);
+          const bf16x4 w4 = *reinterpret_cast<const bf16x4*>(smem + W.whtb_off + (fb * 32 + n) * kOut * 2);
+#pragma unroll
+          for (int c = 0; c < kOut; ++c) {
+            dzb[c] = d4[c];
+            wa[c] = w4[c];
+          }
+        }
+        const f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa, dzb, zero, 0, 0, 0);
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj) dl[jj] = relu_mask(round8(acc, 8 * jj), act[kLayers][jj]);
+      }
+      // W_l^T operands: in-feature n of block fb, the outputs of K slot (hf, e) of block ko
+      const int wc = 4 * (m16 & 3) + 16 * (kg & 1);
+      const int wt0 = (4 * hf + (m16 >> 2)) * kS128 + fb * 32 + colpos(wc);
+#pragma unroll
+      for (int l = kLayers - 1; l >= 0; --l) {
+        // stage delta_l in buf1 and the layer's inputs in buf0 (h_3 lies there already; the first
+        // layer's are the encodings)
+        __syncthreads();  // buf1 and buf0 have been read
+        uint16_t* dst = buf1 + row * kS128 + col;
+        *reinterpret_cast<bf16x8*>(dst) = dl[0];
+        *reinterpret_cast<bf16x8*>(dst + 8) = dl[1];
+        if (l > 0 && l < kLayers - 1) {
+          dst = buf0 + row * kS128 + col;
+          *reinterpret_cast<bf16x8*>(dst) = act[l][0];
+          *reinterpret_cast<bf16x8*>(dst + 8) = act[l][1];
+        }
+        __syncthreads();
+        f32x16 nacc = zero;
+        if (l > 0) {
+          const uint16_t* src = buf1 + row * kS128 + 16 * hf;
+          const __bf16* Wt = reinterpret_cast<const __bf16*>(smem + W.w_off[l]) + wt0;
+#pragma unroll
+          for (int ko = 0; ko < 4; ++ko)
+#pragma unroll
+            for (int jj = 0; jj < 2; ++jj)
+              nacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr_read_pair(Wt + (ko * 32 + 16 * jj) * kS128, 8 * kS128),
+                                                            *reinterpret_cast<const bf16x8*>(src + ko * 32 + 8 * jj), nacc, 0, 0, 0);
+        }
+        // weight gradient: blocks (ob, ib) and (ob, ib + 1) over the 64 samples
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          if (l == 0 && (wave & 1)) break;
+          const bf16x8 da = tr_operand<kS128>(buf1, 16 * s, ob * 32, lane);
+          if (l > 0) {
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+              accW[l - 1][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                  da, tr_operand<kS128>(buf0, 16 * s, (ib + b) * 32, lane), accW[l - 1][b], 0, 0, 0);
+          } else {
+            accW0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(da, tr_operand<kE128>(enc, 16 * s, 0, lane), accW0, 0, 0, 0);
+          }
+          if (!(wave & 1)) accDb[l] = operand_sum(da, accDb[l]);
+        }
+        if (l == 0) break;
+#pragma unroll
+        for (int jj = 0; jj < 2; ++jj) dl[jj] = relu_mask(round8(nacc, 8 * jj), act[l][jj]);
+      }
+      __syncthreads();  // the next sub-tile writes the encodings
+    }  // sub-tiles
+
+    // ---------------- tile result: each wave writes its own gradient blocks
+    int le = lane_;
+    asm volatile("" : "+v"(le));
+    const int lane = le, n = le & 31, hf = le >> 5;
+    int bad = 0;
+    float* dst = a.partial + (size_t)tile * a.p_stride;
+    auto put = [&](int idx, float g) {
+      g *= inv;
+      bad |= partial_bad(g);
+      dst[idx] = g;
+    };
+    int* any_bad = reinterpret_cast<int*>(smem + L.loss_off);
+    if (tid == 0) *any_bad = 0;
+    __syncthreads();
+    // register r of a lane of half hf holds the gradient of output ob 32 + colfeat(rowof(r, hf)),
+    // input block column colfeat(n)
+#pragma unroll
+    for (int l = 0; l < kLayers; ++l) {
+      const int K = (l == 0) ? kEnc : H;
+      const int off = layer_param_off(H, l);
+      if (l > 0 || !(wave & 1)) {
+#pragma unroll
+        for (int b = 0; b < (l == 0 ? 1 : 2); ++b)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            put(off + (ob * 32 + colfeat(rowof(r, hf))) * K + (l == 0 ? 0 : (ib + b) * 32) + colfeat(n),
+                l == 0 ? accW0[r] : accW[l == 0 ? 0 : l - 1][b][r]);
+      }
+      if (!(wave & 1)) {
+        const float db = half_sum(accDb[l]);
+        if (hf == 0) put(off + H * K + ob * 32 + colfeat(n), db);
+      }
+    }
+    const int offh = layer_param_off(H, kLayers);
+    if (lane < 16) {
+#pragma unroll
+      for (int c = 0; c < kOut; ++c) put(offh + c * H + ob * 32 + colfeat(16 * (wave & 1) + lane), accWh[c]);
+    }
+    if (wave == 0) {
+      wave_loss = wave_sum(wave_loss);
+      if (lane == 0) a.tile_loss[tile] = wave_loss;
+#pragma unroll
+      for (int c = 0; c < kOut; ++c) {
+        const float g = wave_sum(accDbH[c]);
+        if (lane == c) put(offh + kOut * H + c, g);
+      }
+    }
+    if (bad) *any_bad = 1;  // every writer stores the same value
+    __syncthreads();
+    if (tid == 0 && *any_bad) atomicOr(&a.flags[k], 1);
+    __syncthreads();
+  }
+}
+
 // ---------------------------------------------------------------------------------------------
 // Tile kernel for wide models (H = 64, 128): the four waves of a workgroup split every weight
 // gradient by rows. Each wave runs the forward, rendering, adjoint and delta chain of its own
@@ -2263,19 +2626,16 @@ __global__ void __launch_bounds__(256, 1) k_step_coop(const StepArgs a_in) {
   const int m16 = lane & 15, kg = lane >> 4;
   const int S = a.S;
   const int rpw = kSlots / S;
-  const int n_tiles = clamp_tiles(a.tile_start[a.n_objects], a.max_tiles);
+  const int n_tiles = clamp_tiles(a.width_start[a.n_objects], a.max_tiles);  // of this width
   float* Bl = reinterpret_cast<float*>(smem + C.B_off);
   if (tid < 3 * kFeatures) Bl[tid] = a.B[tid];
   unsigned char* const scr0 = smem + C.scratch_off;
   int staged = -1;
 
-  for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-    int jlo = 0, jhi = a.n_objects;
-    while (jhi - jlo > 1) {
-      const int mid = (jlo + jhi) >> 1;
-      if (a.tile_start[mid] <= tile) jlo = mid; else jhi = mid;
-    }
-    const int j = jlo;
+  for (int t = first_tile_of_block(blockIdx.x, gridDim.x, n_tiles); t < n_tiles; t += gridDim.x) {
+    const int j = gen_object(a.width_start, a.n_objects, t);
+    const int ti = t - a.width_start[j], tile = a.tile_start[j] + ti;  // of the object; of the work list
+    if (tile < 0 || tile >= a.max_tiles) continue;  // (not for a consistent work list)
     // uniform by construction: the weight-image and partial buffer resources live in SGPRs
     const int k = __builtin_amdgcn_readfirstlane(a.object_ids[j]);
     if (k < 0 || k >= a.max_objects || !a.desc[k].registered) {
@@ -2284,8 +2644,7 @@ __global__ void __launch_bounds__(256, 1) k_step_coop(const StepArgs a_in) {
     }
     if (kernel_width(a.desc[k].hidden) != H) continue;
     const int rpt = tile_rays(H, a.rays_per_tile, a.rays_per_tile_wide);
-    const RayRange rr = tile_ray_range(a.ray_offsets[j], a.ray_offsets[j + 1], tile - a.tile_start[j],
-                                       rpt, a.n_rays);
+    const RayRange rr = tile_ray_range(a.ray_offsets[j], a.ray_offsets[j + 1], ti, rpt, a.n_rays);
     const int ray_lo = rr.lo, ray_hi = rr.hi;
     const unsigned char* wb = smem;
     if constexpr (GW) {
@@ -2798,66 +3157,79 @@ __global__ void __launch_bounds__(256) k_query(const QueryArgs qa) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Tile offsets per batch object (exclusive scan of ceil(rays / rays_per_tile)); clears the
-// non-finite flags of the batch's objects and records each object's next Adam step count, so
-// that the optimiser kernels read it from here while one of their blocks advances the count.
-// Checks the ray offsets as step_table does: a batch that fails gets no tiles, and the optimiser
-// kernels leave every object unchanged (ScalerState::batch_ok).
+// Tile offsets per batch object (exclusive scan of ceil(rays / rays_per_tile)), and the same over
+// the objects of each fused kernel width alone (width_start: three scans of n_objects + 1), so that
+// a width's launch finds its own tiles: workgroup t of it takes the t-th, and none starts only to
+// pass over another width's tile. Clears the non-finite flags of the batch's objects and records
+// each object's next Adam step count, so that the optimiser kernels read it from here while one of
+// their blocks advances the count. Checks the ray offsets as step_table does: a batch that fails
+// gets no tiles, and the optimiser kernels leave every object unchanged (ScalerState::batch_ok).
+// One workgroup, an object per thread, scans by DPP within waves: bound by three dependent loads
+// (offsets and ids, descriptor, stores).
 
 __global__ void __launch_bounds__(1024) k_worklist(int n_objects, int n_rays, const int32_t* ids,
                                                    const int32_t* offs, int rpt, int rpt_wide, int rpt_gen,
                                                    int max_objects, const ObjDesc* __restrict__ desc,
                                                    ScalerState* __restrict__ scaler,
                                                    int32_t* __restrict__ tile_start,
+                                                   int32_t* __restrict__ width_start, int width_pitch,
                                                    int32_t* __restrict__ flags,
                                                    int32_t* __restrict__ t_next,
                                                    const BatchDev* __restrict__ bd) {
-  __shared__ int part[1024];
+  __shared__ int wtot[16][4];
   if (bd) {
     n_objects = bd->n_objects;
     n_rays = bd->n_rays;
     ids = bd->object_ids;
     offs = bd->ray_offsets;
   }
-  const int tid = threadIdx.x, nt = blockDim.x;
-  const int per = (n_objects + nt - 1) / nt;
-  const int j0 = min(tid * per, n_objects), j1 = min(j0 + per, n_objects);
-  int local = 0, bad = 0;
-  // rays per tile of batch object j (by its width; invalid ids take the narrow size)
-  auto rpt_of = [&](int j) {
-    const int k = ids[j];
-    if (k < 0 || k >= max_objects || !desc[k].registered) return rpt;
-    const int h = desc[k].hidden;
-    return generic_width(h) ? rpt_gen : tile_rays(h, rpt, rpt_wide);
-  };
-  auto seg_ok = [&](int j, int o0, int o1) { return batch_segment_ok(j, n_objects, o0, o1, n_rays); };
-  for (int j = j0; j < j1; ++j) {
-    const int o0 = offs[j], o1 = offs[j + 1];
-    const bool ok = seg_ok(j, o0, o1);
-    bad |= !ok;
-    local += ok ? tiles_of(o1 - o0, rpt_of(j)) : 0;
-    const int k = ids[j];
-    const bool valid = k >= 0 && k < max_objects;
-    if (valid) flags[k] = 0;
-    // step count after this batch's update, read by the optimiser kernels
-    t_next[j] = (valid && desc[k].registered) ? desc[k].step + 1 : 0;
-  }
-  part[tid] = local;
+  const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wave = tid >> 6, nw = nt >> 6;
+  int bad = 0;
+  for (int j = tid; j < n_objects; j += nt) bad |= !batch_segment_ok(j, n_objects, offs[j], offs[j + 1], n_rays);
   const bool any_bad = __syncthreads_or(bad) != 0;
-  for (int off = 1; off < nt; off <<= 1) {
-    const int v = (tid >= off) ? part[tid - off] : 0;
+  int carry[4] = {0, 0, 0, 0};  // all tiles, then those of widths 32, 64 and 128
+  for (int base = 0; base < n_objects; base += nt) {
+    const int j = base + tid;
+    int cnt[4] = {0, 0, 0, 0};
+    if (j < n_objects) {
+      const int o0 = offs[j], o1 = offs[j + 1], k = ids[j];
+      const bool in_range = k >= 0 && k < max_objects;
+      const ObjDesc& d = desc[in_range ? k : 0];  // (an id out of range: discarded)
+      const int registered = d.registered, hidden = d.hidden, step = d.step;
+      const bool valid = in_range && registered;
+      // rays per tile by the object's width (invalid ids take the narrow size)
+      const int per = !valid ? rpt : (generic_width(hidden) ? rpt_gen : tile_rays(hidden, rpt, rpt_wide));
+      cnt[0] = any_bad ? 0 : tiles_of(o1 - o0, per);
+      // an invalid object's tiles go to every width's launch, which report it and pass on
+#pragma unroll
+      for (int w = 0; w < 3; ++w) cnt[1 + w] = (!valid || kernel_width(hidden) == (32 << w)) ? cnt[0] : 0;
+      if (in_range) flags[k] = 0;
+      // step count after this batch's update, read by the optimiser kernels
+      t_next[j] = valid ? step + 1 : 0;
+    }
+    int x[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      x[i] = wave_scan(cnt[i]);
+      if (lane == kWave - 1) wtot[wave][i] = x[i];
+    }
     __syncthreads();
-    part[tid] += v;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      int before = carry[i];
+      for (int w = 0; w < nw; ++w) {
+        const int v = wtot[w][i];
+        if (w < wave) before += v;
+        carry[i] += v;
+      }
+      if (j < n_objects) (i == 0 ? tile_start : width_start + (i - 1) * width_pitch)[j] = before + x[i] - cnt[i];
+    }
     __syncthreads();
   }
-  int run = part[tid] - local;
-  for (int j = j0; j < j1; ++j) {
-    tile_start[j] = any_bad ? 0 : run;
-    const int o0 = offs[j], o1 = offs[j + 1];
-    run += seg_ok(j, o0, o1) ? tiles_of(o1 - o0, rpt_of(j)) : 0;
-  }
-  if (tid == nt - 1) {
-    tile_start[n_objects] = any_bad ? 0 : part[nt - 1];
+  if (tid == 0) {
+    tile_start[n_objects] = carry[0];
+#pragma unroll
+    for (int w = 0; w < 3; ++w) width_start[w * width_pitch + n_objects] = carry[1 + w];
     scaler->batch_ok = !any_bad;
     if (any_bad) atomicOr(&scaler->device_error, DERR_OFFSETS);
   }
@@ -3434,6 +3806,10 @@ static hipError_t launch_tiles_t(const StepArgs& a_in, int nwaves, int grid, hip
       a.lds_rays = 2 * (bytes + 3 * words) <= 160 * 1024;
       bytes += (a.lds_rays ? 3 : 1) * words;
     }
+  } else if constexpr (H == 128 && BF && MODE == MODE_TRAIN) {
+    fn = reinterpret_cast<const void*>(k_step_128);
+    bytes = lds128().total;
+    nwaves = 8;
   } else if constexpr (H == 64 && BF) {
     fn = reinterpret_cast<const void*>(k_step_64<MODE>);
     bytes = MODE == MODE_FWD ? lds64().scratch_off : lds64().total;
@@ -3449,6 +3825,8 @@ static hipError_t launch_tiles_t(const StepArgs& a_in, int nwaves, int grid, hip
   // (with the table, a workgroup more: the first publishes it for the optimiser)
   if constexpr (H == 32)
     hipLaunchKernelGGL((k_step_tiles<H, BF, MODE>), dim3(MODE == MODE_STEP ? grid + 1 : grid), dim3(nwaves * kWave), bytes, s, a);
+  else if constexpr (H == 128 && BF && MODE == MODE_TRAIN)
+    hipLaunchKernelGGL(k_step_128, dim3(grid), dim3(nwaves * kWave), bytes, s, a);
   else if constexpr (H == 64 && BF)
     hipLaunchKernelGGL((k_step_64<MODE>), dim3(grid), dim3(nwaves * kWave), bytes, s, a);
   else
@@ -3543,12 +3921,13 @@ hipError_t launch_worklist(int n_objects, int n_rays, const int32_t* object_ids,
                            const int32_t* ray_offsets, int rays_per_tile, int rays_per_tile_wide,
                            int rays_per_tile_gen,
                            int max_objects, const ObjDesc* desc, ScalerState* scaler,
-                           int32_t* tile_start, int32_t* flags, int32_t* t_next,
+                           int32_t* tile_start, int32_t* width_start, int32_t* flags, int32_t* t_next,
                            const BatchDev* bd, hipStream_t s) {
   if (rays_per_tile_gen < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_worklist, dim3(1), dim3(1024), 0, s, n_objects, n_rays, object_ids,
+  // (fewer waves meet at the barriers for a small batch)
+  hipLaunchKernelGGL(k_worklist, dim3(1), dim3(n_objects <= 256 ? 256 : 1024), 0, s, n_objects, n_rays, object_ids,
                      ray_offsets, rays_per_tile, rays_per_tile_wide, rays_per_tile_gen, max_objects,
-                     desc, scaler, tile_start, flags, t_next, bd);
+                     desc, scaler, tile_start, width_start, max_objects + 1, flags, t_next, bd);
   return hipGetLastError();
 }
 
@@ -3761,21 +4140,6 @@ __global__ void __launch_bounds__(256) k_gen_encode(const GenArgs g_in) {
   unsigned int* out = reinterpret_cast<unsigned int*>(g.act + ((int64_t)tl.lo * S + lane) * g.ld);
 #pragma unroll
   for (int i = 0; i < 16; ++i) out[i] = w[i];
-}
-
-// Lane `lane`'s MFMA operand from a row-major BF16 tile T (pitch P elements, a multiple of 4): the
-// operand's K index runs down the rows kb + 8 (lane / 32) + 0..7 and its row or column index is
-// column cb + (lane mod 32). Lanes x, x + 4, x + 8 and x + 12 of each 16-lane group address four
-// consecutive rows at the same four-column run, so each ds_read_b64_tr_b16 hands every lane four
-// consecutive rows of its own column (the lane mapping the fused kernels' weight gradients use);
-// the second read, four rows further down, gives the other four of its eight.
-template <int P>
-__device__ __forceinline__ bf16x8 tr_operand(const uint16_t* T, int kb, int cb, int lane) {
-  typedef __attribute__((address_space(3))) v4i16 lds_v4;
-  const uint16_t* p = T + (kb + 8 * (lane >> 5) + ((lane & 15) >> 2)) * P + cb + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-  const v4i16 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4*)(p));
-  const v4i16 y = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4*)(p + 4 * P));
-  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(x, y, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
 // Rows of product block b of the layered chain: T = 64, row tile b (at most 64 rows, whole rays);
