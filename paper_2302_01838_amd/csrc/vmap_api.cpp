@@ -148,8 +148,8 @@ WorkLayout work_layout(const vmap_config* c) {
   w.max_tiles = (c->max_rays + rpt - 1) / rpt + c->max_objects;
   size_t off = 0;
   w.tile_start = off; off = align256(off + ((size_t)c->max_objects + 1) * 4);
-  // the same over the objects of width 32, 64 and 128 alone
-  w.width_start = off; off = align256(off + 3 * ((size_t)c->max_objects + 1) * 4);
+  // the same over the objects of width 32, 64 and 128 alone, and the optimiser's units
+  w.width_start = off; off = align256(off + 4 * ((size_t)c->max_objects + 1) * 4);
   w.flags = off; off = align256(off + (size_t)c->max_objects * 4);
   w.t_next = off; off = align256(off + (size_t)c->max_objects * 4);
   w.mark = off; off = align256(off + (size_t)c->max_objects * 4);  // debug validation of ids
@@ -253,6 +253,7 @@ struct vmap_ctx {
   int32_t* width_start(int H) {
     return reinterpret_cast<int32_t*>(work + wl.width_start) + (size_t)(H == 32 ? 0 : H == 64 ? 1 : 2) * (cfg.max_objects + 1);
   }
+  int32_t* opt_start() { return width_start(32) + 3 * ((size_t)cfg.max_objects + 1); }
   int32_t* flags() { return reinterpret_cast<int32_t*>(work + wl.flags); }
   int32_t* t_next() { return reinterpret_cast<int32_t*>(work + wl.t_next); }
   int32_t* mark() { return reinterpret_cast<int32_t*>(work + wl.mark); }
@@ -394,6 +395,7 @@ OptArgs make_opt_args(vmap_ctx* c, const vmap_batch* b, float* loss_out, float* 
   a.partial = c->partial();
   a.tile_loss = c->tile_loss();
   a.t_next = c->t_next();
+  a.opt_start = c->opt_start();
   a.p_stride = c->p_stride;
   a.max_objects = c->cfg.max_objects;
   a.desc = c->desc();

@@ -359,6 +359,7 @@ struct OptArgs {
   const float* partial;
   const float* tile_loss;
   const int32_t* t_next;      // per batch object, from k_worklist
+  const int32_t* opt_start;   // [n_objects + 1] scan of k_reduce_adam_wide's units, from k_worklist
   const int32_t* tile_bad;    // [tiles] non-finite partial per tile (MODE_STEP), or NULL: flags
   unsigned char* img32;       // weight images of width-32 objects [max_objects][img32_bytes]
   unsigned char* wimage;      // BF16 weight images of hidden-128 objects [max_objects][stride], or NULL

@@ -938,20 +938,49 @@ __device__ __forceinline__ void render_subtile(const StepArgs& a, int r0, int ns
 // tile launch (below) the table, step counts and cleared flags come from the tile kernel and the
 // non-finite reports from its tiles.
 
-// Sum of an object's tile partials at parameter p, in tile order; up to 32 loads are issued
-// before the first add (objects here have at most a few tens of tiles).
+// Sum of an object's tile partials at parameter p; up to 32 loads are issued before the first add.
+// At most kSplitTiles tiles: in tile order. More: the tiles' four consecutive quarters (tile_quarter),
+// each in tile order, then the quarters in order, so that a workgroup's waves can take a quarter
+// each (k_reduce_adam_wide). The order depends on the object's tile count alone.
+constexpr int kSplitTiles = 32;
+// Units of k_reduce_adam_wide of an object (at least one, for its loss).
+__device__ __forceinline__ int opt_units(int n_params, int tiles) {
+  const int unit = tiles > kSplitTiles ? 256 : 1024;
+  return max(1, (n_params + unit - 1) / unit);
+}
+__device__ __forceinline__ TileRange tile_quarter(int t0, int t1, int q) {
+  const int len = (t1 - t0 + 3) >> 2, a = t0 + q * len;
+  return TileRange{min(a, t1), min(a + len, t1)};
+}
 __device__ __forceinline__ float tile_sum(const float* __restrict__ partial, int p_stride, int t0,
                                           int t1, int p) {
-  float g = 0.f;
-  for (int t = t0; t < t1; t += 32) {
-    float x[32];
+  if (t1 - t0 <= kSplitTiles) {
+    float g = 0.f, x[kSplitTiles];
 #pragma unroll
-    for (int u = 0; u < 32; ++u) x[u] = (t + u < t1) ? partial[(size_t)(t + u) * p_stride + p] : 0.f;
+    for (int u = 0; u < kSplitTiles; ++u) x[u] = (t0 + u < t1) ? partial[(size_t)(t0 + u) * p_stride + p] : 0.f;
 #pragma unroll
-    for (int u = 0; u < 32; ++u)
-      if (t + u < t1) g += x[u];
+    for (int u = 0; u < kSplitTiles; ++u)
+      if (t0 + u < t1) g += x[u];
+    return g;
   }
-  return g;
+  TileRange q[4];
+  float g[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) q[i] = tile_quarter(t0, t1, i);
+  for (int b = 0; b < q[0].t1 - q[0].t0; b += 8) {  // (the first quarter is the longest)
+    float x[4][8];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        x[i][u] = (q[i].t0 + b + u < q[i].t1) ? partial[(size_t)(q[i].t0 + b + u) * p_stride + p] : 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (q[i].t0 + b + u < q[i].t1) g[i] += x[i][u];
+  }
+  return ((g[0] + g[1]) + g[2]) + g[3];
 }
 
 
@@ -1030,9 +1059,18 @@ struct AdamCoef {
   float step, rs, b1, c1, b2, c2, eps;
 };
 
+// b^t for a step count t >= 0, by squaring: one thread works it out while a workgroup's loads are
+// in flight, and the chain of the general pow was longer than theirs.
+__device__ __forceinline__ double pow_step(double b, int t) {
+  double r = 1.0;
+  for (unsigned int e = (unsigned int)max(t, 0); e; e >>= 1, b *= b)
+    if (e & 1u) r *= b;
+  return r;
+}
+
 // Bias-corrected step size and 1/sqrt(bias correction of v) in FP64, then rounded once.
 __device__ __forceinline__ void adam_coef_store(const OptArgs& a, int t, float* sh) {
-  const double bc1 = 1.0 - pow(a.beta1, (double)t), bc2 = 1.0 - pow(a.beta2, (double)t);
+  const double bc1 = 1.0 - pow_step(a.beta1, t), bc2 = 1.0 - pow_step(a.beta2, t);
   sh[0] = (float)(a.lr / bc1);
   sh[1] = (float)(1.0 / sqrt(bc2));
 }
@@ -3158,9 +3196,10 @@ __global__ void __launch_bounds__(256) k_query(const QueryArgs qa) {
 
 // ---------------------------------------------------------------------------------------------
 // Tile offsets per batch object (exclusive scan of ceil(rays / rays_per_tile)), and the same over
-// the objects of each fused kernel width alone (width_start: three scans of n_objects + 1), so that
+// the objects of each fused kernel width alone (width_start: scans of n_objects + 1), so that
 // a width's launch finds its own tiles: workgroup t of it takes the t-th, and none starts only to
-// pass over another width's tile. Clears the non-finite flags of the batch's objects and records
+// pass over another width's tile. A fourth scan counts each object's units of k_reduce_adam_wide.
+// Clears the non-finite flags of the batch's objects and records
 // each object's next Adam step count, so that the optimiser kernels read it from here while one of
 // their blocks advances the count. Checks the ray offsets as step_table does: a batch that fails
 // gets no tiles, and the optimiser kernels leave every object unchanged (ScalerState::batch_ok).
@@ -3176,7 +3215,7 @@ __global__ void __launch_bounds__(1024) k_worklist(int n_objects, int n_rays, co
                                                    int32_t* __restrict__ flags,
                                                    int32_t* __restrict__ t_next,
                                                    const BatchDev* __restrict__ bd) {
-  __shared__ int wtot[16][4];
+  __shared__ int wtot[16][5];
   if (bd) {
     n_objects = bd->n_objects;
     n_rays = bd->n_rays;
@@ -3187,15 +3226,15 @@ __global__ void __launch_bounds__(1024) k_worklist(int n_objects, int n_rays, co
   int bad = 0;
   for (int j = tid; j < n_objects; j += nt) bad |= !batch_segment_ok(j, n_objects, offs[j], offs[j + 1], n_rays);
   const bool any_bad = __syncthreads_or(bad) != 0;
-  int carry[4] = {0, 0, 0, 0};  // all tiles, then those of widths 32, 64 and 128
+  int carry[5] = {0, 0, 0, 0, 0};  // all tiles, those of widths 32, 64 and 128, optimiser units
   for (int base = 0; base < n_objects; base += nt) {
     const int j = base + tid;
-    int cnt[4] = {0, 0, 0, 0};
+    int cnt[5] = {0, 0, 0, 0, 0};
     if (j < n_objects) {
       const int o0 = offs[j], o1 = offs[j + 1], k = ids[j];
       const bool in_range = k >= 0 && k < max_objects;
       const ObjDesc& d = desc[in_range ? k : 0];  // (an id out of range: discarded)
-      const int registered = d.registered, hidden = d.hidden, step = d.step;
+      const int registered = d.registered, hidden = d.hidden, step = d.step, n_params = d.n_params;
       const bool valid = in_range && registered;
       // rays per tile by the object's width (invalid ids take the narrow size)
       const int per = !valid ? rpt : (generic_width(hidden) ? rpt_gen : tile_rays(hidden, rpt, rpt_wide));
@@ -3203,19 +3242,20 @@ __global__ void __launch_bounds__(1024) k_worklist(int n_objects, int n_rays, co
       // an invalid object's tiles go to every width's launch, which report it and pass on
 #pragma unroll
       for (int w = 0; w < 3; ++w) cnt[1 + w] = (!valid || kernel_width(hidden) == (32 << w)) ? cnt[0] : 0;
+      cnt[4] = valid ? opt_units(n_params, cnt[0]) : 1;
       if (in_range) flags[k] = 0;
       // step count after this batch's update, read by the optimiser kernels
       t_next[j] = valid ? step + 1 : 0;
     }
-    int x[4];
+    int x[5];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < 5; ++i) {
       x[i] = wave_scan(cnt[i]);
       if (lane == kWave - 1) wtot[wave][i] = x[i];
     }
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < 5; ++i) {
       int before = carry[i];
       for (int w = 0; w < nw; ++w) {
         const int v = wtot[w][i];
@@ -3229,7 +3269,7 @@ __global__ void __launch_bounds__(1024) k_worklist(int n_objects, int n_rays, co
   if (tid == 0) {
     tile_start[n_objects] = carry[0];
 #pragma unroll
-    for (int w = 0; w < 3; ++w) width_start[w * width_pitch + n_objects] = carry[1 + w];
+    for (int w = 0; w < 4; ++w) width_start[w * width_pitch + n_objects] = carry[1 + w];
     scaler->batch_ok = !any_bad;
     if (any_bad) atomicOr(&scaler->device_error, DERR_OFFSETS);
   }
@@ -3244,10 +3284,7 @@ __global__ void __launch_bounds__(256) k_reduce(const OptArgs a_in, int want_gra
   const TileRange tr = clamp_tile_range(a.tile_start[j], a.tile_start[j + 1], a.max_tiles);
   const int t0 = tr.t0, t1 = tr.t1;
   if (blockIdx.x == 0 && threadIdx.x == 0 && a.loss_out) {
-    float s = 0.f;
-    if (valid)
-      for (int t = t0; t < t1; ++t) s += a.tile_loss[t];
-    a.loss_out[j] = s;
+    a.loss_out[j] = valid ? tile_sum(a.tile_loss, 1, t0, t1, 0) : 0.f;
   }
   if (!want_grad || !valid) return;
   const int P = a.desc[k].n_params;
@@ -3349,76 +3386,151 @@ __global__ void __launch_bounds__(256) k_reduce_adam(const OptArgs a_in) {
   if (lead) a.desc[k].step = t;
 }
 
-// k_reduce_adam for objects of many parameters: a row of workgroups per batch object (its width
-// capped by the launch) walks the object's parameters four at a time per thread, so that the
-// object's descriptor, tile range, skip test and Adam coefficients are settled once per workgroup
-// rather than once per 256 parameters. Per parameter the same arithmetic in the same order:
-// the tiles' partials summed in tile order from zero, then one Adam update.
-__global__ void __launch_bounds__(256) k_reduce_adam_wide(const OptArgs a_in) {
+// k_reduce_adam for stacks with objects of many parameters. The batch's parameters are cut into
+// units of one object each (opt_units, their scan left by k_worklist). Without `rows` every
+// workgroup takes a run of consecutive units, so that an object's descriptor, tile range, skip test
+// and Adam coefficients are settled once per workgroup and object, whatever the objects' widths;
+// with it a row of that many workgroups per object walks the object's units in turn. Per
+// parameter the same arithmetic in the same order: the tiles' partials summed in tile_sum's order
+// from zero, then one Adam update. A unit is 1024 parameters, four to a thread; of an object of more
+// than kSplitTiles tiles it is 256, each wave summing a quarter of the tiles for all of them (four
+// parameters per lane) and each thread updating one.
+//
+// Memory bound where objects are large (hidden 1024: 34 B per parameter), by dependent loads where
+// they are small or have many tiles. A row of workgroups per object, as wide as the largest object
+// needs, took 28 us for a hidden-128 object of 100 tiles beside fifty of hidden 32: some 4,000
+// workgroups of which all but a few hundred found nothing to do, three to a CU; 15 us in runs.
+// Stacks of a layered width (all large objects) keep rows: neighbouring workgroups stream
+// neighbouring memory, 1 % of the hidden-1024 step. The partials are read and the gradients
+// written without caching (nothing reads them again soon): 1 % of the hidden-256 step.
+__global__ void __launch_bounds__(256, 4) k_reduce_adam_wide(const OptArgs a_in, int rows) {
   OptArgs a = a_in;
   read_batch(a);
-  const int j = blockIdx.y;
-  if (j == (int)gridDim.y - 1) {
-    if (blockIdx.x == 0) scaler_update(a);
+  const int blocks = (int)gridDim.x - 1;
+  if ((int)blockIdx.x == blocks) {
+    scaler_update(a);
     return;
   }
-  const int k = a.ids[j];
-  const TileRange tr = clamp_tile_range(a.tile_start[j], a.tile_start[j + 1], a.max_tiles);
-  const int t0 = tr.t0, t1 = tr.t1;
-  const int r0 = a.offs[j], r1 = a.offs[j + 1];
-  const int t = a.t_next[j];
-  const int batch_ok = a.scaler->batch_ok;
-  const bool in_range = k >= 0 && k < a.max_objects;
-  const int kc = in_range ? k : 0;
-  const ObjDesc& d = a.desc[kc];
-  const int registered = d.registered, n_params = d.n_params, hidden = d.hidden;
-  const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
-  float loss = 0.f;
-  if (lead && a.loss_out) loss = tile_sum(a.tile_loss, 1, t0, t1, 0);
   __shared__ float sh[2];
-  if (threadIdx.x == 0) adam_coef_store(a, t, sh);
-  const bool valid = in_range && registered != 0 && batch_ok;
-  if (lead && a.loss_out) a.loss_out[j] = valid ? loss : 0.f;
-  if (!valid || r1 <= r0) return;
-  if (object_bad(a, j, k)) {
-    if (a.tile_bad && lead) a.flags[k] = 1;
-    return;
+  __shared__ __attribute__((aligned(16))) float part[4][256];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  int u0, u1, du = 1;
+  if (rows > 0) {
+    const int j = blockIdx.x / rows;
+    u0 = a.opt_start[j] + (int)blockIdx.x % rows;
+    u1 = a.opt_start[j + 1];
+    du = rows;
+  } else {
+    const int total = a.opt_start[a.n_objects];
+    u0 = (int)((long long)total * blockIdx.x / blocks);
+    u1 = (int)((long long)total * (blockIdx.x + 1) / blocks);
   }
-  const AdamCoef c = adam_coef_load(a, sh);
-  const size_t base = (size_t)k * a.p_stride;
-  // p_stride is a multiple of 4, so p + 3 < p_stride for every p taken
-  for (int p = (blockIdx.x * blockDim.x + threadIdx.x) * 4; p < n_params; p += gridDim.x * blockDim.x * 4) {
+  int first = 0, end = 0, k = 0, t0 = 0, t1 = 0, n_params = 0, hidden = 0;
+  bool live = false;
+  AdamCoef c{};
+  for (int u = u0; u < u1; u += du) {
+    if (u >= end) {  // the next object
+      const int j = gen_object(a.opt_start, a.n_objects, u);
+      first = a.opt_start[j];
+      end = a.opt_start[j + 1];
+      k = a.ids[j];
+      const TileRange tr = clamp_tile_range(a.tile_start[j], a.tile_start[j + 1], a.max_tiles);
+      t0 = tr.t0;
+      t1 = tr.t1;
+      const int r0 = a.offs[j], r1 = a.offs[j + 1], t = a.t_next[j];
+      const bool in_range = k >= 0 && k < a.max_objects;
+      const ObjDesc& d = a.desc[in_range ? k : 0];
+      n_params = d.n_params;
+      hidden = d.hidden;
+      const bool valid = in_range && d.registered != 0 && a.scaler->batch_ok;
+      const bool lead = u == first && tid == 0;
+      __syncthreads();  // the previous object's coefficients have been read
+      if (tid == 0) adam_coef_store(a, t, sh);
+      if (lead && a.loss_out) a.loss_out[j] = valid ? tile_sum(a.tile_loss, 1, t0, t1, 0) : 0.f;
+      live = valid && r1 > r0;
+      // (the barrier of object_bad also publishes the coefficients)
+      if (live && object_bad(a, j, k)) {
+        if (a.tile_bad && lead) a.flags[k] = 1;
+        live = false;
+      }
+      if (live) {
+        c = adam_coef_load(a, sh);
+        if (lead) a.desc[k].step = t;
+      }
+    }
+    if (!live) {
+      u = end - du;  // (a row's workgroups stay with their object)
+      continue;
+    }
+    const size_t base = (size_t)k * a.p_stride;
+    if (t1 - t0 > kSplitTiles) {
+      const int p0 = (u - first) * 256, p = p0 + tid;
+      const bool mine = p < n_params;
+      float th = 0.f, m = 0.f, v = 0.f;
+      if (mine) {
+        th = a.theta[base + p];
+        m = a.m[base + p];
+        v = a.v[base + p];
+      }
+      f32x4 g = {0.f, 0.f, 0.f, 0.f};
+      if (p0 + 4 * lane < n_params) {  // (four slots from a multiple of 4: within p_stride)
+        const TileRange tq = tile_quarter(t0, t1, wave);
+        const float* src = a.partial + padded_index(hidden, p0 + 4 * lane);
+        for (int tt = tq.t0; tt < tq.t1; tt += 8) {
+          f32x4 x[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+            x[i] = (tt + i < tq.t1) ? *reinterpret_cast<const f32x4*>(src + (size_t)(tt + i) * a.p_stride) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+            if (tt + i < tq.t1) g += x[i];
+        }
+      }
+      __syncthreads();  // the previous unit's sums have been read
+      *reinterpret_cast<f32x4*>(&part[wave][4 * lane]) = g;
+      __syncthreads();
+      if (!mine) continue;
+      const float s = ((part[0][tid] + part[1][tid]) + part[2][tid]) + part[3][tid];
+      a.grad[base + p] = s;
+      if (isfinite(s)) {
+        adam_elem(c, s, th, m, v);
+        a.theta[base + p] = th;
+        a.m[base + p] = m;
+        a.v[base + p] = v;
+      } else {
+        atomicOr(&a.flags[k], 2);
+      }
+      update_image(a, k, hidden, p, th);
+      continue;
+    }
+    // p_stride is a multiple of 4, so p + 3 < p_stride for every p taken
+    const int p = (u - first) * 1024 + 4 * tid;
+    if (p >= n_params) continue;
     const size_t i = base + p;
-    const float4 x = *reinterpret_cast<const float4*>(a.theta + i);
-    const float4 y = *reinterpret_cast<const float4*>(a.m + i);
-    const float4 z = *reinterpret_cast<const float4*>(a.v + i);
-    float th[4] = {x.x, x.y, x.z, x.w}, m[4] = {y.x, y.y, y.z, y.w}, v[4] = {z.x, z.y, z.z, z.w};
-    float g[4] = {0.f, 0.f, 0.f, 0.f};
+    const f32x4 x = *reinterpret_cast<const f32x4*>(a.theta + i);
+    const f32x4 y = *reinterpret_cast<const f32x4*>(a.m + i);
+    const f32x4 z = *reinterpret_cast<const f32x4*>(a.v + i);
+    float th[4] = {x[0], x[1], x[2], x[3]}, m[4] = {y[0], y[1], y[2], y[3]}, v[4] = {z[0], z[1], z[2], z[3]};
+    f32x4 g = {0.f, 0.f, 0.f, 0.f};
     // slot of p in the partials (hidden 16: the width-32 layout, where four parameters p..p+3
     // with p a multiple of 4 stay four consecutive slots)
-    const int pq = padded_index(hidden, p);
-    for (int tt = t0; tt < t1; tt += 8) {
-      float4 q[8];
+    const float* src = a.partial + padded_index(hidden, p);
+    for (int tt = t0; tt < t1; tt += 4) {
+      f32x4 q[4];
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
-        q[u] = (tt + u < t1) ? *reinterpret_cast<const float4*>(a.partial + (size_t)(tt + u) * a.p_stride + pq)
-                             : make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int e = 0; e < 4; ++e)
+        q[e] = (tt + e < t1) ? __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(src + (size_t)(tt + e) * a.p_stride)) : f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (tt + u < t1) {
-          g[0] += q[u].x;
-          g[1] += q[u].y;
-          g[2] += q[u].z;
-          g[3] += q[u].w;
-        }
+      for (int e = 0; e < 4; ++e)
+        if (tt + e < t1) g += q[e];
     }
     if (p + 3 < n_params && isfinite(g[0]) && isfinite(g[1]) && isfinite(g[2]) && isfinite(g[3])) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) adam_elem(c, g[e], th[e], m[e], v[e]);
-      *reinterpret_cast<float4*>(a.grad + i) = make_float4(g[0], g[1], g[2], g[3]);
-      *reinterpret_cast<float4*>(a.theta + i) = make_float4(th[0], th[1], th[2], th[3]);
-      *reinterpret_cast<float4*>(a.m + i) = make_float4(m[0], m[1], m[2], m[3]);
-      *reinterpret_cast<float4*>(a.v + i) = make_float4(v[0], v[1], v[2], v[3]);
+      __builtin_nontemporal_store(g, reinterpret_cast<f32x4*>(a.grad + i));
+      *reinterpret_cast<f32x4*>(a.theta + i) = f32x4{th[0], th[1], th[2], th[3]};
+      *reinterpret_cast<f32x4*>(a.m + i) = f32x4{m[0], m[1], m[2], m[3]};
+      *reinterpret_cast<f32x4*>(a.v + i) = f32x4{v[0], v[1], v[2], v[3]};
       if (a.gimg && keeps_gimg(hidden)) {  // the four BF16 copies in one store (i is a multiple of 4)
         typedef unsigned int u2w __attribute__((ext_vector_type(2)));
         *reinterpret_cast<u2w*>(a.gimg + i) = u2w{pack2(th[0], th[1]), pack2(th[2], th[3])};
@@ -3443,7 +3555,6 @@ __global__ void __launch_bounds__(256) k_reduce_adam_wide(const OptArgs a_in) {
       }
     }
   }
-  if (lead) a.desc[k].step = t;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -3931,11 +4042,11 @@ hipError_t launch_worklist(int n_objects, int n_rays, const int32_t* object_ids,
   return hipGetLastError();
 }
 
-// Parameter slots per object from which the optimiser is k_reduce_adam_wide (objects of hidden 128
-// and up: whole vectors of theta, m, v and the partials; four parameters per thread measured 5 %
-// faster on a step with a hidden-128 object). Below, k_reduce_adam's one parameter per thread keeps
-// more workgroups in flight for the few-thousand-parameter objects (four per thread measured 2 %
-// slower at hidden 32).
+// Parameter slots per object from which the optimiser is k_reduce_adam_wide (stacks that may hold
+// objects of hidden 128 and up: whole vectors of theta, m, v and the partials). Below, and in a step
+// whose objects all have width 32 (tile_bad: its tile kernel built the work list), k_reduce_adam's
+// one parameter per thread keeps more workgroups in flight for the few-thousand-parameter objects
+// (four per thread measured 2 % slower at hidden 32).
 constexpr int kReduceWide = 32768;
 
 hipError_t launch_optimizer(int kind, const OptArgs& a, hipStream_t s) {
@@ -3944,10 +4055,17 @@ hipError_t launch_optimizer(int kind, const OptArgs& a, hipStream_t s) {
   if (kind == OPT_REDUCE) hipLaunchKernelGGL(k_reduce, grid, dim3(256), 0, s, a, 1);
   else if (kind == OPT_LOSS) hipLaunchKernelGGL(k_reduce, dim3(1, a.n_objects), dim3(256), 0, s, a, 0);
   else if (kind == OPT_ADAM) hipLaunchKernelGGL(k_adam, grid, dim3(256), 0, s, a);
-  else if (a.p_stride >= kReduceWide && a.p_stride % 4 == 0) {
-    // four parameters per thread, about 4096 workgroups over the batch
-    const int per_object = std::max(1, std::min((a.p_stride / 4 + 255) / 256, (4096 + a.n_objects - 1) / a.n_objects));
-    hipLaunchKernelGGL(k_reduce_adam_wide, dim3(per_object, a.n_objects + 1), dim3(256), 0, s, a);
+  else if (a.tile_bad) {
+    const int blocks = (std::min(a.p_stride, round_up(n_params_of(32), 64)) + 255) / 256;
+    hipLaunchKernelGGL(k_reduce_adam, dim3(blocks, a.n_objects + 1), dim3(256), 0, s, a);
+  } else if (a.p_stride >= kReduceWide && a.p_stride % 4 == 0) {
+    if (!a.opt_start) return hipErrorInvalidValue;
+    const int units = (a.p_stride + 1023) / 1024;  // of the widest object
+    // layered widths: about 4096 workgroups, rows of at most one per unit; otherwise four workgroups
+    // on every CU (registers), each a run of units
+    const int rows = a.gimg ? std::max(1, std::min(units, (4096 + a.n_objects - 1) / a.n_objects)) : 0;
+    const long long blocks = rows ? (long long)rows * a.n_objects : std::min<long long>((long long)a.n_objects * 4 * units, 1024);
+    hipLaunchKernelGGL(k_reduce_adam_wide, dim3((unsigned)blocks + 1), dim3(256), 0, s, a, rows);
   } else {
     if (a.wimage) return hipErrorInvalidValue;  // hidden-128 images are kept by the wide kernel
     hipLaunchKernelGGL(k_reduce_adam, dim3(grid.x, a.n_objects + 1), dim3(256), 0, s, a);
