@@ -376,10 +376,11 @@ int gen_work_rays(const vmap_ctx* c, int S) {
   return std::max(c->min_rays_per_tile, (kGenWorkRows + S - 1) / std::max(S, 1));
 }
 
+// rays_per_tile: of hidden-32 objects (0: the stack's).
 hipError_t enqueue_worklist(vmap_ctx* c, const vmap_batch* b, hipStream_t s,
-                            const BatchDev* bd = nullptr) {
+                            const BatchDev* bd = nullptr, int rays_per_tile = 0) {
   return launch_worklist(b->n_objects, b->n_rays_total, b->object_ids, b->ray_offsets,
-                         c->rays_per_tile, c->rays_per_tile_wide, gen_work_rays(c, b->samples_per_ray),
+                         rays_per_tile > 0 ? rays_per_tile : c->rays_per_tile, c->rays_per_tile_wide, gen_work_rays(c, b->samples_per_ray),
                          c->cfg.max_objects, c->desc(), c->scaler(), c->tile_start(), c->width_start(32), c->flags(),
                          c->t_next(), bd, s);
 }
@@ -424,8 +425,9 @@ OptArgs make_opt_args(vmap_ctx* c, const vmap_batch* b, float* loss_out, float* 
 // Enqueue the tile kernel for every width group.
 int enqueue_tiles(vmap_ctx* c, const vmap_batch* b, int mode, const float* dloss, float* d_out,
                   float* rgb_out, float* occ_out, hipStream_t s, bool allow_timing,
-                  const BatchDev* bd = nullptr) {
+                  const BatchDev* bd = nullptr, int rays_per_tile = 0) {
   StepArgs a = make_step_args(c, b);
+  if (rays_per_tile > 0) a.rays_per_tile = rays_per_tile;  // as given to the work list
   a.bd = bd;
   a.dloss = dloss;
   a.out_depth = d_out;
@@ -504,7 +506,7 @@ int enqueue_tiles(vmap_ctx* c, const vmap_batch* b, int mode, const float* dloss
     // fewer workgroups than the stack's smallest tile size gives (the kernels stride over tiles).
     // At hidden 128 a workgroup takes a CU by itself: no more than 256, which stride over the tiles
     // (the bound counts every width's rays, and a workgroup without a tile waits for a CU too).
-    const int rpt_h = tile_rays(H, c->rays_per_tile, c->rays_per_tile_wide);
+    const int rpt_h = tile_rays(H, a.rays_per_tile, c->rays_per_tile_wide);
     int grid_h = std::min(grid, (b->n_rays_total + rpt_h - 1) / rpt_h + b->n_objects);
     if (H == 128 && mode == MODE_TRAIN) grid_h = std::min(grid_h, 256);
     a.width_start = c->width_start(H);
@@ -909,7 +911,9 @@ static int render_scene(vmap_ctx* c, int32_t n_rays, const float* rays_o, const 
   a.scaler = c->scaler();
   a.counts = reinterpret_cast<int32_t*>(sc + L.counts);
   a.ray_offsets = reinterpret_cast<int32_t*>(sc + L.offsets);
-  a.pair_map = reinterpret_cast<int32_t*>(sc + L.map);
+  a.pair_mask = reinterpret_cast<uint32_t*>(sc + L.map);
+  // (with more than one word a ray's four bytes of the map hold the masks and the bases)
+  a.pair_base = reinterpret_cast<int32_t*>(sc + L.map) + (size_t)n_objects * ((n_rays + 31) / 32);
   a.pair_o = reinterpret_cast<float*>(sc + L.pair_o);
   a.pair_d = reinterpret_cast<float*>(sc + L.pair_d);
   a.pair_t = reinterpret_cast<float*>(sc + L.pair_t);
@@ -933,9 +937,15 @@ static int render_scene(vmap_ctx* c, int32_t n_rays, const float* rays_o, const 
     hb.samples_per_ray = S;
     hb.object_ids = object_ids;
     hb.ray_offsets = a.ray_offsets;
-    e = enqueue_worklist(c, &hb, s, a.bd);
+    // a forward tile leaves no partial and a ray's render does not depend on its tile: longer tiles
+    // than the training step's, which fetch an object's weights less often, while there are enough
+    // for two rounds of the 1024 workgroups that forward mode holds (76,800 rays, 50 objects, 117,000
+    // pairs: 121 us with tiles of 16 rays or of 64, a quarter of the weight fetches)
+    int rpt = c->rays_per_tile;
+    for (int i = 0; i < 2 && max_pairs / (2 * rpt) >= 2048; ++i) rpt *= 2;
+    e = enqueue_worklist(c, &hb, s, a.bd, rpt);
     if (e != hipSuccess) return c->hip_fail(e, "worklist launch");
-    int rc = enqueue_tiles(c, &hb, MODE_FWD, nullptr, a.pair_depth, a.pair_rgb, a.pair_occ, s, false, a.bd);
+    int rc = enqueue_tiles(c, &hb, MODE_FWD, nullptr, a.pair_depth, a.pair_rgb, a.pair_occ, s, false, a.bd, rpt);
     if (rc) return rc;
   }
   e = launch_scene(1, a, s);
@@ -1030,6 +1040,7 @@ int vmap_query_occupancy(vmap_ctx* c, int32_t k, const float* pts, int64_t n, fl
   const int H = kernel_width(c->objs[k].hidden);  // hidden 16: the width-32 kernel, zero-padded
   if (generic_width(H)) return c->fail(VMAP_ENOTSUP, "point queries of layered-path widths are not built");
   q.wimage = c->wimage();
+  q.img32 = c->img32();
   q.wimage_stride = (int64_t)c->wl.wimage_stride;
   q.max_objects = c->cfg.max_objects;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);

@@ -488,6 +488,7 @@ struct QueryArgs {
   float* occ;
   float* rgb;
   unsigned char* wimage;      // as in StepArgs (wide objects)
+  const unsigned char* img32; // as in StepArgs (width 32)
   int64_t wimage_stride;
   int max_objects;
 };
@@ -510,7 +511,8 @@ struct SceneArgs {
   // scratch
   int32_t* counts;           // [n_objects][blocks] hit counts, then their exclusive scan
   int32_t* ray_offsets;      // [n_objects + 1] pairs per object (CSR)
-  int32_t* pair_map;         // [n_objects][n_rays] pair index or -1
+  uint32_t* pair_mask;       // [n_objects][ceil(n_rays / 32)] a bit per ray that meets the object
+  int32_t* pair_base;        // the same shape: first pair of each word with a bit set (if more than one)
   float* pair_o;             // [max_pairs][3]
   float* pair_d;
   float* pair_t;             // [max_pairs][S]

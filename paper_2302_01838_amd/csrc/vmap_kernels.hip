@@ -3167,10 +3167,47 @@ __global__ void __launch_bounds__(256) k_query(const QueryArgs qa) {
   float* Bl = reinterpret_cast<float*>(smem + B_off);
   if (tid < 3 * kFeatures) Bl[tid] = qa.B[tid];
   const unsigned char* wb = smem;
-  if constexpr (GW) wb = qa.wimage + (size_t)qa.k * qa.wimage_stride;
-  else stage_weights<H, BF>(qa.theta + (size_t)qa.k * qa.p_stride, smem, tid, blockDim.x, qa.desc[qa.k].hidden);
+  if constexpr (GW) {
+    wb = qa.wimage + (size_t)qa.k * qa.wimage_stride;
+  } else if constexpr (H == 32) {  // the object's weight image is current
+    fetch_image_lds(qa.img32 + (size_t)qa.k * img32_bytes(BF), smem, B_off, lane, wave, nw);
+    __builtin_amdgcn_s_waitcnt(0);
+  } else stage_weights<H, BF>(qa.theta + (size_t)qa.k * qa.p_stride, smem, tid, blockDim.x, qa.desc[qa.k].hidden);
   __syncthreads();
   const ObjDesc d = qa.desc[qa.k];
+  if constexpr (H == 32) {
+    // a lane's own point; both passes together, as in the tile kernel (one pass after the other,
+    // points, normalisation and logistic computed by both halves: 61 us for 2.1 M points, 48 now)
+    const int64_t step = (int64_t)gridDim.x * nw * kSlots;
+    int64_t i = ((int64_t)blockIdx.x * nw + wave) * kSlots + lane;
+    float q[3] = {0.f, 0.f, 0.f};
+    auto fetch = [&](int64_t at) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) q[c] = at < qa.n ? qa.pts[3 * at + c] : 0.f;
+    };
+    fetch(i);
+    for (; i - lane < qa.n; i += step) {
+      float xt[2][4];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        const float x = i < qa.n ? (float)(((double)q[c] - d.centre[c]) * d.inv_scale) : 0.f;
+        half_split(x, xt[0][c], xt[1][c]);
+      }
+      xt[0][3] = xt[1][3] = 0.f;
+      fetch(i + step);
+      Acts<32, BF> act[2];
+      float zs[kOut];
+      forward_pair<BF>(xt, smem, Bl, lane, act, zs, false);
+      if (i < qa.n) {
+        qa.occ[i] = sigm(zs[3]);
+        if (qa.rgb) {
+#pragma unroll
+          for (int c = 0; c < 3; ++c) qa.rgb[3 * i + c] = sigm(zs[c]);
+        }
+      }
+    }
+    return;
+  }
   for (int64_t chunk = (int64_t)blockIdx.x * nw + wave; chunk * kSlots < qa.n; chunk += (int64_t)gridDim.x * nw) {
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
@@ -3699,51 +3736,122 @@ __device__ __forceinline__ bool scene_pair_valid(const SceneArgs& a, int j, int&
   return k >= 0 && k < a.max_objects && a.desc[k].registered;
 }
 
-// Block (x, j): rays [256 x, 256 x + 256) against batch object j; writes the block's hit count.
-__global__ void __launch_bounds__(256) k_scene_count(const SceneArgs a) {
-  __shared__ int wsum[4];
-  const int j = blockIdx.y, r = blockIdx.x * 256 + threadIdx.x;
-  int k;
-  bool hit = false;
-  if (scene_pair_valid(a, j, k) && r < a.n_rays) {
-    double t0, t1;
-    scene_slab(a.rays_o + 3 * (size_t)r, a.rays_d + 3 * (size_t)r, a.desc[k], a.t_min, t0, t1);
-    hit = t1 > t0;
+// Whether the ray (o, d; inv = 1 / d) certainly misses the box c +- s after t_min, in FP32: the
+// interval widened by more than the rounding of its ends (each is a difference of values up to
+// |c| + s + |o| times inv, a few roundings of 2^-24 of that; widened by 2^-19). Zero direction
+// components and NaN or infinite values are never certain.
+__device__ __forceinline__ bool scene_certain_miss(const float o[3], const float inv[3], const float4& box,
+                                                   float t_min) {
+  const float cc[3] = {box.x, box.y, box.z}, s = box.w;
+  float t0 = -INFINITY, t1 = INFINITY;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const float c = cc[a];
+    const float ta = (c - s - o[a]) * inv[a], tb = (c + s - o[a]) * inv[a];
+    const float e = (fabsf(c) + s + fabsf(o[a])) * fabsf(inv[a]) * 0x1p-19f;
+    t0 = fmaxf(t0, fminf(ta, tb) - e);
+    t1 = fminf(t1, fmaxf(ta, tb) + e);
   }
-  const unsigned long long m = __ballot(hit);
-  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = __popcll(m);
+  return t1 < t0 || t1 <= t_min;
+}
+
+// Block (x, y): rays [256 x, 256 x + 256) against batch objects [y per, (y + 1) per), per at most
+// kSceneGroup: a bit per (object, ray) that meets (words of 32 rays) and the block's hit count per
+// object. A ray is loaded once for all of them, and the FP64 slab test (seven divisions) runs only
+// where the FP32 interval does not settle it: 76,800 rays, 50 objects 23.2 us with a workgroup per
+// object and FP64 for every pair, 12.8 now.
+constexpr int kSceneGroup = 64;
+__global__ void __launch_bounds__(256) k_scene_count(const SceneArgs a, int nblk, int per) {
+  __shared__ int cnt[kSceneGroup];
+  __shared__ float4 box[kSceneGroup];  // centre and half extent in FP32 (negative: no object)
+  const int tid = threadIdx.x, lane = tid & 63, r = blockIdx.x * 256 + tid;
+  const int j0 = blockIdx.y * per, j1 = min(j0 + per, a.n_objects);
+  if (j0 + tid < j1) {
+    int k;
+    const bool valid = scene_pair_valid(a, j0 + tid, k);
+    const ObjDesc& od = a.desc[valid ? k : 0];
+    box[tid] = make_float4((float)od.centre[0], (float)od.centre[1], (float)od.centre[2],
+                           valid ? 1.0f / (float)od.inv_scale : -1.0f);
+    cnt[tid] = 0;
+  }
+  float o[3] = {0.f, 0.f, 0.f}, d[3] = {0.f, 0.f, 0.f}, inv[3];
+  const bool ray = r < a.n_rays;
+  if (ray) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      o[c] = a.rays_o[3 * (size_t)r + c];
+      d[c] = a.rays_d[3 * (size_t)r + c];
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < 3; ++c) inv[c] = 1.0f / d[c];
+  const int words = (a.n_rays + 31) >> 5;
   __syncthreads();
-  if (threadIdx.x == 0)
-    a.counts[(size_t)j * gridDim.x + blockIdx.x] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+  for (int j = j0; j < j1; ++j) {
+    bool hit = false;
+    const float4 b = box[j - j0];
+    if (b.w >= 0.f && ray && !scene_certain_miss(o, inv, b, (float)a.t_min)) {
+      double t0, t1;
+      scene_slab(o, d, a.desc[a.object_ids[j]], a.t_min, t0, t1);
+      hit = t1 > t0;
+    }
+    const unsigned long long m = __ballot(hit);
+    if ((lane & 31) == 0 && (r >> 5) < words) a.pair_mask[(size_t)j * words + (r >> 5)] = (uint32_t)(m >> lane);
+    if (lane == 0 && m) atomicAdd(&cnt[j - j0], __popcll(m));
+  }
+  __syncthreads();
+  for (int j = j0 + tid; j < j1; j += 256) a.counts[(size_t)j * nblk + blockIdx.x] = cnt[j - j0];
 }
 
 // One block: exclusive scan of the counts (object-major), the batch's CSR offsets (clamped to
-// the pair capacity) and its device descriptor.
+// the pair capacity) and its device descriptor. Sixteen consecutive counts per thread, loaded
+// together, and a DPP scan over the waves (a thread's serial loop over its share and a scan of
+// twenty barriers took 17.6 us for 15,000 counts, 9.5 now).
 __global__ void __launch_bounds__(1024) k_scene_scan(const SceneArgs a, int nblk) {
-  __shared__ int part[1024];
+  __shared__ int wtot[16];
   const int n = a.n_objects * nblk;
-  const int tid = threadIdx.x, nt = blockDim.x;
-  const int per = (n + nt - 1) / nt;
-  const int i0 = min(tid * per, n), i1 = min(i0 + per, n);
-  int local = 0;
-  for (int i = i0; i < i1; ++i) local += a.counts[i];
-  part[tid] = local;
-  __syncthreads();
-  for (int off = 1; off < nt; off <<= 1) {
-    const int v = (tid >= off) ? part[tid - off] : 0;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int carry = 0;
+  for (int base = 0; base < n; base += 16384) {
+    const int i0 = base + 16 * tid;
+    int c[16], local = 0;
+#pragma unroll
+    for (int u = 0; u < 16; u += 4) {  // (the counts' region is 256-byte aligned, its end padded)
+      int4 v = make_int4(0, 0, 0, 0);
+      if (i0 + u < n) v = *reinterpret_cast<const int4*>(a.counts + i0 + u);
+      c[u] = v.x;
+      c[u + 1] = v.y;
+      c[u + 2] = v.z;
+      c[u + 3] = v.w;
+    }
+#pragma unroll
+    for (int u = 0; u < 16; ++u) local += (i0 + u < n) ? c[u] : 0;
+    const int x = wave_scan(local);
+    if (lane == kWave - 1) wtot[wave] = x;
     __syncthreads();
-    part[tid] += v;
+    int run = carry + x - local;
+    for (int w = 0; w < 16; ++w) {
+      const int v = wtot[w];
+      if (w < wave) run += v;
+      carry += v;
+    }
+    int j = i0 / nblk, q = i0 - j * nblk;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      if (i0 + u < n) {
+        a.counts[i0 + u] = run;
+        if (q == 0) a.ray_offsets[j] = min(run, a.max_pairs);
+        run += c[u];
+        if (++q == nblk) {
+          q = 0;
+          ++j;
+        }
+      }
+    }
     __syncthreads();
   }
-  int run = part[tid] - local;
-  for (int i = i0; i < i1; ++i) {
-    const int c = a.counts[i];
-    a.counts[i] = run;
-    if (i % nblk == 0) a.ray_offsets[i / nblk] = min(run, a.max_pairs);
-    run += c;
-  }
-  if (tid == nt - 1) {
-    const int total = part[nt - 1];
+  if (tid == 0) {
+    const int total = carry;
     a.ray_offsets[a.n_objects] = min(total, a.max_pairs);
     if (a.n_pairs_out) *a.n_pairs_out = total;
     if (total > a.max_pairs) atomicOr(&a.scaler->device_error, 2);
@@ -3754,61 +3862,103 @@ __global__ void __launch_bounds__(1024) k_scene_scan(const SceneArgs a, int nblk
   }
 }
 
-// Block (x, j): the pairs of its rays with batch object j, in ray order: ray, samples at the
-// midpoints of S equal parts of [t0, t1] (FP64, rounded once), and the (object, ray) -> pair map.
-__global__ void __launch_bounds__(256) k_scene_fill(const SceneArgs a) {
-  __shared__ int wsum[4];
-  const int j = blockIdx.y, r = blockIdx.x * 256 + threadIdx.x;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  int k;
-  bool hit = false;
-  double t0 = 0.0, t1 = 0.0;
-  if (scene_pair_valid(a, j, k) && r < a.n_rays) {
-    scene_slab(a.rays_o + 3 * (size_t)r, a.rays_d + 3 * (size_t)r, a.desc[k], a.t_min, t0, t1);
-    hit = t1 > t0;
-  }
-  const unsigned long long m = __ballot(hit);
-  if (lane == 0) wsum[w] = __popcll(m);
+// Block (x, y): the pairs of its rays with its batch objects, in ray order: ray, and samples at the
+// midpoints of S equal parts of [t0, t1] (FP64, rounded once). A wave's pairs with an object are
+// consecutive, so its lanes write their samples as one run (a lane writing its own pair's S samples
+// one by one: 41.9 us for 76,800 rays, 50 objects, 117,000 pairs; 23 now).
+__global__ void __launch_bounds__(256) k_scene_fill(const SceneArgs a, int nblk, int per) {
+  __shared__ double frac[kSlots];
+  __shared__ double span[4][kWave][2];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r = blockIdx.x * 256 + tid;
+  const int j0 = blockIdx.y * per, j1 = min(j0 + per, a.n_objects);
+  const int S = a.S, words = (a.n_rays + 31) >> 5;
+  if (tid < S) frac[tid] = __ddiv_rn((double)tid + 0.5, (double)S);
   __syncthreads();
-  int pos = a.counts[(size_t)j * gridDim.x + blockIdx.x];
-  for (int i = 0; i < w; ++i) pos += wsum[i];
-  pos += __popcll(m & ((1ull << lane) - 1ull));
-  if (r >= a.n_rays) return;
-  int p = -1;
-  if (hit && pos < a.max_pairs) {
-    p = pos;
+  const int w0 = (r - lane) >> 5;  // the wave's first word
+  if (w0 >= words) return;
+  float o[3] = {0.f, 0.f, 0.f}, d[3] = {0.f, 0.f, 0.f};
+  if (r < a.n_rays) {
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      a.pair_o[3 * (size_t)p + c] = a.rays_o[3 * (size_t)r + c];
-      a.pair_d[3 * (size_t)p + c] = a.rays_d[3 * (size_t)r + c];
-    }
-    const double span = __dsub_rn(t1, t0);
-    for (int i = 0; i < a.S; ++i) {
-      const double frac = __ddiv_rn((double)i + 0.5, (double)a.S);
-      a.pair_t[(size_t)p * a.S + i] = (float)__dadd_rn(t0, __dmul_rn(frac, span));
+      o[c] = a.rays_o[3 * (size_t)r + c];
+      d[c] = a.rays_d[3 * (size_t)r + c];
     }
   }
-  a.pair_map[(size_t)j * a.n_rays + r] = p;
+  for (int j = j0; j < j1; ++j) {
+    const uint32_t m0 = a.pair_mask[(size_t)j * words + w0];
+    const uint32_t m1 = w0 + 1 < words ? a.pair_mask[(size_t)j * words + w0 + 1] : 0u;
+    const unsigned long long m = (unsigned long long)m0 | ((unsigned long long)m1 << 32);
+    if (!m) continue;  // uniform over the wave
+    // first pair of the wave: the block's first (counts, scanned) and the words before in the block
+    int p0 = a.counts[(size_t)j * nblk + blockIdx.x];
+    for (int i = w0 & ~7; i < w0; ++i) p0 += __popc(a.pair_mask[(size_t)j * words + i]);
+    if (lane == 0 && words > 1) {  // for the composite (one word: the block's first)
+      a.pair_base[(size_t)j * words + w0] = p0;
+      if (w0 + 1 < words) a.pair_base[(size_t)j * words + w0 + 1] = p0 + __popc(m0);
+    }
+    const int pairs = min(__popcll(m), a.max_pairs - p0);  // (may be negative)
+    const int rank = __popcll(m & ((1ull << lane) - 1ull));
+    wave_lds_sync();  // the previous object's intervals have been read
+    if (((m >> lane) & 1ull) && rank < pairs) {
+      const int k = a.object_ids[j];  // (a set bit: a registered object)
+      double t0, t1;
+      scene_slab(o, d, a.desc[k], a.t_min, t0, t1);
+      span[w][rank][0] = t0;
+      span[w][rank][1] = __dsub_rn(t1, t0);
+      const size_t p = (size_t)p0 + rank;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        a.pair_o[3 * p + c] = o[c];
+        a.pair_d[3 * p + c] = d[c];
+      }
+    }
+    wave_lds_sync();
+    int q = lane / S, i = lane - q * S;
+    const int dq = kWave / S, di = kWave - dq * S;
+    for (int e = lane; e < pairs * S; e += kWave) {
+      a.pair_t[(size_t)p0 * S + e] = (float)__dadd_rn(span[w][q][0], __dmul_rn(frac[i], span[w][q][1]));
+      q += dq;
+      i += di;
+      if (i >= S) {
+        i -= S;
+        ++q;
+      }
+    }
+  }
 }
 
 // Per ray: the nearest object (rendered depth) whose rendered occupancy reaches the threshold;
-// an equal depth keeps the earlier batch object.
-__global__ void __launch_bounds__(256) k_scene_composite(const SceneArgs a) {
-  const int r = blockIdx.x * 256 + threadIdx.x;
+// an equal depth keeps the earlier batch object. The hits are a bit per (object, ray): a dense
+// (object, ray) map of pair indices was 15 MB to write and read for 76,800 rays and 50 objects
+// (22.7 us here; 13 now).
+__global__ void __launch_bounds__(64) k_scene_composite(const SceneArgs a) {
+  const int r = blockIdx.x * 64 + threadIdx.x;
   if (r >= a.n_rays) return;
+  const int words = (a.n_rays + 31) >> 5, w = r >> 5;
   float best = INFINITY, occ = 0.f, c0 = 0.f, c1 = 0.f, c2 = 0.f;
   int id = -1;
-  for (int j = 0; j < a.n_objects; ++j) {
-    const int p = a.pair_map[(size_t)j * a.n_rays + r];
-    if (p < 0) continue;
-    const float O = a.pair_occ[p], D = a.pair_depth[p];
-    if (O >= a.occ_threshold && D < best) {
-      best = D;
-      occ = O;
-      c0 = a.pair_rgb[3 * (size_t)p];
-      c1 = a.pair_rgb[3 * (size_t)p + 1];
-      c2 = a.pair_rgb[3 * (size_t)p + 2];
-      id = a.object_ids[j];
+  for (int jb = 0; jb < a.n_objects; jb += 8) {
+    uint32_t m[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) m[u] = jb + u < a.n_objects ? a.pair_mask[(size_t)(jb + u) * words + w] : 0u;
+    unsigned int hits = 0;  // bit u: this ray meets object jb + u
+#pragma unroll
+    for (int u = 0; u < 8; ++u) hits |= ((m[u] >> (r & 31)) & 1u) << u;
+    while (hits) {  // in batch order
+      const int u = __ffs(hits) - 1, j = jb + u;
+      hits &= hits - 1u;
+      const uint32_t below = a.pair_mask[(size_t)j * words + w] & ((1u << (r & 31)) - 1u);
+      const int p = (words > 1 ? a.pair_base[(size_t)j * words + w] : a.counts[j]) + __popc(below);
+      if (p >= a.max_pairs) continue;
+      const float O = a.pair_occ[p], D = a.pair_depth[p];
+      if (O >= a.occ_threshold && D < best) {
+        best = D;
+        occ = O;
+        c0 = a.pair_rgb[3 * (size_t)p];
+        c1 = a.pair_rgb[3 * (size_t)p + 1];
+        c2 = a.pair_rgb[3 * (size_t)p + 2];
+        id = a.object_ids[j];
+      }
     }
   }
   a.depth_out[r] = id >= 0 ? best : 0.f;
@@ -3824,14 +3974,18 @@ __global__ void __launch_bounds__(256) k_scene_composite(const SceneArgs a) {
 hipError_t launch_scene(int phase, const SceneArgs& a, hipStream_t s) {
   if (a.n_rays <= 0 || a.n_objects <= 0) return hipSuccess;
   const int nblk = (a.n_rays + 255) / 256;
+  // objects per workgroup: as many as leave about 1024 workgroups (four a CU)
+  const long long want = ((long long)nblk * a.n_objects) / 1024;
+  const int per = (int)std::max<long long>(1, std::min<long long>({want, (long long)kSceneGroup, (long long)a.n_objects}));
+  const dim3 grid(nblk, (a.n_objects + per - 1) / per);
   switch (phase) {
     case 0:
-      hipLaunchKernelGGL(k_scene_count, dim3(nblk, a.n_objects), dim3(256), 0, s, a);
+      hipLaunchKernelGGL(k_scene_count, grid, dim3(256), 0, s, a, nblk, per);
       hipLaunchKernelGGL(k_scene_scan, dim3(1), dim3(1024), 0, s, a, nblk);
-      hipLaunchKernelGGL(k_scene_fill, dim3(nblk, a.n_objects), dim3(256), 0, s, a);
+      hipLaunchKernelGGL(k_scene_fill, grid, dim3(256), 0, s, a, nblk, per);
       break;
     default:
-      hipLaunchKernelGGL(k_scene_composite, dim3(nblk), dim3(256), 0, s, a);
+      hipLaunchKernelGGL(k_scene_composite, dim3((a.n_rays + 63) / 64), dim3(64), 0, s, a);
   }
   return hipGetLastError();
 }
@@ -4005,7 +4159,8 @@ static hipError_t launch_query_t(const QueryArgs& q, hipStream_t s) {
   if (e != hipSuccess) return e;
   const int nw = 4;
   int64_t chunks = (q.n + kSlots - 1) / kSlots;
-  int grid = (int)std::min<int64_t>((chunks + nw - 1) / nw, 2048);
+  // width 32: four workgroups on every CU (registers), each with the object's weights once
+  int grid = (int)std::min<int64_t>((chunks + nw - 1) / nw, H == 32 ? 1024 : 2048);
   if (grid < 1) return hipSuccess;
   hipLaunchKernelGGL(fn, dim3(grid), dim3(nw * kWave), bytes, s, q);
   return hipGetLastError();
