@@ -180,8 +180,8 @@ WorkLayout work_layout(const vmap_config* c) {
     w.gws = off; off = align256(off + ((size_t)c->max_objects + 1) * 4);
     w.gen_loss = off; off = align256(off + (size_t)w.max_gen_tiles * 4);
     w.gact = off; off = align256(off + (size_t)(kLayers + 1) * layer);
-    // deltas: two buffers taken alternately
-    w.gdelta = off; off = align256(off + 2 * layer);
+    // deltas: a buffer per layer (wider objects than gen_chain's use two of them in turn)
+    w.gdelta = off; off = align256(off + kLayers * layer);
     w.gz = off; off = align256(off + (size_t)w.gen_rows * kOut * 4);
     w.gdz = off; off = align256(off + (size_t)w.gen_rows * kOut * 4);
   }
@@ -484,8 +484,7 @@ int enqueue_tiles(vmap_ctx* c, const vmap_batch* b, int mode, const float* dloss
       g.gen_loss = reinterpret_cast<float*>(c->work + c->wl.gen_loss);
       g.act = reinterpret_cast<uint16_t*>(c->work + c->wl.gact);
       const size_t layer = (size_t)c->wl.gen_rows * (size_t)c->wl.gen_ld;
-      g.delta[0] = reinterpret_cast<uint16_t*>(c->work + c->wl.gdelta);
-      g.delta[1] = g.delta[0] + layer;
+      g.delta = reinterpret_cast<uint16_t*>(c->work + c->wl.gdelta);
       g.z = reinterpret_cast<float*>(c->work + c->wl.gz);
       g.dz = reinterpret_cast<float*>(c->work + c->wl.gdz);
       g.ld = c->wl.gen_ld;

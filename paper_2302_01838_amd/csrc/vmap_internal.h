@@ -241,6 +241,10 @@ __host__ __device__ constexpr bool generic_width(int H) {
   return H == 256 || H == 512 || H == 1024;
 }
 
+// Layered widths whose products, forward and back, run in one launch (k_gen_chain).
+__host__ __device__ constexpr bool gen_chain(int H) { return H == 256; }
+
+
 // Width of the fused kernels that run an object of width H: hidden 16 runs in the width-32
 // kernels with its weights zero-padded to 32 units (the padded units' pre-activations are exactly
 // zero, so they stay inactive, add exact zeros to every sum and get zero gradients), sharing their
@@ -448,13 +452,13 @@ struct GenArgs {
   int32_t* gts;          // [n_objects + 1] first row tile of each batch object
   float* gen_loss;       // [max_gen_tiles] loss per row tile
   uint16_t* act;         // BF16 [kLayers + 1][rows][ld]: encoding (32 wide), then h_1 .. h_4
-  uint16_t* delta[2];    // BF16 [rows][ld] each: back-propagated deltas, alternately
+  uint16_t* delta;       // BF16 [kLayers][rows][ld]: back-propagated deltas (gen_delta_out)
   float* z;              // [rows][4] output pre-activations
   float* dz;             // [rows][4] their adjoints (times the seed's scale)
   int64_t ld;            // elements per row of act and delta
   int64_t layer_elems;   // elements per layer of act
   int max_gen_blocks;    // 128-row blocks the block table holds
-  int32_t* gbs;          // [n_objects + 1] first 128-row block of each batch object
+  int32_t* gbs;          // [n_objects + 1] first 128-row block (gen_chain: pair of row tiles) of each batch object
   int work_rays;         // rays per work tile of this chain's objects (the work list's)
   int32_t* gws;          // [n_objects + 1] first work tile of each batch object among this chain's
                          // work tiles (the chain's objects' tiles, counted alone)

@@ -4278,11 +4278,10 @@ hipError_t launch_init_scaler(ScalerState* sc, float scale, hipStream_t s) {
 // Weight gradients (k_gen_dw, k_gen_dw_small): rows = outputs, n = inputs, k = samples;
 // A = delta^T, B = h_l^T, both staged as the sample rows lie and read transposed.
 
-// Buffer of the deltas at layer m's outputs (m = 0..3): the two buffers alternately (layer m in
-// buffer (3 - m) mod 2). A select: indexing the kernel argument's array by a run-time value would
-// put the whole argument block in per-lane scratch memory.
+// Buffer of the deltas at layer m's outputs (m = 0..3): one each where one launch makes them all
+// (gen_chain), else two taken alternately (layer m in buffer (3 - m) mod 2).
 __device__ __forceinline__ uint16_t* gen_delta_out(const GenArgs& g, int m) {
-  return ((3 - m) & 1) ? g.delta[1] : g.delta[0];
+  return g.delta + (gen_chain(g.H) ? (int64_t)m : (int64_t)((3 - m) & 1)) * g.layer_elems;
 }
 
 struct GenTile {
@@ -4320,7 +4319,11 @@ __global__ void __launch_bounds__(1024) k_gen_tiles(const GenArgs g_in) {
     const int nr = a.ray_offsets[j + 1] - a.ray_offsets[j];
     return nr > 0 ? nr : 0;
   };
-  auto nblk = [&](int nr) { return (int)(((long long)nr * a.S + kGenBlockRows - 1) / kGenBlockRows); };
+  // 128-row product blocks, or (gen_chain) pairs of row tiles
+  auto nblk = [&](int nr) {
+    return gen_chain(g.H) ? (tiles_of(nr, g.rpw) + 1) / 2
+                          : (int)(((long long)nr * a.S + kGenBlockRows - 1) / kGenBlockRows);
+  };
   int lt = 0, lb = 0, lw = 0;
   for (int j = j0; j < j1; ++j) {
     const int nr = rays(j);
@@ -4656,8 +4659,9 @@ __device__ __forceinline__ bool gen_work_rows(const GenArgs& g, const StepArgs& 
 // 64 taken in row order. A chunk's rows are staged as they lie in memory (16-byte loads; the next
 // chunk's loads are in flight while the current chunk's products run) and the operands are read
 // transposed; rows past the object's end are staged as zeros.
+// nlayers > 1: the nblk blocks are those of layers l .. l + nlayers - 1 in turn (of equal shapes).
 template <int T>
-__global__ void __launch_bounds__(256) k_gen_dw(const GenArgs g_in, int l, int nblk) {
+__global__ void __launch_bounds__(256) k_gen_dw(const GenArgs g_in, int l, int nblk, int nlayers) {
   static_assert(T == 64 || T == 128, "block sizes");
   GenArgs g = g_in;
   read_batch(g.a);
@@ -4675,6 +4679,9 @@ __global__ void __launch_bounds__(256) k_gen_dw(const GenArgs g_in, int l, int n
   // work tile bj, weight block by (of nblk), the work tiles dealt to the XCDs in turn
   int bj, by;
   xcd_unit_block(nblk, bj, by);
+  const int per_layer = nblk / nlayers;
+  l += by / per_layer;
+  by %= per_layer;
   GenObj ob;
   if (l >= kLayers || O <= 32 || !gen_work_rows(g, a, bj, ob)) return;
   const int64_t ld = g.ld;
@@ -4982,6 +4989,306 @@ hipError_t launch_stage_gimg(const float* theta, uint16_t* gimg, int k, int p_st
   return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------------------------
+// Hidden 256: the forward products, the rendering with its adjoint and the input gradients of two
+// row tiles (at most 128 rows of one object) by one workgroup of eight waves, the activations and
+// deltas passing between layers through LDS. Wave w computes features 32 w .. + 31 of every layer
+// for all rows (four 32 x 32 tiles); its ReLU masks stay in registers, a bit each. What the weight
+// gradients read (encodings, activations, deltas, dz) is written to device memory as rows, while the
+// next layer runs. W comes from the object's BF16 copy: the forward's operands straight from
+// device memory (a wave's rows are its own; the next layer's are fetched during the current one),
+// the input gradient's in chunks of 64 rows staged in LDS and read transposed. Operands, products
+// and sums are those of k_gen_encode, k_gen_gemm and k_gen_render, in their order.
+//
+// One launch per layer and direction, each waiting for its first operands for most of its four
+// chunks of K, took 224 us of a 441 us step (50 objects of 120 rays x 10 samples, 60,000 rows); this
+// one 151. LDS reads of the rows bound it (about 512 KB per layer and workgroup); 500 workgroups
+// on 256 CUs leave it two rounds.
+
+struct LdsChain {
+  int buf_off, enc_off, z_off, dz_off, total;
+};
+constexpr int kChainWidth = 256;
+constexpr int kChainRows = 128;
+constexpr int kChainPitch = kChainWidth + 8;  // BF16 elements per row
+constexpr int kChainEncPitch = kEnc + 8;
+constexpr int kChainBuf = kChainRows * kChainPitch * 2;
+__host__ __device__ constexpr LdsChain lds_chain() {
+  LdsChain L{};
+  int off = 0;
+  L.buf_off = off; off += 2 * kChainBuf;
+  L.enc_off = off; off += kChainRows * kChainEncPitch * 2;
+  L.z_off = off; off += kChainRows * kOut * 4;
+  L.dz_off = off; off += kChainRows * kOut * 2;
+  L.total = off;
+  return L;
+}
+static_assert(lds_chain().total <= 160 * 1024, "the hidden-256 chain's LDS");
+static_assert(2 * 64 * kChainPitch * 2 <= kChainBuf, "two staged chunks of W fit a row buffer");
+
+template <bool TRAIN>
+__global__ void __launch_bounds__(512, 2) k_gen_chain(const GenArgs g_in) {
+  constexpr int H = kChainWidth, P = kChainPitch, KS = H / 16;
+  constexpr LdsChain L = lds_chain();
+  GenArgs g = g_in;
+  read_batch(g.a);
+  const StepArgs& a = g.a;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  uint16_t* const buf0 = reinterpret_cast<uint16_t*>(smem + L.buf_off);
+  uint16_t* const buf1 = buf0 + kChainBuf / 2;
+  uint16_t* const enc = reinterpret_cast<uint16_t*>(smem + L.enc_off);
+  float* const zl = reinterpret_cast<float*>(smem + L.z_off);
+  typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+  typedef unsigned int u2w __attribute__((ext_vector_type(2)));
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = lane & 31, hf = lane >> 5;
+  // unit: row tiles t0 and t0 + 1 of object j (units dealt to the XCDs in turn); rows 0..63 of the
+  // buffers hold the first tile's samples, 64..127 the second's
+  int unit, one;
+  xcd_unit_block(1, unit, one);
+  if (unit >= clamp_tiles(g.gbs[a.n_objects], g.max_gen_tiles)) return;
+  const int j = gen_object(g.gbs, a.n_objects, unit);
+  const int k = a.object_ids[j];
+  const int o0 = a.ray_offsets[j], o1 = a.ray_offsets[j + 1], S = a.S;
+  const int ti = 2 * (unit - g.gbs[j]);
+  const RayRange ra = tile_ray_range(o0, o1, ti, g.rpw, a.n_rays), rb = tile_ray_range(o0, o1, ti + 1, g.rpw, a.n_rays);
+  const int na = (ra.hi - ra.lo) * S, nb = (rb.hi - rb.lo) * S;  // rows of each tile
+  const int64_t base_a = (int64_t)ra.lo * S, base_b = (int64_t)rb.lo * S;
+  // global row of buffer row r, or -1
+  auto row_of = [&](int r) -> int64_t {
+    return r < 64 ? (r < na ? base_a + r : -1) : (r - 64 < nb ? base_b + (r - 64) : -1);
+  };
+  const uint16_t* const W = a.gimg + (size_t)k * a.p_stride;
+  const float* const theta = a.theta + (size_t)k * a.p_stride;
+  const int64_t ld = g.ld;
+
+  // encodings: four threads per row, four frequencies each
+  {
+    const int r = tid >> 2, f0 = 4 * (tid & 3);
+    const int64_t row = row_of(r);
+    u2w sw{0u, 0u}, cw{0u, 0u};
+    if (row >= 0) {
+      const ObjDesc& d = a.desc[k];
+      const int ray = (r < 64 ? ra.lo : rb.lo) + (r & 63) / S;
+      const double tt = (double)a.t[row];
+      const float* o3 = a.rays_o + 3 * (size_t)ray;
+      const float* d3 = a.rays_d + 3 * (size_t)ray;
+      const double inv_s = d.inv_scale;
+      float xt[4];
+      xt[0] = (float)(((double)o3[0] + tt * (double)d3[0] - d.centre[0]) * inv_s);
+      xt[1] = (float)(((double)o3[1] + tt * (double)d3[1] - d.centre[1]) * inv_s);
+      xt[2] = (float)(((double)o3[2] + tt * (double)d3[2] - d.centre[2]) * inv_s);
+      xt[3] = a.var ? (float)((double)a.var[row] * inv_s * inv_s) : 0.f;
+      const float* Bm = a.B;
+      float sv[4], cv[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int ff = f0 + u;
+        const float phi = xt[0] * Bm[ff] + xt[1] * Bm[kFeatures + ff] + xt[2] * Bm[2 * kFeatures + ff];
+        vmap_sincosf(phi, &sv[u], &cv[u]);
+        if (a.var) {
+          const float nbq = Bm[ff] * Bm[ff] + Bm[kFeatures + ff] * Bm[kFeatures + ff] +
+                            Bm[2 * kFeatures + ff] * Bm[2 * kFeatures + ff];
+          const float att = expf(-0.5f * xt[3] * nbq);
+          sv[u] *= att;
+          cv[u] *= att;
+        }
+      }
+      sw = u2w{pack2(sv[0], sv[1]), pack2(sv[2], sv[3])};
+      cw = u2w{pack2(cv[0], cv[1]), pack2(cv[2], cv[3])};
+      if constexpr (TRAIN) {
+        *reinterpret_cast<u2w*>(g.act + row * ld + f0) = sw;
+        *reinterpret_cast<u2w*>(g.act + row * ld + kFeatures + f0) = cw;
+      }
+    }
+    *reinterpret_cast<u2w*>(enc + r * kChainEncPitch + f0) = sw;
+    *reinterpret_cast<u2w*>(enc + r * kChainEncPitch + kFeatures + f0) = cw;
+  }
+
+  // this wave's A operands of a forward layer: rows 32 wave + n of W_l, K step kc: 16 kc + 8 hf ..
+  bf16x8 wa[KS];
+  auto fetch_w = [&](int l) {
+    const int K = l == 0 ? kEnc : H;
+    const uint16_t* src = W + layer_param_off(H, l) + (size_t)(32 * wave + n) * K + 8 * hf;
+#pragma unroll
+    for (int kc = 0; kc < KS; ++kc)
+      if (16 * kc < K) wa[kc] = *reinterpret_cast<const bf16x8*>(src + 16 * kc);
+  };
+  // rows of a buffer to device memory, 16 bytes at a time
+  auto store_rows = [&](const uint16_t* src, uint16_t* dst) {
+#pragma unroll
+    for (int q = 0; q < kChainRows * H / 8 / 512; ++q) {
+      const int p = tid + 512 * q, r = p >> 5, c = (p & 31) * 8;
+      const int64_t row = row_of(r);
+      if (row >= 0) *reinterpret_cast<u4*>(dst + row * ld + c) = *reinterpret_cast<const u4*>(src + r * P + c);
+    }
+  };
+  f32x16 zero;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) zero[r] = 0.f;
+  unsigned int mask[kLayers][2];  // bit 16 (s mod 2) + r of word s / 2: element r of row block s is active
+  fetch_w(0);
+  __syncthreads();
+
+  // ---------------- forward
+#pragma unroll
+  for (int l = 0; l < kLayers; ++l) {
+    const uint16_t* src = l == 0 ? enc : ((l & 1) ? buf0 : buf1);
+    const int pitch = l == 0 ? kChainEncPitch : P;
+    uint16_t* dst = (l & 1) ? buf1 : buf0;
+    const float* bias = theta + layer_param_off(H, l) + H * (l == 0 ? kEnc : H) + 32 * wave + 4 * hf;
+    f32x4 b4[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) b4[q] = *reinterpret_cast<const f32x4*>(bias + 8 * q);
+    f32x16 acc[4] = {zero, zero, zero, zero};
+#pragma unroll
+    for (int kc = 0; kc < (l == 0 ? kEnc / 16 : KS); ++kc)
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+            wa[kc], *reinterpret_cast<const bf16x8*>(src + (32 * s + n) * pitch + 16 * kc + 8 * hf), acc[s], 0, 0, 0);
+    if (l + 1 < kLayers) fetch_w(l + 1);
+    mask[l][0] = mask[l][1] = 0u;
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {  // features 32 wave + 8 q + 4 hf + 0..3 of row 32 s + n
+        float y[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          y[i] = acc[s][4 * q + i] + b4[q][i];
+          y[i] = (y[i] <= 0.f) ? 0.f : y[i];  // ReLU (a NaN stays NaN)
+        }
+        const u2w w{pack2(y[0], y[1]), pack2(y[2], y[3])};
+        *reinterpret_cast<u2w*>(dst + (32 * s + n) * P + 32 * wave + 8 * q + 4 * hf) = w;
+        if constexpr (TRAIN) {
+          const unsigned int m = ((w[0] & 0xffffu) ? 1u : 0u) | ((w[0] >> 16) ? 2u : 0u) | ((w[1] & 0xffffu) ? 4u : 0u) | ((w[1] >> 16) ? 8u : 0u);
+          mask[l][s >> 1] |= m << (16 * (s & 1) + 4 * q);
+        }
+      }
+    __syncthreads();
+    if constexpr (TRAIN) store_rows(dst, g.act + (int64_t)(l + 1) * g.layer_elems);
+  }
+  // output layer: waves 0..3 a row block each (W_out's four rows padded to 32)
+  if (wave < 4) {
+    const uint16_t* wo = W + layer_param_off(H, kLayers) + (size_t)n * H + 8 * hf;
+    const uint16_t* src = buf1 + (32 * wave + n) * P + 8 * hf;
+    f32x16 acc = zero;
+#pragma unroll
+    for (int kc = 0; kc < KS; ++kc) {
+      bf16x8 w = {};
+      if (n < kOut) w = *reinterpret_cast<const bf16x8*>(wo + 16 * kc);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, *reinterpret_cast<const bf16x8*>(src + 16 * kc), acc, 0, 0, 0);
+    }
+    const float* bo = theta + layer_param_off(H, kLayers) + kOut * H;
+    if (hf == 0)
+      *reinterpret_cast<f32x4*>(zl + (32 * wave + n) * kOut) = f32x4{acc[0] + bo[0], acc[1] + bo[1], acc[2] + bo[2], acc[3] + bo[3]};
+  }
+  __syncthreads();
+  // rendering, loss and adjoint: waves 0 and 1 a row tile each
+  if (wave < 2) {
+    const int lo = wave ? rb.lo : ra.lo, nslots = wave ? nb : na;
+    float zs[kOut], dzs[kOut] = {0.f, 0.f, 0.f, 0.f}, loss = 0.f, wseed = 1.0f;
+#pragma unroll
+    for (int c = 0; c < kOut; ++c) zs[c] = lane < nslots ? zl[(64 * wave + lane) * kOut + c] : 0.f;
+    if constexpr (TRAIN) {
+      if (a.dloss) wseed = a.dloss[j];
+      if (a.use_scale) wseed *= a.scaler->scale;
+    }
+    const RenderIn rin = render_inputs<TRAIN>(a, lo, nslots);
+    render_subtile<TRAIN>(a, lo, nslots, wseed, rin, zs, dzs, loss);
+    if constexpr (TRAIN) {
+      if (lane < nslots)
+        *reinterpret_cast<f32x4*>(g.dz + ((int64_t)lo * S + lane) * kOut) = f32x4{dzs[0], dzs[1], dzs[2], dzs[3]};
+      *reinterpret_cast<u2w*>(smem + L.dz_off + (64 * wave + lane) * kOut * 2) = u2w{pack2(dzs[0], dzs[1]), pack2(dzs[2], dzs[3])};
+    }
+    loss = wave_sum(loss);
+    if (lane == 0 && nslots > 0) g.gen_loss[g.gts[j] + ti + wave] = loss;
+  }
+  if constexpr (!TRAIN) return;
+  __syncthreads();
+
+  // ---------------- input gradients (deltas in buf0, W chunks in buf1)
+  uint16_t* const D = buf0;
+  // a lane's deltas of its four row blocks: rounded, masked by ReLU' of layer m, staged
+  auto put_delta = [&](const f32x16 (&acc)[4], int m) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const unsigned int bits = mask[m][s >> 1] >> (16 * (s & 1) + 4 * q);
+        u2w w{pack2(acc[s][4 * q], acc[s][4 * q + 1]), pack2(acc[s][4 * q + 2], acc[s][4 * q + 3])};
+        w[0] &= ((bits & 1u) ? 0xffffu : 0u) | ((bits & 2u) ? 0xffff0000u : 0u);
+        w[1] &= ((bits & 4u) ? 0xffffu : 0u) | ((bits & 8u) ? 0xffff0000u : 0u);
+        *reinterpret_cast<u2w*>(D + (32 * s + n) * P + 32 * wave + 8 * q + 4 * hf) = w;
+      }
+  };
+  // chunk c (rows 64 c .. + 63) of W_l: 64 x 256 elements, four 16-byte pieces per thread
+  u4 wc[4];
+  auto fetch_chunk = [&](int l, int c) {
+    const uint16_t* src = W + layer_param_off(H, l) + (size_t)64 * c * H;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) wc[q] = *reinterpret_cast<const u4*>(src + (size_t)(tid + 512 * q) * 8);
+  };
+  auto put_chunk = [&](int c) {
+    uint16_t* dst = buf1 + (c & 1) * 64 * P;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int p = tid + 512 * q;
+      *reinterpret_cast<u4*>(dst + (p >> 5) * P + (p & 31) * 8) = wc[q];
+    }
+  };
+  fetch_chunk(kLayers - 1, 0);
+  {
+    // delta of the last hidden layer: W_out^T dz (K = 4 outputs padded to 16)
+    bf16x8 w = {};
+    if (hf == 0) {
+      const uint16_t* wo = W + layer_param_off(H, kLayers) + 32 * wave + n;
+#pragma unroll
+      for (int c = 0; c < kOut; ++c) w[c] = __builtin_bit_cast(__bf16, wo[(size_t)c * H]);
+    }
+    f32x16 acc[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      bf16x8 d = {};
+      if (hf == 0) {
+        const bf16x4 d4 = *reinterpret_cast<const bf16x4*>(smem + L.dz_off + (32 * s + n) * kOut * 2);
+#pragma unroll
+        for (int c = 0; c < kOut; ++c) d[c] = d4[c];
+      }
+      acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, d, zero, 0, 0, 0);
+    }
+    put_delta(acc, kLayers - 1);
+  }
+  // (buf1, the last activations, has been read: by the output layer and store_rows, before the
+  // barriers above)
+  put_chunk(0);
+  __syncthreads();
+#pragma unroll
+  for (int l = kLayers - 1; l > 0; --l) {
+    f32x16 acc[4] = {zero, zero, zero, zero};
+#pragma unroll 1
+    for (int c = 0; c < 4; ++c) {
+      if (c < 3) fetch_chunk(l, c + 1);
+      else if (l > 1) fetch_chunk(l - 1, 0);
+      const uint16_t* wt = buf1 + (c & 1) * 64 * P;
+#pragma unroll
+      for (int kc = 0; kc < 4; ++kc) {
+        const bf16x8 w = tr_operand<P>(wt, 16 * kc, 32 * wave, lane);
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+          acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+              w, *reinterpret_cast<const bf16x8*>(D + (32 * s + n) * P + 64 * c + 16 * kc + 8 * hf), acc[s], 0, 0, 0);
+      }
+      if (c == 0) store_rows(D, gen_delta_out(g, l));  // the layer's own deltas, for its weight gradient
+      if (c < 3 || l > 1) put_chunk(c + 1);
+      __syncthreads();  // (after the last chunk: the deltas have been read)
+    }
+    put_delta(acc, l - 1);
+    __syncthreads();
+  }
+  store_rows(D, gen_delta_out(g, 0));
+}
+
 hipError_t launch_generic(int mode, const GenArgs& g, int tiles_bound, int blocks_bound, int work_bound,
                           hipStream_t s) {
   if (tiles_bound <= 0 || g.a.n_objects <= 0) return hipSuccess;
@@ -5010,6 +5317,24 @@ hipError_t launch_generic(int mode, const GenArgs& g, int tiles_bound, int block
     }
   };
   hipLaunchKernelGGL(k_gen_tiles, dim3(1), dim3(1024), 0, s, g);
+  if (gen_chain(H)) {
+    static int allowed[2] = {0, 0};
+    const void* fn = train ? reinterpret_cast<const void*>(k_gen_chain<true>) : reinterpret_cast<const void*>(k_gen_chain<false>);
+    const hipError_t e = allow_lds(fn, lds_chain().total, &allowed[train]);
+    if (e != hipSuccess) return e;
+    // pairs of row tiles: at most half of them and one per object
+    const dim3 grid = grid1((tiles_bound + g.a.n_objects) / 2 + 1, 1);
+    if (train) hipLaunchKernelGGL(k_gen_chain<true>, grid, dim3(512), lds_chain().total, s, g);
+    else hipLaunchKernelGGL(k_gen_chain<false>, grid, dim3(512), lds_chain().total, s, g);
+    hipLaunchKernelGGL(k_gen_loss, dim3((g.a.n_objects + 3) / 4), dim3(256), 0, s, g);
+    if (train) {
+      const int nb = blocks(H, 128) * blocks(H, 128) * (kLayers - 1), nb0 = blocks(H, 64);
+      hipLaunchKernelGGL(k_gen_dw<128>, grid1(work_bound, nb), dim3(256), 0, s, g, 1, nb, kLayers - 1);
+      hipLaunchKernelGGL(k_gen_dw<64>, grid1(work_bound, nb0), dim3(256), 0, s, g, 0, nb0, 1);
+      hipLaunchKernelGGL(k_gen_dw_small, dim3(work_bound, blocks(H, 32)), dim3(kGenDwWaves * 64), 0, s, g);
+    }
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_gen_encode, dim3(wave_blocks), dim3(256), 0, s, g);
   for (int l = 0; l <= kLayers; ++l) fwd_dx(GEN_FWD, (l == kLayers) ? kOut : H, l);
   if (train) hipLaunchKernelGGL(k_gen_render<true>, dim3(wave_blocks), dim3(256), 0, s, g);
@@ -5022,10 +5347,10 @@ hipError_t launch_generic(int mode, const GenArgs& g, int tiles_bound, int block
         hipLaunchKernelGGL(k_gen_dw_small, dim3(work_bound, blocks(K, 32)), dim3(kGenDwWaves * 64), 0, s, g);
       else if (O >= 128 && K >= 128) {
         const int nb = blocks(O, 128) * blocks(K, 128);
-        hipLaunchKernelGGL(k_gen_dw<128>, grid1(work_bound, nb), dim3(256), 0, s, g, l, nb);
+        hipLaunchKernelGGL(k_gen_dw<128>, grid1(work_bound, nb), dim3(256), 0, s, g, l, nb, 1);
       } else {
         const int nb = blocks(O, 64) * blocks(K, 64);
-        hipLaunchKernelGGL(k_gen_dw<64>, grid1(work_bound, nb), dim3(256), 0, s, g, l, nb);
+        hipLaunchKernelGGL(k_gen_dw<64>, grid1(work_bound, nb), dim3(256), 0, s, g, l, nb, 1);
       }
       if (l > 0) fwd_dx(GEN_DX, K, l);
     }
