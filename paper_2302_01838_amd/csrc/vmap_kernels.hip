@@ -5002,7 +5002,7 @@ hipError_t launch_stage_gimg(const float* theta, uint16_t* gimg, int k, int p_st
 //
 // One launch per layer and direction, each waiting for its first operands for most of its four
 // chunks of K, took 224 us of a 441 us step (50 objects of 120 rays x 10 samples, 60,000 rows); this
-// one 151. LDS reads of the rows bound it (about 512 KB per layer and workgroup); 500 workgroups
+// one 134. LDS reads of the rows bound it (about 512 KB per layer and workgroup); 500 workgroups
 // on 256 CUs leave it two rounds.
 
 struct LdsChain {
@@ -5115,9 +5115,11 @@ __global__ void __launch_bounds__(512, 2) k_gen_chain(const GenArgs g_in) {
   };
   // rows of a buffer to device memory, 16 bytes at a time
   auto store_rows = [&](const uint16_t* src, uint16_t* dst) {
+    int t = tid;
+    asm volatile("" : "+v"(t));  // (addresses are computed here, not kept across the layers)
 #pragma unroll
     for (int q = 0; q < kChainRows * H / 8 / 512; ++q) {
-      const int p = tid + 512 * q, r = p >> 5, c = (p & 31) * 8;
+      const int p = t + 512 * q, r = p >> 5, c = (p & 31) * 8;
       const int64_t row = row_of(r);
       if (row >= 0) *reinterpret_cast<u4*>(dst + row * ld + c) = *reinterpret_cast<const u4*>(src + r * P + c);
     }
@@ -5125,7 +5127,9 @@ __global__ void __launch_bounds__(512, 2) k_gen_chain(const GenArgs g_in) {
   f32x16 zero;
 #pragma unroll
   for (int r = 0; r < 16; ++r) zero[r] = 0.f;
-  unsigned int mask[kLayers][2];  // bit 16 (s mod 2) + r of word s / 2: element r of row block s is active
+  // ReLU masks: element 2 i + e of row block s is active where bit 16 e + 8 (s mod 2) + i of word
+  // s / 2 is set (packed words of two elements, their non-zero flags shifted together)
+  unsigned int mask[kLayers][2];
   fetch_w(0);
   __syncthreads();
 
@@ -5160,10 +5164,8 @@ __global__ void __launch_bounds__(512, 2) k_gen_chain(const GenArgs g_in) {
         }
         const u2w w{pack2(y[0], y[1]), pack2(y[2], y[3])};
         *reinterpret_cast<u2w*>(dst + (32 * s + n) * P + 32 * wave + 8 * q + 4 * hf) = w;
-        if constexpr (TRAIN) {
-          const unsigned int m = ((w[0] & 0xffffu) ? 1u : 0u) | ((w[0] >> 16) ? 2u : 0u) | ((w[1] & 0xffffu) ? 4u : 0u) | ((w[1] >> 16) ? 8u : 0u);
-          mask[l][s >> 1] |= m << (16 * (s & 1) + 4 * q);
-        }
+        if constexpr (TRAIN)
+          mask[l][s >> 1] |= (nonzero16(w[0]) << (8 * (s & 1) + 2 * q)) | (nonzero16(w[1]) << (8 * (s & 1) + 2 * q + 1));
       }
     __syncthreads();
     if constexpr (TRAIN) store_rows(dst, g.act + (int64_t)(l + 1) * g.layer_elems);
@@ -5215,29 +5217,35 @@ __global__ void __launch_bounds__(512, 2) k_gen_chain(const GenArgs g_in) {
     for (int s = 0; s < 4; ++s)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const unsigned int bits = mask[m][s >> 1] >> (16 * (s & 1) + 4 * q);
+        typedef unsigned short us2 __attribute__((ext_vector_type(2)));
         u2w w{pack2(acc[s][4 * q], acc[s][4 * q + 1]), pack2(acc[s][4 * q + 2], acc[s][4 * q + 3])};
-        w[0] &= ((bits & 1u) ? 0xffffu : 0u) | ((bits & 2u) ? 0xffff0000u : 0u);
-        w[1] &= ((bits & 4u) ? 0xffffu : 0u) | ((bits & 8u) ? 0xffff0000u : 0u);
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {  // each packed delta times its flag (0 or 1)
+          const unsigned int f = (mask[m][s >> 1] >> (8 * (s & 1) + 2 * q + e)) & 0x00010001u, we = w[e];
+          w[e] = __builtin_bit_cast(unsigned int, (us2)(__builtin_bit_cast(us2, we) * __builtin_bit_cast(us2, f)));
+        }
         *reinterpret_cast<u2w*>(D + (32 * s + n) * P + 32 * wave + 8 * q + 4 * hf) = w;
       }
   };
-  // chunk c (rows 64 c .. + 63) of W_l: 64 x 256 elements, four 16-byte pieces per thread
-  u4 wc[4];
-  auto fetch_chunk = [&](int l, int c) {
-    const uint16_t* src = W + layer_param_off(H, l) + (size_t)64 * c * H;
+  // chunk i of the input gradients: rows 64 (i mod 4) .. + 63 of W_(3 - i / 4), 64 x 256 elements,
+  // four 16-byte pieces per thread. Two chunks ahead are in flight or in registers, one in LDS.
+  constexpr int kChunks = 4 * (kLayers - 1);
+  u4 wc[2][4];
+  auto fetch_chunk = [&](int i) {
+    const uint16_t* src = W + layer_param_off(H, kLayers - 1 - i / 4) + (size_t)64 * (i & 3) * H;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) wc[q] = *reinterpret_cast<const u4*>(src + (size_t)(tid + 512 * q) * 8);
+    for (int q = 0; q < 4; ++q) wc[i & 1][q] = *reinterpret_cast<const u4*>(src + (size_t)(tid + 512 * q) * 8);
   };
-  auto put_chunk = [&](int c) {
-    uint16_t* dst = buf1 + (c & 1) * 64 * P;
+  auto put_chunk = [&](int i) {
+    uint16_t* dst = buf1 + (i & 1) * 64 * P;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int p = tid + 512 * q;
-      *reinterpret_cast<u4*>(dst + (p >> 5) * P + (p & 31) * 8) = wc[q];
+      *reinterpret_cast<u4*>(dst + (p >> 5) * P + (p & 31) * 8) = wc[i & 1][q];
     }
   };
-  fetch_chunk(kLayers - 1, 0);
+  fetch_chunk(0);
+  fetch_chunk(1);
   {
     // delta of the last hidden layer: W_out^T dz (K = 4 outputs padded to 16)
     bf16x8 w = {};
@@ -5266,11 +5274,11 @@ __global__ void __launch_bounds__(512, 2) k_gen_chain(const GenArgs g_in) {
 #pragma unroll
   for (int l = kLayers - 1; l > 0; --l) {
     f32x16 acc[4] = {zero, zero, zero, zero};
-#pragma unroll 1
+#pragma unroll
     for (int c = 0; c < 4; ++c) {
-      if (c < 3) fetch_chunk(l, c + 1);
-      else if (l > 1) fetch_chunk(l - 1, 0);
-      const uint16_t* wt = buf1 + (c & 1) * 64 * P;
+      const int i = 4 * (kLayers - 1 - l) + c;
+      if (i + 2 < kChunks) fetch_chunk(i + 2);
+      const uint16_t* wt = buf1 + (i & 1) * 64 * P;
 #pragma unroll
       for (int kc = 0; kc < 4; ++kc) {
         const bf16x8 w = tr_operand<P>(wt, 16 * kc, 32 * wave, lane);
@@ -5280,7 +5288,7 @@ __global__ void __launch_bounds__(512, 2) k_gen_chain(const GenArgs g_in) {
               w, *reinterpret_cast<const bf16x8*>(D + (32 * s + n) * P + 64 * c + 16 * kc + 8 * hf), acc[s], 0, 0, 0);
       }
       if (c == 0) store_rows(D, gen_delta_out(g, l));  // the layer's own deltas, for its weight gradient
-      if (c < 3 || l > 1) put_chunk(c + 1);
+      if (i + 1 < kChunks) put_chunk(i + 1);
       __syncthreads();  // (after the last chunk: the deltas have been read)
     }
     put_delta(acc, l - 1);
