@@ -180,7 +180,7 @@ WorkLayout work_layout(const vmap_config* c) {
     w.gws = off; off = align256(off + ((size_t)c->max_objects + 1) * 4);
     w.gen_loss = off; off = align256(off + (size_t)w.max_gen_tiles * 4);
     w.gact = off; off = align256(off + (size_t)(kLayers + 1) * layer);
-    // deltas: a buffer per layer (wider objects than gen_chain's use two of them in turn)
+    // deltas: a buffer per layer
     w.gdelta = off; off = align256(off + kLayers * layer);
     w.gz = off; off = align256(off + (size_t)w.gen_rows * kOut * 4);
     w.gdz = off; off = align256(off + (size_t)w.gen_rows * kOut * 4);

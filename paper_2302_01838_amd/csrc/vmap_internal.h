@@ -457,8 +457,8 @@ struct GenArgs {
   float* dz;             // [rows][4] their adjoints (times the seed's scale)
   int64_t ld;            // elements per row of act and delta
   int64_t layer_elems;   // elements per layer of act
-  int max_gen_blocks;    // 128-row blocks the block table holds
-  int32_t* gbs;          // [n_objects + 1] first 128-row block (gen_chain: pair of row tiles) of each batch object
+  int max_gen_blocks;    // 256-row blocks the block table holds
+  int32_t* gbs;          // [n_objects + 1] first 256-row block (gen_chain: pair of row tiles) of each batch object
   int work_rays;         // rays per work tile of this chain's objects (the work list's)
   int32_t* gws;          // [n_objects + 1] first work tile of each batch object among this chain's
                          // work tiles (the chain's objects' tiles, counted alone)
@@ -467,7 +467,7 @@ struct GenArgs {
 enum GenKind { GEN_FWD = 0, GEN_DX = 1 };
 // Rows of a block of the wide products (128 x 128 output blocks): an object's rows in order, cut
 // every kGenBlockRows rows regardless of ray boundaries (rows are independent in those products).
-constexpr int kGenBlockRows = 128;
+constexpr int kGenBlockRows = 256;
 // LDS of the product kernels: k_gen_gemm and k_gen_dw stage two BF16 operand tiles of up to
 // 128 x (kGenKChunk + 8) or kGenKChunk x (128 + 16) elements; k_gen_dw_small (the output layer)
 // its kGenDwWaves waves' pairs of 32-row tiles (rows of kGenPitch elements), then the waves' FP32 sums (16

@@ -4278,11 +4278,8 @@ hipError_t launch_init_scaler(ScalerState* sc, float scale, hipStream_t s) {
 // Weight gradients (k_gen_dw, k_gen_dw_small): rows = outputs, n = inputs, k = samples;
 // A = delta^T, B = h_l^T, both staged as the sample rows lie and read transposed.
 
-// Buffer of the deltas at layer m's outputs (m = 0..3): one each where one launch makes them all
-// (gen_chain), else two taken alternately (layer m in buffer (3 - m) mod 2).
-__device__ __forceinline__ uint16_t* gen_delta_out(const GenArgs& g, int m) {
-  return g.delta + (gen_chain(g.H) ? (int64_t)m : (int64_t)((3 - m) & 1)) * g.layer_elems;
-}
+// Buffer of the deltas at layer m's outputs (m = 0..3).
+__device__ __forceinline__ uint16_t* gen_delta_out(const GenArgs& g, int m) { return g.delta + m * g.layer_elems; }
 
 struct GenTile {
   int j, k, lo, hi;  // batch object, object id, rays [lo, hi)
@@ -4299,7 +4296,7 @@ __device__ __forceinline__ bool gen_tile(const GenArgs& g, const StepArgs& a, in
   return true;
 }
 
-// Row tiles per batch object, ceil(rays / rpw), 128-row product blocks, ceil(rays S / 128), and
+// Row tiles per batch object, ceil(rays / rpw), 256-row product blocks, ceil(rays S / 256), and
 // work tiles, ceil(rays / work_rays) (as the work list counts them), for the objects of width H;
 // none for the others or for a batch that failed the offsets check (ScalerState::batch_ok, from
 // the work-list launch). gts, gbs and gws: their exclusive scans.
@@ -4319,7 +4316,7 @@ __global__ void __launch_bounds__(1024) k_gen_tiles(const GenArgs g_in) {
     const int nr = a.ray_offsets[j + 1] - a.ray_offsets[j];
     return nr > 0 ? nr : 0;
   };
-  // 128-row product blocks, or (gen_chain) pairs of row tiles
+  // 256-row product blocks, or (gen_chain) pairs of row tiles
   auto nblk = [&](int nr) {
     return gen_chain(g.H) ? (tiles_of(nr, g.rpw) + 1) / 2
                           : (int)(((long long)nr * a.S + kGenBlockRows - 1) / kGenBlockRows);
@@ -4419,8 +4416,8 @@ __global__ void __launch_bounds__(256) k_gen_encode(const GenArgs g_in) {
 }
 
 // Rows of product block b of the layered chain: T = 64, row tile b (at most 64 rows, whole rays);
-// T = 128, the 128-row block b of the block table (an object's rows in order, cut every 128 rows).
-// False if b is past the chain's blocks or holds no row.
+// T = 256, block b of the block table (an object's rows in order, cut every 256 rows); T = 128,
+// half b mod 2 of block b / 2. False if b is past the chain's blocks or holds no row.
 template <int T>
 __device__ __forceinline__ bool gen_rows(const GenArgs& g, const StepArgs& a, int b, int& k, int64_t& r0, int& nrows) {
   if constexpr (T == 64) {
@@ -4430,18 +4427,19 @@ __device__ __forceinline__ bool gen_rows(const GenArgs& g, const StepArgs& a, in
     r0 = (int64_t)tl.lo * a.S;
     nrows = (tl.hi - tl.lo) * a.S;
   } else {
-    static_assert(T == kGenBlockRows, "row blocks of 128");
+    constexpr int D = kGenBlockRows / T;
+    static_assert(D == 1 || D == 2, "whole or half row blocks");
     const int total = clamp_tiles(g.gbs[a.n_objects], g.max_gen_blocks);
-    if (b >= total) return false;
-    const int j = gen_object(g.gbs, a.n_objects, b);
+    if (b / D >= total) return false;
+    const int j = gen_object(g.gbs, a.n_objects, b / D);
     const RayRange rr = tile_ray_range(a.ray_offsets[j], a.ray_offsets[j + 1], 0, kWholeObject, a.n_rays);
-    const int64_t first = (int64_t)(b - g.gbs[j]) * T;
+    const int64_t first = (int64_t)(b / D - g.gbs[j]) * kGenBlockRows + (b % D) * T;
     const int64_t rows = (int64_t)(rr.hi - rr.lo) * a.S;
     k = a.object_ids[j];
     r0 = (int64_t)rr.lo * a.S + first;
     nrows = (int)(rows - first < T ? rows - first : T);
   }
-  return nrows > 0;  // (a validated batch has no empty block)
+  return nrows > 0;  // (the second half of an object's last block may hold none)
 }
 
 // Forward and input-gradient products of one row block: a workgroup (four waves, 2 x 2) computes
@@ -4781,6 +4779,252 @@ __global__ void __launch_bounds__(256) k_gen_dw(const GenArgs g_in, int l, int n
     }
   }
   if (__syncthreads_or(bad) && tid == 0) atomicOr(&a.flags[ob.k], 1);
+}
+
+// 256 x 256 blocks of the products above, for the square layers of widths that are multiples of
+// 256: D[feature][column] over K in chunks of 64, eight waves of 128 features x 64 columns each.
+//   GEN_FWD: feature = output, column = sample, k = input;  operands W rows, h_l rows
+//   GEN_DX:  feature = input, column = sample, k = output;  operands W (transposed reads), delta rows
+//   GEN_DW:  feature = output, column = input, k = sample;  operands delta, h_l (transposed reads)
+// Products and sums are those of k_gen_gemm and k_gen_dw, each element's over k in the same order.
+//
+// k_gen_gemm's and k_gen_dw's 128 x 128 blocks run at 560 to 670 TFLOP/s because the LDS is busy
+// for longer than the matrix cores: per chunk 416 cycles of writes and 290 (590 where both operands
+// are read transposed) of reads for 512 of products. Here an operand read feeds four or two
+// products instead of two, and chunks go from memory to LDS without passing registers, into two
+// buffers in turn: one barrier per chunk, a chunk's loads in flight while the other is used. 50 objects
+// of 1,200 rows at hidden 1024: forward 187 to 157 us per layer, input gradient 208 to 163, the three
+// layers' weight gradients 672 to 488 in one launch. The chunks' loads bound it, 16 to 18 bytes per
+// cycle and CU from the L2 (without them a chunk takes 2.3 thousand cycles instead of 3.6, without the
+// products 3.5); padded row pitches, operands read a step ahead and lines touched a few chunks ahead
+// changed nothing.
+//
+// LDS holds a chunk as the loads deliver it, 16-byte pieces in order of (row, piece). Operands read
+// as rows: 256 rows of 64 k (8 pieces), piece c at c ^ ((row / 2) mod 8), so that sixteen rows of
+// one column of pieces cover the banks once; operands read transposed: 64 rows (k) of 256 (32
+// pieces), piece c at c ^ (4 (row mod 4)), so that a read's four rows of 64 bytes do.
+enum { GEN_DW = GEN_DX + 1 };
+constexpr int kWideK = 64;
+
+__device__ __forceinline__ bf16x8 wide_rows_operand(const uint16_t* T, int rb, int kc, int lane) {
+  const int n = lane & 31;
+  return *reinterpret_cast<const bf16x8*>(T + (rb + n) * kWideK + (((2 * kc + (lane >> 5)) ^ ((n >> 1) & 7)) << 3));
+}
+__device__ __forceinline__ bf16x8 wide_tr_operand(const uint16_t* T, int kc, int cb, int lane) {
+  typedef __attribute__((address_space(3))) v4i16 lds_v4;
+  const int r = 8 * (lane >> 5) + ((lane & 15) >> 2);
+  const int c = ((cb >> 3) ^ ((r & 3) << 2)) + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
+  const uint16_t* p = T + (16 * kc + r) * 256 + 8 * c + 4 * (lane & 1);
+  const v4i16 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4*)(p));
+  const v4i16 y = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4*)(p + 4 * 256));
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(x, y, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+// 16 bytes per lane from device memory to LDS: lane i's to dst + 16 i (dst: the wave's, uniform).
+__device__ __forceinline__ void wide_load(const uint16_t* src, uint16_t* dst) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                   (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+}
+// Unit (of nblk workgroups each) and block of this workgroup, the units in eight runs, one per XCD:
+// neighbouring units share an object's weights or rows, and so one L2. False past the last unit.
+__device__ __forceinline__ bool xcd_run_block(int units, int nblk, int& unit, int& blk) {
+  const int b = (int)blockIdx.x, x = b & 7, i = (b >> 3) / nblk;
+  const int lo = (int)((long long)units * x / 8), hi = (int)((long long)units * (x + 1) / 8);
+  unit = lo + i;
+  blk = (b >> 3) % nblk;
+  return unit < hi;
+}
+
+// Barrier for LDS alone: loads from and stores to device memory stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+template <int KIND>
+__global__ void __launch_bounds__(512, 2) k_gen_wide(const GenArgs g_in, int l) {
+  GenArgs g = g_in;
+  read_batch(g.a);
+  const StepArgs& a = g.a;
+  constexpr bool XT = KIND != GEN_FWD, YT = KIND == GEN_DW;  // operand read transposed
+  __shared__ __attribute__((aligned(1024))) uint16_t X0[256 * kWideK], X1[256 * kWideK];
+  __shared__ __attribute__((aligned(1024))) uint16_t Y0[256 * kWideK], Y1[256 * kWideK];
+  typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+  typedef unsigned int u2w __attribute__((ext_vector_type(2)));
+  const int H = g.H, nb = H / 256;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wf = wave & 1, ws = wave >> 1, n = lane & 31, kh = lane >> 5;
+  const int64_t ld = g.ld;
+  const uint16_t *xs, *ys;  // first row and column of the operands
+  int64_t xld = ld;         // (of the samples' rows: ld)
+  int k, nrows, ktot, n0, m0 = 0, ts = 0;
+  int64_t r0;
+  if constexpr (KIND == GEN_DW) {  // unit: a work tile's layer (1 .. kLayers - 1)
+    if (!a.scaler->batch_ok) return;
+    int u, by;
+    if (!xcd_run_block(clamp_tiles(g.gws[a.n_objects], a.max_tiles) * (kLayers - 1), nb * nb, u, by)) return;
+    GenObj ob;
+    if (!gen_work_rows(g, a, u / (kLayers - 1), ob)) return;
+    l = 1 + u % (kLayers - 1);
+    k = ob.k;
+    r0 = ob.r0;
+    ktot = nrows = ob.nrows;
+    ts = ob.ts;
+    m0 = (by / nb) * 256;
+    n0 = (by % nb) * 256;
+    xs = gen_delta_out(g, l) + r0 * ld + m0;
+    ys = g.act + l * g.layer_elems + r0 * ld + n0;
+  } else {
+    int bx, by;
+    if (!xcd_run_block(clamp_tiles(g.gbs[a.n_objects], g.max_gen_blocks), nb, bx, by)) return;
+    if (!gen_rows<kGenBlockRows>(g, a, bx, k, r0, nrows)) return;
+    ktot = H;
+    n0 = by * 256;
+    const uint16_t* Wb = a.gimg + (size_t)k * a.p_stride + layer_param_off(H, l);
+    xs = (KIND == GEN_FWD) ? Wb + (size_t)n0 * H : Wb + n0;
+    xld = H;
+    ys = ((KIND == GEN_FWD) ? g.act + l * g.layer_elems : gen_delta_out(g, l)) + r0 * ld;
+  }
+  // this thread's four pieces of an operand's chunk. Rows past the samples' end repeat the last one
+  // (their results are not written; as k they are zeroed below).
+  auto fetch = [&](int c, uint16_t* xb, uint16_t* yb) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int rr = (tid >> 3) + 64 * q, rc = 8 * ((tid & 7) ^ ((tid >> 4) & 7));            // as rows
+      const int tr = kWideK * c + (tid >> 5) + 16 * q, tc = 8 * ((tid & 31) ^ (((tid >> 5) & 3) << 2));  // transposed
+      const int xr = XT ? (KIND == GEN_DW ? min(tr, nrows - 1) : tr) : rr;
+      wide_load(xs + xr * xld + (XT ? tc : rc + kWideK * c), xb + (512 * q + 64 * wave) * 8);
+      wide_load(ys + min(YT ? tr : rr, nrows - 1) * ld + (YT ? tc : rc + kWideK * c), yb + (512 * q + 64 * wave) * 8);
+    }
+  };
+  f32x16 acc[4][2];
+#pragma unroll
+  for (int mi = 0; mi < 4; ++mi)
+#pragma unroll
+    for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[mi][ni][i] = 0.f;
+  const bool bias = (KIND == GEN_DW) && n0 == 0 && ws == 0;
+  float db[4] = {0.f, 0.f, 0.f, 0.f};
+  const int nchunks = (ktot + kWideK - 1) / kWideK;
+  // chunk c from (xb, yb), the next one's loads to (xn, yn)
+  auto step = [&](int c, uint16_t* xb, uint16_t* yb, uint16_t* xn, uint16_t* yn) {
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's pieces of chunk c are in LDS
+    if constexpr (KIND == GEN_DW) {
+      if (kWideK * (c + 1) > ktot) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (kWideK * c + (tid >> 5) + 16 * q >= ktot) {
+            *reinterpret_cast<u4*>(xb + (tid + 512 * q) * 8) = u4{0u, 0u, 0u, 0u};
+            *reinterpret_cast<u4*>(yb + (tid + 512 * q) * 8) = u4{0u, 0u, 0u, 0u};
+          }
+      }
+    }
+    __syncthreads();  // chunk c is complete, chunk c - 1 has been read
+    if (c + 1 < nchunks) fetch(c + 1, xn, yn);
+#pragma unroll
+    for (int kc = 0; kc < kWideK / 16; ++kc) {
+      bf16x8 x[4], y[2];
+#pragma unroll
+      for (int mi = 0; mi < 4; ++mi)
+        x[mi] = XT ? wide_tr_operand(xb, kc, 128 * wf + 32 * mi, lane) : wide_rows_operand(xb, 128 * wf + 32 * mi, kc, lane);
+#pragma unroll
+      for (int ni = 0; ni < 2; ++ni)
+        y[ni] = YT ? wide_tr_operand(yb, kc, 64 * ws + 32 * ni, lane) : wide_rows_operand(yb, 64 * ws + 32 * ni, kc, lane);
+#pragma unroll
+      for (int mi = 0; mi < 4; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < 2; ++ni)
+          acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[mi], y[ni], acc[mi][ni], 0, 0, 0);
+      if (bias) {
+#pragma unroll
+        for (int mi = 0; mi < 4; ++mi) db[mi] = operand_sum(x[mi], db[mi]);
+      }
+    }
+  };
+  fetch(0, X0, Y0);
+  for (int c = 0; c < nchunks; c += 2) {
+    step(c, X0, Y0, X1, Y1);
+    if (c + 1 < nchunks) step(c + 1, X1, Y1, X0, Y0);
+  }
+  if constexpr (KIND == GEN_DW) {
+    const float inv = a.use_scale ? 1.0f / a.scaler->scale : 1.0f;
+    float* dst = a.partial + (size_t)ts * a.p_stride + layer_param_off(H, l);
+    // (the check first: nothing waits for the stores)
+    int bad = 0;
+#pragma unroll
+    for (int mi = 0; mi < 4; ++mi) {
+#pragma unroll
+      for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          acc[mi][ni][i] *= inv;
+          bad |= partial_bad(acc[mi][ni][i]);
+        }
+      db[mi] = (db[mi] + __shfl(db[mi], lane ^ 32)) * inv;  // (the output's other eight rows of each step)
+      if (bias) bad |= partial_bad(db[mi]);
+    }
+    if (__syncthreads_or(bad) && tid == 0) atomicOr(&a.flags[k], 1);
+#pragma unroll
+    for (int mi = 0; mi < 4; ++mi) {
+#pragma unroll
+      for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          dst[(size_t)(m0 + 128 * wf + 32 * mi + 8 * (i >> 2) + 4 * kh + (i & 3)) * H + n0 + 64 * ws + 32 * ni + n] = acc[mi][ni][i];
+      if (bias && kh == 0) dst[(size_t)H * H + m0 + 128 * wf + 32 * mi + n] = db[mi];
+    }
+  } else {
+    // Rounded to BF16 into rows of samples in LDS (64 samples, those of two waves, per buffer; piece
+    // c of a row at c ^ (row mod 16)), then written as rows: forward ReLU(D + b); input gradient D
+    // where layer l - 1's unit is active (its output h_l is +0 exactly where it is not).
+    const uint16_t* act_l = g.act + l * g.layer_elems + r0 * ld + n0;
+    const float* bp = a.theta + (size_t)k * a.p_stride + layer_param_off(H, l) + (size_t)H * H + n0;
+    u4 h[16];  // in flight while the results are rounded: h_l's rows, or the biases
+#pragma unroll
+    for (int q = 0; q < 16; ++q)
+      h[q] = (KIND == GEN_FWD)
+                 ? *reinterpret_cast<const u4*>(bp + 128 * wf + 8 * q + 4 * kh)
+                 : *reinterpret_cast<const u4*>(act_l + min(16 * q + (tid >> 5), nrows - 1) * ld + 8 * (tid & 31));
+    lds_barrier();  // every wave is done with the operands
+    uint16_t* out = (ws == 0) ? X0 : (ws == 1) ? X1 : (ws == 2) ? Y0 : Y1;
+#pragma unroll
+    for (int mi = 0; mi < 4; ++mi)
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) {
+        const int f = 128 * wf + 32 * mi + 8 * jj;  // features f + 4 kh .. + 3
+#pragma unroll
+        for (int ni = 0; ni < 2; ++ni) {
+          float y[4] = {acc[mi][ni][4 * jj], acc[mi][ni][4 * jj + 1], acc[mi][ni][4 * jj + 2], acc[mi][ni][4 * jj + 3]};
+          if constexpr (KIND == GEN_FWD) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const unsigned int b = h[4 * mi + jj][e];
+              y[e] += __builtin_bit_cast(float, b);
+              y[e] = (y[e] <= 0.f) ? 0.f : y[e];  // ReLU (a NaN stays NaN)
+            }
+          }
+          *reinterpret_cast<u2w*>(out + (32 * ni + n) * 256 + (((f >> 3) ^ (n & 15)) << 3) + 4 * kh) =
+              u2w{pack2(y[0], y[1]), pack2(y[2], y[3])};
+        }
+      }
+    lds_barrier();
+    uint16_t* dst = ((KIND == GEN_FWD) ? g.act + (l + 1) * g.layer_elems : gen_delta_out(g, l - 1)) + r0 * ld + n0;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {  // piece tid mod 32 of row 16 q + tid / 32
+      const int r = 16 * q + (tid >> 5), c = tid & 31;
+      const uint16_t* in = (q < 4) ? X0 : (q < 8) ? X1 : (q < 12) ? Y0 : Y1;
+      if (r >= nrows) continue;
+      u4 v = *reinterpret_cast<const u4*>(in + (r & 63) * 256 + ((c ^ (r & 15)) << 3));
+      const int64_t off = r * ld + 8 * c;
+      if constexpr (KIND == GEN_DX) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] &= ((h[q][e] & 0xffffu) ? 0xffffu : 0u) | ((h[q][e] >> 16) ? 0xffff0000u : 0u);
+      }
+      *reinterpret_cast<u4*>(dst + off) = v;
+    }
+  }
 }
 
 // Weight gradient of the output layer (4 outputs) of the layered path: a workgroup computes
@@ -5313,16 +5557,36 @@ hipError_t launch_generic(int mode, const GenArgs& g, int tiles_bound, int block
   // narrower ones 64 x 64 blocks over the row tiles
   // one-dimensional grids of 8 ceil(units / 8) x blocks-per-unit workgroups (xcd_unit_block)
   auto grid1 = [&](int units, int nblk) { return dim3((unsigned)(8 * blocks(units, 8) * nblk)); };
+  const int nw = H / 256;
+  // k_gen_wide from 256 workgroups of 256 x 256, one per CU; the 128 x 128 blocks, four times as many,
+  // fill the chip better below that. Steps of objects of 1,200 rows in us, wide against 128: hidden
+  // 512, 8 objects (92 workgroups, rows' bound) 275 against 255, 16 (182) 365 / 370, 32 (364) 654 / 665;
+  // hidden 1024, 4 (92) 447 / 407, 8 (184) 560 / 566, 16 (364) 1041 / 1059. Weight gradients likewise at
+  // hidden 512 (8 objects, 192 workgroups: 262 / 255; 16, 384: 367 / 370); at hidden 1024 always: the
+  // 128 x 128 blocks of one object all run on one XCD (1 object 263 / 306, 4 368 / 407, 16 1021 / 1059).
+  constexpr int kCUs = 256;
+  const bool wide = nw > 1 && (long long)blocks_bound * nw >= kCUs;
+  const bool wide_dw = nw > 1 && (nw >= 4 || (long long)work_bound * nw * nw * (kLayers - 1) >= kCUs);
   auto fwd_dx = [&](int kind, int ncols, int l) {
-    if (ncols >= 128) {
+    if (wide && l > 0 && l < kLayers) {
+      if (kind == GEN_FWD) hipLaunchKernelGGL(k_gen_wide<GEN_FWD>, grid1(blocks_bound, nw), dim3(512), 0, s, g, l);
+      else hipLaunchKernelGGL(k_gen_wide<GEN_DX>, grid1(blocks_bound, nw), dim3(512), 0, s, g, l);
+    } else if (ncols >= 128) {
       const int nb = blocks(ncols, 128);
-      if (kind == GEN_FWD) hipLaunchKernelGGL((k_gen_gemm<GEN_FWD, 128>), grid1(blocks_bound, nb), dim3(256), 0, s, g, l, nb);
-      else hipLaunchKernelGGL((k_gen_gemm<GEN_DX, 128>), grid1(blocks_bound, nb), dim3(256), 0, s, g, l, nb);
+      if (kind == GEN_FWD) hipLaunchKernelGGL((k_gen_gemm<GEN_FWD, 128>), grid1(2 * blocks_bound, nb), dim3(256), 0, s, g, l, nb);
+      else hipLaunchKernelGGL((k_gen_gemm<GEN_DX, 128>), grid1(2 * blocks_bound, nb), dim3(256), 0, s, g, l, nb);
     } else {
       const int nb = blocks(ncols, 64);
       if (kind == GEN_FWD) hipLaunchKernelGGL((k_gen_gemm<GEN_FWD, 64>), grid1(tiles_bound, nb), dim3(256), 0, s, g, l, nb);
       else hipLaunchKernelGGL((k_gen_gemm<GEN_DX, 64>), grid1(tiles_bound, nb), dim3(256), 0, s, g, l, nb);
     }
+  };
+  auto launch_dw = [&]() {  // every layer's weight gradients, from the deltas of all layers
+    const int nb = blocks(H, 128) * blocks(H, 128) * (kLayers - 1), nb0 = blocks(H, 64) * blocks(kEnc, 64);
+    if (wide_dw) hipLaunchKernelGGL(k_gen_wide<GEN_DW>, grid1(work_bound * (kLayers - 1), nw * nw), dim3(512), 0, s, g, 0);
+    else hipLaunchKernelGGL(k_gen_dw<128>, grid1(work_bound, nb), dim3(256), 0, s, g, 1, nb, kLayers - 1);
+    hipLaunchKernelGGL(k_gen_dw<64>, grid1(work_bound, nb0), dim3(256), 0, s, g, 0, nb0, 1);
+    hipLaunchKernelGGL(k_gen_dw_small, dim3(work_bound, blocks(H, 32)), dim3(kGenDwWaves * 64), 0, s, g);
   };
   hipLaunchKernelGGL(k_gen_tiles, dim3(1), dim3(1024), 0, s, g);
   if (gen_chain(H)) {
@@ -5335,12 +5599,7 @@ hipError_t launch_generic(int mode, const GenArgs& g, int tiles_bound, int block
     if (train) hipLaunchKernelGGL(k_gen_chain<true>, grid, dim3(512), lds_chain().total, s, g);
     else hipLaunchKernelGGL(k_gen_chain<false>, grid, dim3(512), lds_chain().total, s, g);
     hipLaunchKernelGGL(k_gen_loss, dim3((g.a.n_objects + 3) / 4), dim3(256), 0, s, g);
-    if (train) {
-      const int nb = blocks(H, 128) * blocks(H, 128) * (kLayers - 1), nb0 = blocks(H, 64);
-      hipLaunchKernelGGL(k_gen_dw<128>, grid1(work_bound, nb), dim3(256), 0, s, g, 1, nb, kLayers - 1);
-      hipLaunchKernelGGL(k_gen_dw<64>, grid1(work_bound, nb0), dim3(256), 0, s, g, 0, nb0, 1);
-      hipLaunchKernelGGL(k_gen_dw_small, dim3(work_bound, blocks(H, 32)), dim3(kGenDwWaves * 64), 0, s, g);
-    }
+    if (train) launch_dw();
     return hipGetLastError();
   }
   hipLaunchKernelGGL(k_gen_encode, dim3(wave_blocks), dim3(256), 0, s, g);
@@ -5349,19 +5608,8 @@ hipError_t launch_generic(int mode, const GenArgs& g, int tiles_bound, int block
   else hipLaunchKernelGGL(k_gen_render<false>, dim3(wave_blocks), dim3(256), 0, s, g);
   hipLaunchKernelGGL(k_gen_loss, dim3((g.a.n_objects + 3) / 4), dim3(256), 0, s, g);
   if (train) {
-    for (int l = kLayers; l >= 0; --l) {
-      const int K = (l == 0) ? kEnc : H, O = (l == kLayers) ? kOut : H;
-      if (l == kLayers)
-        hipLaunchKernelGGL(k_gen_dw_small, dim3(work_bound, blocks(K, 32)), dim3(kGenDwWaves * 64), 0, s, g);
-      else if (O >= 128 && K >= 128) {
-        const int nb = blocks(O, 128) * blocks(K, 128);
-        hipLaunchKernelGGL(k_gen_dw<128>, grid1(work_bound, nb), dim3(256), 0, s, g, l, nb, 1);
-      } else {
-        const int nb = blocks(O, 64) * blocks(K, 64);
-        hipLaunchKernelGGL(k_gen_dw<64>, grid1(work_bound, nb), dim3(256), 0, s, g, l, nb, 1);
-      }
-      if (l > 0) fwd_dx(GEN_DX, K, l);
-    }
+    for (int l = kLayers; l > 0; --l) fwd_dx(GEN_DX, H, l);
+    launch_dw();
   }
   return hipGetLastError();
 }
