@@ -121,8 +121,8 @@ __device__ __forceinline__ int first_tile_of_block(int b, int blocks, int n_tile
 // and each XCD takes its units' nblk blocks one unit after another, so that the blocks of a unit
 // (which share its rows and its object's weights) share one L2, and the units that exist (the
 // first ones of a bound with slack) are spread evenly over the XCDs.
-__device__ __forceinline__ void xcd_unit_block(int nblk, int& unit, int& blk) {
-  const int b = (int)blockIdx.x, x = b & 7, s = b >> 3;
+__device__ __forceinline__ void xcd_unit_block(int b, int nblk, int& unit, int& blk) {
+  const int x = b & 7, s = b >> 3;
   unit = x + 8 * (s / nblk);
   blk = s % nblk;
 }
@@ -4526,7 +4526,7 @@ __global__ void __launch_bounds__(256, (KIND == GEN_DX && T == 128) ? 3 : 1) k_g
   const uint16_t* dout = head ? nullptr : gen_delta_out(g, l);  // delta at layer l's outputs
   // row block bx, column block by (of ncol_blocks), the row blocks dealt to the XCDs in turn
   int bx, by;
-  xcd_unit_block(ncol_blocks, bx, by);
+  xcd_unit_block((int)blockIdx.x, ncol_blocks, bx, by);
   int k, nrows;
   int64_t r0;
   if (!gen_rows<T>(g, a, bx, k, r0, nrows)) return;
@@ -4704,25 +4704,27 @@ __device__ __forceinline__ bool gen_work_rows(const GenArgs& g, const StepArgs& 
 // chunk's loads are in flight while the current chunk's products run) and the operands are read
 // transposed; rows past the object's end are staged as zeros.
 // nlayers > 1: the nblk blocks are those of layers l .. l + nlayers - 1 in turn (of equal shapes).
+// b: this workgroup among those of the call; lds: 2 dw_tile<T> elements.
 template <int T>
-__global__ void __launch_bounds__(256) k_gen_dw(const GenArgs g_in, int l, int nblk, int nlayers) {
+constexpr int dw_tile = 64 * (T + T / 8);
+template <int T>
+__device__ __forceinline__ void gen_dw_block(const GenArgs& g, int b, int l, int nblk, int nlayers, uint16_t* lds) {
   static_assert(T == 64 || T == 128, "block sizes");
-  GenArgs g = g_in;
-  read_batch(g.a);
   const StepArgs& a = g.a;
   constexpr int R = 64, P = T + T / 8;      // rows per chunk; LDS pitch (elements)
   constexpr int WT = T / 2, NS = WT / 32;   // wave tile, 32 x 32 MFMA tiles per dimension
   constexpr int CPR = T / 8;                // 16-byte pieces per staged row
   constexpr int NP = R * CPR / 256;         // pieces per thread and operand
-  __shared__ __attribute__((aligned(16))) uint16_t As[R * P];
-  __shared__ __attribute__((aligned(16))) uint16_t Bs[R * P];
+  static_assert(R * P == dw_tile<T>, "staged rows");
+  uint16_t* const As = lds;
+  uint16_t* const Bs = lds + R * P;
   const int H = g.H;
   const int K = (l == 0) ? kEnc : H, O = H;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1, m32 = lane & 31, kh = lane >> 5;
   // work tile bj, weight block by (of nblk), the work tiles dealt to the XCDs in turn
   int bj, by;
-  xcd_unit_block(nblk, bj, by);
+  xcd_unit_block(b, nblk, bj, by);
   const int per_layer = nblk / nlayers;
   l += by / per_layer;
   by %= per_layer;
@@ -4825,6 +4827,43 @@ __global__ void __launch_bounds__(256) k_gen_dw(const GenArgs g_in, int l, int n
     }
   }
   if (__syncthreads_or(bad) && tid == 0) atomicOr(&a.flags[ob.k], 1);
+}
+
+// Loss of each object of the chain: its row tiles' losses in order, into its first work tile (its
+// other work tiles hold zero, so the optimiser's sum over them is the object's loss).
+__device__ __forceinline__ void gen_loss_block(const GenArgs& g, int b) {
+  const StepArgs& a = g.a;
+  const int lane = threadIdx.x & 63;
+  const int j = b * 4 + (threadIdx.x >> 6);  // a wave per batch object
+  if (j >= a.n_objects) return;
+  const int total = clamp_tiles(g.gts[a.n_objects], g.max_gen_tiles);
+  const TileRange tr = clamp_tile_range(g.gts[j], g.gts[j + 1], total);
+  const TileRange wr = clamp_tile_range(a.tile_start[j], a.tile_start[j + 1], a.max_tiles);
+  if (tr.t1 <= tr.t0 || wr.t1 <= wr.t0) return;
+  // the row tiles' losses are read 64 at a time (one per lane) and added one after another in
+  // tile order from lane registers: the same sum as a serial loop, without a load per addition
+  float s = 0.f;
+  for (int t0 = tr.t0; t0 < tr.t1; t0 += 64) {
+    const float v = (t0 + lane < tr.t1) ? g.gen_loss[t0 + lane] : 0.f;
+    const int n = min(64, tr.t1 - t0);
+    for (int i = 0; i < n; ++i) s += __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), i));
+  }
+  if (lane == 0) a.tile_loss[wr.t0] = s;
+  for (int t = wr.t0 + 1 + lane; t < wr.t1; t += 64) a.tile_loss[t] = 0.f;
+}
+
+// Weight gradients of the first layer (64 x 64 blocks, too few to fill the chip: 24 us of a launch
+// of their own at 50 objects of 1,200 rows, hidden 256), of the square layers in 128 x 128 blocks
+// (n1 > 0), and the losses (5 us of a launch): n0 and n1 workgroups, nb0 and nb1 to a work tile, and
+// the rest. That step's launches took 98 us apart, 82 in one.
+__global__ void __launch_bounds__(256) k_gen_dw(const GenArgs g_in, int n0, int nb0, int n1, int nb1) {
+  GenArgs g = g_in;
+  read_batch(g.a);
+  __shared__ __attribute__((aligned(16))) uint16_t lds[2 * dw_tile<128>];
+  const int b = (int)blockIdx.x;
+  if (b < n0) gen_dw_block<64>(g, b, 0, nb0, 1, lds);
+  else if (b < n0 + n1) gen_dw_block<128>(g, b - n0, 1, nb1, kLayers - 1, lds);
+  else gen_loss_block(g, b - n0 - n1);
 }
 
 // 256 x 256 blocks of the products above, for the square layers of widths that are multiples of
@@ -5236,29 +5275,10 @@ __global__ void __launch_bounds__(256) k_gen_render(const GenArgs g_in) {
   if (lane == 0) g.gen_loss[t] = loss;
 }
 
-// Loss of each object of the chain: its row tiles' losses in order, into its first work tile (its
-// other work tiles hold zero, so the optimiser's sum over them is the object's loss).
 __global__ void __launch_bounds__(256) k_gen_loss(const GenArgs g_in) {
   GenArgs g = g_in;
   read_batch(g.a);
-  const StepArgs& a = g.a;
-  const int lane = threadIdx.x & 63;
-  const int j = blockIdx.x * 4 + (threadIdx.x >> 6);  // a wave per batch object
-  if (j >= a.n_objects) return;
-  const int total = clamp_tiles(g.gts[a.n_objects], g.max_gen_tiles);
-  const TileRange tr = clamp_tile_range(g.gts[j], g.gts[j + 1], total);
-  const TileRange wr = clamp_tile_range(a.tile_start[j], a.tile_start[j + 1], a.max_tiles);
-  if (tr.t1 <= tr.t0 || wr.t1 <= wr.t0) return;
-  // the row tiles' losses are read 64 at a time (one per lane) and added one after another in
-  // tile order from lane registers: the same sum as a serial loop, without a load per addition
-  float s = 0.f;
-  for (int t0 = tr.t0; t0 < tr.t1; t0 += 64) {
-    const float v = (t0 + lane < tr.t1) ? g.gen_loss[t0 + lane] : 0.f;
-    const int n = min(64, tr.t1 - t0);
-    for (int i = 0; i < n; ++i) s += __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), i));
-  }
-  if (lane == 0) a.tile_loss[wr.t0] = s;
-  for (int t = wr.t0 + 1 + lane; t < wr.t1; t += 64) a.tile_loss[t] = 0.f;
+  gen_loss_block(g, (int)blockIdx.x);
 }
 
 // BF16 copy of object k's parameter slots (round to nearest even), eight per thread.
@@ -5334,7 +5354,7 @@ __global__ void __launch_bounds__(512, 2) k_gen_chain(const GenArgs g_in) {
   // unit: row tiles t0 and t0 + 1 of object j (units dealt to the XCDs in turn); rows 0..63 of the
   // buffers hold the first tile's samples, 64..127 the second's
   int unit, one;
-  xcd_unit_block(1, unit, one);
+  xcd_unit_block((int)blockIdx.x, 1, unit, one);
   if (unit >= clamp_tiles(g.gbs[a.n_objects], g.max_gen_tiles)) return;
   const int j = gen_object(g.gbs, a.n_objects, unit);
   const int k = a.object_ids[j];
@@ -5610,9 +5630,10 @@ hipError_t launch_generic(int mode, const GenArgs& g, int tiles_bound, int block
   // hidden 1024, 4 (92) 447 / 407, 8 (184) 560 / 566, 16 (364) 1041 / 1059. Weight gradients likewise at
   // hidden 512 (8 objects, 192 workgroups: 262 / 255; 16, 384: 367 / 370); at hidden 1024 always: the
   // 128 x 128 blocks of one object all run on one XCD (1 object 263 / 306, 4 368 / 407, 16 1021 / 1059).
+  // Hidden 256: 50 objects of 1,200 rows 318 / 318, of 4,800 941 / 980, 16 of 1,200 164 / 151.
   constexpr int kCUs = 256;
   const bool wide = nw > 1 && (long long)blocks_bound * nw >= kCUs;
-  const bool wide_dw = nw > 1 && (nw >= 4 || (long long)work_bound * nw * nw * (kLayers - 1) >= kCUs);
+  const bool wide_dw = (nw >= 4 || (long long)work_bound * nw * nw * (kLayers - 1) >= kCUs);
   auto fwd_dx = [&](int kind, int ncols, int l) {
     if (wide && l > 0 && l < kLayers) {
       if (kind == GEN_FWD) hipLaunchKernelGGL(k_gen_wide<GEN_FWD>, grid1(blocks_bound, nw), dim3(512), 0, s, g, l);
@@ -5627,11 +5648,12 @@ hipError_t launch_generic(int mode, const GenArgs& g, int tiles_bound, int block
       else hipLaunchKernelGGL((k_gen_gemm<GEN_DX, 64>), grid1(tiles_bound, nb), dim3(256), 0, s, g, l, nb);
     }
   };
-  auto launch_dw = [&]() {  // every layer's weight gradients, from the deltas of all layers
-    const int nb = blocks(H, 128) * blocks(H, 128) * (kLayers - 1), nb0 = blocks(H, 64) * blocks(kEnc, 64);
+  const int nloss = blocks(g.a.n_objects, 4);
+  auto launch_dw = [&]() {  // every layer's weight gradients, from the deltas of all layers, and the losses
     if (wide_dw) hipLaunchKernelGGL(k_gen_wide<GEN_DW>, grid1(work_bound * (kLayers - 1), nw * nw), dim3(512), 0, s, g, 0);
-    else hipLaunchKernelGGL(k_gen_dw<128>, grid1(work_bound, nb), dim3(256), 0, s, g, 1, nb, kLayers - 1);
-    hipLaunchKernelGGL(k_gen_dw<64>, grid1(work_bound, nb0), dim3(256), 0, s, g, 0, nb0, 1);
+    const int nb0 = blocks(H, 64) * blocks(kEnc, 64), nb1 = wide_dw ? 0 : blocks(H, 128) * blocks(H, 128) * (kLayers - 1);
+    const int n0 = (int)grid1(work_bound, nb0).x, n1 = (int)grid1(work_bound, nb1).x;
+    hipLaunchKernelGGL(k_gen_dw, dim3(n0 + n1 + nloss), dim3(256), 0, s, g, n0, nb0, n1, nb1);
     hipLaunchKernelGGL(k_gen_dw_small, dim3(work_bound, blocks(H, 32)), dim3(kGenDwWaves * 64), 0, s, g);
   };
   hipLaunchKernelGGL(k_gen_tiles, dim3(1), dim3(1024), 0, s, g);
@@ -5644,15 +5666,15 @@ hipError_t launch_generic(int mode, const GenArgs& g, int tiles_bound, int block
     const dim3 grid = grid1((tiles_bound + g.a.n_objects) / 2 + 1, 1);
     if (train) hipLaunchKernelGGL(k_gen_chain<true>, grid, dim3(512), lds_chain().total, s, g);
     else hipLaunchKernelGGL(k_gen_chain<false>, grid, dim3(512), lds_chain().total, s, g);
-    hipLaunchKernelGGL(k_gen_loss, dim3((g.a.n_objects + 3) / 4), dim3(256), 0, s, g);
     if (train) launch_dw();
+    else hipLaunchKernelGGL(k_gen_loss, dim3(nloss), dim3(256), 0, s, g);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(k_gen_encode, dim3(wave_blocks), dim3(256), 0, s, g);
   for (int l = 0; l <= kLayers; ++l) fwd_dx(GEN_FWD, (l == kLayers) ? kOut : H, l);
   if (train) hipLaunchKernelGGL(k_gen_render<true>, dim3(wave_blocks), dim3(256), 0, s, g);
   else hipLaunchKernelGGL(k_gen_render<false>, dim3(wave_blocks), dim3(256), 0, s, g);
-  hipLaunchKernelGGL(k_gen_loss, dim3((g.a.n_objects + 3) / 4), dim3(256), 0, s, g);
+  if (!train) hipLaunchKernelGGL(k_gen_loss, dim3(nloss), dim3(256), 0, s, g);
   if (train) {
     for (int l = kLayers; l > 0; --l) fwd_dx(GEN_DX, H, l);
     launch_dw();
