@@ -87,8 +87,8 @@ typedef struct {
   int32_t precision;            /* VMAP_FP32, or VMAP_BF16: MLP products on BF16 MFMA */
   int32_t rays_per_tile;        /* rays per work tile; 0 = library default for (H, S) */
   int32_t scale_growth_interval;/* BF16: good steps before the loss scale doubles (2000) */
-  int32_t rays_per_tile_wide;   /* rays per work tile of objects wider than 32; 0 = one round
-                                 * of the cooperative kernel (4 waves x floor(64 / S) rays) */
+  int32_t rays_per_tile_wide;   /* rays per work tile of objects wider than 32; 0 = one to eight
+                                 * rounds of 4 x floor(64 / S) rays, by the rays per object slot */
   int32_t split_step;           /* 0: when every object has width 32 and a batch has at most
                                  * 2048 objects, the training step's tile kernel builds its work
                                  * list itself (two launches per step: tiles, then gradient sums

@@ -100,8 +100,8 @@ int default_rays_per_tile(const vmap_config* c) {
   return round * 2;
 }
 
-// Objects wider than 32 run in the cooperative kernel, whose tiles hold whole rounds (a sub-tile
-// for each of its four waves). Few rays per object (a room's background: 1,200 rays) want one
+// Tiles of objects wider than 32 hold whole rounds of four sub-tiles (hidden 64: one for each of a
+// workgroup's four waves). Few rays per object (a room's background: 1,200 rays) want one
 // round per tile, to spread the object over many workgroups; many rays per object want longer
 // tiles, to write fewer partial gradients (each is a whole object's parameter vector). Default:
 // about max_rays / max_objects / 32 rays, in whole rounds, between one and eight rounds.

@@ -124,16 +124,12 @@ __host__ __device__ constexpr int n_params_of(int H) {
   return (H * kEnc + H) + (kLayers - 1) * (H * H + H) + (kOut * H + kOut);
 }
 
-// Per-wave staging: the output-layer seeds dz (FP32 [32][4], or BF16 [4][40]) and two transposed
-// tiles (delta and activations): FP32 [32 samples][H + 4], BF16 [H features][40].
-// dL/dz of a 32-sample pass: BF16 as four output rows of 40 (the output layer's weight-gradient
-// operand), then sample-major, four per sample (the output layer's delta operand); FP32
-// sample-major.
+// dL/dz of a 32-sample pass in BF16 (hidden 64): four output rows of 40 (the output layer's
+// weight-gradient operand), then sample-major, four per sample (its delta operand).
 constexpr int kDzRowsBytes = 4 * 40 * 2;
-__host__ __device__ constexpr int dz_tile_bytes(bool bf16) { return bf16 ? kDzRowsBytes + 32 * kOut * 2 : 32 * kOut * 4; }
-__host__ __device__ constexpr int tr_tile_bytes(int H, bool bf16) {
-  return bf16 ? H * 40 * 2 : 32 * (H + 4) * 4;
-}
+// A wave's staging in the FP32 cooperative kernel: dz [32][4] and tiles [32 samples][H + 4].
+constexpr int kDzTileBytes = 32 * kOut * 4;
+__host__ __device__ constexpr int tr_tile_bytes(int H) { return 32 * (H + 4) * 4; }
 
 // Per-wave staging of the width-32 tile kernel, which takes a sub-tile's two 32-sample passes
 // together. dL/dz of the 64 slots: BF16 as four output rows of kDzPitch (the output layer's
@@ -196,16 +192,17 @@ __host__ __device__ constexpr LdsLayout lds_layout(int H, bool bf16, int nwaves)
   return L;
 }
 
-// Wide models (H >= 128) keep their weights in a per-object image in device memory with the byte
-// layout of the LDS staging above (offsets below B_off), since weights and BF16 transposes do not
-// fit in LDS next to the cooperative kernel's staging tiles.
+// Weight image of a hidden-128 object (BF16) in device memory: the byte layout of the LDS staging
+// above (offsets below B_off). The training kernel copies it to LDS, rendering and point queries
+// read their operands from it.
 __host__ __device__ constexpr int image_bytes(int H, bool bf16) {
   return round_up(lds_layout(H, bf16, 1).B_off, 256);
 }
 
-// LDS of the cooperative tile kernel (H >= 64): the weights as in lds_layout unless they live in
-// the device image, then the encoding matrix, the tile's loss / output-bias sums and a flag, and
-// four waves' staging tiles, which the waves read from each other.
+// LDS of the cooperative tile kernel (hidden 64 in FP32, rendering with hidden 128): the weights as
+// in lds_layout unless they live in the device image, then the encoding matrix, the tile's loss /
+// output-bias sums and a flag, and (training) four waves' staging tiles, which the waves read from
+// each other.
 struct CoopLayout {
   int B_off;
   int loss_off;     // float loss, float head-bias gradient [4], int non-finite flag
@@ -220,7 +217,7 @@ __host__ __device__ constexpr CoopLayout coop_layout(int H, bool bf16) {
   off = round_up(off + 3 * kFeatures * 4, 16);
   C.loss_off = off;
   off = round_up(off + 32, 16);
-  C.scratch_wave = round_up(dz_tile_bytes(bf16) + 2 * tr_tile_bytes(H, bf16), 16);
+  C.scratch_wave = bf16 ? 0 : round_up(kDzTileBytes + 2 * tr_tile_bytes(H), 16);
   C.scratch_off = off;
   off += 4 * C.scratch_wave;
   C.total = off;
