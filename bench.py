@@ -60,7 +60,7 @@ def tile_kernel_fingerprint() -> str:
     csrc = os.path.join(ROOT, "paper_2302_01838_amd", "csrc")
     k = open(os.path.join(csrc, "vmap_kernels.hip")).read()
     a = k.index("// Activations of one 32-sample pass")
-    b = k.index("// Tile kernel for wide models")
+    b = k.index("// Tile kernel for hidden 64 in BF16")
     h = hashlib.sha256(k[a:b].encode())
     for name in ("vmap_internal.h", "vmap_math.h", "vmap_bf16.h"):
         h.update(open(os.path.join(csrc, name)).read().encode())
