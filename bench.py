@@ -535,7 +535,7 @@ def main():
                                 shape.get("split_step", False))
                if headline else None)
     if not headline:
-        kname = ("tile kernels of the step (cooperative kernel of the wide models, with the "
+        kname = ("tile kernels of the step (kernel of the wide models, with the "
                  "hidden-32 tile kernel where present), events around all of a step's tile launches")
     elif shape.get("split_step"):
         kname = "tile kernel (encode+MLP+render+loss+backward; work list launched apart)"
