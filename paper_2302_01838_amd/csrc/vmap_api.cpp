@@ -379,10 +379,18 @@ int gen_work_rays(const vmap_ctx* c, int S) {
 // rays_per_tile: of hidden-32 objects (0: the stack's).
 hipError_t enqueue_worklist(vmap_ctx* c, const vmap_batch* b, hipStream_t s,
                             const BatchDev* bd = nullptr, int rays_per_tile = 0) {
+  GenScan gen{};
+  if (c->cfg.precision == VMAP_BF16 && generic_width(c->cfg.max_hidden)) {
+    gen.rpw = std::max(1, kSlots / b->samples_per_ray);
+    gen.S = b->samples_per_ray;
+    gen.start[0] = reinterpret_cast<int32_t*>(c->work + c->wl.gts);
+    gen.start[1] = reinterpret_cast<int32_t*>(c->work + c->wl.gbs);
+    gen.start[2] = reinterpret_cast<int32_t*>(c->work + c->wl.gws);
+  }
   return launch_worklist(b->n_objects, b->n_rays_total, b->object_ids, b->ray_offsets,
                          rays_per_tile > 0 ? rays_per_tile : c->rays_per_tile, c->rays_per_tile_wide, gen_work_rays(c, b->samples_per_ray),
                          c->cfg.max_objects, c->desc(), c->scaler(), c->tile_start(), c->width_start(32), c->flags(),
-                         c->t_next(), bd, s);
+                         c->t_next(), bd, gen, s);
 }
 
 OptArgs make_opt_args(vmap_ctx* c, const vmap_batch* b, float* loss_out, float* grad_out,

@@ -529,6 +529,13 @@ struct SceneArgs {
   int32_t* id_out;
 };
 
+// Layered-path scans of a work list: start[0] row tiles (rpw rays each), start[1] product blocks,
+// start[2] work tiles, [n_objects + 1] each; NULL where the stack holds no layered width.
+struct GenScan {
+  int rpw, S;
+  int32_t* start[3];
+};
+
 // Kernel launchers (vmap_kernels.hip). Return hipSuccess or the launch error.
 hipError_t launch_fill_zero(void* dst, size_t bytes, hipStream_t s);
 hipError_t launch_worklist(int n_objects, int n_rays, const int32_t* object_ids,
@@ -536,7 +543,7 @@ hipError_t launch_worklist(int n_objects, int n_rays, const int32_t* object_ids,
                            int rays_per_tile_gen,
                            int max_objects, const ObjDesc* desc, ScalerState* scaler,
                            int32_t* tile_start, int32_t* width_start, int32_t* flags, int32_t* t_next,
-                           const BatchDev* bd, hipStream_t s);
+                           const BatchDev* bd, const GenScan& gen, hipStream_t s);
 hipError_t launch_tiles(int H, bool bf16, int mode, const StepArgs& a, int nwaves, int grid,
                         hipStream_t s);
 // Debug validation of a batch (distinct ids, ascending sample depths); mark: [max_objects] int32.

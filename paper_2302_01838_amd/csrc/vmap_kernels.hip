@@ -3062,7 +3062,9 @@ __global__ void __launch_bounds__(256) k_query(const QueryArgs qa) {
 // Tile offsets per batch object (exclusive scan of ceil(rays / rays_per_tile)), and the same over
 // the objects of each fused kernel width alone (width_start: scans of n_objects + 1), so that
 // a width's launch finds its own tiles: workgroup t of it takes the t-th, and none starts only to
-// pass over another width's tile. A fourth scan counts each object's units of k_reduce_adam_wide.
+// pass over another width's tile. A fourth scan counts each object's units of k_reduce_adam_wide; in a
+// stack that may hold a layered width (GEN), three more its row tiles, product blocks and work tiles
+// (a launch of their own took 6 us of a 310 us step).
 // Clears the non-finite flags of the batch's objects and records
 // each object's next Adam step count, so that the optimiser kernels read it from here while one of
 // their blocks advances the count. Checks the ray offsets as step_table does: a batch that fails
@@ -3070,6 +3072,7 @@ __global__ void __launch_bounds__(256) k_query(const QueryArgs qa) {
 // One workgroup, an object per thread, scans by DPP within waves: bound by three dependent loads
 // (offsets and ids, descriptor, stores).
 
+template <bool GEN>
 __global__ void __launch_bounds__(1024) k_worklist(int n_objects, int n_rays, const int32_t* ids,
                                                    const int32_t* offs, int rpt, int rpt_wide, int rpt_gen,
                                                    int max_objects, const ObjDesc* __restrict__ desc,
@@ -3078,8 +3081,9 @@ __global__ void __launch_bounds__(1024) k_worklist(int n_objects, int n_rays, co
                                                    int32_t* __restrict__ width_start, int width_pitch,
                                                    int32_t* __restrict__ flags,
                                                    int32_t* __restrict__ t_next,
-                                                   const BatchDev* __restrict__ bd) {
-  __shared__ int wtot[16][5];
+                                                   const BatchDev* __restrict__ bd, const GenScan gen) {
+  constexpr int N = GEN ? 8 : 5;  // scans
+  __shared__ int wtot[16][N];
   if (bd) {
     n_objects = bd->n_objects;
     n_rays = bd->n_rays;
@@ -3090,10 +3094,12 @@ __global__ void __launch_bounds__(1024) k_worklist(int n_objects, int n_rays, co
   int bad = 0;
   for (int j = tid; j < n_objects; j += nt) bad |= !batch_segment_ok(j, n_objects, offs[j], offs[j + 1], n_rays);
   const bool any_bad = __syncthreads_or(bad) != 0;
-  int carry[5] = {0, 0, 0, 0, 0};  // all tiles, those of widths 32, 64 and 128, optimiser units
+  // all tiles, those of widths 32, 64 and 128, optimiser units; of layered objects row tiles, product
+  // blocks (256 rows, or pairs of row tiles) and work tiles
+  int carry[N] = {};
   for (int base = 0; base < n_objects; base += nt) {
     const int j = base + tid;
-    int cnt[5] = {0, 0, 0, 0, 0};
+    int cnt[N] = {};
     if (j < n_objects) {
       const int o0 = offs[j], o1 = offs[j + 1], k = ids[j];
       const bool in_range = k >= 0 && k < max_objects;
@@ -3107,26 +3113,35 @@ __global__ void __launch_bounds__(1024) k_worklist(int n_objects, int n_rays, co
 #pragma unroll
       for (int w = 0; w < 3; ++w) cnt[1 + w] = (!valid || kernel_width(hidden) == (32 << w)) ? cnt[0] : 0;
       cnt[4] = valid ? opt_units(n_params, cnt[0]) : 1;
+      if constexpr (GEN) {
+        if (valid && !any_bad && generic_width(hidden) && o1 > o0) {
+          cnt[5] = tiles_of(o1 - o0, gen.rpw);
+          cnt[6] = gen_chain(hidden) ? (cnt[5] + 1) / 2
+                                     : (int)(((long long)(o1 - o0) * gen.S + kGenBlockRows - 1) / kGenBlockRows);
+          cnt[7] = cnt[0];
+        }
+      }
       if (in_range) flags[k] = 0;
       // step count after this batch's update, read by the optimiser kernels
       t_next[j] = valid ? step + 1 : 0;
     }
-    int x[5];
+    int x[N];
 #pragma unroll
-    for (int i = 0; i < 5; ++i) {
+    for (int i = 0; i < N; ++i) {
       x[i] = wave_scan(cnt[i]);
       if (lane == kWave - 1) wtot[wave][i] = x[i];
     }
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 5; ++i) {
+    for (int i = 0; i < N; ++i) {
       int before = carry[i];
       for (int w = 0; w < nw; ++w) {
         const int v = wtot[w][i];
         if (w < wave) before += v;
         carry[i] += v;
       }
-      if (j < n_objects) (i == 0 ? tile_start : width_start + (i - 1) * width_pitch)[j] = before + x[i] - cnt[i];
+      int32_t* dst = i == 0 ? tile_start : i < 5 ? width_start + (i - 1) * width_pitch : gen.start[i < 5 ? 0 : i - 5];
+      if (j < n_objects) dst[j] = before + x[i] - cnt[i];
     }
     __syncthreads();
   }
@@ -3134,6 +3149,10 @@ __global__ void __launch_bounds__(1024) k_worklist(int n_objects, int n_rays, co
     tile_start[n_objects] = carry[0];
 #pragma unroll
     for (int w = 0; w < 4; ++w) width_start[w * width_pitch + n_objects] = carry[1 + w];
+    if constexpr (GEN) {
+#pragma unroll
+      for (int i = 0; i < 3; ++i) gen.start[i][n_objects] = carry[5 + i];
+    }
     scaler->batch_ok = !any_bad;
     if (any_bad) atomicOr(&scaler->device_error, DERR_OFFSETS);
   }
@@ -4064,12 +4083,18 @@ hipError_t launch_worklist(int n_objects, int n_rays, const int32_t* object_ids,
                            int rays_per_tile_gen,
                            int max_objects, const ObjDesc* desc, ScalerState* scaler,
                            int32_t* tile_start, int32_t* width_start, int32_t* flags, int32_t* t_next,
-                           const BatchDev* bd, hipStream_t s) {
+                           const BatchDev* bd, const GenScan& gen, hipStream_t s) {
   if (rays_per_tile_gen < 1) return hipErrorInvalidValue;
   // (fewer waves meet at the barriers for a small batch)
-  hipLaunchKernelGGL(k_worklist, dim3(1), dim3(n_objects <= 256 ? 256 : 1024), 0, s, n_objects, n_rays, object_ids,
-                     ray_offsets, rays_per_tile, rays_per_tile_wide, rays_per_tile_gen, max_objects,
-                     desc, scaler, tile_start, width_start, max_objects + 1, flags, t_next, bd);
+  const dim3 block(n_objects <= 256 ? 256 : 1024);
+  if (gen.start[0])
+    hipLaunchKernelGGL(k_worklist<true>, dim3(1), block, 0, s, n_objects, n_rays, object_ids,
+                       ray_offsets, rays_per_tile, rays_per_tile_wide, rays_per_tile_gen, max_objects,
+                       desc, scaler, tile_start, width_start, max_objects + 1, flags, t_next, bd, gen);
+  else
+    hipLaunchKernelGGL(k_worklist<false>, dim3(1), block, 0, s, n_objects, n_rays, object_ids,
+                       ray_offsets, rays_per_tile, rays_per_tile_wide, rays_per_tile_gen, max_objects,
+                       desc, scaler, tile_start, width_start, max_objects + 1, flags, t_next, bd, gen);
   return hipGetLastError();
 }
 
@@ -4170,69 +4195,6 @@ __device__ __forceinline__ bool gen_tile(const GenArgs& g, const StepArgs& a, in
                                      a.n_rays);
   o = GenTile{j, a.object_ids[j], rr.lo, rr.hi};
   return true;
-}
-
-// Row tiles per batch object, ceil(rays / rpw), 256-row product blocks, ceil(rays S / 256), and
-// work tiles, ceil(rays / work_rays) (as the work list counts them), for the objects of width H;
-// none for the others or for a batch that failed the offsets check (ScalerState::batch_ok, from
-// the work-list launch). gts, gbs and gws: their exclusive scans.
-__global__ void __launch_bounds__(1024) k_gen_tiles(const GenArgs g_in) {
-  GenArgs g = g_in;
-  read_batch(g.a);
-  const StepArgs& a = g.a;
-  __shared__ int part[3][1024];
-  const bool ok = a.scaler->batch_ok != 0;
-  const int tid = threadIdx.x, nt = blockDim.x;
-  const int per = (a.n_objects + nt - 1) / nt;
-  const int j0 = min(tid * per, a.n_objects), j1 = min(j0 + per, a.n_objects);
-  auto rays = [&](int j) {
-    const int k = a.object_ids[j];
-    if (!ok || k < 0 || k >= a.max_objects) return 0;
-    if (!a.desc[k].registered || a.desc[k].hidden != g.H) return 0;
-    const int nr = a.ray_offsets[j + 1] - a.ray_offsets[j];
-    return nr > 0 ? nr : 0;
-  };
-  // 256-row product blocks, or (gen_chain) pairs of row tiles
-  auto nblk = [&](int nr) {
-    return gen_chain(g.H) ? (tiles_of(nr, g.rpw) + 1) / 2
-                          : (int)(((long long)nr * a.S + kGenBlockRows - 1) / kGenBlockRows);
-  };
-  int lt = 0, lb = 0, lw = 0;
-  for (int j = j0; j < j1; ++j) {
-    const int nr = rays(j);
-    lt += tiles_of(nr, g.rpw);
-    lb += nblk(nr);
-    lw += tiles_of(nr, g.work_rays);
-  }
-  part[0][tid] = lt;
-  part[1][tid] = lb;
-  part[2][tid] = lw;
-  __syncthreads();
-  for (int off = 1; off < nt; off <<= 1) {
-    const int vt = (tid >= off) ? part[0][tid - off] : 0;
-    const int vb = (tid >= off) ? part[1][tid - off] : 0;
-    const int vw = (tid >= off) ? part[2][tid - off] : 0;
-    __syncthreads();
-    part[0][tid] += vt;
-    part[1][tid] += vb;
-    part[2][tid] += vw;
-    __syncthreads();
-  }
-  int rt = part[0][tid] - lt, rb = part[1][tid] - lb, rw = part[2][tid] - lw;
-  for (int j = j0; j < j1; ++j) {
-    const int nr = rays(j);
-    g.gts[j] = rt;
-    g.gbs[j] = rb;
-    g.gws[j] = rw;
-    rt += tiles_of(nr, g.rpw);
-    rb += nblk(nr);
-    rw += tiles_of(nr, g.work_rays);
-  }
-  if (tid == nt - 1) {
-    g.gts[a.n_objects] = part[0][nt - 1];
-    g.gbs[a.n_objects] = part[1][nt - 1];
-    g.gws[a.n_objects] = part[2][nt - 1];
-  }
 }
 
 // Encoding of sample `slot` of row tile tl: normalised point in FP64 rounded once, Gaussian Fourier
@@ -5486,7 +5448,6 @@ hipError_t launch_generic(int mode, const GenArgs& g, int tiles_bound, int block
     hipLaunchKernelGGL(k_gen_dw, dim3(n0 + n1 + nloss), dim3(256), 0, s, g, n0, nb0, n1, nb1);
     hipLaunchKernelGGL(k_gen_dw_small, dim3(work_bound, blocks(H, 32)), dim3(kGenDwWaves * 64), 0, s, g);
   };
-  hipLaunchKernelGGL(k_gen_tiles, dim3(1), dim3(1024), 0, s, g);
   if (gen_chain(H)) {
     static int allowed[2] = {0, 0};
     const void* fn = train ? reinterpret_cast<const void*>(k_gen_chain<true>) : reinterpret_cast<const void*>(k_gen_chain<false>);
