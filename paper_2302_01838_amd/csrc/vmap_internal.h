@@ -192,6 +192,24 @@ __host__ __device__ constexpr LdsLayout lds_layout(int H, bool bf16, int nwaves)
   return L;
 }
 
+// The training step's tile table in LDS (MODE_STEP), behind the layout's `bytes`: the objects' first
+// tiles, and with `rays` the batch's ray offsets and object ids, `pitch` words apart. More than a
+// wave's objects leave the last two out where they would cost a CU its second workgroup (past about
+// 500 objects: a load per tile from the batch costs less than half the waves). A batch of at most
+// 64 objects always keeps all three: the waves write them whatever the launch's shape.
+struct TableLayout {
+  int pitch;
+  bool rays;
+  int total;  // bytes of the launch's LDS
+};
+__host__ __device__ constexpr TableLayout table_layout(int bytes, int n_objects) {
+  TableLayout T{};
+  T.pitch = round_up(n_objects + 1, 4);
+  T.rays = n_objects <= 64 || 2 * (bytes + 3 * T.pitch * 4) <= 160 * 1024;
+  T.total = bytes + (T.rays ? 3 : 1) * T.pitch * 4;
+  return T;
+}
+
 // Weight image of a hidden-128 object (BF16) in device memory: the byte layout of the LDS staging
 // above (offsets below B_off). The training kernel copies it to LDS, rendering and point queries
 // read their operands from it.

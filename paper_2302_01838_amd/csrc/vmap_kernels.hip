@@ -1224,10 +1224,10 @@ __global__ void __launch_bounds__((BF && H == 32) ? 512 : 256, 1) k_step_tiles(c
 
   // first tile of every batch object: from the LDS table or from k_worklist
   // (and, with the LDS table, its ray offsets and object ids)
-  const int tbl_words = round_up(a.n_objects + 1, 4);
+  const int tbl_pitch = table_layout(0, a.n_objects).pitch;
   int32_t* tbl = reinterpret_cast<int32_t*>(smem + a.lds_table);
-  int32_t* tray = tbl + tbl_words;
-  int32_t* tk = tray + tbl_words;
+  int32_t* tray = tbl + tbl_pitch;
+  int32_t* tk = tray + tbl_pitch;
   auto first_tile = [&](int j) { return TABLE ? tbl[j] : a.width_start[j]; };  // among this width's tiles
   int n_tiles;
   LaneTable lt{};
@@ -3956,12 +3956,10 @@ static hipError_t launch_tiles_t(const StepArgs& a_in, int nwaves, int grid, hip
     bytes = MODE == MODE_FWD ? lds_layout(H, BF, nwaves).scratch_off : lds_layout(H, BF, nwaves).total;
     if constexpr (MODE == MODE_STEP) {  // the tile table follows the layout
       if (a.n_objects > kTableMaxObjects || !a.tile_bad) return hipErrorInvalidValue;
-      a.lds_table = bytes;  // first tiles, ray offsets and object ids
-      const int words = round_up(a.n_objects + 1, 4) * 4;
-      // past about 500 objects the three arrays would leave room for one workgroup on a CU, not
-      // two: a load per tile from the batch costs less than half the waves
-      a.lds_rays = 2 * (bytes + 3 * words) <= 160 * 1024;
-      bytes += (a.lds_rays ? 3 : 1) * words;
+      const TableLayout T = table_layout(bytes, a.n_objects);
+      a.lds_table = bytes;
+      a.lds_rays = T.rays;
+      bytes = T.total;
     }
   } else if constexpr (H == 128 && BF && MODE == MODE_TRAIN) {
     fn = reinterpret_cast<const void*>(k_step_128);
