@@ -54,7 +54,8 @@ enum { VMAP_FP32 = 0, VMAP_BF16 = 1 };
 
 /* Which per-object array vmap_get_state / vmap_set_state move. */
 enum { VMAP_STATE_PARAMS = 0, VMAP_STATE_ADAM_M = 1, VMAP_STATE_ADAM_V = 2,
-       VMAP_STATE_GRAD = 3, VMAP_STATE_STEP = 4, VMAP_STATE_SCALER = 5 };
+       VMAP_STATE_GRAD = 3, VMAP_STATE_STEP = 4, VMAP_STATE_SCALER = 5,
+       VMAP_STATE_TILES = 6 };
 
 typedef struct vmap_ctx vmap_ctx; /* opaque; created by vmap_init_objects, freed by vmap_destroy */
 
@@ -85,7 +86,8 @@ typedef struct {
   int32_t max_samples_per_ray;  /* S bound for batches */
   int32_t max_rays;             /* rays per batch the workspace is sized for */
   int32_t precision;            /* VMAP_FP32, or VMAP_BF16: MLP products on BF16 MFMA */
-  int32_t rays_per_tile;        /* rays per work tile; 0 = library default for (H, S) */
+  int32_t rays_per_tile;        /* rays per work tile; 0 = library default for the precision,
+                                 * max_samples_per_ray, max_rays and max_objects */
   int32_t scale_growth_interval;/* BF16: good steps before the loss scale doubles (2000) */
   int32_t rays_per_tile_wide;   /* rays per work tile of objects wider than 32; 0 = one to eight
                                  * rounds of 4 x floor(64 / S) rays, by the rays per object slot */
@@ -270,12 +272,26 @@ int vmap_adam_step(vmap_ctx* ctx, const vmap_batch* batch, void* stream);
  * these a training run stops and resumes where it was (Sec. 3.2: objects stop and resume without
  * interference): saving every object's four entries and the scaler after N steps and restoring
  * them into a fresh context gives, after M more steps, bitwise the state of N + M straight steps.
+ * A context of another capacity (max_rays, max_objects) also needs the first one's tiles, since an
+ * object's gradient is summed tile by tile and the default tiles follow capacity: VMAP_STATE_TILES
+ * (object_id ignored, bytes = 8, read only) gives int32 rays_per_tile and rays_per_tile_wide as they
+ * are in force, for the new context's config or for vmap_set_tiles.
  * A scaler written must hold a power-of-two scale in [2^-125, 2^126] (VMAP_EINVAL otherwise).
  * Synchronises `stream`. */
 int vmap_get_state(vmap_ctx* ctx, int32_t object_id, int32_t which, void* host_dst,
                    size_t bytes, void* stream);
 int vmap_set_state(vmap_ctx* ctx, int32_t object_id, int32_t which, const void* host_src,
                    size_t bytes, void* stream);
+
+/* Cut the objects' rays into tiles of these sizes from now on (0: leave as it is), in a workspace
+ * for them: vmap_workspace_bytes of the context's config with both set, caller-owned, 256-byte
+ * aligned, the present one again if it is large enough. Objects and their state stay; captured
+ * graphs are dropped and the weight images staged again. Synchronises `stream`, which must be
+ * behind all work on the present workspace; that is no longer used when the call returns.
+ * VMAP_EINVAL for a size or an alignment out of range, VMAP_ECAPACITY for too few bytes: the
+ * context is then as it was. */
+int vmap_set_tiles(vmap_ctx* ctx, int32_t rays_per_tile, int32_t rays_per_tile_wide,
+                   void* workspace_dev, size_t workspace_bytes, void* stream);
 
 /* Loss scale, objects skipped by the last step (non-finite gradients) and the device error
  * flags, sticky until the context is destroyed:

@@ -20,11 +20,12 @@ import numpy as np
 
 __all__ = ["VmapError", "load_library", "library_path", "ObjectSet", "DeviceBatch", "RenderLoss",
            "VMAP_FP32", "VMAP_BF16", "STATE_PARAMS", "STATE_ADAM_M", "STATE_ADAM_V",
-           "STATE_GRAD", "STATE_STEP", "STATE_SCALER", "DERR_OBJECT", "DERR_PAIRS",
+           "STATE_GRAD", "STATE_STEP", "STATE_SCALER", "STATE_TILES", "DERR_OBJECT", "DERR_PAIRS",
            "DERR_OFFSETS", "DERR_T_ORDER", "DERR_DUP_ID", "EXPORTED"]
 
 VMAP_FP32, VMAP_BF16 = 0, 1
 STATE_PARAMS, STATE_ADAM_M, STATE_ADAM_V, STATE_GRAD, STATE_STEP, STATE_SCALER = 0, 1, 2, 3, 4, 5
+STATE_TILES = 6
 # device error bits reported by step_info() (include/vmap.h, vmap_step_info)
 DERR_OBJECT, DERR_PAIRS, DERR_OFFSETS, DERR_T_ORDER, DERR_DUP_ID = 1, 2, 4, 8, 16
 _STATUS = {0: "VMAP_OK", 1: "VMAP_EINVAL", 2: "VMAP_ECAPACITY", 3: "VMAP_EHIP", 4: "VMAP_ESTATE",
@@ -100,6 +101,7 @@ EXPORTED = {
     "vmap_adam_step": (ctypes.c_int, [_P, _BATCH, _P]),
     "vmap_get_state": (ctypes.c_int, [_P, _I, _I, _P, ctypes.c_size_t, _P]),
     "vmap_set_state": (ctypes.c_int, [_P, _I, _I, _P, ctypes.c_size_t, _P]),
+    "vmap_set_tiles": (ctypes.c_int, [_P, _I, _I, _P, ctypes.c_size_t, _P]),
     "vmap_step_info": (ctypes.c_int, [_P, ctypes.POINTER(ctypes.c_float), ctypes.POINTER(_I),
                                       ctypes.POINTER(_I), _P]),
     "vmap_param_layout": (ctypes.c_int, [_P, _I, ctypes.POINTER(_I), ctypes.POINTER(_I)]),
@@ -208,6 +210,8 @@ class ObjectSet:
         self.log_path = log_path
         self.steps_taken = 0
         self.device = device or torch.device("cuda", torch.cuda.current_device())
+        # tiles a checkpoint does not change (load())
+        self._own_tiles = (rays_per_tile != 0, rays_per_tile_wide != 0)
         # launch shape from the autotuner's cache when none is given
         self.tuned = None
         if rays_per_tile == 0 and autotune:
@@ -250,9 +254,7 @@ class ObjectSet:
         self.ctx = ctx
         self.n_params: Dict[int, int] = {}
         self.p_stride = 0
-        # launch shape (without a tuned one the library picks the tile from the capacity; the figure
-        # kept here is its tile of two sub-tiles of floor(64 / S) rays for each of four waves)
-        self.rays_per_tile = rays_per_tile or max(1, 64 // max_samples_per_ray) * 8
+        # launch shape
         self.waves, self.grid = 4, 0
         if self.tuned:
             self.set_launch(int(self.tuned["waves"]), int(self.tuned["grid"]))
@@ -272,6 +274,31 @@ class ObjectSet:
             self.close()
         except Exception:
             pass
+
+    @property
+    def tiles(self):
+        """(rays per tile, rays per tile of objects wider than 32), as they are in force."""
+        out = np.zeros(2, dtype=np.int32)
+        self._check(self.lib.vmap_get_state(self.ctx, -1, STATE_TILES, out.ctypes.data, 8, _stream()))
+        return int(out[0]), int(out[1])
+
+    @property
+    def rays_per_tile(self) -> int:
+        return self.tiles[0]
+
+    def _set_tiles(self, rays_per_tile: int, rays_per_tile_wide: int) -> None:
+        cfg = VmapConfig.from_buffer_copy(self.cfg)
+        cfg.rays_per_tile, cfg.rays_per_tile_wide = rays_per_tile, rays_per_tile_wide
+        need = self.lib.vmap_workspace_bytes(ctypes.byref(cfg))
+        if need == 0:
+            raise VmapError(1, "invalid configuration")
+        torch = _torch()
+        work = self.workspace
+        if need > work.numel():
+            work = torch.empty(need, dtype=torch.uint8, device=self.device)
+        self._check(self.lib.vmap_set_tiles(self.ctx, rays_per_tile, rays_per_tile_wide,
+                                            work.data_ptr(), work.numel(), _stream()))
+        self.cfg, self.workspace = cfg, work
 
     # -- model stack
     def add(self, centre, scale: float, hidden: int = 0, seed: int = 0,
@@ -448,9 +475,10 @@ class ObjectSet:
                                             _stream()))
 
     def save(self, path: str) -> None:
-        """Checkpoint every object's parameters, Adam moments and step count, and the loss
-        scaler, to an .npz file (plain arrays, no pickled objects)."""
-        arrays = {}
+        """Checkpoint every object's parameters, Adam moments and step count, the loss scaler and
+        the tile sizes, to an .npz file (plain arrays, no pickled objects)."""
+        tiles = self.tiles if self.cfg.max_hidden > 32 else (self.tiles[0], 0)  # 0: has none
+        arrays = {"rays_per_tile": np.asarray(tiles, np.int32)}
         for k in sorted(self.n_params):
             arrays[f"theta_{k}"] = self.get_state(k, STATE_PARAMS)
             arrays[f"m_{k}"] = self.get_state(k, STATE_ADAM_M)
@@ -463,8 +491,21 @@ class ObjectSet:
 
     def load(self, path: str) -> None:
         """Restore a checkpoint written by save() into objects already added with the same ids
-        and widths."""
+        and widths. Training then goes on bitwise as in the stack that was saved, also in a stack of
+        another capacity: its tiles are taken over (the default follows capacity, and a gradient is
+        summed tile by tile), unless this stack was created with rays_per_tile or
+        rays_per_tile_wide of its own, or has no memory for the workspace they need (a warning)."""
         with np.load(path, allow_pickle=False) as z:
+            if "rays_per_tile" in z:
+                have = self.tiles
+                want = tuple(h if own else int(x) or h for h, own, x in zip(have, self._own_tiles, z["rays_per_tile"]))
+                if want != have:
+                    try:
+                        self._set_tiles(*want)
+                    except _torch().OutOfMemoryError:
+                        import warnings
+                        warnings.warn(f"no memory for a workspace of tiles of {want} rays: {have} stay, and "
+                                      "gradients are summed in another order than in the saved stack")
             for k in sorted(self.n_params):
                 self.set_state(k, STATE_PARAMS, z[f"theta_{k}"])
                 self.set_state(k, STATE_ADAM_M, z[f"m_{k}"])

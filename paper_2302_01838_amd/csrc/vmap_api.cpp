@@ -1103,6 +1103,12 @@ static int state_ptr(vmap_ctx* c, int32_t k, int32_t which, size_t bytes, void**
 int vmap_get_state(vmap_ctx* c, int32_t k, int32_t which, void* host_dst, size_t bytes, void* stream) {
   if (!c) return VMAP_EINVAL;
   if (!host_dst) return c->fail(VMAP_EINVAL, "host_dst must not be NULL");
+  if (which == VMAP_STATE_TILES) {
+    const int32_t tiles[2] = {c->rays_per_tile, c->rays_per_tile_wide};
+    if (bytes != sizeof(tiles)) return c->fail(VMAP_EINVAL, "tiles are 8 bytes (int32 rays_per_tile, rays_per_tile_wide)");
+    std::memcpy(host_dst, tiles, sizeof(tiles));
+    return VMAP_OK;
+  }
   void* dev = nullptr;
   int rc = state_ptr(c, k, which, bytes, &dev);
   if (rc) return rc;
@@ -1134,6 +1140,39 @@ int vmap_set_state(vmap_ctx* c, int32_t k, int32_t which, const void* host_src, 
   if (e == hipSuccess && which == VMAP_STATE_PARAMS) e = restage_image(c, k, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return c->hip_fail(e, "writing state");
+  return VMAP_OK;
+}
+
+int vmap_set_tiles(vmap_ctx* c, int32_t rays_per_tile, int32_t rays_per_tile_wide, void* workspace_dev,
+                   size_t workspace_bytes, void* stream) {
+  if (!c) return VMAP_EINVAL;
+  if (!workspace_dev || ((uintptr_t)workspace_dev & 255))
+    return c->fail(VMAP_EINVAL, "workspace_dev must be a 256-byte aligned buffer");
+  vmap_config cfg = c->cfg;  // (both sizes as they are in force, so that neither follows the other)
+  cfg.rays_per_tile = rays_per_tile ? rays_per_tile : c->rays_per_tile;
+  cfg.rays_per_tile_wide = rays_per_tile_wide ? rays_per_tile_wide : c->rays_per_tile_wide;
+  if (const char* m = check_config(&cfg)) return c->fail(VMAP_EINVAL, m);
+  const WorkLayout wl = work_layout(&cfg);
+  if (workspace_bytes < wl.total)
+    return c->fail(VMAP_ECAPACITY, "workspace smaller than vmap_workspace_bytes for these tiles");
+  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+  hipError_t e = hipStreamSynchronize(s);  // nothing queued reads the present workspace or a graph
+  if (e != hipSuccess) return c->hip_fail(e, "hipStreamSynchronize");
+  for (auto& kv : c->graphs) {
+    if (kv.second.exec) (void)hipGraphExecDestroy(kv.second.exec);
+    if (kv.second.graph) (void)hipGraphDestroy(kv.second.graph);
+  }
+  c->graphs.clear();
+  c->cfg = cfg;
+  c->wl = wl;
+  c->work = reinterpret_cast<unsigned char*>(workspace_dev);
+  c->rays_per_tile = cfg.rays_per_tile;
+  c->rays_per_tile_wide = cfg.rays_per_tile_wide;
+  c->min_rays_per_tile = min_rays_per_tile(&cfg);
+  e = launch_fill_zero(workspace_dev, wl.total, s);
+  for (int k = 0; k < c->n_registered && e == hipSuccess; ++k) e = restage_image(c, k, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (e != hipSuccess) return c->hip_fail(e, "initialising the workspace");
   return VMAP_OK;
 }
 
