@@ -2295,7 +2295,7 @@ __device__ __forceinline__ bf16x8 tr_operand(const uint16_t* T, int kb, int cb, 
 // stores and read back as the next layer's operands.
 
 struct Lds128 {
-  int B_off, loss_off, dz_off, enc_off, buf_off, total;
+  int B_off, loss_off, lane_loss_off, dz_off, enc_off, buf_off, total;
 };
 constexpr int kS128 = 136;  // BF16 elements per staged sample of 128 features
 constexpr int kE128 = 40;   // ... of 32 encodings
@@ -2304,6 +2304,7 @@ __host__ __device__ constexpr Lds128 lds128() {
   int off = lds_layout(128, true, 1).B_off;  // the weight image's bytes
   L.B_off = off; off += 3 * kFeatures * 4;
   L.loss_off = off; off += 32;
+  L.lane_loss_off = off; off += 4 * kWave * 4;
   L.dz_off = off; off += pair_dz_bytes(true);
   L.enc_off = off; off += 64 * kE128 * 2;
   L.buf_off = off; off += 2 * 64 * kS128 * 2;
@@ -2334,6 +2335,8 @@ __global__ void __launch_bounds__(512, 2) k_step_128(const StepArgs a_in) {
   uint16_t* const buf0 = reinterpret_cast<uint16_t*>(smem + L.buf_off);
   uint16_t* const buf1 = buf0 + 64 * kS128;
   unsigned char* const dzt = smem + L.dz_off;
+  // wave 0's losses: lane l's of sub-tiles c, c + 4, ... at [c][l]
+  float* const lane_loss = reinterpret_cast<float*>(smem + L.lane_loss_off);
 
   for (int t = first_tile_of_block(blockIdx.x, gridDim.x, n_tiles); t < n_tiles; t += gridDim.x) {
     const int j = gen_object(a.width_start, a.n_objects, t);
@@ -2348,6 +2351,10 @@ __global__ void __launch_bounds__(512, 2) k_step_128(const StepArgs a_in) {
     const int rpt = tile_rays(H, a.rays_per_tile, a.rays_per_tile_wide);
     const RayRange rr = tile_ray_range(a.ray_offsets[j], a.ray_offsets[j + 1], ti, rpt, a.n_rays);
     const int ray_lo = rr.lo, ray_hi = rr.hi;
+    if (tid < kWave) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) lane_loss[c * kWave + tid] = 0.f;
+    }
     if (k != staged) {
       __syncthreads();
       fetch_image_lds(a.wimage + (size_t)k * a.wimage_stride, smem, W.B_off, lane_, wave, 8);
@@ -2376,7 +2383,6 @@ __global__ void __launch_bounds__(512, 2) k_step_128(const StepArgs a_in) {
     for (int l = 0; l < kLayers; ++l) accDb[l] = 0.f;
 #pragma unroll
     for (int c = 0; c < kOut; ++c) accDbH[c] = 0.f;
-    float wave_loss = 0.f;
     __builtin_amdgcn_s_waitcnt(0);  // this thread's part of the image is in LDS
     __syncthreads();
 
@@ -2481,7 +2487,9 @@ __global__ void __launch_bounds__(512, 2) k_step_128(const StepArgs a_in) {
           float unused;
           half_join(acc[0][c] + bh[c], acc[1][c] + bh[c], zs[c], unused);
         }
-        render_subtile<true>(a, r0, nslots, wseed, in.r, zs, dzs, wave_loss);
+        float loss = 0.f;
+        render_subtile<true>(a, r0, nslots, wseed, in.r, zs, dzs, loss);
+        lane_loss[(sub & 3) * kWave + lane] += loss;
         bf16x4 d4;
 #pragma unroll
         for (int c = 0; c < kOut; ++c) {
@@ -2609,8 +2617,12 @@ __global__ void __launch_bounds__(512, 2) k_step_128(const StepArgs a_in) {
       for (int c = 0; c < kOut; ++c) put(offh + c * H + ob * 32 + colfeat(16 * (wave & 1) + lane), accWh[c]);
     }
     if (wave == 0) {
-      wave_loss = wave_sum(wave_loss);
-      if (lane == 0) a.tile_loss[tile] = wave_loss;
+      // the loss in the order of k_step_coop, whose waves take every fourth sub-tile each, so that
+      // forward and step report the same sum
+      float loss = 0.f;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) loss += wave_sum(lane_loss[c * kWave + lane]);
+      if (lane == 0) a.tile_loss[tile] = loss;
 #pragma unroll
       for (int c = 0; c < kOut; ++c) {
         const float g = wave_sum(accDbH[c]);
