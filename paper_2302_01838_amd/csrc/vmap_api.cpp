@@ -376,9 +376,8 @@ int gen_work_rays(const vmap_ctx* c, int S) {
   return std::max(c->min_rays_per_tile, (kGenWorkRows + S - 1) / std::max(S, 1));
 }
 
-// rays_per_tile: of hidden-32 objects (0: the stack's).
 hipError_t enqueue_worklist(vmap_ctx* c, const vmap_batch* b, hipStream_t s,
-                            const BatchDev* bd = nullptr, int rays_per_tile = 0) {
+                            const BatchDev* bd = nullptr) {
   GenScan gen{};
   if (c->cfg.precision == VMAP_BF16 && generic_width(c->cfg.max_hidden)) {
     gen.rpw = std::max(1, kSlots / b->samples_per_ray);
@@ -388,7 +387,7 @@ hipError_t enqueue_worklist(vmap_ctx* c, const vmap_batch* b, hipStream_t s,
     gen.start[2] = reinterpret_cast<int32_t*>(c->work + c->wl.gws);
   }
   return launch_worklist(b->n_objects, b->n_rays_total, b->object_ids, b->ray_offsets,
-                         rays_per_tile > 0 ? rays_per_tile : c->rays_per_tile, c->rays_per_tile_wide, gen_work_rays(c, b->samples_per_ray),
+                         c->rays_per_tile, c->rays_per_tile_wide, gen_work_rays(c, b->samples_per_ray),
                          c->cfg.max_objects, c->desc(), c->scaler(), c->tile_start(), c->width_start(32), c->flags(),
                          c->t_next(), bd, gen, s);
 }
@@ -430,12 +429,13 @@ OptArgs make_opt_args(vmap_ctx* c, const vmap_batch* b, float* loss_out, float* 
   return a;
 }
 
-// Enqueue the tile kernel for every width group.
+// Enqueue the tile kernel for every width group. grid_tile: rays per tile that sizes the grid of the
+// hidden-32 objects, whose tiles the device descriptor gives (0: the stack's).
 int enqueue_tiles(vmap_ctx* c, const vmap_batch* b, int mode, const float* dloss, float* d_out,
                   float* rgb_out, float* occ_out, hipStream_t s, bool allow_timing,
-                  const BatchDev* bd = nullptr, int rays_per_tile = 0) {
+                  const BatchDev* bd = nullptr, int grid_tile = 0) {
   StepArgs a = make_step_args(c, b);
-  if (rays_per_tile > 0) a.rays_per_tile = rays_per_tile;  // as given to the work list
+  if (grid_tile > 0) a.rays_per_tile = grid_tile;
   a.bd = bd;
   a.dloss = dloss;
   a.out_depth = d_out;
@@ -443,8 +443,8 @@ int enqueue_tiles(vmap_ctx* c, const vmap_batch* b, int mode, const float* dloss
   a.out_occ = occ_out;
   a.use_scale = (mode == MODE_TRAIN && c->cfg.precision == VMAP_BF16) ? 1 : 0;
   const bool bf = c->cfg.precision == VMAP_BF16;
-  const int bound = (b->n_rays_total + c->min_rays_per_tile - 1) / c->min_rays_per_tile + b->n_objects;
-  int grid = bound;
+  const int least = std::min(c->min_rays_per_tile, a.rays_per_tile);
+  int grid = (b->n_rays_total + least - 1) / least + b->n_objects;
   if (c->grid_blocks > 0) grid = std::min(grid, c->grid_blocks);
   TimedLaunch tl{};
   const bool timed = allow_timing && c->timing;
@@ -909,6 +909,9 @@ static int render_scene(vmap_ctx* c, int32_t n_rays, const float* rays_o, const 
   a.S = S;
   a.max_objects = c->cfg.max_objects;
   a.max_pairs = max_pairs;
+  const int round = std::max(1, kSlots / S) * c->waves;
+  a.tile_low = scene_tile_low(round, max_pairs, c->wl.max_tiles - n_objects);
+  a.tile_longest = std::max(a.tile_low, kSceneRounds * round);
   a.occ_threshold = occ_threshold;
   a.t_min = (double)t_min;
   a.rays_o = rays_o;
@@ -944,15 +947,12 @@ static int render_scene(vmap_ctx* c, int32_t n_rays, const float* rays_o, const 
     hb.samples_per_ray = S;
     hb.object_ids = object_ids;
     hb.ray_offsets = a.ray_offsets;
-    // a forward tile leaves no partial and a ray's render does not depend on its tile: longer tiles
-    // than the training step's, which fetch an object's weights less often, while there are enough
-    // for two rounds of the 1024 workgroups that forward mode holds (76,800 rays, 50 objects, 117,000
-    // pairs: 121 us with tiles of 16 rays or of 64, a quarter of the weight fetches)
-    int rpt = c->rays_per_tile;
-    for (int i = 0; i < 2 && max_pairs / (2 * rpt) >= 2048; ++i) rpt *= 2;
-    e = enqueue_worklist(c, &hb, s, a.bd, rpt);
+    e = enqueue_worklist(c, &hb, s, a.bd);
     if (e != hipSuccess) return c->hip_fail(e, "worklist launch");
-    int rc = enqueue_tiles(c, &hb, MODE_FWD, nullptr, a.pair_depth, a.pair_rgb, a.pair_occ, s, false, a.bd, rpt);
+    // a workgroup for every tile that the device may choose: fewer than 2 kSceneTiles (and one per
+    // object) below the longest tile, or the longest tiles of max_pairs
+    const int grid_tile = std::max(a.tile_low, std::min(a.tile_longest, max_pairs / (2 * kSceneTiles)));
+    int rc = enqueue_tiles(c, &hb, MODE_FWD, nullptr, a.pair_depth, a.pair_rgb, a.pair_occ, s, false, a.bd, grid_tile);
     if (rc) return rc;
   }
   e = launch_scene(1, a, s);

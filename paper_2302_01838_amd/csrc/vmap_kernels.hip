@@ -713,6 +713,7 @@ __device__ __forceinline__ void read_batch(StepArgs& a) {
     a.n_objects = b->n_objects;
     a.n_rays = b->n_rays;
     a.S = b->S;
+    if (b->rays_per_tile > 0) a.rays_per_tile = b->rays_per_tile;
     a.object_ids = b->object_ids;
     a.ray_offsets = b->ray_offsets;
     a.rays_o = b->rays_o;
@@ -3099,6 +3100,7 @@ __global__ void __launch_bounds__(1024) k_worklist(int n_objects, int n_rays, co
   if (bd) {
     n_objects = bd->n_objects;
     n_rays = bd->n_rays;
+    if (bd->rays_per_tile > 0) rpt = bd->rays_per_tile;
     ids = bd->object_ids;
     offs = bd->ray_offsets;
   }
@@ -3762,7 +3764,8 @@ __global__ void __launch_bounds__(1024) k_scene_scan(const SceneArgs a, int nblk
     // one store of the whole descriptor: every field is written (the scratch holding it is not
     // cleared, and a field left out would be read as garbage); no targets or losses, point samples
     *a.bd = make_batch_dev(a.n_objects, a.S, min(total, a.max_pairs), a.object_ids, a.ray_offsets,
-                           a.pair_o, a.pair_d, a.pair_t, nullptr, nullptr, nullptr, nullptr, nullptr);
+                           a.pair_o, a.pair_d, a.pair_t, nullptr, nullptr, nullptr, nullptr, nullptr,
+                           scene_tile(a.tile_low, a.tile_longest, min(total, a.max_pairs)));
   }
 }
 
