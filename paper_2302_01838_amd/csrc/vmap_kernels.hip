@@ -5440,8 +5440,21 @@ hipError_t launch_generic(int mode, const GenArgs& g, int tiles_bound, int block
   // hidden 512 (8 objects, 192 workgroups: 262 / 255; 16, 384: 367 / 370); at hidden 1024 always: the
   // 128 x 128 blocks of one object all run on one XCD (1 object 263 / 306, 4 368 / 407, 16 1021 / 1059).
   // Hidden 256: 50 objects of 1,200 rows 318 / 318, of 4,800 941 / 980, 16 of 1,200 164 / 151.
+  // A workgroup of k_gen_wide holds a CU alone, so just past 256 of them a second round of nearly empty
+  // CUs takes as long as the first. Workgroups of evenly filled objects (the batch's own counts are on
+  // the device), wide against 128, render and step: hidden 512, 280 (28 objects of 1,200 rows) 160 / 151
+  // and 599 / 585, 304 (4 of 9,500) 165 / 142 and 536 / 512, 316 (one of 40,000) 184 / 162 and 511 / 484, 320
+  // (16 of 2,400) 162 / 147 and 536 / 528, 320 (32 of 1,200) 161 / 168 and 630 / 636, 346 (one of 44,000)
+  // 191 / 182 and 523 / 517, 402 (one of 51,200) 203 / 208 and 562 / 584; hidden 1024, 288 (8 of 2,260)
+  // 234 / 207 and 815 / 767, 320 (16 of 1,200) 242 / 231 and 982 / 983, 320 (20 of 1,000) 247 / 256 and
+  // 1109 / 1130, 360 (18 of 1,200) 250 / 260 and 1091 / 1112. The line lies at a quarter of the second
+  // round, for renders of up to 16 objects, whose 128-row blocks share weights more, at three eighths. In
+  // the third round the sides are within 5 % of each other either way.
   constexpr int kCUs = 256;
-  const bool wide = nw > 1 && (long long)blocks_bound * nw >= kCUs;
+  const long long rows = (long long)g.a.n_rays * g.a.S;
+  const long long even = ((rows / g.a.n_objects + kGenBlockRows - 1) / kGenBlockRows) * g.a.n_objects * nw;
+  const int second = !train && g.a.n_objects <= 16 ? 3 * kCUs / 8 : kCUs / 4;  // workgroups worth a second round
+  const bool wide = nw > 1 && (long long)blocks_bound * nw >= kCUs && !(even > kCUs && even < kCUs + second);
   const bool wide_dw = (nw >= 4 || (long long)work_bound * nw * nw * (kLayers - 1) >= kCUs);
   auto fwd_dx = [&](int kind, int ncols, int l) {
     if (wide && l > 0 && l < kLayers) {
