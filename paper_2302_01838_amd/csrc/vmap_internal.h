@@ -329,7 +329,7 @@ struct BatchDev {
   int32_t n_objects;
   int32_t S;
   int32_t n_rays;
-  int32_t rays_per_tile;  // of hidden-32 objects; 0: the launch's
+  int32_t rays_per_tile;  // of hidden-32 objects in forward mode; 0: the launch's
   const int32_t* object_ids;
   const int32_t* ray_offsets;
   const float* rays_o;

@@ -713,7 +713,6 @@ __device__ __forceinline__ void read_batch(StepArgs& a) {
     a.n_objects = b->n_objects;
     a.n_rays = b->n_rays;
     a.S = b->S;
-    if (b->rays_per_tile > 0) a.rays_per_tile = b->rays_per_tile;
     a.object_ids = b->object_ids;
     a.ray_offsets = b->ray_offsets;
     a.rays_o = b->rays_o;
@@ -1213,6 +1212,9 @@ template <int H, bool BF, int MODE>
 __global__ void __launch_bounds__((BF && H == 32) ? 512 : 256, 1) k_step_tiles(const StepArgs a_in) {
   StepArgs a = a_in;
   read_batch(a);
+  if constexpr (MODE == MODE_FWD) {
+    if (a.bd && a.bd->rays_per_tile > 0) a.rays_per_tile = a.bd->rays_per_tile;  // (a scene's)
+  }
   constexpr int MT = H / 32;
   constexpr bool TABLE = (MODE == MODE_STEP);  // tile table built here, not by k_worklist
   constexpr bool TRAIN = (MODE == MODE_TRAIN) || TABLE;
