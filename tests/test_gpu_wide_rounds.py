@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 import scenes
-from vmap_testlib import make_pair, same_state, snapshot
+from vmap_testlib import same_state, snapshot
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -28,7 +28,10 @@ def test_rows_of_one_and_two_rounds(hidden, rays, objects):
     n_rays[0] = 37
     runs = []
     for members in ([0], list(range(objects))):
-        objs, _ = make_pair(sc, "bf16", max_rays=sum(n_rays.values()))
+        objs = vm.ObjectSet(max_objects=objects, B=sc.B, hidden=hidden, precision="bf16",
+                            max_rays=sum(n_rays.values()), max_samples_per_ray=sc.S)
+        for ob in sc.objects:
+            objs.add(ob.norm_centre, ob.norm_scale, seed=ob.seed)
         db = vm.DeviceBatch(scenes.make_batch(sc, 0, object_ids=members, n_rays={k: n_rays[k] for k in members}))
         renders = [x[: n_rays[0]].cpu().numpy() for x in objs.render(db)]
         loss = objs.step(db).cpu().numpy()[:1]
