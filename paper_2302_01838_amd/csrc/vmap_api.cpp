@@ -422,6 +422,9 @@ OptArgs make_opt_args(vmap_ctx* c, const vmap_batch* b, float* loss_out, float* 
   a.bf16 = c->cfg.precision == VMAP_BF16;
   a.growth = c->cfg.scale_growth_interval;
   a.max_tiles = c->wl.max_tiles;
+  // an object of more tiles than that has more rays than as many of the smallest tiles hold
+  if (b->n_objects <= kSpreadObjects)
+    a.spread = (int)std::min<long long>(b->n_objects, b->n_rays_total / ((long long)kSpreadTiles * c->min_rays_per_tile + 1));
   a.img32 = c->img32();
   a.wimage = c->wimage();
   a.wimage_stride = (int64_t)c->wl.wimage_stride;

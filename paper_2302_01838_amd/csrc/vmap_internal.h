@@ -391,6 +391,10 @@ __host__ __device__ constexpr int scene_tile_low(int round, int max_pairs, int t
   return (least > 1 ? (least + round - 1) / round : 1) * round;
 }
 
+// Tiles of an object from which the optimiser spreads its partials over more workgroups, in batches
+// of at most kSpreadObjects objects (every workgroup of an extra row looks its object up among them).
+constexpr int kSpreadTiles = 64, kSpreadObjects = 256;
+
 // Arguments of the gradient / optimiser kernels.
 struct OptArgs {
   int n_objects;
@@ -422,6 +426,7 @@ struct OptArgs {
   int bf16;
   int growth;
   int max_tiles;              // tiles the workspace holds (bounds every tile range)
+  int spread;                 // bound on the batch's objects of more than kSpreadTiles tiles; 0 if not spread
   const BatchDev* bd;         // if not NULL, n_objects, ids, offs and loss_out come from here
 };
 

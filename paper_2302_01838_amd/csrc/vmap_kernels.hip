@@ -939,6 +939,7 @@ __device__ __forceinline__ void render_subtile(const StepArgs& a, int r0, int ns
 // each in tile order, then the quarters in order, so that a workgroup's waves can take a quarter
 // each (k_reduce_adam_wide). The order depends on the object's tile count alone.
 constexpr int kSplitTiles = 32;
+static_assert(kSpreadTiles >= kSplitTiles, "spread objects are summed in quarters");
 // Units of k_reduce_adam_wide of an object (at least one, for its loss).
 __device__ __forceinline__ int opt_units(int n_params, int tiles) {
   const int unit = tiles > kSplitTiles ? 256 : 1024;
@@ -979,6 +980,81 @@ __device__ __forceinline__ float tile_sum(const float* __restrict__ partial, int
   return ((g[0] + g[1]) + g[2]) + g[3];
 }
 
+// Sum of an object's tile losses in tile_sum's order, by a whole wave: 64 tiles (of many: of each
+// quarter) are read at once, one per lane, and added one after another from lane registers, the
+// quarters side by side (past a quarter's end zeros are added, which change no sum).
+__device__ __forceinline__ float loss_sum(const float* __restrict__ tile_loss, int t0, int t1) {
+  const int lane = threadIdx.x & 63;
+  auto from = [](float v, int l) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l)); };
+  float g[4] = {0.f, 0.f, 0.f, 0.f};
+  if (t1 - t0 <= kSplitTiles) {
+    const float x = t0 + lane < t1 ? tile_loss[t0 + lane] : 0.f;
+    for (int u = 0; u < t1 - t0; ++u) g[0] += from(x, u);
+    return g[0];
+  }
+  const int len = (t1 - t0 + 3) >> 2;
+  for (int b = 0; b < len; b += kWave) {
+    float x[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const TileRange q = tile_quarter(t0, t1, i);
+      x[i] = q.t0 + b + lane < q.t1 ? tile_loss[q.t0 + b + lane] : 0.f;
+    }
+    const int n = min(kWave, len - b);
+    for (int u = 0; u < n; ++u) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) g[i] += from(x[i], u);
+    }
+  }
+  return ((g[0] + g[1]) + g[2]) + g[3];
+}
+
+// Objects of many tiles (more than kSpreadTiles), in a kernel of a row of workgroups per object and a
+// thread per parameter: the CUs that a row runs on read its partials at some 6 bytes per cycle each,
+// however many loads are in flight, so the rows of such objects are spread over four times as many
+// workgroups. A workgroup of 256 parameters keeps the first 64 of them and three extra rows take the
+// others (OptArgs::spread of them, the host's bound on such objects), every wave a quarter of the tiles,
+// in tile_sum's order. The step of one object of 12,000 rays x 10 samples (BF16, 500 tiles): 56 us with
+// its row alone, 38 of them here; 34 spread. One of 5,000 rays x 20 beside fifty of 20: 44 and 34.
+// The s-th object of many tiles, or -1 (called by whole waves; four loads per lane at most).
+__device__ __forceinline__ int spread_object(const OptArgs& a, int s) {
+  const int lane = threadIdx.x & 63;
+  for (int base = 0; base < a.n_objects; base += kWave) {
+    const int j = base + lane;
+    bool many = false;
+    if (j < a.n_objects) {
+      const TileRange tr = clamp_tile_range(a.tile_start[j], a.tile_start[j + 1], a.max_tiles);
+      many = tr.t1 - tr.t0 > kSpreadTiles;
+    }
+    unsigned long long m = __ballot(many);
+    const int c = __popcll(m);
+    if (s < c) {
+      for (; s > 0; --s) m &= m - 1ull;
+      return base + __ffsll((long long)m) - 1;
+    }
+    s -= c;
+  }
+  return -1;
+}
+// Sum of an object's tile partials at 64 parameters, p the lane's (below p_stride), by a workgroup of
+// four waves; valid in wave 0.
+__device__ __forceinline__ float spread_sum(const float* __restrict__ partial, int p_stride, int t0, int t1, int p) {
+  __shared__ float part[4][kWave];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const TileRange q = tile_quarter(t0, t1, wave);
+  float g = 0.f;
+  for (int t = q.t0; t < q.t1; t += 32) {
+    float x[32];
+#pragma unroll
+    for (int u = 0; u < 32; ++u) x[u] = t + u < q.t1 ? partial[(size_t)(t + u) * p_stride + p] : 0.f;
+#pragma unroll
+    for (int u = 0; u < 32; ++u)
+      if (t + u < q.t1) g += x[u];
+  }
+  part[wave][lane] = g;
+  __syncthreads();
+  return ((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane];
+}
 
 __device__ __forceinline__ bool obj_valid(const OptArgs& a, int k) {
   return k >= 0 && k < a.max_objects && a.desc[k].registered;
@@ -1020,16 +1096,34 @@ __device__ void scaler_update(const OptArgs& a) {
   if (threadIdx.x == 0) count = 0;
   __syncthreads();
   int skipped = 0;
-  for (int jj = threadIdx.x; jj < a.n_objects; jj += blockDim.x) {
-    const int kk = a.ids[jj];
-    const int r0 = a.offs[jj], r1 = a.offs[jj + 1];
-    const TileRange tr = clamp_tile_range(a.tile_start[jj], a.tile_start[jj + 1], a.max_tiles);
-    const int t0 = tr.t0, t1 = tr.t1;
+  for (int base = 0; base < a.n_objects; base += blockDim.x) {
+    const int jj = base + (int)threadIdx.x;
+    int kk = -1, r0 = 0, r1 = 0, t0 = 0, t1 = 0;
+    if (jj < a.n_objects) {
+      kk = a.ids[jj];
+      r0 = a.offs[jj];
+      r1 = a.offs[jj + 1];
+      const TileRange tr = clamp_tile_range(a.tile_start[jj], a.tile_start[jj + 1], a.max_tiles);
+      t0 = tr.t0;
+      t1 = tr.t1;
+    }
     const bool in_range = kk >= 0 && kk < a.max_objects;
     const int kc = in_range ? kk : 0;
     const bool registered = a.desc[kc].registered != 0;
     // from the tiles: the objects' flags are being written by this launch
-    const int bad = a.tile_bad ? tile_or(a.tile_bad, t0, t1) : a.flags[kc];
+    int bad = 0;
+    if (a.tile_bad) {
+      const bool many = t1 - t0 > kSpreadTiles;
+      if (!many) bad = tile_or(a.tile_bad, t0, t1);
+      for (unsigned long long m = __ballot(many); m; m &= m - 1ull) {  // by the whole wave, in turn
+        const int l = __ffsll((long long)m) - 1, s1 = __builtin_amdgcn_readlane(t1, l);
+        int any = 0;
+        for (int t = __builtin_amdgcn_readlane(t0, l) + (int)(threadIdx.x & 63); t < s1; t += kWave) any |= a.tile_bad[t];
+        if (__ballot(any != 0) && (int)(threadIdx.x & 63) == l) bad = 1;
+      }
+    } else {
+      bad = a.flags[kc];
+    }
     if (in_range && registered && r1 > r0 && bad != 0) ++skipped;
   }
   if (skipped) atomicAdd(&count, skipped);
@@ -3174,23 +3268,37 @@ __global__ void __launch_bounds__(1024) k_worklist(int n_objects, int n_rays, co
   }
 }
 
+// SPREAD: with the extra rows of objects of many tiles (spread_object).
+template <bool SPREAD>
 __global__ void __launch_bounds__(256) k_reduce(const OptArgs a_in, int want_grad) {
   OptArgs a = a_in;
   read_batch(a);
-  const int j = blockIdx.y;
+  int j = blockIdx.y, part = 0;
+  if (SPREAD && j >= a.n_objects) {
+    part = 1 + (j - a.n_objects) % 3;
+    j = spread_object(a, (j - a.n_objects) / 3);
+    if (j < 0) return;
+  }
   const int k = a.ids[j];
   const bool valid = obj_valid(a, k) && a.scaler->batch_ok;
   const TileRange tr = clamp_tile_range(a.tile_start[j], a.tile_start[j + 1], a.max_tiles);
   const int t0 = tr.t0, t1 = tr.t1;
-  if (blockIdx.x == 0 && threadIdx.x == 0 && a.loss_out) {
-    a.loss_out[j] = valid ? tile_sum(a.tile_loss, 1, t0, t1, 0) : 0.f;
+  if (a.loss_out && part == 0 && blockIdx.x == gridDim.x - 1 && threadIdx.x < kWave) {  // (the fewest parameters)
+    const float loss = loss_sum(a.tile_loss, t0, t1);
+    if (threadIdx.x == 0) a.loss_out[j] = valid ? loss : 0.f;
   }
   if (!want_grad || !valid) return;
-  const int P = a.desc[k].n_params;
+  const int P = a.desc[k].n_params, hidden = a.desc[k].hidden;
+  const bool spread = SPREAD && t1 - t0 > kSpreadTiles;
   bool bad = false;
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
+  const int p = blockIdx.x * blockDim.x + (spread ? part * kWave + ((int)threadIdx.x & 63) : (int)threadIdx.x);
+  float sum = 0.f;
+  if (spread) {
+    sum = spread_sum(a.partial, a.p_stride, t0, t1, p < P ? padded_index(hidden, p) : 0);
+    if (threadIdx.x >= kWave) return;
+  }
   if (p < a.p_stride) {
-    const float g = (p < P) ? tile_sum(a.partial, a.p_stride, t0, t1, padded_index(a.desc[k].hidden, p)) : 0.f;
+    const float g = p >= P ? 0.f : spread ? sum : tile_sum(a.partial, a.p_stride, t0, t1, padded_index(hidden, p));
     bad = !isfinite(g);
     a.grad[(size_t)k * a.p_stride + p] = g;
     if (a.grad_out) a.grad_out[(size_t)j * a.p_stride + p] = g;
@@ -3226,15 +3334,22 @@ __global__ void __launch_bounds__(256) k_adam(const OptArgs a_in) {
 // store; the element test below is a guard that this bound makes unreachable. Every load of a thread depends on at most the batch object's id, ray
 // range and tile range, so a workgroup waits for device memory twice (those, then the object's
 // data); the validity checks only decide what is stored. Thread 0 works out the Adam
-// coefficients while the loads are in flight. The grid has one row of workgroups per batch object
-// and a last row whose first workgroup updates the loss scaler (its own chain of loads).
+// coefficients while the loads are in flight. The grid has one row of workgroups per batch object,
+// one whose first workgroup updates the loss scaler (its own chain of loads), and the extra rows of
+// objects of many tiles (spread_object).
+template <bool SPREAD>
 __global__ void __launch_bounds__(256) k_reduce_adam(const OptArgs a_in) {
   OptArgs a = a_in;
   read_batch(a);
-  const int j = blockIdx.y;
-  if (j == (int)gridDim.y - 1) {
+  int j = blockIdx.y, part = 0;
+  if (j == a.n_objects) {
     if (blockIdx.x == 0) scaler_update(a);
     return;
+  }
+  if (SPREAD && j > a.n_objects) {  // an extra row (spread_object)
+    part = 1 + (j - a.n_objects - 1) % 3;
+    j = spread_object(a, (j - a.n_objects - 1) / 3);
+    if (j < 0) return;
   }
   const int k = a.ids[j];
   const TileRange tr = clamp_tile_range(a.tile_start[j], a.tile_start[j + 1], a.max_tiles);
@@ -3246,23 +3361,29 @@ __global__ void __launch_bounds__(256) k_reduce_adam(const OptArgs a_in) {
   const int kc = in_range ? k : 0;  // loads of an id out of range are discarded
   const ObjDesc& d = a.desc[kc];
   const int registered = d.registered, n_params = d.n_params, hidden = d.hidden;
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
+  const bool spread = SPREAD && t1 - t0 > kSpreadTiles;
+  const int p = blockIdx.x * blockDim.x + (spread ? part * kWave + ((int)threadIdx.x & 63) : (int)threadIdx.x);
   const size_t i = (size_t)kc * a.p_stride + p;
   float th = 0.f, m = 0.f, v = 0.f, g = 0.f;
-  if (p < a.p_stride) {
+  // slot of p in the partials, which hold the kernel width's layout (hidden 16: padded to 32)
+  const int slot = (hidden == 16 && p < n_params) ? padded_index(16, p) : min(p, a.p_stride - 1);
+  const bool mine = p < a.p_stride && (!spread || threadIdx.x < kWave);
+  if (mine) {
     th = a.theta[i];
     m = a.m[i];
     v = a.v[i];
-    // the partials hold the kernel width's layout (hidden 16: padded to 32)
-    g = tile_sum(a.partial, a.p_stride, t0, t1, (hidden == 16 && p < n_params) ? padded_index(16, p) : p);
+    if (!spread) g = tile_sum(a.partial, a.p_stride, t0, t1, slot);
   }
-  const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
+  const bool lead = blockIdx.x == 0 && part == 0 && threadIdx.x == 0;
+  // the loss: a wave of the workgroup with the fewest parameters
+  const bool lossy = a.loss_out && part == 0 && blockIdx.x == gridDim.x - 1 && threadIdx.x < kWave;
   float loss = 0.f;
-  if (lead && a.loss_out) loss = tile_sum(a.tile_loss, 1, t0, t1, 0);
+  if (lossy) loss = loss_sum(a.tile_loss, t0, t1);
+  if (spread) g = spread_sum(a.partial, a.p_stride, t0, t1, slot);
   __shared__ float sh[2];
   if (threadIdx.x == 0) adam_coef_store(a, t, sh);
   const bool valid = in_range && registered != 0 && batch_ok;
-  if (lead && a.loss_out) a.loss_out[j] = valid ? loss : 0.f;
+  if (lossy && threadIdx.x == 0) a.loss_out[j] = valid ? loss : 0.f;
   if (!valid || r1 <= r0) return;
   // the barrier of object_bad also publishes the coefficients
   if (object_bad(a, j, k)) {
@@ -3270,7 +3391,7 @@ __global__ void __launch_bounds__(256) k_reduce_adam(const OptArgs a_in) {
     return;
   }
   const AdamCoef c = adam_coef_load(a, sh);
-  if (p < n_params) {
+  if (mine && p < n_params) {
     a.grad[i] = g;
     if (isfinite(g)) {
       adam_elem(c, g, th, m, v);
@@ -3345,7 +3466,10 @@ __global__ void __launch_bounds__(256, 4) k_reduce_adam_wide(const OptArgs a_in,
       const bool lead = u == first && tid == 0;
       __syncthreads();  // the previous object's coefficients have been read
       if (tid == 0) adam_coef_store(a, t, sh);
-      if (lead && a.loss_out) a.loss_out[j] = valid ? tile_sum(a.tile_loss, 1, t0, t1, 0) : 0.f;
+      if (u == first && wave == 0 && a.loss_out) {
+        const float loss = loss_sum(a.tile_loss, t0, t1);
+        if (tid == 0) a.loss_out[j] = valid ? loss : 0.f;
+      }
       live = valid && r1 > r0;
       // (the barrier of object_bad also publishes the coefficients)
       if (live && object_bad(a, j, k)) {
@@ -4122,13 +4246,25 @@ constexpr int kReduceWide = 32768;
 
 hipError_t launch_optimizer(int kind, const OptArgs& a, hipStream_t s) {
   if (a.n_objects <= 0) return hipSuccess;
-  const dim3 grid((a.p_stride + 255) / 256, a.n_objects);
-  if (kind == OPT_REDUCE) hipLaunchKernelGGL(k_reduce, grid, dim3(256), 0, s, a, 1);
-  else if (kind == OPT_LOSS) hipLaunchKernelGGL(k_reduce, dim3(1, a.n_objects), dim3(256), 0, s, a, 0);
+  const int narrow = (std::min(a.p_stride, round_up(n_params_of(32), 64)) + 255) / 256;
+  const dim3 grid(a.tile_bad ? narrow : (a.p_stride + 255) / 256, a.n_objects);
+  // rows that fill the chip (four workgroups on every CU) gain nothing from more of them
+  const int spread = (long long)grid.x * a.n_objects <= 1024 ? 3 * a.spread : 0;  // extra rows
+  auto reduce = [&](dim3 g, int want_grad) {
+    g.y += want_grad ? spread : 0;
+    if (spread && want_grad) hipLaunchKernelGGL(k_reduce<true>, g, dim3(256), 0, s, a, want_grad);
+    else hipLaunchKernelGGL(k_reduce<false>, g, dim3(256), 0, s, a, want_grad);
+  };
+  auto reduce_adam = [&]() {
+    const dim3 g(grid.x, a.n_objects + 1 + spread);
+    if (spread) hipLaunchKernelGGL(k_reduce_adam<true>, g, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(k_reduce_adam<false>, g, dim3(256), 0, s, a);
+  };
+  if (kind == OPT_REDUCE) reduce(grid, 1);
+  else if (kind == OPT_LOSS) reduce(dim3(1, a.n_objects), 0);
   else if (kind == OPT_ADAM) hipLaunchKernelGGL(k_adam, grid, dim3(256), 0, s, a);
   else if (a.tile_bad) {
-    const int blocks = (std::min(a.p_stride, round_up(n_params_of(32), 64)) + 255) / 256;
-    hipLaunchKernelGGL(k_reduce_adam, dim3(blocks, a.n_objects + 1), dim3(256), 0, s, a);
+    reduce_adam();
   } else if (a.p_stride >= kReduceWide && a.p_stride % 4 == 0) {
     if (!a.opt_start) return hipErrorInvalidValue;
     const int units = (a.p_stride + 1023) / 1024;  // of the widest object
@@ -4139,7 +4275,7 @@ hipError_t launch_optimizer(int kind, const OptArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(k_reduce_adam_wide, dim3((unsigned)blocks + 1), dim3(256), 0, s, a, rows);
   } else {
     if (a.wimage) return hipErrorInvalidValue;  // hidden-128 images are kept by the wide kernel
-    hipLaunchKernelGGL(k_reduce_adam, dim3(grid.x, a.n_objects + 1), dim3(256), 0, s, a);
+    reduce_adam();
   }
   return hipGetLastError();
 }
