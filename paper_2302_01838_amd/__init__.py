@@ -221,7 +221,8 @@ class ObjectSet:
             if self.tuned:
                 rays_per_tile = int(self.tuned["rays_per_tile"])
                 if (max_hidden or hidden) <= 32 and rays_per_tile > 0:
-                    rays_per_tile = fit_rays_per_tile(self.tuned, max_samples_per_ray, max_rays, max_objects)
+                    rays_per_tile = fit_rays_per_tile(self.tuned, max_samples_per_ray, max_rays, max_objects,
+                                                      precision)
         if rays_per_tile_wide == 0 and autotune and (max_hidden or hidden) > 32:
             from .tune import lookup
             wide = lookup(max_hidden or hidden, max_samples_per_ray, precision)

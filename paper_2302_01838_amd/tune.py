@@ -5,7 +5,7 @@ fastest per (GPU arch, hidden width, samples per ray, precision) in ``tune_cache
 this file; ``ObjectSet`` reads the cache when it is created without an explicit shape.
 
 Shapes: rays per tile of the hidden-32 tile kernel (fixed when an object stack is created) with
-waves per workgroup, or, for workloads with wider models, rays per tile of the cooperative kernel
+waves per workgroup, or, for workloads with wider models, rays per tile of the wider objects
 (``rays_per_tile_wide``, whole rounds of four sub-tiles). Each shape is timed the way the
 benchmark times a step: pre-generated batches resident on the device, plain launches, HIP events
 around every step; the figure is the median per-step time over ``steps`` steps after a warmup,
@@ -54,21 +54,25 @@ def lookup(hidden: int, S: int, precision: str, arch: Optional[str] = None,
     return cache.get(_key(arch, hidden, S, precision))
 
 
-def fit_rays_per_tile(entry: dict, S: int, max_rays: int, max_objects: int) -> int:
+def fit_rays_per_tile(entry: dict, S: int, max_rays: int, max_objects: int,
+                      precision: Optional[str] = None) -> int:
     """Rays per tile for a stack of this capacity, from the tuned entry of the hidden-32 kernel.
 
     A tile is whole rounds of the tuned workgroup (a sub-tile of floor(64 / S) rays for each wave),
     and the step lasts as long as the most rounds a workgroup slot of the chip gets. So: the fewest
-    rounds whose tiles at full capacity all run at once (512 slots; an object's last tile is half
-    empty on average), up to a third more than the tuned tile; the tuned tile if none fits. 50
+    rounds whose tiles at full capacity all run at once (an object's last tile is half empty on
+    average), up to a third more than the tuned tile; the tuned tile if none fits. Slots: a CU holds
+    eight waves of the kernel in BF16 and four in FP32 (registers), and two workgroups at most
+    (LDS): 512 for the tuned four waves in BF16 and two in FP32, taken where no precision is given. 50
     objects of 60 to 600 rays at S = 20 (tuned: 36 rays): 18,132 rays are 530 tiles of 36, 55.0 us
     per step in BF16 and 224 us in FP32, against 46.8 us with 48 rays and 182 us or less with 42."""
     tuned, waves = int(entry["rays_per_tile"]), int(entry["waves"])
     if max_objects < 1 or max_rays < 1:
         return tuned
+    slots = 512 if precision is None else 256 * min(2, max(1, (8 if precision == "bf16" else 4) // waves))
     rnd = max(1, 64 // S) * waves
     for m in range(1, -(-tuned * 4 // (3 * rnd)) + 1):
-        if -(-max_rays // (rnd * m)) + max_objects // 2 <= 512:
+        if -(-max_rays // (rnd * m)) + max_objects // 2 <= slots:
             return rnd * m
     return tuned
 
@@ -114,7 +118,7 @@ def tune(workload: str = "k50_uneven", precision: str = "bf16", steps: int = 100
         rpts = list(rays_per_tile) or sorted({rpw * m for m in (8, 10, 12, 14, 16, 20, 28)})
         ws = list(waves) or ([4, 8] if precision == "bf16" else [1, 2, 4])
         shapes = [(r, 0, w) for r in rpts for w in ws]
-    else:  # wider models: rays per cooperative tile, in whole rounds of four sub-tiles
+    else:  # wider models: rays per tile of the wider objects, in whole rounds of four sub-tiles
         rnd = 4 * rpw
         cur = lookup(32, S, precision, path=path) or {}
         rpt32 = int(cur.get("rays_per_tile", 0))
