@@ -143,9 +143,13 @@ __host__ __device__ constexpr int pair_tile_bytes(bool bf16) { return 32 * 36 * 
 
 // Every offset except `total` is independent of the wave count, so kernels evaluate the layout at
 // compile time (immediate LDS offsets) and only the host needs `total`.
-// Copies of the tile's gradient in the width-32 tile kernel's end-of-tile reduction: wave w adds
-// into copy w mod copies, and the partial is the copies' sum in order.
+// Copies of the tile's gradient in the width-32 tile kernel's end-of-tile reduction: wave w's gradient
+// is added into copy w mod red_copies, and the partial is the copies' sum in order. (Four waves add in
+// that order too, from a copy each.)
 __host__ __device__ constexpr int red_copies(int nwaves) { return nwaves >= 8 ? 4 : (nwaves >= 2 ? 2 : 1); }
+
+// ... of which in the scratch space: four waves write a copy each, the fourth over the weights.
+__host__ __device__ constexpr int scratch_copies(int nwaves) { return nwaves == 4 ? 3 : red_copies(nwaves); }
 
 constexpr int kRedCopyBytes = (n_params_of(32) + 3) / 4 * 16;
 
@@ -183,9 +187,8 @@ __host__ __device__ constexpr LdsLayout lds_layout(int H, bool bf16, int nwaves)
   L.scratch_wave = round_up(pair_dz_bytes(bf16) + pair_tiles(bf16) * pair_tile_bytes(bf16), 16);
   L.scratch_off = off;
   int scratch = nwaves * L.scratch_wave;
-  // the tile's gradient at the end: red_copies(nwaves) copies, each summing a fixed set of waves
-  // (four waves: a copy each, the fourth over the weights)
-  const int red = (nwaves == 4 ? 3 : red_copies(nwaves)) * round_up(n_params_of(H), 4) * 4;
+  // the tile's gradient at the end: scratch_copies(nwaves) copies, each summing a fixed set of waves
+  const int red = scratch_copies(nwaves) * round_up(n_params_of(H), 4) * 4;
   if (red > scratch) scratch = red;
   off = round_up(off + scratch, 16);
   L.total = off;

@@ -1757,6 +1757,7 @@ __global__ void __launch_bounds__((BF && H == 32) ? 512 : 256, 1) k_step_tiles(c
     // waves write them, the others then add theirs in turn (copy c = waves c, c + nc, ..., in that
     // order), and the partial is the sum of the copies in order: the same sum for four waves.
     constexpr int kRedWords = kRedCopyBytes / 4;
+    static_assert(kRedCopyBytes <= L.B_off, "the fourth copy ends before the encoding matrix, which is loaded once");
     const bool four = (nw == 4);
     const int nc = four ? 4 : red_copies(nw);
     float* red0 = reinterpret_cast<float*>(smem + L.scratch_off);
