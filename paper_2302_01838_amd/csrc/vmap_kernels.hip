@@ -356,13 +356,12 @@ __device__ __forceinline__ void stage_weights(const float* __restrict__ th, unsi
 // ---------------------------------------------------------------------------------------------
 // Forward of one 32-sample pass for the calling wave. xt: this lane's normalised point (the
 // sample of column n = lane & 31; both lane halves hold the same point); Bm: the encoding matrix.
-// ENC = false: the encoding is already in A.v[0] (kept from an earlier pass; xt unused).
 // ipe: xt[3] holds the sample's variance in the object frame; each feature is its expectation
 // under the isotropic Gaussian (integrated positional encoding). Fills the activations
 // and, with WITH_HEAD, returns the four output pre-activations z of sample n (valid in both lane
 // halves).
 
-template <int H, bool BF, bool WITH_HEAD, bool ENC = true>
+template <int H, bool BF, bool WITH_HEAD>
 __device__ __forceinline__ void forward_pass(const float xt[4], const unsigned char* smem,
                                              const float* Bm, Acts<H, BF>& A, float z[4],
                                              bool ipe = false) {
@@ -374,9 +373,8 @@ __device__ __forceinline__ void forward_pass(const float xt[4], const unsigned c
   const int lane = threadIdx.x & 63, n = lane & 31, hf = lane >> 5;
   // Gaussian Fourier features: register r of block 0 holds feature rowof(r, hf):
   // r = 0..3 sin(phi[4hf + r]), 4..7 sin(phi[8 + 4hf + r - 4]), 8..15 the cosines.
-  // Without ENC the caller has already placed them in A.v[0].
 #pragma unroll
-  for (int g = 0; g < (ENC ? 2 : 0); ++g) {
+  for (int g = 0; g < 2; ++g) {
 #pragma unroll
     for (int i = 0; i < 4; i += 2) {  // two features at a time: one packed pair per half
       float s[2], c[2];
