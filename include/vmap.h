@@ -148,7 +148,8 @@ size_t vmap_state_bytes(const vmap_config* cfg);
  * config.max_objects objects: tile partial gradients, work lists, weight images (hidden 16 and
  * 32, one per object slot in either precision; hidden 128 in VMAP_BF16: the training kernels read
  * them) and, when max_hidden is a layered-path width, every sample's activations and deltas for
- * max_rays rays of max_samples_per_ray samples, and a BF16 copy of each object slot's parameters.
+ * max_rays rays of max_samples_per_ray samples (18 max_hidden bytes a sample; 14 where that would pass
+ * 64 GiB, at some speed), and a BF16 copy of each object slot's parameters.
  * Returns 0 for an invalid config. Host only. */
 size_t vmap_workspace_bytes(const vmap_config* cfg);
 

@@ -38,6 +38,7 @@ struct WorkLayout {
   size_t gts, gbs, gws, gen_loss, gact, gdelta, gz, gdz;
   int max_gen_tiles, max_gen_blocks;
   int64_t gen_ld, gen_rows;
+  int gen_deltas;  // delta buffers
 };
 
 bool hidden_ok(int H, int precision) { return tiles_supported(H, precision == VMAP_BF16) != 0; }
@@ -180,8 +181,8 @@ WorkLayout work_layout(const vmap_config* c) {
     w.gws = off; off = align256(off + ((size_t)c->max_objects + 1) * 4);
     w.gen_loss = off; off = align256(off + (size_t)w.max_gen_tiles * 4);
     w.gact = off; off = align256(off + (size_t)(kLayers + 1) * layer);
-    // deltas: a buffer per layer
-    w.gdelta = off; off = align256(off + kLayers * layer);
+    w.gen_deltas = layered_deltas(layer);
+    w.gdelta = off; off = align256(off + w.gen_deltas * layer);
     w.gz = off; off = align256(off + (size_t)w.gen_rows * kOut * 4);
     w.gdz = off; off = align256(off + (size_t)w.gen_rows * kOut * 4);
   }
@@ -376,12 +377,19 @@ int gen_work_rays(const vmap_ctx* c, int S) {
   return std::max(c->min_rays_per_tile, (kGenWorkRows + S - 1) / std::max(S, 1));
 }
 
-hipError_t enqueue_worklist(vmap_ctx* c, const vmap_batch* b, hipStream_t s,
+// Whether the layered products of a training (or forward) chain of width H run in k_gen_chain.
+bool runs_chain(const vmap_ctx* c, int H, bool train) {
+  return gen_chain(H) && (!train || c->wl.gen_deltas == kLayers);
+}
+
+// train: for the tiles of a training step or backward pass.
+hipError_t enqueue_worklist(vmap_ctx* c, const vmap_batch* b, bool train, hipStream_t s,
                             const BatchDev* bd = nullptr) {
   GenScan gen{};
   if (c->cfg.precision == VMAP_BF16 && generic_width(c->cfg.max_hidden)) {
     gen.rpw = std::max(1, kSlots / b->samples_per_ray);
     gen.S = b->samples_per_ray;
+    gen.chain = runs_chain(c, c->gen_width, train);
     gen.start[0] = reinterpret_cast<int32_t*>(c->work + c->wl.gts);
     gen.start[1] = reinterpret_cast<int32_t*>(c->work + c->wl.gbs);
     gen.start[2] = reinterpret_cast<int32_t*>(c->work + c->wl.gws);
@@ -496,6 +504,8 @@ int enqueue_tiles(vmap_ctx* c, const vmap_batch* b, int mode, const float* dloss
       g.act = reinterpret_cast<uint16_t*>(c->work + c->wl.gact);
       const size_t layer = (size_t)c->wl.gen_rows * (size_t)c->wl.gen_ld;
       g.delta = reinterpret_cast<uint16_t*>(c->work + c->wl.gdelta);
+      g.deltas = c->wl.gen_deltas;
+      g.chain = runs_chain(c, H, mode == MODE_TRAIN);
       g.z = reinterpret_cast<float*>(c->work + c->wl.gz);
       g.dz = reinterpret_cast<float*>(c->work + c->wl.gdz);
       g.ld = c->wl.gen_ld;
@@ -583,7 +593,7 @@ int enqueue_train(vmap_ctx* c, const vmap_batch* b, float* loss_out, hipStream_t
                   const BatchDev* bd = nullptr) {
   if (int rc = enqueue_debug(c, b, s, bd)) return rc;
   if (table_in_tiles(c, b)) return enqueue_step(c, b, loss_out, s, allow_timing, bd);
-  hipError_t e = enqueue_worklist(c, b, s, bd);
+  hipError_t e = enqueue_worklist(c, b, true, s, bd);
   if (e != hipSuccess) return c->hip_fail(e, "worklist launch");
   int rc = enqueue_tiles(c, b, MODE_TRAIN, nullptr, nullptr, nullptr, nullptr, s, allow_timing, bd);
   if (rc) return rc;
@@ -851,7 +861,7 @@ int vmap_forward(vmap_ctx* c, const vmap_batch* b, float* loss_out, float* depth
   if (b->n_objects == 0) return VMAP_OK;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   if ((rc = enqueue_debug(c, b, s))) return rc;
-  hipError_t e = enqueue_worklist(c, b, s);
+  hipError_t e = enqueue_worklist(c, b, false, s);
   if (e != hipSuccess) return c->hip_fail(e, "worklist launch");
   rc = enqueue_tiles(c, b, MODE_FWD, nullptr, depth_out, rgb_out, occ_out, s, true);
   if (rc) return rc;
@@ -950,7 +960,7 @@ static int render_scene(vmap_ctx* c, int32_t n_rays, const float* rays_o, const 
     hb.samples_per_ray = S;
     hb.object_ids = object_ids;
     hb.ray_offsets = a.ray_offsets;
-    e = enqueue_worklist(c, &hb, s, a.bd);
+    e = enqueue_worklist(c, &hb, false, s, a.bd);
     if (e != hipSuccess) return c->hip_fail(e, "worklist launch");
     // a workgroup for every tile that the device may choose: fewer than 2 kSceneTiles (and one per
     // object) below the longest tile, or the longest tiles of max_pairs
@@ -1007,7 +1017,7 @@ int vmap_backward(vmap_ctx* c, const vmap_batch* b, const float* dloss, float* g
   if (b->n_objects == 0) return VMAP_OK;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   if ((rc = enqueue_debug(c, b, s))) return rc;
-  hipError_t e = enqueue_worklist(c, b, s);
+  hipError_t e = enqueue_worklist(c, b, true, s);
   if (e != hipSuccess) return c->hip_fail(e, "worklist launch");
   rc = enqueue_tiles(c, b, MODE_TRAIN, dloss, nullptr, nullptr, nullptr, s, true);
   if (rc) return rc;

@@ -262,6 +262,17 @@ __host__ __device__ constexpr bool generic_width(int H) {
 // Layered widths whose products, forward and back, run in one launch (k_gen_chain).
 __host__ __device__ constexpr bool gen_chain(int H) { return H == 256; }
 
+// Buffers of a layered stack's deltas, `layer` bytes each beside kLayers + 1 of activations: one for
+// every layer, so that all weight gradients run in one launch after the backward (and hidden 256's
+// backward in one launch); or two taken in turn, each layer's weight gradient launched before its deltas
+// are written over. Two buffers cost time (steps of 60,000 rows: hidden 256 301 us with four and 423
+// with two, 512 852 and 937, 1024 2,627 and 2,806), four cost memory, which the largest stacks do not
+// have: those whose nine layers pass 64 GiB (3.7 million rows at hidden 1024, 14.9 at 256) take two, so
+// that no stack gives more than 14 GiB for the speed.
+__host__ __device__ constexpr int layered_deltas(size_t layer) {
+  return (2 * kLayers + 1) * layer <= ((size_t)64 << 30) ? kLayers : 2;
+}
+
 
 // Width of the fused kernels that run an object of width H: hidden 16 runs in the width-32
 // kernels with its weights zero-padded to 32 units (the padded units' pre-activations are exactly
@@ -497,13 +508,15 @@ struct GenArgs {
   int32_t* gts;          // [n_objects + 1] first row tile of each batch object
   float* gen_loss;       // [max_gen_tiles] loss per row tile
   uint16_t* act;         // BF16 [kLayers + 1][rows][ld]: encoding (32 wide), then h_1 .. h_4
-  uint16_t* delta;       // BF16 [kLayers][rows][ld]: back-propagated deltas (gen_delta_out)
+  uint16_t* delta;       // BF16 [deltas][rows][ld]: back-propagated deltas (gen_delta_out)
+  int deltas;            // kLayers, or 2 taken in turn (layered_deltas)
   float* z;              // [rows][4] output pre-activations
   float* dz;             // [rows][4] their adjoints (times the seed's scale)
+  bool chain;            // k_gen_chain runs the products (gen_chain widths, a buffer for every layer's deltas)
   int64_t ld;            // elements per row of act and delta
   int64_t layer_elems;   // elements per layer of act
   int max_gen_blocks;    // 256-row blocks the block table holds
-  int32_t* gbs;          // [n_objects + 1] first 256-row block (gen_chain: pair of row tiles) of each batch object
+  int32_t* gbs;          // [n_objects + 1] first 256-row block (chain: pair of row tiles) of each batch object
   int work_rays;         // rays per work tile of this chain's objects (the work list's)
   int32_t* gws;          // [n_objects + 1] first work tile of each batch object among this chain's
                          // work tiles (the chain's objects' tiles, counted alone)
@@ -578,10 +591,12 @@ struct SceneArgs {
   int32_t* id_out;
 };
 
-// Layered-path scans of a work list: start[0] row tiles (rpw rays each), start[1] product blocks,
-// start[2] work tiles, [n_objects + 1] each; NULL where the stack holds no layered width.
+// Layered-path scans of a work list: start[0] row tiles (rpw rays each), start[1] product blocks (chain:
+// pairs of row tiles for gen_chain widths), start[2] work tiles, [n_objects + 1] each; NULL where the
+// stack holds no layered width.
 struct GenScan {
   int rpw, S;
+  bool chain;
   int32_t* start[3];
 };
 

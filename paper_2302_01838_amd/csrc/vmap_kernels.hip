@@ -3225,8 +3225,9 @@ __global__ void __launch_bounds__(1024) k_worklist(int n_objects, int n_rays, co
       if constexpr (GEN) {
         if (valid && !any_bad && generic_width(hidden) && o1 > o0) {
           cnt[5] = tiles_of(o1 - o0, gen.rpw);
-          cnt[6] = gen_chain(hidden) ? (cnt[5] + 1) / 2
-                                     : (int)(((long long)(o1 - o0) * gen.S + kGenBlockRows - 1) / kGenBlockRows);
+          cnt[6] = gen.chain && gen_chain(hidden)
+                       ? (cnt[5] + 1) / 2
+                       : (int)(((long long)(o1 - o0) * gen.S + kGenBlockRows - 1) / kGenBlockRows);
           cnt[7] = cnt[0];
         }
       }
@@ -4329,8 +4330,10 @@ hipError_t launch_init_scaler(ScalerState* sc, float scale, hipStream_t s) {
 // Weight gradients (k_gen_dw, k_gen_dw_small): rows = outputs, n = inputs, k = samples;
 // A = delta^T, B = h_l^T, both staged as the sample rows lie and read transposed.
 
-// Buffer of the deltas at layer m's outputs (m = 0..3).
-__device__ __forceinline__ uint16_t* gen_delta_out(const GenArgs& g, int m) { return g.delta + m * g.layer_elems; }
+// Buffer of the deltas at layer m's outputs (m = 0..3): each layer's own, or two in turn.
+__device__ __forceinline__ uint16_t* gen_delta_out(const GenArgs& g, int m) {
+  return g.delta + (m & (g.deltas - 1)) * g.layer_elems;
+}
 
 struct GenTile {
   int j, k, lo, hi;  // batch object, object id, rays [lo, hi)
@@ -4795,16 +4798,16 @@ __device__ __forceinline__ void gen_loss_block(const GenArgs& g, int b) {
 }
 
 // Weight gradients of the first layer (64 x 64 blocks, too few to fill the chip: 24 us of a launch
-// of their own at 50 objects of 1,200 rows, hidden 256), of the square layers in 128 x 128 blocks
-// (n1 > 0), and the losses (5 us of a launch): n0 and n1 workgroups, nb0 and nb1 to a work tile, and
-// the rest. That step's launches took 98 us apart, 82 in one.
-__global__ void __launch_bounds__(256) k_gen_dw(const GenArgs g_in, int n0, int nb0, int n1, int nb1) {
+// of their own at 50 objects of 1,200 rows, hidden 256), of square layers l .. l + nl - 1 in 128 x 128
+// blocks (n1 > 0), and the losses (5 us of a launch): n0 and n1 workgroups, nb0 and nb1 to a work tile,
+// and the rest. That step's launches took 98 us apart, 82 in one.
+__global__ void __launch_bounds__(256) k_gen_dw(const GenArgs g_in, int n0, int nb0, int n1, int nb1, int l, int nl) {
   GenArgs g = g_in;
   read_batch(g.a);
   __shared__ __attribute__((aligned(16))) uint16_t lds[2 * dw_tile<128>];
   const int b = (int)blockIdx.x;
   if (b < n0) gen_dw_block<64>(g, b, 0, nb0, 1, lds);
-  else if (b < n0 + n1) gen_dw_block<128>(g, b - n0, 1, nb1, kLayers - 1, lds);
+  else if (b < n0 + n1) gen_dw_block<128>(g, b - n0, l, nb1, nl, lds);
   else gen_loss_block(g, b - n0 - n1);
 }
 
@@ -5543,14 +5546,14 @@ __global__ void __launch_bounds__(512, 2) k_gen_chain(const GenArgs g_in) {
           acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
               w, *reinterpret_cast<const bf16x8*>(D + (32 * s + n) * P + 64 * c + 16 * kc + 8 * hf), acc[s], 0, 0, 0);
       }
-      if (c == 0) store_rows(D, gen_delta_out(g, l));  // the layer's own deltas, for its weight gradient
+      if (c == 0) store_rows(D, g.delta + l * g.layer_elems);  // the layer's own deltas, for its weight gradient
       if (i + 1 < kChunks) put_chunk(i + 1);
       __syncthreads();  // (after the last chunk: the deltas have been read)
     }
     put_delta(acc, l - 1);
     __syncthreads();
   }
-  store_rows(D, gen_delta_out(g, 0));
+  store_rows(D, g.delta);
 }
 
 hipError_t launch_generic(int mode, const GenArgs& g, int tiles_bound, int blocks_bound, int work_bound,
@@ -5608,14 +5611,22 @@ hipError_t launch_generic(int mode, const GenArgs& g, int tiles_bound, int block
     }
   };
   const int nloss = blocks(g.a.n_objects, 4);
-  auto launch_dw = [&]() {  // every layer's weight gradients, from the deltas of all layers, and the losses
-    if (wide_dw) hipLaunchKernelGGL(k_gen_wide<GEN_DW>, grid1(work_bound * (kLayers - 1), nw * nw), dim3(512), 0, s, g, 0);
-    const int nb0 = blocks(H, 64) * blocks(kEnc, 64), nb1 = wide_dw ? 0 : blocks(H, 128) * blocks(H, 128) * (kLayers - 1);
+  const int dw_blocks = blocks(H, 128) * blocks(H, 128);  // 128 x 128 blocks of a square layer
+  auto launch_dw_layer = [&](int l) {  // a square layer's weight gradient alone
+    const int n1 = (int)grid1(work_bound, dw_blocks).x;
+    hipLaunchKernelGGL(k_gen_dw, dim3(n1), dim3(256), 0, s, g, 0, 1, n1, dw_blocks, l, 1);
+  };
+  // every layer's weight gradients, from the deltas of all layers, and the losses; square = false: those
+  // of the square layers have been launched
+  auto launch_dw = [&](bool square) {
+    if (wide_dw && square) hipLaunchKernelGGL(k_gen_wide<GEN_DW>, grid1(work_bound * (kLayers - 1), nw * nw), dim3(512), 0, s, g, 0);
+    const int nb0 = blocks(H, 64) * blocks(kEnc, 64), nb1 = wide_dw || !square ? 0 : dw_blocks * (kLayers - 1);
     const int n0 = (int)grid1(work_bound, nb0).x, n1 = (int)grid1(work_bound, nb1).x;
-    hipLaunchKernelGGL(k_gen_dw, dim3(n0 + n1 + nloss), dim3(256), 0, s, g, n0, nb0, n1, nb1);
+    hipLaunchKernelGGL(k_gen_dw, dim3(n0 + n1 + nloss), dim3(256), 0, s, g, n0, nb0, n1, nb1, 1, kLayers - 1);
     hipLaunchKernelGGL(k_gen_dw_small, grid1(work_bound, blocks(H, 32)), dim3(kGenDwWaves * 64), 0, s, g, blocks(H, 32));
   };
-  if (gen_chain(H)) {
+  if (g.chain) {
+    if (!gen_chain(H) || (train && g.deltas != kLayers)) return hipErrorInvalidValue;
     static int allowed[2] = {0, 0};
     const void* fn = train ? reinterpret_cast<const void*>(k_gen_chain<true>) : reinterpret_cast<const void*>(k_gen_chain<false>);
     const hipError_t e = allow_lds(fn, lds_chain().total, &allowed[train]);
@@ -5624,7 +5635,7 @@ hipError_t launch_generic(int mode, const GenArgs& g, int tiles_bound, int block
     const dim3 grid = grid1((tiles_bound + g.a.n_objects) / 2 + 1, 1);
     if (train) hipLaunchKernelGGL(k_gen_chain<true>, grid, dim3(512), lds_chain().total, s, g);
     else hipLaunchKernelGGL(k_gen_chain<false>, grid, dim3(512), lds_chain().total, s, g);
-    if (train) launch_dw();
+    if (train) launch_dw(true);
     else hipLaunchKernelGGL(k_gen_loss, dim3(nloss), dim3(256), 0, s, g);
     return hipGetLastError();
   }
@@ -5634,8 +5645,12 @@ hipError_t launch_generic(int mode, const GenArgs& g, int tiles_bound, int block
   else hipLaunchKernelGGL(k_gen_render<false>, dim3(wave_blocks), dim3(256), 0, s, g);
   if (!train) hipLaunchKernelGGL(k_gen_loss, dim3(nloss), dim3(256), 0, s, g);
   if (train) {
-    for (int l = kLayers; l > 0; --l) fwd_dx(GEN_DX, H, l);
-    launch_dw();
+    const bool turns = g.deltas != kLayers;
+    for (int l = kLayers; l > 0; --l) {
+      fwd_dx(GEN_DX, H, l);  // writes the deltas of layer l - 1's outputs over those of l + 1's
+      if (turns && l > 1) launch_dw_layer(l - 1);
+    }
+    launch_dw(!turns);
   }
   return hipGetLastError();
 }
