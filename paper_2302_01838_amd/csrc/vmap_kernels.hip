@@ -3770,8 +3770,9 @@ __device__ __forceinline__ bool scene_pair_valid(const SceneArgs& a, int j, int&
 
 // Whether the ray (o, d; inv = 1 / d) certainly misses the box c +- s after t_min, in FP32: the
 // interval widened by more than the rounding of its ends (each is a difference of values up to
-// |c| + s + |o| times inv, a few roundings of 2^-24 of that; widened by 2^-19). Zero direction
-// components and NaN or infinite values are never certain.
+// |c| + s + |o| times inv, a few roundings of 2^-24 of that; widened by 2^-19), and in the sum and the
+// product by 1e-37, where values so small that FP32 holds them to fewer digits, or not at all, round
+// by more. Zero direction components and NaN or infinite values are never certain.
 __device__ __forceinline__ bool scene_certain_miss(const float o[3], const float inv[3], const float4& box,
                                                    float t_min) {
   const float cc[3] = {box.x, box.y, box.z}, s = box.w;
@@ -3780,7 +3781,7 @@ __device__ __forceinline__ bool scene_certain_miss(const float o[3], const float
   for (int a = 0; a < 3; ++a) {
     const float c = cc[a];
     const float ta = (c - s - o[a]) * inv[a], tb = (c + s - o[a]) * inv[a];
-    const float e = (fabsf(c) + s + fabsf(o[a])) * fabsf(inv[a]) * 0x1p-19f;
+    const float e = (fabsf(c) + s + fabsf(o[a]) + 1e-37f) * fabsf(inv[a]) * 0x1p-19f + 1e-37f;
     t0 = fmaxf(t0, fminf(ta, tb) - e);
     t1 = fminf(t1, fmaxf(ta, tb) + e);
   }
@@ -3803,7 +3804,7 @@ __global__ void __launch_bounds__(256) k_scene_count(const SceneArgs a, int nblk
     const bool valid = scene_pair_valid(a, j0 + tid, k);
     const ObjDesc& od = a.desc[valid ? k : 0];
     box[tid] = make_float4((float)od.centre[0], (float)od.centre[1], (float)od.centre[2],
-                           valid ? 1.0f / (float)od.inv_scale : -1.0f);
+                           valid ? (float)(1.0 / od.inv_scale) : -1.0f);
     cnt[tid] = 0;
   }
   float o[3] = {0.f, 0.f, 0.f}, d[3] = {0.f, 0.f, 0.f}, inv[3];
