@@ -3773,15 +3773,17 @@ __device__ __forceinline__ bool scene_pair_valid(const SceneArgs& a, int j, int&
 // |c| + s + |o| times inv, a few roundings of 2^-24 of that; widened by 2^-19), and in the sum and the
 // product by 1e-37, where values so small that FP32 holds them to fewer digits, or not at all, round
 // by more. Zero direction components and NaN or infinite values are never certain.
-__device__ __forceinline__ bool scene_certain_miss(const float o[3], const float inv[3], const float4& box,
-                                                   float t_min) {
+// widen[0], widen[1]: the ray's share of the widening, that of a box a centre and half extent of which
+// add up to x is x widen[0] + widen[1].
+__device__ __forceinline__ bool scene_certain_miss(const float o[3], const float inv[3], const float (*widen)[2],
+                                                   const float4& box, float t_min) {
   const float cc[3] = {box.x, box.y, box.z}, s = box.w;
   float t0 = -INFINITY, t1 = INFINITY;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
     const float c = cc[a];
     const float ta = (c - s - o[a]) * inv[a], tb = (c + s - o[a]) * inv[a];
-    const float e = (fabsf(c) + s + fabsf(o[a]) + 1e-37f) * fabsf(inv[a]) * 0x1p-19f + 1e-37f;
+    const float e = fmaf(fabsf(c) + s, widen[a][0], widen[a][1]);
     t0 = fmaxf(t0, fminf(ta, tb) - e);
     t1 = fminf(t1, fmaxf(ta, tb) + e);
   }
@@ -3807,7 +3809,7 @@ __global__ void __launch_bounds__(256) k_scene_count(const SceneArgs a, int nblk
                            valid ? (float)(1.0 / od.inv_scale) : -1.0f);
     cnt[tid] = 0;
   }
-  float o[3] = {0.f, 0.f, 0.f}, d[3] = {0.f, 0.f, 0.f}, inv[3];
+  float o[3] = {0.f, 0.f, 0.f}, d[3] = {0.f, 0.f, 0.f}, inv[3], widen[3][2];
   const bool ray = r < a.n_rays;
   if (ray) {
 #pragma unroll
@@ -3817,13 +3819,17 @@ __global__ void __launch_bounds__(256) k_scene_count(const SceneArgs a, int nblk
     }
   }
 #pragma unroll
-  for (int c = 0; c < 3; ++c) inv[c] = 1.0f / d[c];
+  for (int c = 0; c < 3; ++c) {
+    inv[c] = 1.0f / d[c];
+    widen[c][0] = fabsf(inv[c]) * 0x1p-19f;
+    widen[c][1] = fmaf(fabsf(o[c]) + 1e-37f, widen[c][0], 1e-37f);
+  }
   const int words = (a.n_rays + 31) >> 5;
   __syncthreads();
   for (int j = j0; j < j1; ++j) {
     bool hit = false;
     const float4 b = box[j - j0];
-    if (b.w >= 0.f && ray && !scene_certain_miss(o, inv, b, (float)a.t_min)) {
+    if (b.w >= 0.f && ray && !scene_certain_miss(o, inv, widen, b, (float)a.t_min)) {
       double t0, t1;
       scene_slab(o, d, a.desc[a.object_ids[j]], a.t_min, t0, t1);
       hit = t1 > t0;
