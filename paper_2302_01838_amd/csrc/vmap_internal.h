@@ -407,7 +407,7 @@ __host__ __device__ constexpr int scene_tile_low(int round, int max_pairs, int t
 
 // Tiles of an object from which the optimiser spreads its partials over more workgroups, in batches
 // of at most kSpreadObjects objects (every workgroup of an extra row looks its object up among them).
-constexpr int kSpreadTiles = 64, kSpreadObjects = 256;
+constexpr int kSpreadTiles = 128, kSpreadObjects = 256;
 
 // Arguments of the gradient / optimiser kernels.
 struct OptArgs {
@@ -515,6 +515,7 @@ struct GenArgs {
   bool chain;            // k_gen_chain runs the products (gen_chain widths, a buffer for every layer's deltas)
   int64_t ld;            // elements per row of act and delta
   int64_t layer_elems;   // elements per layer of act
+  int64_t delta_elems;   // from one layer's deltas to the next one's (launch_generic sets it with delta)
   int max_gen_blocks;    // 256-row blocks the block table holds
   int32_t* gbs;          // [n_objects + 1] first 256-row block (chain: pair of row tiles) of each batch object
   int work_rays;         // rays per work tile of this chain's objects (the work list's)

@@ -4337,10 +4337,9 @@ hipError_t launch_init_scaler(ScalerState* sc, float scale, hipStream_t s) {
 // Weight gradients (k_gen_dw, k_gen_dw_small): rows = outputs, n = inputs, k = samples;
 // A = delta^T, B = h_l^T, both staged as the sample rows lie and read transposed.
 
-// Buffer of the deltas at layer m's outputs (m = 0..3): each layer's own, or two in turn.
-__device__ __forceinline__ uint16_t* gen_delta_out(const GenArgs& g, int m) {
-  return g.delta + (m & (g.deltas - 1)) * g.layer_elems;
-}
+// Buffer of the deltas at layer m's outputs (m = 0..3). Where two buffers are taken in turn, delta and
+// delta_elems are those of the launch's own two layers.
+__device__ __forceinline__ uint16_t* gen_delta_out(const GenArgs& g, int m) { return g.delta + m * g.delta_elems; }
 
 struct GenTile {
   int j, k, lo, hi;  // batch object, object id, rays [lo, hi)
@@ -4805,17 +4804,25 @@ __device__ __forceinline__ void gen_loss_block(const GenArgs& g, int b) {
 }
 
 // Weight gradients of the first layer (64 x 64 blocks, too few to fill the chip: 24 us of a launch
-// of their own at 50 objects of 1,200 rows, hidden 256), of square layers l .. l + nl - 1 in 128 x 128
-// blocks (n1 > 0), and the losses (5 us of a launch): n0 and n1 workgroups, nb0 and nb1 to a work tile,
-// and the rest. That step's launches took 98 us apart, 82 in one.
-__global__ void __launch_bounds__(256) k_gen_dw(const GenArgs g_in, int n0, int nb0, int n1, int nb1, int l, int nl) {
+// of their own at 50 objects of 1,200 rows, hidden 256), of the square layers in 128 x 128 blocks
+// (n1 > 0), and the losses (5 us of a launch): n0 and n1 workgroups, nb0 and nb1 to a work tile, and
+// the rest. That step's launches took 98 us apart, 82 in one.
+__global__ void __launch_bounds__(256) k_gen_dw(const GenArgs g_in, int n0, int nb0, int n1, int nb1) {
   GenArgs g = g_in;
   read_batch(g.a);
   __shared__ __attribute__((aligned(16))) uint16_t lds[2 * dw_tile<128>];
   const int b = (int)blockIdx.x;
   if (b < n0) gen_dw_block<64>(g, b, 0, nb0, 1, lds);
-  else if (b < n0 + n1) gen_dw_block<128>(g, b - n0, l, nb1, nl, lds);
+  else if (b < n0 + n1) gen_dw_block<128>(g, b - n0, 1, nb1, kLayers - 1, lds);
   else gen_loss_block(g, b - n0 - n1);
+}
+
+// A square layer's alone, nb workgroups to a work tile (deltas in two buffers in turn).
+__global__ void __launch_bounds__(256) k_gen_dw_layer(const GenArgs g_in, int l, int nb) {
+  GenArgs g = g_in;
+  read_batch(g.a);
+  __shared__ __attribute__((aligned(16))) uint16_t lds[2 * dw_tile<128>];
+  gen_dw_block<128>(g, (int)blockIdx.x, l, nb, 1, lds);
 }
 
 // 256 x 256 blocks of the products above, for the square layers of widths that are multiples of
@@ -5553,18 +5560,20 @@ __global__ void __launch_bounds__(512, 2) k_gen_chain(const GenArgs g_in) {
           acc[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
               w, *reinterpret_cast<const bf16x8*>(D + (32 * s + n) * P + 64 * c + 16 * kc + 8 * hf), acc[s], 0, 0, 0);
       }
-      if (c == 0) store_rows(D, g.delta + l * g.layer_elems);  // the layer's own deltas, for its weight gradient
+      if (c == 0) store_rows(D, gen_delta_out(g, l));  // the layer's own deltas, for its weight gradient
       if (i + 1 < kChunks) put_chunk(i + 1);
       __syncthreads();  // (after the last chunk: the deltas have been read)
     }
     put_delta(acc, l - 1);
     __syncthreads();
   }
-  store_rows(D, g.delta);
+  store_rows(D, gen_delta_out(g, 0));
 }
 
-hipError_t launch_generic(int mode, const GenArgs& g, int tiles_bound, int blocks_bound, int work_bound,
+hipError_t launch_generic(int mode, const GenArgs& g_in, int tiles_bound, int blocks_bound, int work_bound,
                           hipStream_t s) {
+  GenArgs g = g_in;
+  g.delta_elems = g.layer_elems;
   if (tiles_bound <= 0 || g.a.n_objects <= 0) return hipSuccess;
   if (!generic_width(g.H) || g.a.S < 1 || g.a.S > kSlots || blocks_bound <= 0 || work_bound <= 0 ||
       g.work_rays < 1)
@@ -5619,17 +5628,13 @@ hipError_t launch_generic(int mode, const GenArgs& g, int tiles_bound, int block
   };
   const int nloss = blocks(g.a.n_objects, 4);
   const int dw_blocks = blocks(H, 128) * blocks(H, 128);  // 128 x 128 blocks of a square layer
-  auto launch_dw_layer = [&](int l) {  // a square layer's weight gradient alone
-    const int n1 = (int)grid1(work_bound, dw_blocks).x;
-    hipLaunchKernelGGL(k_gen_dw, dim3(n1), dim3(256), 0, s, g, 0, 1, n1, dw_blocks, l, 1);
-  };
   // every layer's weight gradients, from the deltas of all layers, and the losses; square = false: those
   // of the square layers have been launched
   auto launch_dw = [&](bool square) {
     if (wide_dw && square) hipLaunchKernelGGL(k_gen_wide<GEN_DW>, grid1(work_bound * (kLayers - 1), nw * nw), dim3(512), 0, s, g, 0);
     const int nb0 = blocks(H, 64) * blocks(kEnc, 64), nb1 = wide_dw || !square ? 0 : dw_blocks * (kLayers - 1);
     const int n0 = (int)grid1(work_bound, nb0).x, n1 = (int)grid1(work_bound, nb1).x;
-    hipLaunchKernelGGL(k_gen_dw, dim3(n0 + n1 + nloss), dim3(256), 0, s, g, n0, nb0, n1, nb1, 1, kLayers - 1);
+    hipLaunchKernelGGL(k_gen_dw, dim3(n0 + n1 + nloss), dim3(256), 0, s, g, n0, nb0, n1, nb1);
     hipLaunchKernelGGL(k_gen_dw_small, grid1(work_bound, blocks(H, 32)), dim3(kGenDwWaves * 64), 0, s, g, blocks(H, 32));
   };
   if (g.chain) {
@@ -5652,10 +5657,17 @@ hipError_t launch_generic(int mode, const GenArgs& g, int tiles_bound, int block
   else hipLaunchKernelGGL(k_gen_render<false>, dim3(wave_blocks), dim3(256), 0, s, g);
   if (!train) hipLaunchKernelGGL(k_gen_loss, dim3(nloss), dim3(256), 0, s, g);
   if (train) {
+    // two buffers in turn: the deltas of layer m's outputs lie in buffer m mod 2, so that an input
+    // gradient writes those of layer l - 1's over those of l + 1's, whose weight gradient has run
     const bool turns = g.deltas != kLayers;
     for (int l = kLayers; l > 0; --l) {
-      fwd_dx(GEN_DX, H, l);  // writes the deltas of layer l - 1's outputs over those of l + 1's
-      if (turns && l > 1) launch_dw_layer(l - 1);
+      if (turns) {  // buffers of m = l and l - 1
+        g.delta_elems = (l & 1) || l == kLayers ? g.layer_elems : -g.layer_elems;
+        g.delta = g_in.delta + ((l - 1) & 1) * g.layer_elems - (l - 1) * g.delta_elems;
+      }
+      fwd_dx(GEN_DX, H, l);
+      if (turns && l > 1)
+        hipLaunchKernelGGL(k_gen_dw_layer, grid1(work_bound, dw_blocks), dim3(256), 0, s, g, l - 1, dw_blocks);
     }
     launch_dw(!turns);
   }
