@@ -34,6 +34,7 @@ struct WorkLayout {
   size_t tile_start, width_start, flags, t_next, mark, batch, tile_bad, tile_loss, partial, wimage, img32, gimg, total;
   size_t wimage_stride;
   int max_tiles;
+  int forward_tiles;  // tiles of a forward launch without losses: one round each, no partials
   // layered path (generic widths): row tiles, their losses, activations, deltas, z and dz
   size_t gts, gbs, gws, gen_loss, gact, gdelta, gz, gdz;
   int max_gen_tiles, max_gen_blocks;
@@ -147,6 +148,8 @@ WorkLayout work_layout(const vmap_config* c) {
   const int rpt = min_rays_per_tile(c);
   const size_t ps = (size_t)param_stride(c);
   w.max_tiles = (c->max_rays + rpt - 1) / rpt + c->max_objects;
+  const int round = std::max(1, kSlots / c->max_samples_per_ray) * 4;
+  w.forward_tiles = std::max(w.max_tiles, (c->max_rays + round - 1) / round + c->max_objects);
   size_t off = 0;
   w.tile_start = off; off = align256(off + ((size_t)c->max_objects + 1) * 4);
   // the same over the objects of width 32, 64 and 128 alone, and the optimiser's units
@@ -155,7 +158,7 @@ WorkLayout work_layout(const vmap_config* c) {
   w.t_next = off; off = align256(off + (size_t)c->max_objects * 4);
   w.mark = off; off = align256(off + (size_t)c->max_objects * 4);  // debug validation of ids
   w.batch = off; off = align256(off + sizeof(BatchDev));
-  w.tile_loss = off; off = align256(off + (size_t)w.max_tiles * 4);
+  w.tile_loss = off; off = align256(off + (size_t)w.forward_tiles * 4);
   w.tile_bad = off; off = align256(off + (size_t)w.max_tiles * 4);
   w.partial = off; off = align256(off + (size_t)w.max_tiles * ps * 4);
   // weight images of hidden-128 objects (weights read from device memory by the tile kernel)
@@ -382,9 +385,10 @@ bool runs_chain(const vmap_ctx* c, int H, bool train) {
   return gen_chain(H) && (!train || c->wl.gen_deltas == kLayers);
 }
 
-// train: for the tiles of a training step or backward pass.
+// train: for the tiles of a training step or backward pass. tile: rays per tile of hidden-32 objects
+// (0: the stack's; a device descriptor's goes before both).
 hipError_t enqueue_worklist(vmap_ctx* c, const vmap_batch* b, bool train, hipStream_t s,
-                            const BatchDev* bd = nullptr) {
+                            const BatchDev* bd = nullptr, int tile = 0) {
   GenScan gen{};
   if (c->cfg.precision == VMAP_BF16 && generic_width(c->cfg.max_hidden)) {
     gen.rpw = std::max(1, kSlots / b->samples_per_ray);
@@ -395,7 +399,7 @@ hipError_t enqueue_worklist(vmap_ctx* c, const vmap_batch* b, bool train, hipStr
     gen.start[2] = reinterpret_cast<int32_t*>(c->work + c->wl.gws);
   }
   return launch_worklist(b->n_objects, b->n_rays_total, b->object_ids, b->ray_offsets,
-                         c->rays_per_tile, c->rays_per_tile_wide, gen_work_rays(c, b->samples_per_ray),
+                         tile > 0 ? tile : c->rays_per_tile, c->rays_per_tile_wide, gen_work_rays(c, b->samples_per_ray),
                          c->cfg.max_objects, c->desc(), c->scaler(), c->tile_start(), c->width_start(32), c->flags(),
                          c->t_next(), bd, gen, s);
 }
@@ -440,13 +444,16 @@ OptArgs make_opt_args(vmap_ctx* c, const vmap_batch* b, float* loss_out, float* 
   return a;
 }
 
-// Enqueue the tile kernel for every width group. grid_tile: rays per tile that sizes the grid of the
-// hidden-32 objects, whose tiles the device descriptor gives (0: the stack's).
+// Enqueue the tile kernel for every width group. tile (forward mode without losses): as given to the
+// work list, or, where the device descriptor gives the tile, the one that sizes the grid.
 int enqueue_tiles(vmap_ctx* c, const vmap_batch* b, int mode, const float* dloss, float* d_out,
                   float* rgb_out, float* occ_out, hipStream_t s, bool allow_timing,
-                  const BatchDev* bd = nullptr, int grid_tile = 0) {
+                  const BatchDev* bd = nullptr, int tile = 0) {
   StepArgs a = make_step_args(c, b);
-  if (grid_tile > 0) a.rays_per_tile = grid_tile;
+  if (tile > 0) {
+    a.rays_per_tile = tile;
+    a.max_tiles = c->wl.forward_tiles;
+  }
   a.bd = bd;
   a.dloss = dloss;
   a.out_depth = d_out;
@@ -861,9 +868,17 @@ int vmap_forward(vmap_ctx* c, const vmap_batch* b, float* loss_out, float* depth
   if (b->n_objects == 0) return VMAP_OK;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   if ((rc = enqueue_debug(c, b, s))) return rc;
-  hipError_t e = enqueue_worklist(c, b, false, s);
+  // without losses, which are summed tile by tile, a tile that suits the batch, if the stack's are
+  // whole sub-tiles too (a ray's place in its sub-tile decides the last bits of its render)
+  const int rpw = std::max(1, kSlots / b->samples_per_ray), round = rpw * c->waves;
+  int tile = 0;
+  if (!loss_out && c->rays_per_tile % rpw == 0) {
+    tile = scene_tile_low(round, b->n_rays_total, c->wl.forward_tiles - b->n_objects);
+    tile = scene_tile(tile, std::max(tile, kSceneRounds * round), b->n_rays_total);
+  }
+  hipError_t e = enqueue_worklist(c, b, false, s, nullptr, tile);
   if (e != hipSuccess) return c->hip_fail(e, "worklist launch");
-  rc = enqueue_tiles(c, b, MODE_FWD, nullptr, depth_out, rgb_out, occ_out, s, true);
+  rc = enqueue_tiles(c, b, MODE_FWD, nullptr, depth_out, rgb_out, occ_out, s, true, nullptr, tile);
   if (rc) return rc;
   if (loss_out) {
     e = launch_optimizer(OPT_LOSS, make_opt_args(c, b, loss_out, nullptr), s);
@@ -923,7 +938,7 @@ static int render_scene(vmap_ctx* c, int32_t n_rays, const float* rays_o, const 
   a.max_objects = c->cfg.max_objects;
   a.max_pairs = max_pairs;
   const int round = std::max(1, kSlots / S) * c->waves;
-  a.tile_low = scene_tile_low(round, max_pairs, c->wl.max_tiles - n_objects);
+  a.tile_low = scene_tile_low(round, max_pairs, c->wl.forward_tiles - n_objects);
   a.tile_longest = std::max(a.tile_low, kSceneRounds * round);
   a.occ_threshold = occ_threshold;
   a.t_min = (double)t_min;
