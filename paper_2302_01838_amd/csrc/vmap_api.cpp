@@ -178,7 +178,7 @@ WorkLayout work_layout(const vmap_config* c) {
     w.gen_ld = std::max(kEnc, c->max_hidden);
     w.gen_rows = (int64_t)c->max_rays * c->max_samples_per_ray;
     const size_t layer = (size_t)w.gen_rows * (size_t)w.gen_ld * 2;
-    w.max_gen_blocks = (int)((w.gen_rows + kGenBlockRows - 1) / kGenBlockRows) + c->max_objects;
+    w.max_gen_blocks = (int)((w.gen_rows + kGenHalfRows - 1) / kGenHalfRows) + c->max_objects;
     w.gts = off; off = align256(off + ((size_t)c->max_objects + 1) * 4);
     w.gbs = off; off = align256(off + ((size_t)c->max_objects + 1) * 4);
     w.gws = off; off = align256(off + ((size_t)c->max_objects + 1) * 4);
@@ -385,6 +385,11 @@ bool runs_chain(const vmap_ctx* c, int H, bool train) {
   return gen_chain(H) && (!train || c->wl.gen_deltas == kLayers);
 }
 
+int gen_block_rows(int H, const vmap_batch* b, bool train) {
+  const long long rows = (long long)b->n_rays_total * b->samples_per_ray;
+  return gen_wide_products(H, rows, b->n_objects, train) ? kGenBlockRows : kGenHalfRows;
+}
+
 // train: for the tiles of a training step or backward pass. tile: rays per tile of hidden-32 objects
 // (0: the stack's; a device descriptor's goes before both).
 hipError_t enqueue_worklist(vmap_ctx* c, const vmap_batch* b, bool train, hipStream_t s,
@@ -394,6 +399,7 @@ hipError_t enqueue_worklist(vmap_ctx* c, const vmap_batch* b, bool train, hipStr
     gen.rpw = std::max(1, kSlots / b->samples_per_ray);
     gen.S = b->samples_per_ray;
     gen.chain = runs_chain(c, c->gen_width, train);
+    gen.block_rows = gen_block_rows(c->gen_width, b, train);
     gen.start[0] = reinterpret_cast<int32_t*>(c->work + c->wl.gts);
     gen.start[1] = reinterpret_cast<int32_t*>(c->work + c->wl.gbs);
     gen.start[2] = reinterpret_cast<int32_t*>(c->work + c->wl.gws);
@@ -513,6 +519,7 @@ int enqueue_tiles(vmap_ctx* c, const vmap_batch* b, int mode, const float* dloss
       g.delta = reinterpret_cast<uint16_t*>(c->work + c->wl.gdelta);
       g.deltas = c->wl.gen_deltas;
       g.chain = runs_chain(c, H, mode == MODE_TRAIN);
+      g.block_rows = gen_block_rows(H, b, mode == MODE_TRAIN);
       g.z = reinterpret_cast<float*>(c->work + c->wl.gz);
       g.dz = reinterpret_cast<float*>(c->work + c->wl.gdz);
       g.ld = c->wl.gen_ld;
@@ -520,7 +527,7 @@ int enqueue_tiles(vmap_ctx* c, const vmap_batch* b, int mode, const float* dloss
       const int tiles_bound = (b->n_rays_total + g.rpw - 1) / g.rpw + b->n_objects;
       if (tiles_bound > g.max_gen_tiles) return c->fail(VMAP_ECAPACITY, "batch needs more row tiles than the workspace holds");
       const long long rows = (long long)b->n_rays_total * b->samples_per_ray;
-      const long long blocks_bound = (rows + kGenBlockRows - 1) / kGenBlockRows + b->n_objects;
+      const long long blocks_bound = (rows + g.block_rows - 1) / g.block_rows + b->n_objects;
       if (blocks_bound > g.max_gen_blocks) return c->fail(VMAP_ECAPACITY, "batch needs more row blocks than the workspace holds");
       g.work_rays = gen_work_rays(c, b->samples_per_ray);
       const int work_bound = (b->n_rays_total + g.work_rays - 1) / g.work_rays + b->n_objects;

@@ -518,17 +518,53 @@ struct GenArgs {
   int64_t ld;            // elements per row of act and delta
   int64_t layer_elems;   // elements per layer of act
   int64_t delta_elems;   // from one layer's deltas to the next one's (launch_generic sets it with delta)
-  int max_gen_blocks;    // 256-row blocks the block table holds
-  int32_t* gbs;          // [n_objects + 1] first 256-row block (chain: pair of row tiles) of each batch object
+  int max_gen_blocks;    // row blocks the block table holds
+  int block_rows;        // rows of a row block: 256 where gen_wide_products, else 128
+  int32_t* gbs;          // [n_objects + 1] first row block (chain: pair of row tiles) of each batch object
   int work_rays;         // rays per work tile of this chain's objects (the work list's)
   int32_t* gws;          // [n_objects + 1] first work tile of each batch object among this chain's
                          // work tiles (the chain's objects' tiles, counted alone)
 };
 // Kinds of the layered path's row-block product kernel (the weight gradients have their own).
 enum GenKind { GEN_FWD = 0, GEN_DX = 1 };
-// Rows of a block of the wide products (128 x 128 output blocks): an object's rows in order, cut
-// every kGenBlockRows rows regardless of ray boundaries (rows are independent in those products).
-constexpr int kGenBlockRows = 256;
+// Rows of a block of the wide products (256 x 256 or 128 x 128 output blocks): an object's rows in
+// order, cut every so many regardless of ray boundaries (rows are independent in those products).
+constexpr int kGenBlockRows = 256, kGenHalfRows = 128;
+// Whether a chain's square layers of width H (512 and up) take 256 x 256 blocks (k_gen_wide) in a batch
+// of so many rows and objects: from 256 workgroups, one per CU; the 128 x 128 blocks, four times as many,
+// fill the chip better below that. Steps of objects of 1,200 rows in us, wide against 128: hidden
+// 512, 8 objects (92 workgroups, rows' bound) 275 against 255, 16 (182) 365 / 370, 32 (364) 654 / 665;
+// hidden 1024, 4 (92) 447 / 407, 8 (184) 560 / 566, 16 (364) 1041 / 1059.
+// A workgroup of k_gen_wide holds a CU alone, so just past 256 of them a second round of nearly empty
+// CUs takes as long as the first. Workgroups of evenly filled objects (the batch's own counts are on
+// the device), wide against 128, render and step: hidden 512, 280 (28 objects of 1,200 rows) 160 / 151
+// and 599 / 585, 304 (4 of 9,500) 165 / 142 and 536 / 512, 316 (one of 40,000) 184 / 162 and 511 / 484, 320
+// (16 of 2,400) 162 / 147 and 536 / 528, 320 (32 of 1,200) 161 / 168 and 630 / 636, 346 (one of 44,000)
+// 191 / 182 and 523 / 517, 402 (one of 51,200) 203 / 208 and 562 / 584; hidden 1024, 288 (8 of 2,260)
+// 234 / 207 and 815 / 767, 320 (16 of 1,200) 242 / 231 and 982 / 983, 320 (20 of 1,000) 247 / 256 and
+// 1109 / 1130, 360 (18 of 1,200) 250 / 260 and 1091 / 1112. The line lies at a quarter of the second
+// round; for renders of up to 16 objects, whose 128-row blocks share weights more, at three eighths of the
+// second and the third (hidden 512, 564, two of 36,000: 273 / 255). Steps of three rounds are within 3 %
+// of each other either way.
+// Objects whose last 256-row block is half empty or more, so that the wide blocks hold a third more rows
+// than the narrow ones (320 rows, say), take the narrow ones if the last round is not nearly full: hidden
+// 512, 400 workgroups (100 of 300 rows) 179 / 177 and 1052 / 1047, 800 (200 of 300) 319 / 292 and 2052 /
+// 2010; hidden 1024, 400 (50 of 320) 256 / 247 and 1841 / 1847, 480 (60 of 280) 262 / 271 and 2121 / 2147,
+// 800 (100 of 300) 461 / 426 and 3622 / 3569.
+constexpr int kCUs = 256;
+inline bool gen_wide_products(int H, long long rows, int n_objects, bool train) {
+  const int nw = H / 256;
+  const long long bound = (rows + kGenBlockRows - 1) / kGenBlockRows + n_objects;
+  if (nw < 2 || n_objects < 1 || bound * nw < kCUs) return false;
+  const long long each = rows / n_objects;
+  auto blocks = [&](int t) { return (each + t - 1) / t; };
+  const long long even = blocks(kGenBlockRows) * n_objects * nw;
+  const int last = (int)((even - 1) % kCUs) + 1;  // workgroups of the last round
+  const bool few = !train && n_objects <= 16;
+  if (even > kCUs && even <= (few ? 3 : 2) * kCUs && last < (few ? 3 * kCUs / 8 : kCUs / 4)) return false;
+  const bool loose = 8 * blocks(kGenBlockRows) > 5 * blocks(kGenHalfRows);
+  return !loose || last >= 7 * kCUs / 8;
+}
 // LDS of the product kernels: k_gen_gemm and k_gen_dw stage two BF16 operand tiles of up to
 // 128 x (kGenKChunk + 8) or kGenKChunk x (128 + 16) elements; k_gen_dw_small (the output layer)
 // its kGenDwWaves waves' pairs of 32-row tiles (rows of kGenPitch elements), then the waves' FP32 sums (16
@@ -598,7 +634,7 @@ struct SceneArgs {
 // pairs of row tiles for gen_chain widths), start[2] work tiles, [n_objects + 1] each; NULL where the
 // stack holds no layered width.
 struct GenScan {
-  int rpw, S;
+  int rpw, S, block_rows;
   bool chain;
   int32_t* start[3];
 };

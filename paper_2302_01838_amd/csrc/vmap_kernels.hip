@@ -3204,7 +3204,7 @@ __global__ void __launch_bounds__(1024) k_worklist(int n_objects, int n_rays, co
   for (int j = tid; j < n_objects; j += nt) bad |= !batch_segment_ok(j, n_objects, offs[j], offs[j + 1], n_rays);
   const bool any_bad = __syncthreads_or(bad) != 0;
   // all tiles, those of widths 32, 64 and 128, optimiser units; of layered objects row tiles, product
-  // blocks (256 rows, or pairs of row tiles) and work tiles
+  // blocks (block_rows rows, or pairs of row tiles) and work tiles
   int carry[N] = {};
   for (int base = 0; base < n_objects; base += nt) {
     const int j = base + tid;
@@ -3227,7 +3227,7 @@ __global__ void __launch_bounds__(1024) k_worklist(int n_objects, int n_rays, co
           cnt[5] = tiles_of(o1 - o0, gen.rpw);
           cnt[6] = gen.chain && gen_chain(hidden)
                        ? (cnt[5] + 1) / 2
-                       : (int)(((long long)(o1 - o0) * gen.S + kGenBlockRows - 1) / kGenBlockRows);
+                       : (int)(((long long)(o1 - o0) * gen.S + gen.block_rows - 1) / gen.block_rows);
           cnt[7] = cnt[0];
         }
       }
@@ -4413,8 +4413,11 @@ __global__ void __launch_bounds__(256) k_gen_encode(const GenArgs g_in) {
 }
 
 // Rows of product block b of the layered chain: T = 64, row tile b (at most 64 rows, whole rays);
-// T = 256, block b of the block table (an object's rows in order, cut every 256 rows); T = 128,
-// half b mod 2 of block b / 2. False if b is past the chain's blocks or holds no row.
+// T = 256, block b of the block table (an object's rows in order, cut every block_rows rows); T = 128,
+// block b, or in a table of 256-row blocks half b mod 2 of block b / 2. False if b is past the chain's
+// blocks or holds no row. (As halves the 128-row blocks leave every object whose last block is at most
+// half full a workgroup without rows, and with objects of one size always on the same XCDs: rendering
+// 50 hidden-512 objects of 320 rows, in halves 130 us, in 128-row blocks 106; the step 607 and 547.)
 template <int T>
 __device__ __forceinline__ bool gen_rows(const GenArgs& g, const StepArgs& a, int b, int& k, int64_t& r0, int& nrows) {
   if constexpr (T == 64) {
@@ -4424,13 +4427,13 @@ __device__ __forceinline__ bool gen_rows(const GenArgs& g, const StepArgs& a, in
     r0 = (int64_t)tl.lo * a.S;
     nrows = (tl.hi - tl.lo) * a.S;
   } else {
-    constexpr int D = kGenBlockRows / T;
-    static_assert(D == 1 || D == 2, "whole or half row blocks");
+    static_assert(T == kGenBlockRows || 2 * T == kGenBlockRows, "whole or half row blocks");
+    const int sh = T == kGenBlockRows || g.block_rows == T ? 0 : 1;  // halves
     const int total = clamp_tiles(g.gbs[a.n_objects], g.max_gen_blocks);
-    if (b / D >= total) return false;
-    const int j = gen_object(g.gbs, a.n_objects, b / D);
+    if ((b >> sh) >= total) return false;
+    const int j = gen_object(g.gbs, a.n_objects, b >> sh);
     const RayRange rr = tile_ray_range(a.ray_offsets[j], a.ray_offsets[j + 1], 0, kWholeObject, a.n_rays);
-    const int64_t first = (int64_t)(b / D - g.gbs[j]) * kGenBlockRows + (b % D) * T;
+    const int64_t first = (int64_t)(b - (g.gbs[j] << sh)) * T;
     const int64_t rows = (int64_t)(rr.hi - rr.lo) * a.S;
     k = a.object_ids[j];
     r0 = (int64_t)rr.lo * a.S + first;
@@ -5589,28 +5592,13 @@ hipError_t launch_generic(int mode, const GenArgs& g_in, int tiles_bound, int bl
   // one-dimensional grids of 8 ceil(units / 8) x blocks-per-unit workgroups (xcd_unit_block)
   auto grid1 = [&](int units, int nblk) { return dim3((unsigned)(8 * blocks(units, 8) * nblk)); };
   const int nw = H / 256;
-  // k_gen_wide from 256 workgroups of 256 x 256, one per CU; the 128 x 128 blocks, four times as many,
-  // fill the chip better below that. Steps of objects of 1,200 rows in us, wide against 128: hidden
-  // 512, 8 objects (92 workgroups, rows' bound) 275 against 255, 16 (182) 365 / 370, 32 (364) 654 / 665;
-  // hidden 1024, 4 (92) 447 / 407, 8 (184) 560 / 566, 16 (364) 1041 / 1059. Weight gradients likewise at
-  // hidden 512 (8 objects, 192 workgroups: 262 / 255; 16, 384: 367 / 370); at hidden 1024 always: the
-  // 128 x 128 blocks of one object all run on one XCD (1 object 263 / 306, 4 368 / 407, 16 1021 / 1059).
-  // Hidden 256: 50 objects of 1,200 rows 318 / 318, of 4,800 941 / 980, 16 of 1,200 164 / 151.
-  // A workgroup of k_gen_wide holds a CU alone, so just past 256 of them a second round of nearly empty
-  // CUs takes as long as the first. Workgroups of evenly filled objects (the batch's own counts are on
-  // the device), wide against 128, render and step: hidden 512, 280 (28 objects of 1,200 rows) 160 / 151
-  // and 599 / 585, 304 (4 of 9,500) 165 / 142 and 536 / 512, 316 (one of 40,000) 184 / 162 and 511 / 484, 320
-  // (16 of 2,400) 162 / 147 and 536 / 528, 320 (32 of 1,200) 161 / 168 and 630 / 636, 346 (one of 44,000)
-  // 191 / 182 and 523 / 517, 402 (one of 51,200) 203 / 208 and 562 / 584; hidden 1024, 288 (8 of 2,260)
-  // 234 / 207 and 815 / 767, 320 (16 of 1,200) 242 / 231 and 982 / 983, 320 (20 of 1,000) 247 / 256 and
-  // 1109 / 1130, 360 (18 of 1,200) 250 / 260 and 1091 / 1112. The line lies at a quarter of the second
-  // round, for renders of up to 16 objects, whose 128-row blocks share weights more, at three eighths. In
-  // the third round the sides are within 5 % of each other either way.
-  constexpr int kCUs = 256;
-  const long long rows = (long long)g.a.n_rays * g.a.S;
-  const long long even = ((rows / g.a.n_objects + kGenBlockRows - 1) / kGenBlockRows) * g.a.n_objects * nw;
-  const int second = !train && g.a.n_objects <= 16 ? 3 * kCUs / 8 : kCUs / 4;  // workgroups worth a second round
-  const bool wide = nw > 1 && (long long)blocks_bound * nw >= kCUs && !(even > kCUs && even < kCUs + second);
+  const bool wide = g.block_rows == kGenBlockRows;
+  constexpr int kHalves = kGenBlockRows / kGenHalfRows;
+  const int halves_bound = (wide ? kHalves : 1) * blocks_bound;
+  // Weight gradients take k_gen_wide from 256 workgroups: hidden 512, objects of 1,200 rows, wide against
+  // 128, steps in us: 8 objects (192 workgroups) 262 / 255, 16 (384) 367 / 370; hidden 256, 50 objects 318 /
+  // 318, of 4,800 rows 941 / 980, 16 of 1,200 164 / 151. At hidden 1024 always: the 128 x 128 blocks of one
+  // object all run on one XCD (1 object 263 / 306, 4 368 / 407, 16 1021 / 1059).
   const bool wide_dw = (nw >= 4 || (long long)work_bound * nw * nw * (kLayers - 1) >= kCUs);
   auto fwd_dx = [&](int kind, int ncols, int l) {
     if (wide && l > 0 && l < kLayers) {
@@ -5618,8 +5606,8 @@ hipError_t launch_generic(int mode, const GenArgs& g_in, int tiles_bound, int bl
       else hipLaunchKernelGGL(k_gen_wide<GEN_DX>, grid1(blocks_bound, nw), dim3(512), 0, s, g, l);
     } else if (ncols >= 128) {
       const int nb = blocks(ncols, 128);
-      if (kind == GEN_FWD) hipLaunchKernelGGL((k_gen_gemm<GEN_FWD, 128>), grid1(2 * blocks_bound, nb), dim3(256), 0, s, g, l, nb);
-      else hipLaunchKernelGGL((k_gen_gemm<GEN_DX, 128>), grid1(2 * blocks_bound, nb), dim3(256), 0, s, g, l, nb);
+      if (kind == GEN_FWD) hipLaunchKernelGGL((k_gen_gemm<GEN_FWD, 128>), grid1(halves_bound, nb), dim3(256), 0, s, g, l, nb);
+      else hipLaunchKernelGGL((k_gen_gemm<GEN_DX, 128>), grid1(halves_bound, nb), dim3(256), 0, s, g, l, nb);
     } else {
       const int nb = blocks(ncols, 64);
       if (kind == GEN_FWD) hipLaunchKernelGGL((k_gen_gemm<GEN_FWD, 64>), grid1(tiles_bound, nb), dim3(256), 0, s, g, l, nb);
