@@ -387,17 +387,30 @@ __host__ __device__ inline BatchDev make_batch_dev(int n_objects, int S, int n_r
 // Rays per tile of a scene's hidden-32 objects, and of a batch's that is rendered without losses. A
 // forward tile leaves no partial, and a ray's render does not depend on its tile as long as tiles are
 // whole sub-tiles, so the tile follows the rays of the call (a scene's pairs, which its scan counts on
-// the device), not the stack's capacity: whole rounds of a workgroup (a sub-tile per wave), the fewest while
-// the tiles do not fill the 1024 workgroups that forward mode holds, and doubled from there while they
-// still do, up to eight rounds, which fetch an object's weights less often. Following max_pairs, mostly
-// far above them, left few long tiles: FP32, 3,991 pairs of at most 153,600, 130 us against 97 here;
-// 9,609 of 307,200, 126 against 108 (BF16, 99,200 pairs: 189 either way). A render of 3,456 rays x 64 by
-// three-round training tiles took 21.9 us (BF16), 17.2 so.
-constexpr int kSceneTiles = 1024, kSceneRounds = 8;
-__host__ __device__ constexpr int scene_tile(int low, int longest, int pairs) {
-  int rpt = low;
-  while (2 * rpt <= longest && pairs >= 2 * rpt * kSceneTiles) rpt *= 2;
-  return rpt;
+// the device), not the stack's capacity or max_pairs: of tiles of whole rounds of a workgroup (a
+// sub-tile per wave), one to eight, the one whose estimated time is least. That is the rounds of the
+// `slots` workgroups that forward mode holds (1024 of four waves in BF16, 512 in FP32) times a tile's own
+// rounds and half a one for its start; of equal ones the longest, which fetches weights least often.
+// Following max_pairs, mostly far above the pairs, left few long tiles: FP32, 3,991 pairs of at most
+// 153,600, 130 us against 97 here; 9,609 of 307,200, 126 against 104 (BF16, 99,200 pairs: 189 either way). A
+// render of 3,456 rays x 64 by three-round training tiles took 21.9 us (BF16), 17.2 so.
+constexpr int kSceneRounds = 8;
+// Cost of tiles of k rounds (0 <= cost < 2^31 for up to 2^26 rays).
+__host__ __device__ constexpr int forward_tile_cost(int k, int round, int rays, int n_objects, int slots) {
+  const int tiles = rays / (k * round) + (n_objects + 1) / 2;  // an object's last tile is half empty
+  return (tiles + slots - 1) / slots * (2 * k + 1);
+}
+// low: scene_tile_low; at least that, in whole rounds.
+__host__ __device__ constexpr int forward_tile(int round, int low, int rays, int n_objects, int slots) {
+  int best = low, cost = 0x7fffffff;
+  for (int k = low / round; k <= kSceneRounds; ++k) {
+    const int c = forward_tile_cost(k, round, rays, n_objects, slots);
+    if (c <= cost) {
+      cost = c;
+      best = k * round;
+    }
+  }
+  return best;
 }
 // Its shortest tile: the fewest rounds whose tiles fit a work list of `tiles` tiles beside one per object
 // for any number of pairs. (Tiles of the scene's wider objects are the stack's, whose list they fit at
@@ -602,7 +615,7 @@ struct SceneArgs {
   int S;
   int max_objects;
   int max_pairs;
-  int tile_low, tile_longest;  // rays per tile of hidden-32 objects (scene_tile)
+  int tile_round, tile_low, slots;  // of hidden-32 objects' tiles (forward_tile)
   float occ_threshold;
   double t_min;
   const float* rays_o;       // [n_rays][3]

@@ -3889,6 +3889,16 @@ __global__ void __launch_bounds__(1024) k_scene_scan(const SceneArgs a, int nblk
     }
     __syncthreads();
   }
+  // the tile: forward_tile, a candidate per lane (fewest rounds at equal cost lose)
+  const int pairs = min(carry, a.max_pairs), k = lane + 1;
+  int cost = 0x7fffffff;
+  if (k <= kSceneRounds && k >= a.tile_low / a.tile_round)
+    cost = forward_tile_cost(k, a.tile_round, pairs, a.n_objects, a.slots);
+  int least = cost;
+#pragma unroll
+  for (int off = 4; off >= 1; off >>= 1) least = min(least, __shfl_xor(least, off));
+  const unsigned long long best = __ballot(k <= kSceneRounds && cost == least && cost != 0x7fffffff);
+  const int tile = best ? (64 - __clzll((long long)best)) * a.tile_round : a.tile_low;
   if (tid == 0) {
     const int total = carry;
     a.ray_offsets[a.n_objects] = min(total, a.max_pairs);
@@ -3898,7 +3908,7 @@ __global__ void __launch_bounds__(1024) k_scene_scan(const SceneArgs a, int nblk
     // cleared, and a field left out would be read as garbage); no targets or losses, point samples
     *a.bd = make_batch_dev(a.n_objects, a.S, min(total, a.max_pairs), a.object_ids, a.ray_offsets,
                            a.pair_o, a.pair_d, a.pair_t, nullptr, nullptr, nullptr, nullptr, nullptr,
-                           scene_tile(a.tile_low, a.tile_longest, min(total, a.max_pairs)));
+                           tile);
   }
 }
 

@@ -1,6 +1,7 @@
-"""Rays per tile of a scene's hidden-32 objects (scene_tile, scene_tile_low in
-paper_2302_01838_amd/csrc/vmap_internal.h), evaluated on the host: the tiles of any number of pairs fit
-the workspace's list, the shortest tile that does is the start, and the tile grows with the pairs."""
+"""Rays per tile of forward launches without losses (forward_tile, scene_tile_low in
+paper_2302_01838_amd/csrc/vmap_internal.h), evaluated on the host: the tiles of any number of rays fit the
+work list, the shortest tile that does is the start, and of the tiles of up to eight rounds none has a
+smaller estimate of the rounds that the chip's workgroup slots get."""
 import os
 import shutil
 import subprocess
@@ -23,12 +24,12 @@ int main() {
             const int least = wide > 0 && wide < rpt ? wide : rpt;
             const int max_tiles = (max_rays + least - 1) / least + n;  // of a stack of n objects
             for (int share : {1, 3, 100}) {
-              const int max_pairs = max_rays / share;
-              const int low = scene_tile_low(round, max_pairs, max_tiles - n);
-              const int longest = low > kSceneRounds * round ? low : kSceneRounds * round;
+              const int bound = max_rays / share;
+              const int low = scene_tile_low(round, bound, max_tiles - n);
               for (int part : {1, 2, 7, 1000}) {
-                const int pairs = max_pairs / part, tile = scene_tile(low, longest, pairs);
-                std::printf("%d %d %d %d %d %d %d %d %d %d\n", round, rpt, wide, max_pairs, n, max_tiles, low, longest, pairs, tile);
+                const int rays = bound / part, slots = part % 2 ? 1024 : 512;
+                const int tile = forward_tile(round, low, rays, n, slots);
+                std::printf("%d %d %d %d %d %d %d %d %d %d\n", round, rpt, wide, bound, n, max_tiles, low, rays, slots, tile);
               }
             }
           }
@@ -37,7 +38,7 @@ int main() {
 """
 
 
-def test_scene_tiles_fit_and_follow_the_pairs(tmp_path):
+def test_forward_tiles_fit_and_follow_the_rays(tmp_path):
     if not os.path.exists(HIPCC) or shutil.which("g++") is None:
         pytest.skip("hipcc not available")
     src = tmp_path / "drv.cpp"
@@ -49,14 +50,17 @@ def test_scene_tiles_fit_and_follow_the_pairs(tmp_path):
     rows = [list(map(int, ln.split())) for ln in
             subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.splitlines()]
     assert len(rows) == 5 * 7 * 3 * 5 * 3 * 3 * 4
-    for rnd, rpt, wide, max_pairs, n, max_tiles, low, longest, pairs, tile in rows:
-        what = (rnd, rpt, wide, max_pairs, n, pairs, low, tile)
-        bound = lambda t: -(-pairs // (min(t, wide) if wide else t)) + n
-        assert bound(tile) <= max_tiles, what
+    for rnd, rpt, wide, bound, n, max_tiles, low, rays, slots, tile in rows:
+        what = (rnd, rpt, wide, bound, n, rays, low, tile)
+        assert -(-rays // (min(tile, wide) if wide else tile)) + n <= max_tiles, what
         assert low % rnd == 0 and low < max(rpt, wide) + rnd, what
-        assert low <= tile <= longest and tile % low == 0, what
         if low > rnd:  # a shorter one would not fit
-            assert -(-max_pairs // (low - rnd)) + n > max_tiles, what
-        # as many tiles as forward mode holds workgroups, or the shortest tile
-        assert tile == low or pairs // tile >= 1024, what
-        assert 2 * tile > longest or pairs // (2 * tile) < 1024, what
+            assert -(-bound // (low - rnd)) + n > max_tiles, what
+        assert tile % rnd == 0 and low <= tile <= max(low, 8 * rnd), what
+        cost = lambda k: -(-(rays // (k * rnd) + (n + 1) // 2) // slots) * (2 * k + 1)
+        if tile <= 8 * rnd:
+            ks = range(low // rnd, 9)
+            assert cost(tile // rnd) == min(map(cost, ks)), what
+            assert all(cost(k) > cost(tile // rnd) for k in ks if k * rnd > tile), what  # the longest of equals
+        if rays > 0 and -(-rays // low) + n <= slots:  # one round of the chip: no longer than it need be
+            assert tile == low or tile > 8 * rnd, what
