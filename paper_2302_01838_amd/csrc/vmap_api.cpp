@@ -82,11 +82,14 @@ const char* check_config(const vmap_config* c) {
 // S = 10, 22.9 us per step with one round a tile against 27.0 with two, and 18.9 against 23.4 with
 // one object. Past one round two are kept (200 such objects: 56 against 60 us), and in BF16 three
 // or four where they fit and two do not: 18,132 rays at S = 20, 530 tiles of three rounds take
-// 55 us, 404 of four 47. FP32 takes one round also where the estimate is up to an eighth over the
-// slots: it gains 17 us where the tiles fit after all (50 objects of 120 rays: 36 against 51 us)
-// and loses 11 where they do not. Capacity decides, not the batch: an object's sums do not depend
-// on the other objects of its batch. Stacks with wider objects keep two rounds (the tile bounds
-// the number of their far larger partials).
+// 55 us, 404 of four 47 (a batch far below its stack's capacity pays for them: 1,000 of 40,000 rays at
+// S = 10, 33 us against 23 by two rounds). FP32 takes one round also where the estimate is up to an
+// eighth over the slots. Measured with 1, 4, 20 and 50 objects, even and uneven, S = 10, 20 and 32, at
+// capacities of 257 to 288 estimated tiles: where the tiles fit after all, 34-37 us against 48-53 with
+// two rounds (nearly every batch at nine tenths of the capacity), where they do not, 54-61 against
+// 48-52. Capacity decides, not the batch: an object's sums do not depend on the other objects of its
+// batch. Stacks with wider objects keep two rounds (the tile bounds the number of their far larger
+// partials).
 int default_rays_per_tile(const vmap_config* c) {
   if (c->rays_per_tile > 0) return c->rays_per_tile;
   const int rpw = std::max(1, kSlots / c->max_samples_per_ray);
