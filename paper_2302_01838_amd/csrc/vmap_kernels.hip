@@ -3225,9 +3225,10 @@ __global__ void __launch_bounds__(1024) k_worklist(int n_objects, int n_rays, co
       if constexpr (GEN) {
         if (valid && !any_bad && generic_width(hidden) && o1 > o0) {
           cnt[5] = tiles_of(o1 - o0, gen.rpw);
-          cnt[6] = gen.chain && gen_chain(hidden)
-                       ? (cnt[5] + 1) / 2
-                       : (int)(((long long)(o1 - o0) * gen.S + gen.block_rows - 1) / gen.block_rows);
+          const long long rows = (long long)(o1 - o0) * gen.S;
+          cnt[6] = gen.chain && gen_chain(hidden) ? (cnt[5] + 1) / 2
+                   : gen.block_rows == kGenBlockRows ? (int)((rows + kGenBlockRows - 1) / kGenBlockRows)
+                                                     : (int)((rows + kGenHalfRows - 1) / kGenHalfRows);
           cnt[7] = cnt[0];
         }
       }
