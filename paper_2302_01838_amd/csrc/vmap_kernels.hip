@@ -3427,6 +3427,7 @@ __global__ void __launch_bounds__(256) k_reduce_adam(const OptArgs a_in) {
 __global__ void __launch_bounds__(256, 4) k_reduce_adam_wide(const OptArgs a_in, int rows) {
   OptArgs a = a_in;
   read_batch(a);
+  a.tile_bad = nullptr;  // (launches of stacks of width 32 alone have them, which take k_reduce_adam)
   const int blocks = (int)gridDim.x - 1;
   if ((int)blockIdx.x == blocks) {
     scaler_update(a);
@@ -3467,9 +3468,9 @@ __global__ void __launch_bounds__(256, 4) k_reduce_adam_wide(const OptArgs a_in,
       const bool lead = u == first && tid == 0;
       __syncthreads();  // the previous object's coefficients have been read
       if (tid == 0) adam_coef_store(a, t, sh);
-      if (u == first && wave == 0 && a.loss_out) {
+      if (u == first && wave == 1 && a.loss_out) {  // (wave 0 has the coefficients to work out)
         const float loss = loss_sum(a.tile_loss, t0, t1);
-        if (tid == 0) a.loss_out[j] = valid ? loss : 0.f;
+        if (lane == 0) a.loss_out[j] = valid ? loss : 0.f;
       }
       live = valid && r1 > r0;
       // (the barrier of object_bad also publishes the coefficients)
