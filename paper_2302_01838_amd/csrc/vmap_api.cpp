@@ -393,10 +393,6 @@ int gen_block_rows(int H, const vmap_batch* b, bool train) {
   return gen_wide_products(H, rows, b->n_objects, train) ? kGenBlockRows : kGenHalfRows;
 }
 
-// Workgroups of the hidden-32 kernel that run at once in forward mode: four waves per SIMD in BF16, two
-// in FP32 (registers).
-int forward_slots(const vmap_ctx* c) { return 256 * (c->cfg.precision == VMAP_BF16 ? 16 : 8) / c->waves; }
-
 // train: for the tiles of a training step or backward pass. tile: rays per tile of hidden-32 objects
 // (0: the stack's; a device descriptor's goes before both).
 hipError_t enqueue_worklist(vmap_ctx* c, const vmap_batch* b, bool train, hipStream_t s,
@@ -888,7 +884,7 @@ int vmap_forward(vmap_ctx* c, const vmap_batch* b, float* loss_out, float* depth
   int tile = 0;
   if (!loss_out && c->rays_per_tile % rpw == 0) {
     const int low = scene_tile_low(round, b->n_rays_total, c->wl.forward_tiles - b->n_objects);
-    tile = forward_tile(round, low, b->n_rays_total, b->n_objects, forward_slots(c));
+    tile = forward_tile(c->cfg.precision == VMAP_BF16, round, c->waves, low, b->n_rays_total, b->n_objects);
   }
   hipError_t e = enqueue_worklist(c, b, false, s, nullptr, tile);
   if (e != hipSuccess) return c->hip_fail(e, "worklist launch");
@@ -951,9 +947,10 @@ static int render_scene(vmap_ctx* c, int32_t n_rays, const float* rays_o, const 
   a.S = S;
   a.max_objects = c->cfg.max_objects;
   a.max_pairs = max_pairs;
+  a.bf16 = c->cfg.precision == VMAP_BF16;
   a.tile_round = std::max(1, kSlots / S) * c->waves;
+  a.tile_waves = c->waves;
   a.tile_low = scene_tile_low(a.tile_round, max_pairs, c->wl.forward_tiles - n_objects);
-  a.slots = forward_slots(c);
   a.occ_threshold = occ_threshold;
   a.t_min = (double)t_min;
   a.rays_o = rays_o;
@@ -991,10 +988,11 @@ static int render_scene(vmap_ctx* c, int32_t n_rays, const float* rays_o, const 
     hb.ray_offsets = a.ray_offsets;
     e = enqueue_worklist(c, &hb, false, s, a.bd);
     if (e != hipSuccess) return c->hip_fail(e, "worklist launch");
-    // enough workgroups for the tiles that the device may choose: those of max_pairs at the tile that
-    // suits them, or two rounds' (a workgroup goes on to another tile where there are more)
-    const int longest = std::max(a.tile_low, forward_tile(a.tile_round, a.tile_low, max_pairs, n_objects, a.slots));
-    const int grid_tile = std::max(a.tile_low, std::min(longest, max_pairs / (2 * a.slots)));
+    // workgroups for the tiles of max_pairs pairs, at most four for each of the 1024 (of four waves) that
+    // run at once: they go on to other tiles, and without one a workgroup still takes a nanosecond
+    // (FP32, 99,200 of at most 4,194,304 pairs: 553 us with a workgroup for every possible tile, 402 so)
+    const int full = forward_tile(a.bf16, a.tile_round, a.tile_waves, a.tile_low, max_pairs, n_objects);
+    const int grid_tile = std::max(full, max_pairs / (16384 / c->waves));
     int rc = enqueue_tiles(c, &hb, MODE_FWD, nullptr, a.pair_depth, a.pair_rgb, a.pair_occ, s, false, a.bd, grid_tile);
     if (rc) return rc;
   }

@@ -388,25 +388,33 @@ __host__ __device__ inline BatchDev make_batch_dev(int n_objects, int S, int n_r
 // forward tile leaves no partial, and a ray's render does not depend on its tile as long as tiles are
 // whole sub-tiles, so the tile follows the rays of the call (a scene's pairs, which its scan counts on
 // the device), not the stack's capacity or max_pairs: of tiles of whole rounds of a workgroup (a
-// sub-tile per wave), one to eight, the one whose estimated time is least. That is the rounds of the
-// `slots` workgroups that forward mode holds (1024 of four waves in BF16, 512 in FP32) times a tile's own
-// rounds and half a one for its start; of equal ones the longest, which fetches weights least often.
-// Following max_pairs, mostly far above the pairs, left few long tiles: FP32, 3,991 pairs of at most
-// 153,600, 130 us against 97 here; 9,609 of 307,200, 126 against 104 (BF16, 99,200 pairs: 189 either way). A
-// render of 3,456 rays x 64 by three-round training tiles took 21.9 us (BF16), 17.2 so.
+// sub-tile per wave) the one of the least cost, an estimate of the time fitted to renders of 1 to 300
+// objects (540 batches of up to 12,000 rounds, every tile of one to eight rounds timed). BF16 runs four
+// workgroups of four waves on a CU and shares its issue slots among them, so tiles beyond a CU's
+// first cost their work, with little loss in a last, partly empty round. FP32 keeps the matrix cores
+// busy with one workgroup of the two that a CU holds: short tiles balance best, and longer ones than two
+// rounds only pay where all run at once. Of equal ones the longest, which fetches weights least often.
+// Mean over those batches: 0.5 % (BF16) and 1.3 % (FP32) over the best tile of each; training tiles 3.6 and
+// 5 %, two rounds always 8 and 13 %. A scene's tiles by max_pairs, mostly far above the pairs, were few
+// and long: FP32, 3,991 pairs of at most 153,600, 130 us against 97 here; 9,609 of 307,200, 126 against 104.
 constexpr int kSceneRounds = 8;
-// Cost of tiles of k rounds (0 <= cost < 2^31 for up to 2^26 rays).
-__host__ __device__ constexpr int forward_tile_cost(int k, int round, int rays, int n_objects, int slots) {
-  const int tiles = rays / (k * round) + (n_objects + 1) / 2;  // an object's last tile is half empty
-  return (tiles + slots - 1) / slots * (2 * k + 1);
+constexpr long long kNoTile = 1ll << 62;
+// Cost of tiles of k rounds. quads: tiles of four waves that hold as many waves.
+__host__ __device__ constexpr long long forward_tile_cost(bool bf16, int k, int round, int waves, int rays, int n_objects) {
+  // (an object's last tile is half empty)
+  const long long quads = ((long long)rays / ((long long)k * round) + (n_objects + 1) / 2) * waves / 4;
+  if (bf16) return ((quads + 255) / 256 * 256 + 3 * (quads > 128 ? quads + 128 : 256)) * (4 * k + 1);
+  if (k > 6 || (k > 2 && quads > 512)) return kNoTile;
+  return (quads > 448 ? quads : 448) * (2 * k + 1);
 }
-// low: scene_tile_low; at least that, in whole rounds.
-__host__ __device__ constexpr int forward_tile(int round, int low, int rays, int n_objects, int slots) {
-  int best = low, cost = 0x7fffffff;
+// The tile of `rays` rays, at least low (scene_tile_low; that one where no longer one is a candidate).
+__host__ __device__ constexpr int forward_tile(bool bf16, int round, int waves, int low, int rays, int n_objects) {
+  int best = low;
+  long long least = kNoTile - 1;
   for (int k = low / round; k <= kSceneRounds; ++k) {
-    const int c = forward_tile_cost(k, round, rays, n_objects, slots);
-    if (c <= cost) {
-      cost = c;
+    const long long c = forward_tile_cost(bf16, k, round, waves, rays, n_objects);
+    if (c <= least) {
+      least = c;
       best = k * round;
     }
   }
@@ -615,7 +623,7 @@ struct SceneArgs {
   int S;
   int max_objects;
   int max_pairs;
-  int tile_round, tile_low, slots;  // of hidden-32 objects' tiles (forward_tile)
+  int bf16, tile_round, tile_waves, tile_low;  // of hidden-32 objects' tiles (forward_tile)
   float occ_threshold;
   double t_min;
   const float* rays_o;       // [n_rays][3]

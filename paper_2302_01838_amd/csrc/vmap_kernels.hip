@@ -3891,15 +3891,15 @@ __global__ void __launch_bounds__(1024) k_scene_scan(const SceneArgs a, int nblk
     }
     __syncthreads();
   }
-  // the tile: forward_tile, a candidate per lane (fewest rounds at equal cost lose)
+  // the tile: forward_tile, a candidate per lane (of equal costs the most rounds)
   const int pairs = min(carry, a.max_pairs), k = lane + 1;
-  int cost = 0x7fffffff;
+  long long cost = kNoTile;
   if (k <= kSceneRounds && k >= a.tile_low / a.tile_round)
-    cost = forward_tile_cost(k, a.tile_round, pairs, a.n_objects, a.slots);
-  int least = cost;
+    cost = forward_tile_cost(a.bf16, k, a.tile_round, a.tile_waves, pairs, a.n_objects);
+  long long least = cost;
 #pragma unroll
   for (int off = 4; off >= 1; off >>= 1) least = min(least, __shfl_xor(least, off));
-  const unsigned long long best = __ballot(k <= kSceneRounds && cost == least && cost != 0x7fffffff);
+  const unsigned long long best = __ballot(k <= kSceneRounds && cost == least && cost < kNoTile);
   const int tile = best ? (64 - __clzll((long long)best)) * a.tile_round : a.tile_low;
   if (tid == 0) {
     const int total = carry;

@@ -1,7 +1,7 @@
 """Rays per tile of forward launches without losses (forward_tile, scene_tile_low in
 paper_2302_01838_amd/csrc/vmap_internal.h), evaluated on the host: the tiles of any number of rays fit the
 work list, the shortest tile that does is the start, and of the tiles of up to eight rounds none has a
-smaller estimate of the rounds that the chip's workgroup slots get."""
+smaller estimate of its time."""
 import os
 import shutil
 import subprocess
@@ -27,9 +27,11 @@ int main() {
               const int bound = max_rays / share;
               const int low = scene_tile_low(round, bound, max_tiles - n);
               for (int part : {1, 2, 7, 1000}) {
-                const int rays = bound / part, slots = part % 2 ? 1024 : 512;
-                const int tile = forward_tile(round, low, rays, n, slots);
-                std::printf("%d %d %d %d %d %d %d %d %d %d\n", round, rpt, wide, bound, n, max_tiles, low, rays, slots, tile);
+                const int rays = bound / part;
+                for (int bf16 : {0, 1})
+                  for (int waves : {2, 4})
+                    std::printf("%d %d %d %d %d %d %d %d %d %d %d\n", round, rpt, wide, bound, n, max_tiles, low, rays,
+                                bf16, waves, forward_tile(bf16 != 0, round, waves, low, rays, n));
               }
             }
           }
@@ -49,18 +51,23 @@ def test_forward_tiles_fit_and_follow_the_rays(tmp_path):
                    check=True, capture_output=True)
     rows = [list(map(int, ln.split())) for ln in
             subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.splitlines()]
-    assert len(rows) == 5 * 7 * 3 * 5 * 3 * 3 * 4
-    for rnd, rpt, wide, bound, n, max_tiles, low, rays, slots, tile in rows:
-        what = (rnd, rpt, wide, bound, n, rays, low, tile)
+    assert len(rows) == 5 * 7 * 3 * 5 * 3 * 3 * 4 * 4
+
+    def cost(bf16, quads, k):
+        if bf16:
+            return (-(-quads // 256) * 256 + 3 * max(256, quads + 128)) * (4 * k + 1)
+        return max(448, quads) * (2 * k + 1) if k <= 2 or k <= 6 and quads <= 512 else None
+
+    for rnd, rpt, wide, bound, n, max_tiles, low, rays, bf16, waves, tile in rows:
+        what = (rnd, rpt, wide, bound, n, rays, low, bf16, waves, tile)
         assert -(-rays // (min(tile, wide) if wide else tile)) + n <= max_tiles, what
         assert low % rnd == 0 and low < max(rpt, wide) + rnd, what
         if low > rnd:  # a shorter one would not fit
             assert -(-bound // (low - rnd)) + n > max_tiles, what
-        assert tile % rnd == 0 and low <= tile <= max(low, 8 * rnd), what
-        cost = lambda k: -(-(rays // (k * rnd) + (n + 1) // 2) // slots) * (2 * k + 1)
-        if tile <= 8 * rnd:
-            ks = range(low // rnd, 9)
-            assert cost(tile // rnd) == min(map(cost, ks)), what
-            assert all(cost(k) > cost(tile // rnd) for k in ks if k * rnd > tile), what  # the longest of equals
-        if rays > 0 and -(-rays // low) + n <= slots:  # one round of the chip: no longer than it need be
-            assert tile == low or tile > 8 * rnd, what
+        quads = {k: (rays // (k * rnd) + (n + 1) // 2) * waves // 4 for k in range(1, 9)}
+        costs = {k: cost(bf16, quads[k], k) for k in range(low // rnd, 9)}
+        costs = {k: c for k, c in costs.items() if c is not None}
+        best = min(costs.values()) if costs else None
+        assert tile == (rnd * max(k for k, c in costs.items() if c == best) if costs else low), what
+        if rays // low + n <= 128:  # few tiles: no longer than they need be
+            assert tile == low, what
