@@ -393,8 +393,9 @@ __host__ __device__ inline BatchDev make_batch_dev(int n_objects, int S, int n_r
 // workgroups of four waves on a CU and shares its issue slots among them, so tiles beyond a CU's
 // first cost their work, with little loss in a last, partly empty round. FP32 keeps the matrix cores
 // busy with one workgroup of the two that a CU holds: short tiles balance best, and longer ones than two
-// rounds only pay where all run at once. Of equal ones the longest, which fetches weights least often.
-// Mean over those batches: 0.5 % (BF16) and 1.3 % (FP32) over the best tile of each; training tiles 3.6 and
+// rounds only pay where all run at once (173 objects of 55 rays x 64: 519 tiles of six, 91 us; of two
+// 69). Of equal ones the longest, which fetches weights least often. Mean over those batches: 0.5 %
+// (BF16) and 1.4 % (FP32) over the best tile of each; training tiles 3.6 and
 // 5 %, two rounds always 8 and 13 %. A scene's tiles by max_pairs, mostly far above the pairs, were few
 // and long: FP32, 3,991 pairs of at most 153,600, 130 us against 97 here; 9,609 of 307,200, 126 against 104.
 constexpr int kSceneRounds = 8;
@@ -402,9 +403,10 @@ constexpr long long kNoTile = 1ll << 62;
 // Cost of tiles of k rounds. quads: tiles of four waves that hold as many waves.
 __host__ __device__ constexpr long long forward_tile_cost(bool bf16, int k, int round, int waves, int rays, int n_objects) {
   // (an object's last tile is half empty)
-  const long long quads = ((long long)rays / ((long long)k * round) + (n_objects + 1) / 2) * waves / 4;
+  const long long whole = (long long)rays / ((long long)k * round);
+  const long long quads = (whole + (n_objects + 1) / 2) * waves / 4;
   if (bf16) return ((quads + 255) / 256 * 256 + 3 * (quads > 128 ? quads + 128 : 256)) * (4 * k + 1);
-  if (k > 6 || (k > 2 && quads > 512)) return kNoTile;
+  if (k > 6 || (k > 2 && (whole + n_objects) * waves / 4 > 512)) return kNoTile;
   return (quads > 448 ? quads : 448) * (2 * k + 1);
 }
 // The tile of `rays` rays, at least low (scene_tile_low; that one where no longer one is a candidate).

@@ -53,10 +53,10 @@ def test_forward_tiles_fit_and_follow_the_rays(tmp_path):
             subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.splitlines()]
     assert len(rows) == 5 * 7 * 3 * 5 * 3 * 3 * 4 * 4
 
-    def cost(bf16, quads, k):
+    def cost(bf16, quads, most, k):
         if bf16:
             return (-(-quads // 256) * 256 + 3 * max(256, quads + 128)) * (4 * k + 1)
-        return max(448, quads) * (2 * k + 1) if k <= 2 or k <= 6 and quads <= 512 else None
+        return max(448, quads) * (2 * k + 1) if k <= 2 or k <= 6 and most <= 512 else None
 
     for rnd, rpt, wide, bound, n, max_tiles, low, rays, bf16, waves, tile in rows:
         what = (rnd, rpt, wide, bound, n, rays, low, bf16, waves, tile)
@@ -64,8 +64,8 @@ def test_forward_tiles_fit_and_follow_the_rays(tmp_path):
         assert low % rnd == 0 and low < max(rpt, wide) + rnd, what
         if low > rnd:  # a shorter one would not fit
             assert -(-bound // (low - rnd)) + n > max_tiles, what
-        quads = {k: (rays // (k * rnd) + (n + 1) // 2) * waves // 4 for k in range(1, 9)}
-        costs = {k: cost(bf16, quads[k], k) for k in range(low // rnd, 9)}
+        costs = {k: cost(bf16, (rays // (k * rnd) + (n + 1) // 2) * waves // 4, (rays // (k * rnd) + n) * waves // 4, k)
+                 for k in range(low // rnd, 9)}
         costs = {k: c for k, c in costs.items() if c is not None}
         best = min(costs.values()) if costs else None
         assert tile == (rnd * max(k for k, c in costs.items() if c == best) if costs else low), what
